@@ -190,6 +190,13 @@ locc_status locc::check_call(locc_ctx* c, const locc_object* objs, int32_t n_obj
 
 namespace {
 
+// Device views of the FP32 weights and of their bf16 parts.
+Fp32Net fp32_net(const locc_ctx* c) {
+  Fp32Net w = fp32_view(c->d_wfp32, c->cfg.enc_h1, c->cfg.enc_h2, c->cfg.head_h);
+  split_bind(w, c->d_wsplit);
+  return w;
+}
+
 // Scale of an fp8 activation with maximum amax (448 is e4m3's largest finite value).
 float fp8_scale(float amax) { return amax > 0.f ? amax / 448.f : 1.f; }
 
@@ -215,10 +222,11 @@ locc_status locc::run_path(locc_ctx* c, const locc_object* objs, int32_t n_objs,
     CropArgs ca{objs, n_objs, pairs, n_pairs, n_dev, c->lib(), c->cfg.K, c->cfg.pad_m,
                 nullptr, counts, w.meta, w.rows, nullptr, c->d_err, w.setup};
     HIP_TRY(timed(c, "crop", s, [&] { return launch_crop(ca, s, unroll); }));
-    const Fp32Net net = fp32_view(c->d_wfp32, c->cfg.enc_h1, c->cfg.enc_h2, c->cfg.head_h);
-    NetArgs na{w.rows, w.meta, objs, n_pairs, n_dev, c->cfg.K, z_out ? z_out : w.z, y_out, out};
-    HIP_TRY(timed(c, "encoder_fp32", s, [&] { return launch_encoder_fp32(net, na, c->n_cu, s); }));
-    HIP_TRY(timed(c, "head_fp32", s, [&] { return launch_head_fp32(net, na, s); }));
+    const Fp32Net net = fp32_net(c);
+    NetArgs na{w.rows, w.meta, objs, n_pairs, n_dev, c->cfg.K, z_out ? z_out : w.z, y_out, out, nullptr,
+               own ? own->queue : c->d_queue};
+    HIP_TRY(timed(c, "encoder_fp32", s, [&] { return launch_encoder_split(net, na, c->n_cu, s); }));
+    HIP_TRY(timed(c, "head_fp32", s, [&] { return launch_head_split(net, na, c->n_cu, s); }));
     return LOCC_OK;
   }
   const int h1 = c->cfg.enc_h1, h2 = c->cfg.enc_h2, hh = c->cfg.head_h;
@@ -484,6 +492,7 @@ void locc_destroy(locc_ctx* c) {
   (void)hipFree(c->d_wfp8);
   (void)hipFree(c->d_wraw);
   (void)hipFree(c->d_wgrad);
+  (void)hipFree(c->d_wsplit);
   (void)hipFree(c->d_pack_idx);
   (void)hipFree(c->d_tr_idx);
   (void)hipFree(c->d_train);
@@ -498,6 +507,34 @@ void locc_destroy(locc_ctx* c) {
   (void)hipFree(c->d_err);
   delete c;
 }
+
+}  // extern "C"
+
+namespace {
+
+// The halves of the FP32 weights, with scales for the weights and the library as they are (synchronous).
+locc_status split_repack(locc_ctx* c) {
+  const int h1 = c->cfg.enc_h1, h2 = c->cfg.enc_h2, hh = c->cfg.head_h;
+  const SplitLayout L = split_layout(h1, h2, hh);
+  // a b row lies in the crop box (a's box widened by the margin); a rotation keeps a normal's length
+  std::vector<float> head(L.scale / 4 + split_scale_floats(h2, hh), 0.f);  // the flag word, then the scales
+  split_scales(c->h_flat.data(), h1, h2, hh, c->lib_xmax + (float)c->cfg.pad_m, 1.75f * c->lib_nmax,
+               head.data() + L.scale / 4);
+  HIP_TRY(hipMemcpy(c->d_wsplit, head.data(), head.size() * sizeof(float), hipMemcpyHostToDevice));
+  RepackArgs ra{};
+  ra.raw = c->d_wraw;
+  ra.h1 = h1;
+  ra.h2 = h2;
+  ra.hh = hh;
+  ra.split = c->d_wsplit;
+  HIP_TRY(launch_repack(ra, nullptr));
+  HIP_TRY(hipStreamSynchronize(nullptr));
+  return LOCC_OK;
+}
+
+}  // namespace
+
+extern "C" {
 
 locc_status locc_upload_weights(locc_ctx* c, const float* h, size_t n) {
   if (!c || !h) return fail(LOCC_ERR_INVALID_ARG, "null context or weights");
@@ -539,6 +576,11 @@ locc_status locc_upload_weights(locc_ctx* c, const float* h, size_t n) {
     if (!c->d_wgrad) HIP_TRY(hipMalloc(&c->d_wgrad, t.size() * sizeof(float)));
     HIP_TRY(hipMemcpy(c->d_wraw, h, n * sizeof(float), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(c->d_wgrad, t.data(), t.size() * sizeof(float), hipMemcpyHostToDevice));
+    const SplitLayout SL = split_layout(h1, h2, hh);
+    if (!c->d_wsplit) HIP_TRY(hipMalloc(&c->d_wsplit, SL.total));
+    c->h_flat.assign(h, h + n);
+    const locc_status ss = split_repack(c);
+    if (ss != LOCC_OK) return ss;
   }
   if (c->cfg.precision == LOCC_FP32) {
     // training: where each packed value comes from (the packing is positional, so packing the
@@ -682,6 +724,7 @@ locc_status locc_upload_shapes(locc_ctx* c, int32_t n_shapes, const int64_t* off
                 c->live_graphs);
   std::vector<float> soa((size_t)total * 6);
   std::vector<ShapeDesc> desc(n_shapes);
+  float xmax = 0.f, nmax = 0.f;  // largest coordinate and normal component
   for (int s = 0; s < n_shapes; ++s) {
     ShapeDesc d{};
     d.off = (int32_t)off[s];
@@ -696,6 +739,8 @@ locc_status locc_upload_shapes(locc_ctx* c, int32_t n_shapes, const int64_t* off
         if (!std::isfinite(row[k]))
           return fail(LOCC_ERR_INVALID_ARG, "shape %d point %lld: non-finite value", s, (long long)(r - off[s]));
         soa[(size_t)k * total + r] = row[k];
+        float& mx = k < 3 ? xmax : nmax;
+        mx = std::fabs(row[k]) > mx ? std::fabs(row[k]) : mx;
       }
       for (int k = 0; k < 3; ++k) {
         d.lo[k] = row[k] < d.lo[k] ? row[k] : d.lo[k];
@@ -717,6 +762,9 @@ locc_status locc_upload_shapes(locc_ctx* c, int32_t n_shapes, const int64_t* off
   HIP_TRY(hipMemcpy(c->d_points, soa.data(), sizeof(float) * soa.size(), hipMemcpyHostToDevice));
   c->n_shapes = n_shapes;
   c->n_points = total;
+  c->lib_xmax = xmax;
+  c->lib_nmax = nmax;
+  if (c->d_wsplit && c->cfg.precision == LOCC_FP32) return split_repack(c);  // layer 1's scale depends on them
   return LOCC_OK;
 }
 
@@ -1067,8 +1115,8 @@ locc_status locc_pose_gradients(locc_ctx* c, const locc_object* objs, int32_t n_
   CropArgs ca{objs, n_objs, pairs, n_pairs, nullptr, c->lib(), K, c->cfg.pad_m,
               idx, nullptr, meta, rows, rows16, c->d_err, setup};
   HIP_TRY(timed(c, "crop", s, [&] { return launch_crop(ca, s, c->sched.crop_unroll); }));
-  const Fp32Net net = fp32_view(c->d_wfp32, h1, h2, hh);
-  NetArgs na{rows, meta, objs, n_pairs, nullptr, K, z, nullptr, out, amax};
+  const Fp32Net net = fp32_net(c);
+  NetArgs na{rows, meta, objs, n_pairs, nullptr, K, z, nullptr, out, amax, c->d_queue};
   if (bf16) {
     // the BF16 encoder of the split schedule, recording the pooled features and the argmax rows
     FusedArgs fa{};
@@ -1097,9 +1145,13 @@ locc_status locc_pose_gradients(locc_ctx* c, const locc_object* objs, int32_t n_
                     [&] { return launch_encoder_bf16_argmax(fa, h1, h2, hh, grid, s); }));
     }
   } else {
+    if (out) {  // the contacts are locc_detect's, from its own encoder
+      HIP_TRY(timed(c, "encoder_split", s, [&] { return launch_encoder_split(net, na, c->n_cu, s); }));
+      HIP_TRY(timed(c, "head_fp32", s, [&] { return launch_head_split(net, na, c->n_cu, s); }));
+    }
     HIP_TRY(timed(c, "encoder_fp32", s, [&] { return launch_encoder_fp32(net, na, c->n_cu, s); }));
   }
-  if (out) HIP_TRY(timed(c, "head_fp32", s, [&] { return launch_head_fp32(net, na, s); }));
+  if (out && bf16) HIP_TRY(timed(c, "head_fp32", s, [&] { return launch_head_split(net, na, c->n_cu, s); }));
   GradArgs ga{};
   ga.objs = objs;
   ga.n_objs = n_objs;
@@ -1201,7 +1253,7 @@ locc_status locc_train_step(locc_ctx* c, const locc_object* objs, int32_t n_objs
   CropArgs ca{objs, n_objs, pairs, n_pairs, nullptr, c->lib(), K, c->cfg.pad_m,
               nullptr, nullptr, w.meta, w.rows, nullptr, c->d_err, w.setup};
   HIP_TRY(timed(c, "crop", s, [&] { return launch_crop(ca, s, c->sched.crop_unroll); }));
-  const Fp32Net net = fp32_view(c->d_wfp32, h1, h2, hh);
+  const Fp32Net net = fp32_net(c);
   NetArgs na{w.rows, w.meta, objs, n_pairs, nullptr, K, w.z, nullptr, nullptr, amax};
   HIP_TRY(timed(c, "encoder_fp32", s, [&] { return launch_encoder_fp32(net, na, c->n_cu, s); }));
   ta.n_pairs = n_pairs;
@@ -1247,12 +1299,8 @@ locc_status locc_train_step(locc_ctx* c, const locc_object* objs, int32_t n_objs
   ta.corr1 = (float)(1.0 / (1.0 - std::pow((double)beta1, (double)t_next)));
   ta.corr2 = (float)(1.0 / (1.0 - std::pow((double)beta2, (double)t_next)));
   ta.loss = loss;
-  ta.pack_dst = c->d_wfp32;
-  ta.pack_idx = c->d_pack_idx;
-  ta.pack_n = fp32_pack_floats(h1, h2, hh);
-  ta.tr_dst = c->d_wgrad;
-  ta.tr_idx = c->d_tr_idx;
-  ta.tr_n = (size_t)2 * h2 * hh + (size_t)hh * hh + (size_t)h1 * h2;
+  ta.repack = RepackArgs{c->d_wraw, h1, h2, hh, c->d_wfp32, c->d_pack_idx, (int32_t)fp32_pack_floats(h1, h2, hh),
+                         c->d_wgrad, c->d_tr_idx, 2 * h2 * hh + hh * hh + h1 * h2, c->d_wsplit};
   if (argmax) HIP_TRY(hipMemcpyAsync(argmax, amax, P * 2 * h2, hipMemcpyDeviceToDevice, s));
   HIP_TRY(timed(c, "train", s, [&] { return launch_train_step(ta, h1, h2, hh, s); }));
   c->train_t = t_next;

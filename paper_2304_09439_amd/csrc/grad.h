@@ -69,13 +69,7 @@ struct TrainArgs {
   size_t n;
   float lr, beta1, beta2, eps, corr1, corr2;  // corr = 1 / (1 - beta^t)
   float* loss;            // [2] out: mean cross-entropy, alpha x mean squared feature norm
-  // repacking: dst[i] = src_idx[i] >= 0 ? raw[src_idx[i]] : 0
-  float* pack_dst;
-  const int32_t* pack_idx;
-  size_t pack_n;
-  float* tr_dst;          // H1^T, H2^T, W2^T
-  const int32_t* tr_idx;
-  size_t tr_n;
+  RepackArgs repack;      // every packed form of the weights: the FP32 layout, H1^T, H2^T, W2^T, the halves
 };
 
 hipError_t launch_train_step(const TrainArgs& a, int h1, int h2, int hh, hipStream_t s);

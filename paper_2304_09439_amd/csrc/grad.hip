@@ -310,8 +310,8 @@ hipError_t launch_pose_gradients(const GradArgs& a, int h1, int h2, int hh, hipS
 // enc_grad_kernel (one workgroup per channel and range of pairs) walks its
 // (pair, object) entries in order, staging 256 argmax rows at a time in LDS,
 // and train_reduce_kernel sums the partials of dW2, db2, dW1, db1 and the
-// loss terms; adam_kernel updates the master weights; two gathers
-// repack them into the layouts the forward and gradient kernels read.  Every
+// loss terms; adam_kernel updates the master weights; one launch
+// repacks them into the layouts the forward and gradient kernels read.  Every
 // reduction has a fixed order, so a step is reproducible bit for bit.
 namespace locc {
 namespace {
@@ -697,19 +697,13 @@ __global__ __launch_bounds__(256) void train_reduce_kernel(TrainArgs A, float in
 __global__ __launch_bounds__(256) void adam_kernel(TrainArgs A) {
   const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= A.n) return;
+  if (i == 0) *reinterpret_cast<int32_t*>(A.repack.split) = 0;  // set by the repacking that follows
   const float gr = A.grad[i];
   const float m = A.beta1 * A.m[i] + (1.f - A.beta1) * gr;
   const float v = A.beta2 * A.v[i] + (1.f - A.beta2) * gr * gr;
   A.m[i] = m;
   A.v[i] = v;
   A.raw[i] -= A.lr * (m * A.corr1) / (sqrtf(v * A.corr2) + A.eps);
-}
-
-__global__ __launch_bounds__(256) void gather_kernel(float* dst, const int32_t* idx, size_t n, const float* src) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  const int32_t k = idx[i];
-  dst[i] = k >= 0 ? src[k] : 0.f;
 }
 
 template <int H1, int H2, int HH>
@@ -739,11 +733,7 @@ hipError_t run_train(const TrainArgs& a, hipStream_t s) {
   kernel_launch((train_reduce_kernel<H1, H2>), dim3((H2 * (H1 + 1) + 255) / 256 + (H1 * 7 + 3) / 4 + 1),
                      dim3(256), 0, s, a, invB);
   kernel_launch(adam_kernel, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, s, a);
-  kernel_launch(gather_kernel, dim3((unsigned)((a.pack_n + 255) / 256)), dim3(256), 0, s, a.pack_dst,
-                     a.pack_idx, a.pack_n, (const float*)a.raw);
-  kernel_launch(gather_kernel, dim3((unsigned)((a.tr_n + 255) / 256)), dim3(256), 0, s, a.tr_dst, a.tr_idx,
-                     a.tr_n, (const float*)a.raw);
-  return hipGetLastError();
+  return launch_repack(a.repack, s);
 }
 
 }  // namespace

@@ -153,6 +153,19 @@ struct Fp32Net {
   const float* c2;      // [hh]
   const float* h3;      // [8][hh] plain row-major
   const float* c3;      // [8]
+  // both halves of every weight of W2, H1 and H2 in 32x32x16 B operand order, rows times powers of two, and the
+  // factors that undo them (net_split.hip)
+  const float* w1s;           // w1pack times the activation scale
+  const unsigned short* w2s;  // [2][h2/32][h1/16][64][8]
+  const unsigned short* h1s;  // [2][hh/32][2 h2/16][64][8]
+  const unsigned short* h2s;  // [2][hh/32][hh/16][64][8]
+  const unsigned short* h3s;  // [2][hh/16][64][8] (8 rows, zero to 32)
+  const float* head_bound;    // of layers 1 and 2: the largest row sum of absolute weights, the largest bias
+  const float* unscale2;      // [h2], the activation scale included
+  const float* unscale_h1;    // [hh]
+  const float* unscale_h2;    // [hh]
+  const float* unscale_h3;    // [8]
+  const int32_t* split_bad;   // not 0: a weight is not finite or too large, the halves are not usable
 };
 
 struct NetArgs {
@@ -166,10 +179,67 @@ struct NetArgs {
   float* y_dbg;           // [P][8] or null
   locc_contact* out;      // [P]
   uint8_t* amax;          // [P][2][h2] row of the largest raw layer-2 sum per channel (first on ties), or null
+  unsigned int* queue;    // launch_encoder_split: [2], 0 between launches, or null (static order)
 };
 
+// The encoder on the FP32 matrix cores, recording the argmax rows (amax).
 hipError_t launch_encoder_fp32(const Fp32Net& w, const NetArgs& a, int n_cu, hipStream_t s);
-hipError_t launch_head_fp32(const Fp32Net& w, const NetArgs& a, hipStream_t s);
+
+// The same features without the argmax rows, layer 2 as products of halves.
+hipError_t launch_encoder_split(const Fp32Net& w, const NetArgs& a, int n_cu, hipStream_t s);
+
+// The head on the features in z (products of halves).
+hipError_t launch_head_split(const Fp32Net& w, const NetArgs& a, int n_cu, hipStream_t s);
+
+// Largest finite half: a float up to it has finite halves.
+constexpr float kSplitLimit = 65504.f;
+
+// Chunks of pairs a workgroup of the split encoder claims: level l holds
+// claims[l] chunks of size[l] pairs from pair base[l] on (the last level as
+// many as it takes).
+constexpr int kSplitChunk = 32;
+struct SplitChunks {
+  static constexpr int kLevels = 8;
+  int32_t grid;
+  int32_t size[kLevels], base[kLevels], claims[kLevels];
+};
+__host__ __device__ inline void split_chunk(const SplitChunks& c, int claim, int& base, int& n) {
+  int l = 0;
+#pragma unroll
+  for (int k = 0; k + 1 < SplitChunks::kLevels; ++k)
+    if (l == k && claim >= c.claims[k]) {
+      claim -= c.claims[k];
+      l = k + 1;
+    }
+  base = 0x7fffffff;
+  n = 0;
+#pragma unroll
+  for (int k = 0; k < SplitChunks::kLevels; ++k)
+    if (l == k) {
+      n = c.size[k];
+      const long long at = c.base[k] + (long long)claim * n;
+      if (at < base) base = (int)at;
+    }
+}
+
+// Device views of the halves (split_layout() in pack.h at base).
+void split_bind(Fp32Net& w, const char* base);
+
+// Repacking on the device from the flat weights raw: pack[i] = raw[pack_idx[i]]
+// (0 where the index is negative) and the same for tr, when given, and the
+// halves at split (their scales in place, the flag word zero before).
+struct RepackArgs {
+  const float* raw;
+  int32_t h1, h2, hh;
+  float* pack;
+  const int32_t* pack_idx;
+  int32_t pack_n;
+  float* tr;
+  const int32_t* tr_idx;
+  int32_t tr_n;
+  char* split;
+};
+hipError_t launch_repack(const RepackArgs& a, hipStream_t s);
 
 // Device views of the FP32 weights packed by fp32_pack (pack.h).
 Fp32Net fp32_view(const float* dev_base, int h1, int h2, int hh);

@@ -1,0 +1,766 @@
+// FP32 per-point encoder with per-object max-pool, and the FP32 head, on the
+// half-precision matrix cores.
+//
+//   h1 = ReLU(W1 r + b1), h2 = ReLU(W2 h1 + b2), f = max over the valid rows
+// of each object (0 when none; Sec. III, appendix).  Layer 1 runs on the FP32
+// matrix cores.  Layer 2, 97% of the work, runs on 16-bit ones: a float x is
+// the sum of two halves, x0 = half(x) and x1 = half(x - x0), to 2^-24 of x,
+// and of the four products of two such sums all but x1 y1 (below 2^-24 of the
+// product) are accumulated in FP32.  x0 y0 has a sum of its own, so that the
+// large partial sums round 8 times per output where a chain of FP32
+// multiply-adds rounds 128 times; the result is as near the 64-bit one as
+// that chain's.  Three 32x32x16 products take 96 cycles for the 1024 that
+// 16 reduction steps of 32x32x2 FP32 products take.  16,384 pairs of 2048-point
+// shapes at K = 128, widths 128 / 256: 0.63 ms, 1.83 ms on the FP32 matrix
+// cores (error of the whole path against 64 bits 5.8e-7, 7.9e-7 before).  The
+// matrix cores are busy 0.60 of its cycles and draw enough power that the
+// clock falls to 1.93 GHz.  Six products of three bf16 parts (no scales
+// needed) took 0.98 ms.
+//
+// Halves span 2^-14 to 2^16 with all their bits, so layer 1's weights come
+// multiplied by a power of two that puts the largest output any row of the
+// library can give at 2^13, W2's rows by one that puts their largest weight at
+// 2^8, and the pooled sum is scaled back (all exact).  A step of rows whose
+// layer-1 outputs are not all finite and in the range of a half, and every
+// step when a weight is not, is computed as net_fp32.hip's FP32 chain.
+//
+// A persistent workgroup of h2 / 32 waves takes chunks of pairs from a queue
+// (chunk sizes fall from 32 to 1 towards the end of the batch, so that the
+// last chunks even out the unequal row counts) and walks their objects in
+// steps of 64 rows.  Wave w owns 32 of layer 2's columns, its W2 fragments of
+// both parts in registers; layer 1 of the next step is computed one 32 x 32
+// tile per wave, split, and written to the other of two LDS buffers while
+// layer 2 of the current step runs (one barrier per step).
+#include "locc_internal.h"
+#include "post.h"
+
+namespace locc {
+namespace {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ float vmax(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+__device__ __forceinline__ f32x16 mfma32x32x2(float a, float b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x16 mfma_k16(u32x4 a, u32x4 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0,
+                                                0);
+}
+__device__ __forceinline__ int perm_feature(int ft, int g, int r) { return 32 * ft + 8 * (r / 4) + 4 * g + r % 4; }
+
+// Two floats to halves (round to nearest even), packed; the floats become the exact remainders.
+__device__ __forceinline__ unsigned split_part(float& a, float& b) {
+  const f16x2 h = __builtin_convertvector((f32x2){a, b}, f16x2);
+  a = __builtin_fmaf((float)h[0], -1.f, a);
+  b = __builtin_fmaf((float)h[1], -1.f, b);
+  return __builtin_bit_cast(unsigned, h);
+}
+__device__ __forceinline__ unsigned last_part(float a, float b) {
+  return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a, b}, f16x2));
+}
+
+constexpr int kStepRows = 64;
+constexpr int kMaxSteps = kSplitChunk * 2 * (kMaxK / kStepRows);
+static_assert(kSplitChunk == 32, "one lane per object of a chunk");
+
+template <int H1, int H2>
+struct SplitSmem {
+  static constexpr int HS = H1 + 8;  // bf16 per row: 16 bytes past a multiple of 64 or 128, so that rows start in other banks
+  alignas(16) unsigned short h[2][2][kStepRows * HS];  // layer-1 outputs of a step: [buffer][part][row][permuted feature]
+  int32_t step[kMaxSteps];       // object of the chunk (0-63) | row block << 8
+  int32_t m[2 * kSplitChunk];    // rows per object; -1: invalid pair
+  int32_t n_steps;
+  int32_t claim;
+  int32_t bad[2];                // per buffer: the step whose layer-1 outputs are out of range
+};
+
+template <int H1, int H2>
+__global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, NetArgs A, SplitChunks C) {
+  using S_t = SplitSmem<H1, H2>;
+  constexpr int HS = S_t::HS;
+  constexpr int FT = H1 / 32;        // layer-1 feature tiles
+  constexpr int NW = H2 / 32;        // waves, one layer-2 column tile each
+  constexpr int KS = H1 / 16;        // layer-2 k-steps
+  static_assert(2 * FT == NW, "one layer-1 tile of a step per wave");
+  __shared__ S_t S;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ft1 = wave % FT, rt1 = wave / FT;  // this wave's layer-1 tile of a step
+  const int K = A.K;
+  const int P = pair_count(A.n_pairs, A.n_pairs_dev);
+  const bool slow = *W.split_bad != 0;
+
+  u32x4 w2f[2][KS];
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+      w2f[q][s] = reinterpret_cast<const u32x4*>(W.w2s)[((size_t)(q * NW + wave) * KS + s) * 64 + lane];
+  float w1f[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) w1f[s] = W.w1s[(ft1 * 4 + s) * 64 + lane];
+  const float bias2 = W.b2[wave * 32 + l32], unscale2 = W.unscale2[wave * 32 + l32];
+  if (tid < 2) S.bad[tid] = -1;
+
+  int gstep = 0;  // steps this workgroup has started (tags S.bad)
+  for (int claim = blockIdx.x;; claim += gridDim.x) {
+    if (A.queue) {
+      if (tid == 0) S.claim = (int)atomicAdd(A.queue, 1u);
+      __syncthreads();
+      claim = S.claim;
+    }
+    int base, n;
+    split_chunk(C, claim, base, n);
+    if (base >= P) break;  // uniform
+    if (base + n > P) n = P - base;
+    // the chunk's steps: a lane per object, prefix of the step counts
+    if (wave == 0) {
+      int m = 0;
+      if (lane < 2 * n) {
+        const PairMeta mt = A.meta[base + (lane >> 1)];
+        m = mt.a < 0 ? -1 : (lane & 1 ? mt.m_b : mt.m_a);
+      }
+      S.m[lane] = m;
+      const int ns = m > 0 ? (m + kStepRows - 1) / kStepRows : 0;
+      int at = ns;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const int o = __shfl_up(at, d, 64);
+        if (lane >= d) at += o;
+      }
+      if (lane == 63) S.n_steps = at;
+      at -= ns;
+      for (int b = 0; b < ns; ++b) S.step[at + b] = lane | (b << 8);
+    }
+    __syncthreads();
+    const int ns = S.n_steps;
+    // objects without rows: f = 0; both objects of an invalid pair: NaN
+    for (int o = wave; o < 2 * n; o += NW) {
+      const int m = S.m[o];  // uniform
+      if (m > 0) continue;
+      const float v = m < 0 ? __builtin_nanf("") : 0.f;
+      if (lane < H2 / 4)
+        reinterpret_cast<float4*>(A.z + ((size_t)base * 2 + o) * H2)[lane] = make_float4(v, v, v, v);
+    }
+
+    // this lane's layer-1 input of step k (rows past the object's count are not needed and may not exist)
+    auto load_rows = [&](int k) __attribute__((always_inline)) -> float4 {
+      const int e = __builtin_amdgcn_readfirstlane(S.step[k]);
+      const int o = e & 0xff, r0 = (e >> 8) * kStepRows + 32 * rt1;
+      if (r0 >= __builtin_amdgcn_readfirstlane(S.m[o])) return make_float4(0.f, 0.f, 0.f, 0.f);
+      return *reinterpret_cast<const float4*>(A.rows + (((size_t)base * 2 + o) * K + r0 + l32) * kRowFloats + 4 * g);
+    };
+    f32x16 acc1 = f32x16{};
+    auto layer1_issue = [&](float4 x) __attribute__((always_inline)) {
+      acc1 = mfma32x32x2(w1f[0], x.x, f32x16{});
+      acc1 = mfma32x32x2(w1f[1], x.y, acc1);
+      acc1 = mfma32x32x2(w1f[2], x.z, acc1);
+      acc1 = mfma32x32x2(w1f[3], x.w, acc1);
+    };
+    // One of the eight pairs of layer-1 outputs of this lane to their parts (h = pair / 4, e = pair % 4); the
+    // fourth of a half writes the half's 16 bytes of each part.
+    u32x4 q0, q1;
+    float mx = 0.f;
+    auto layer1_pair = [&](int pair, int buf) __attribute__((always_inline)) {
+      const int hf = pair >> 2, e = pair & 3;
+      float a = vmax(acc1[2 * pair], 0.f), b = vmax(acc1[2 * pair + 1], 0.f);
+      mx = vmax(vmax(mx, a), b);
+      q0[e] = split_part(a, b);
+      q1[e] = last_part(a, b);
+      if (e == 3) {
+        unsigned short* dst = &S.h[buf][0][(32 * rt1 + l32) * HS + 32 * ft1 + 8 * g + 16 * hf];
+        *reinterpret_cast<u32x4*>(dst) = q0;
+        *reinterpret_cast<u32x4*>(dst + kStepRows * HS) = q1;
+      }
+    };
+    auto layer1_check = [&](int buf, int tag) __attribute__((always_inline)) {
+      if (__ballot(!(mx <= kSplitLimit)) != 0 && lane == 0) S.bad[buf] = tag;
+    };
+
+    if (ns > 0) {
+      layer1_issue(load_rows(0));
+#pragma unroll
+      for (int q = 0; q < 8; ++q) layer1_pair(q, 0);
+      layer1_check(0, gstep);
+      mx = 0.f;
+    }
+    float4 xv = ns > 1 ? load_rows(1) : make_float4(0.f, 0.f, 0.f, 0.f);
+    __syncthreads();
+    float run = -__builtin_inff();
+    for (int k = 0; k < ns; ++k, ++gstep) {
+      const int e = __builtin_amdgcn_readfirstlane(S.step[k]);
+      const int o = e & 0xff, r0 = (e >> 8) * kStepRows;
+      const int m = __builtin_amdgcn_readfirstlane(S.m[o]);
+      const bool more = k + 1 < ns;
+      const int buf = k & 1;
+      const bool chain = slow || __builtin_amdgcn_readfirstlane(S.bad[buf]) == gstep;
+      if (more) layer1_issue(xv);
+      if (k + 2 < ns) xv = load_rows(k + 2);
+      // max of a row tile's raw sums (bias and ReLU once per column afterwards: rounding is monotone)
+      float best = -__builtin_inff();
+      auto pool = [&](const f32x16& v, int row0) __attribute__((always_inline)) {
+        if (row0 + 32 <= m) {
+#pragma unroll
+          for (int r = 0; r < 16; r += 2) best = vmax(vmax(best, v[r]), v[r + 1]);
+        } else {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int row = row0 + 8 * (r >> 2) + 4 * g + (r & 3);
+            if (row < m) best = vmax(best, v[r]);
+          }
+        }
+      };
+      // the products of row tile rt; between(s) is issued among those of k-step s
+      f32x16 hi, lo;
+      auto layer2 = [&](int rt, auto between) __attribute__((always_inline)) {
+        const unsigned short* src = &S.h[buf][0][(32 * rt + l32) * HS + 8 * g];
+        auto part = [&](int q, int s) __attribute__((always_inline)) {
+          return *reinterpret_cast<const u32x4*>(src + q * kStepRows * HS + 16 * s);
+        };
+        hi = lo = f32x16{};
+        u32x4 a0 = part(0, 0), a1 = part(1, 0);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+          u32x4 n0, n1;
+          if (s + 1 < KS) {
+            n0 = part(0, s + 1);
+            n1 = part(1, s + 1);
+          }
+          lo = mfma_k16(a1, w2f[0][s], lo);
+          hi = mfma_k16(a0, w2f[0][s], hi);
+          lo = mfma_k16(a0, w2f[1][s], lo);
+          between(s);
+          if (s + 1 < KS) {
+            a0 = n0;
+            a1 = n1;
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      };
+      if (!chain) {
+        // (after the chunk's last step the parts of stale values go to the buffer that nobody reads again)
+        layer2(0, [&](int s) __attribute__((always_inline)) {
+          if (KS == 8) {
+            if (s > 0) layer1_pair(s - 1, buf ^ 1);
+            if (s == 7) layer1_pair(7, buf ^ 1);
+          } else {
+            if (s > 0) {
+              layer1_pair(2 * s - 2, buf ^ 1);
+              layer1_pair(2 * s - 1, buf ^ 1);
+            }
+            if (s == 3) {
+              layer1_pair(6, buf ^ 1);
+              layer1_pair(7, buf ^ 1);
+            }
+          }
+        });
+        if (r0 + 32 < m) {
+          const f32x16 v = hi + lo;
+          layer2(1, [&](int s) __attribute__((always_inline)) {
+#pragma unroll
+            for (int r = 16 / KS * s; r < 16 / KS * (s + 1); r += 2) best = vmax(vmax(best, v[r]), v[r + 1]);
+          });
+          pool(hi + lo, r0 + 32);
+        } else {
+          pool(hi + lo, r0);
+        }
+      } else {  // uniform over the workgroup
+        for (int rt = 0; rt < 2 && r0 + 32 * rt < m; ++rt) {
+          const float4 x = *reinterpret_cast<const float4*>(
+              A.rows + (((size_t)base * 2 + o) * K + r0 + 32 * rt + l32) * kRowFloats + 4 * g);
+          f32x16 acc2 = f32x16{};
+#pragma unroll 1
+          for (int ft = 0; ft < FT; ++ft) {
+            const float* w1 = W.w1pack + (size_t)ft * 4 * 64 + lane;
+            const float* w2 = W.w2pack + ((size_t)wave * (H1 / 2) + 16 * ft) * 64 + lane;
+            f32x16 h = mfma32x32x2(w1[0], x.x, f32x16{});
+            h = mfma32x32x2(w1[64], x.y, h);
+            h = mfma32x32x2(w1[128], x.z, h);
+            h = mfma32x32x2(w1[192], x.w, h);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc2 = mfma32x32x2(vmax(h[r], 0.f), w2[r * 64], acc2);
+          }
+          pool(acc2, r0 + 32 * rt);
+        }
+      }
+      if (more) {
+        if (chain)
+#pragma unroll
+          for (int q = 0; q < 8; ++q) layer1_pair(q, buf ^ 1);
+        layer1_check(buf ^ 1, gstep + 1);
+      }
+      mx = 0.f;
+      run = vmax(run, chain ? best : best * unscale2);
+      if (r0 + kStepRows >= m) {  // the object's last step
+        const float f = fmaxf(fmaxf(run, __shfl_xor(run, 32, 64)) + bias2, 0.f);
+        run = -__builtin_inff();
+        if (lane < 32) A.z[((size_t)base * 2 + o) * H2 + wave * 32 + lane] = f;
+      }
+      __syncthreads();
+    }
+  }
+  if (A.queue && tid == 0) {
+    __threadfence();
+    if (atomicAdd(A.queue + 1, 1u) == gridDim.x - 1) {  // last workgroup out resets the queue
+      atomicExch(A.queue, 0u);
+      atomicExch(A.queue + 1, 0u);
+    }
+  }
+}
+
+// ----------------------------------------------------------------------- head
+//
+// y = H3 ReLU(H2 ReLU(H1 [f_a, f_b] + c1) + c2) + c3 on RT tiles of 32 pairs
+// per workgroup of eight waves, as products of halves like the encoder's layer
+// 2.  The activations stay in LDS as halves (one buffer: a layer's outputs
+// overwrite its inputs once every wave has read them); each wave owns HH / 8
+// columns of layers 1 and 2 and streams their weight halves from L2 two steps
+// ahead, each fragment serving all row tiles; layer 3 splits its reduction
+// over the waves.  A pair's row is scaled by the power of two that puts its
+// largest feature (layer 1's input), or the bound its weights give from there
+// (layers 2 and 3), at 2^13.  16,384 pairs at width 512: 66 us (0.350 ms as FP32
+// products, 32 pairs and four waves per workgroup); 80 pairs at width 256: 14 us
+// (40 us).  Bound by the 2 MB of weights each workgroup streams from L2 (RT = 1)
+// or by the matrix cores (RT = 2).  A pair with a value out of range gets the FP32
+// chain's result instead.
+
+template <int Z, int HH, int RT>
+struct HeadSmem {
+  static constexpr int T = 32 * RT;
+  static constexpr int W = (Z > HH ? Z : HH);
+  static constexpr int AS = W + 8;      // halves per row
+  static constexpr int LZ = W + 1;      // floats per row of the chain's tiles (odd: conflict-free column reads)
+  union {
+    alignas(16) unsigned short a[2][T * AS];   // activations: [part][row][feature]
+    float chain[2][32 * LZ];                   // the FP32 chain's input and output of a layer, 32 pairs
+  } u;
+  alignas(16) float unscale[T];   // per row: undoes the scale of the current input
+  alignas(16) float top[T];       // per row: the largest absolute input, later its bound
+  float part[8][T][8];            // layer 3: each wave's part
+  int32_t bad[T];                 // per row: a value out of range
+  int32_t any_bad;
+};
+
+// 2^(13 - e) for v in (2^(e - 1), 2^e], within 2^+-100; 1 for 0.
+__device__ __forceinline__ float row_scale(float v) {
+  const int e = (int)((__float_as_uint(v) + 0x007fffffu) >> 23) - 127;  // ceil(log2 v)
+  int t = 13 - e;
+  t = t > 100 ? 100 : (t < -100 ? -100 : t);
+  return v > 0.f ? __uint_as_float((unsigned)(t + 127) << 23) : 1.f;
+}
+
+// acc[c][t] = rows of tile t times the wave's column tile c, over KDIM inputs
+template <int KDIM, int AS, int CT, int RT>
+__device__ __forceinline__ void head_products(const unsigned short* __restrict__ pack, size_t part_stride,
+                                              const unsigned short* a, size_t a_part, int wave, int lane,
+                                              f32x16 (&acc)[CT][RT]) {
+  constexpr int KS = KDIM / 16, D = 2;
+  static_assert(KS % D == 0, "k-steps");
+  const int g = lane >> 5, l32 = lane & 31;
+  const u32x4* b0 = reinterpret_cast<const u32x4*>(pack) + (size_t)wave * CT * KS * 64 + lane;
+  const u32x4* b1 = reinterpret_cast<const u32x4*>(pack + part_stride) + (size_t)wave * CT * KS * 64 + lane;
+  const unsigned short* row = a + l32 * AS + 8 * g;
+  // sums of the small products: apart where the registers allow it (by the width alone, so that a pair's result does
+  // not depend on the tiles of its batch)
+  constexpr bool APART = CT == 1;
+  f32x16 low[APART ? CT : 1][APART ? RT : 1];
+#pragma unroll
+  for (int c = 0; c < CT; ++c)
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      acc[c][t] = f32x16{};
+      if constexpr (APART) low[c][t] = f32x16{};
+    }
+  auto lo = [&](int c, int t) __attribute__((always_inline)) -> f32x16& {
+    if constexpr (APART)
+      return low[c][t];
+    else
+      return acc[c][t];
+  };
+  u32x4 q0[D][CT], q1[D][CT];
+#pragma unroll
+  for (int d = 0; d < D; ++d)
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+      q0[d][c] = b0[(c * KS + d) * 64];
+      q1[d][c] = b1[(c * KS + d) * 64];
+    }
+#pragma unroll 1
+  for (int s0 = 0; s0 < KS; s0 += D) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      const int s = s0 + d;
+      u32x4 x0[RT], x1[RT];
+#pragma unroll
+      for (int t = 0; t < RT; ++t) {
+        x0[t] = *reinterpret_cast<const u32x4*>(row + 32 * t * AS + 16 * s);
+        x1[t] = *reinterpret_cast<const u32x4*>(row + a_part + 32 * t * AS + 16 * s);
+      }
+#pragma unroll
+      for (int c = 0; c < CT; ++c)
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+          lo(c, t) = mfma_k16(x1[t], q0[d][c], lo(c, t));
+          lo(c, t) = mfma_k16(x0[t], q1[d][c], lo(c, t));
+          acc[c][t] = mfma_k16(x0[t], q0[d][c], acc[c][t]);
+        }
+      const int n = s + D < KS ? s + D : s;  // (past the end: a repeated load that nothing uses)
+#pragma unroll
+      for (int c = 0; c < CT; ++c) {
+        q0[d][c] = b0[(c * KS + n) * 64];
+        q1[d][c] = b1[(c * KS + n) * 64];
+      }
+    }
+  }
+  if constexpr (APART)
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+      for (int t = 0; t < RT; ++t) acc[c][t] = acc[c][t] + low[c][t];
+}
+
+// The head as a chain of FP32 products for the pairs of a tile with a value or weight out of the halves' range: 32 at
+// a time, by the first four waves of the workgroup (all of it enters); zt and gt are [32][ld] tiles, ys receives the
+// raw outputs of the marked rows of T.
+template <int Z, int HH>
+__device__ __forceinline__ void head_chain(const Fp32Net& W, const NetArgs& A, int p0, int P, int T, float* zt, float* gt,
+                                           int ld, const int32_t* bad, float (*ys)[8]) {
+  constexpr int CT = HH / 128;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  for (int r0 = 0; r0 < T; r0 += 32) {
+    __syncthreads();
+    for (int e = tid; e < 32 * Z; e += 512) {
+      const int i = e / Z, k = e - i * Z, p = p0 + r0 + i;
+      const float v = p < P ? A.z[(size_t)p * Z + k] : 0.f;
+      zt[i * ld + k] = v == v ? v : 0.f;
+    }
+    __syncthreads();
+    for (int layer = 0; layer < 2; ++layer) {
+      const float* src = layer ? gt : zt;
+      float* dst = layer ? zt : gt;
+      const int KS = (layer ? HH : Z) / 2;
+      const float* pack = layer ? W.h2pack : W.h1pack;
+      const float* bias = layer ? W.c2 : W.c1;
+      f32x16 acc[CT];
+#pragma unroll
+      for (int c = 0; c < CT; ++c) acc[c] = f32x16{};
+      if (wave < 4)
+#pragma unroll 1
+        for (int s = 0; s < KS; ++s) {
+          const float av = src[l32 * ld + 2 * s + g];
+#pragma unroll
+          for (int c = 0; c < CT; ++c)
+            acc[c] = mfma32x32x2(av, pack[((size_t)(wave * CT + c) * KS + s) * 64 + lane], acc[c]);
+        }
+      __syncthreads();
+      if (wave < 4)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+          const int col = (wave * CT + c) * 32 + l32;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) dst[(8 * (r >> 2) + 4 * g + (r & 3)) * ld + col] = fmaxf(acc[c][r] + bias[col], 0.f);
+        }
+      __syncthreads();
+    }
+    if (tid < 256 && bad[r0 + (tid >> 3)]) {
+      const int i = tid >> 3, o = tid & 7;
+      float y = 0.f;
+      for (int k = 0; k < HH; ++k) y += zt[i * ld + k] * W.h3[(size_t)o * HH + k];
+      ys[r0 + i][o] = y + W.c3[o];
+    }
+  }
+  __syncthreads();
+}
+
+template <int Z, int HH, int RT>
+__global__ __launch_bounds__(512, 2) void head_split_kernel(Fp32Net W, NetArgs A) {
+  using S_t = HeadSmem<Z, HH, RT>;
+  constexpr int T = S_t::T, AS = S_t::AS, CT = HH / 256, KS3 = HH / 16;
+  constexpr size_t AP = (size_t)T * AS;
+  extern __shared__ __align__(16) unsigned char smem[];
+  S_t& S = *reinterpret_cast<S_t*>(smem);
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int p0 = blockIdx.x * T;
+  const int P = pair_count(A.n_pairs, A.n_pairs_dev);
+  if (p0 >= P) return;  // uniform
+  const int weights_bad = *W.split_bad;
+  if (tid < T) S.bad[tid] = weights_bad;
+  if (tid == 0) S.any_bad = weights_bad;
+  __syncthreads();
+
+  // the features of a pair per wave at a time: 4 consecutive ones per lane and load
+  constexpr int NL = (Z + 255) / 256;
+  for (int r = wave; r < T; r += 8) {
+    const int p = p0 + r;
+    float4 v[NL];
+    float mx = 0.f;
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+      v[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (p < P) v[k] = *reinterpret_cast<const float4*>(A.z + (size_t)p * Z + 256 * k + 4 * lane);
+      // an invalid pair's NaN features: its outputs are NaN-ed in the epilogue
+      v[k].x = v[k].x == v[k].x ? v[k].x : 0.f;
+      v[k].y = v[k].y == v[k].y ? v[k].y : 0.f;
+      v[k].z = v[k].z == v[k].z ? v[k].z : 0.f;
+      v[k].w = v[k].w == v[k].w ? v[k].w : 0.f;
+      mx = fmaxf(mx, fmaxf(fmaxf(fabsf(v[k].x), fabsf(v[k].y)), fmaxf(fabsf(v[k].z), fabsf(v[k].w))));
+    }
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) mx = fmaxf(mx, __shfl_xor(mx, d, 64));
+    const float sc = row_scale(mx);
+    if (lane == 0) {
+      S.top[r] = mx;
+      S.unscale[r] = 1.f / sc;
+      if (!(mx <= 0x1p100f)) S.bad[r] = S.any_bad = 1;
+    }
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+      float a = v[k].x * sc, b = v[k].y * sc, c = v[k].z * sc, d = v[k].w * sc;
+      uint2 h, l;
+      h.x = split_part(a, b);
+      h.y = split_part(c, d);
+      l.x = last_part(a, b);
+      l.y = last_part(c, d);
+      unsigned short* dst = &S.u.a[0][r * AS + 256 * k + 4 * lane];
+      *reinterpret_cast<uint2*>(dst) = h;
+      *reinterpret_cast<uint2*>(dst + AP) = l;
+    }
+  }
+  __syncthreads();
+
+  f32x16 acc[CT][RT];
+#pragma unroll
+  for (int layer = 0; layer < 2; ++layer) {
+    if (layer == 0)
+      head_products<Z, AS, CT, RT>(W.h1s, (size_t)HH * Z, S.u.a[0], AP, wave, lane, acc);
+    else
+      head_products<HH, AS, CT, RT>(W.h2s, (size_t)HH * HH, S.u.a[0], AP, wave, lane, acc);
+    __syncthreads();  // every wave has read the layer's inputs
+    const float* bias = layer ? W.c2 : W.c1;
+    const float* un = layer ? W.unscale_h2 : W.unscale_h1;
+    const float amp = W.head_bound[2 * layer], off = W.head_bound[2 * layer + 1];
+    float mx = 0.f;
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int r0 = 32 * t + 8 * q + 4 * g;
+        const float4 u4 = *reinterpret_cast<const float4*>(&S.unscale[r0]);
+        const float4 t4 = *reinterpret_cast<const float4*>(&S.top[r0]);
+        const float us[4] = {u4.x, u4.y, u4.z, u4.w}, tp[4] = {t4.x, t4.y, t4.z, t4.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float sc = row_scale(__builtin_fmaf(tp[e], amp, off));
+#pragma unroll
+          for (int c = 0; c < CT; ++c) {
+            const int col = (wave * CT + c) * 32 + l32;
+            const float v = vmax(__builtin_fmaf(acc[c][t][4 * q + e], us[e] * un[col], bias[col]), 0.f) * sc;
+            mx = vmax(mx, v);
+            const _Float16 h = (_Float16)v;
+            const _Float16 l = (_Float16)(v - (float)h);
+            unsigned short* dst = &S.u.a[0][(r0 + e) * AS + col];
+            dst[0] = __builtin_bit_cast(unsigned short, h);
+            dst[AP] = __builtin_bit_cast(unsigned short, l);
+          }
+        }
+      }
+    if (__ballot(!(mx <= kSplitLimit)) != 0) {  // rare: mark the rows
+#pragma unroll 1
+      for (int r = 0; r < T; ++r) {
+        float top = 0.f;
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+          const unsigned short h = S.u.a[0][r * AS + (wave * CT + c) * 32 + l32];
+          top = vmax(top, (float)__builtin_bit_cast(_Float16, h));  // infinite or NaN past the range
+        }
+        if (__ballot(!(top <= kSplitLimit)) != 0 && lane == 0) S.bad[r] = S.any_bad = 1;
+      }
+    }
+    __syncthreads();
+    if (tid < T) {  // the scale just used, and what bounds the next layer's input
+      const float b = __builtin_fmaf(S.top[tid], amp, off);
+      S.unscale[tid] = 1.f / row_scale(b);
+      S.top[tid] = b;
+      if (!(b <= 0x1p100f)) S.bad[tid] = S.any_bad = 1;
+    }
+    __syncthreads();
+  }
+
+  // layer 3: 8 outputs padded to 32 columns, the reduction split over the waves
+  {
+    constexpr int KW = KS3 / 8;
+    const u32x4* b0 = reinterpret_cast<const u32x4*>(W.h3s) + lane;
+    const u32x4* b1 = b0 + KS3 * 64;
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      f32x16 hi = f32x16{}, lo = f32x16{};
+      const unsigned short* row = &S.u.a[0][(32 * t + l32) * AS + 8 * g];
+#pragma unroll
+      for (int s = wave * KW; s < (wave + 1) * KW; ++s) {
+        const u32x4 x0 = *reinterpret_cast<const u32x4*>(row + 16 * s);
+        const u32x4 x1 = *reinterpret_cast<const u32x4*>(row + AP + 16 * s);
+        const u32x4 w0 = b0[s * 64], w1 = b1[s * 64];
+        lo = mfma_k16(x1, w0, lo);
+        hi = mfma_k16(x0, w0, hi);
+        lo = mfma_k16(x0, w1, lo);
+      }
+      if (l32 < 8)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) S.part[wave][32 * t + 8 * (r >> 2) + 4 * g + (r & 3)][l32] = hi[r] + lo[r];
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < T * 8; i += 512) {
+    const int r = i >> 3, j = i & 7;
+    float y = 0.f;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) y += S.part[w][r][j];
+    S.part[0][r][j] = __builtin_fmaf(y, S.unscale[r] * W.unscale_h3[j], W.c3[j]);
+  }
+  __syncthreads();
+  if (S.any_bad)  // uniform
+    head_chain<Z, HH>(W, A, p0, P, T, S.u.chain[0], S.u.chain[1], S_t::LZ, S.bad, S.part[0]);
+  if (tid < T && p0 + tid < P) {
+    const PairMeta mt = A.meta[p0 + tid];
+    post_contact(A.objs, mt.a, mt.swapped, S.part[0][tid], A.out, A.y_dbg, p0 + tid);
+  }
+}
+
+// ------------------------------------------------------------- weights, launch
+
+// Repacking, an element per thread: first the two gathers, then the halves of
+// W2, H1, H2 and H3, each row times its power of two, in the B operand order
+// of 32x32x16 products (W2's reduction index in layer 1's output order), and
+// layer 1's operand times its own; the flag word becomes 1 where a weight has
+// no halves.  One launch: training runs it every step.
+__global__ __launch_bounds__(256) void repack_kernel(RepackArgs A, SplitLayout L) {
+  char* const base = A.split;
+  const float* scale = reinterpret_cast<const float*>(base + L.scale);
+  int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < A.pack_n + A.tr_n) {
+    const int32_t k = i < A.pack_n ? A.pack_idx[i] : A.tr_idx[i - A.pack_n];
+    (i < A.pack_n ? A.pack[i] : A.tr[i - A.pack_n]) = k >= 0 ? A.raw[k] : 0.f;
+    return;
+  }
+  i -= A.pack_n + A.tr_n;
+  const float* raw = A.raw;
+  if (i < 8 * L.h1) {  // [W1 | b1 | 0][f][c], f = 32 ft + l % 32, c = 2 s + l / 32, at (4 ft + s) 64 + l
+    const int l = i & 63, f = 32 * (i >> 8) + l % 32, c = 2 * ((i >> 6) & 3) + l / 32;
+    reinterpret_cast<float*>(base + L.w1)[i] =
+        (c < 6 ? raw[6 * f + c] : (c == 6 ? raw[6 * L.h1 + f] : 0.f)) * scale[0];
+    return;
+  }
+  i -= 8 * L.h1;
+  const int n2 = L.h2 * L.h1, nh1 = L.hh * 2 * L.h2, nh2 = L.hh * L.hh, nh3 = 32 * L.hh;  // H3: 8 rows, zero to 32
+  if (i >= n2 + nh1 + nh2 + nh3) return;
+  const int mat = i < n2 ? 0 : (i < n2 + nh1 ? 1 : (i < n2 + nh1 + nh2 ? 2 : 3));
+  const int at = i - (mat == 0 ? 0 : (mat == 1 ? n2 : (mat == 2 ? n2 + nh1 : n2 + nh1 + nh2)));
+  const int count = mat == 0 ? n2 : (mat == 1 ? nh1 : (mat == 2 ? nh2 : nh3));
+  const int in = mat == 0 ? L.h1 : (mat == 1 ? 2 * L.h2 : L.hh), ks = in / 16;
+  const int e = at & 7, l = (at >> 3) & 63, s = (at >> 9) % ks, row = 32 * ((at >> 9) / ks) + l % 32;
+  const int k = mat == 0 ? perm_feature(s / 2, l / 32, 8 * (s % 2) + e) : 16 * s + 8 * (l / 32) + e;
+  const float* up = scale + kSplitScale0 + (mat == 0 ? 0 : (mat == 1 ? L.h2 : (mat == 2 ? L.h2 + L.hh : L.h2 + 2 * L.hh)));
+  const int oW2 = 7 * L.h1, oH1 = oW2 + n2 + L.h2, oH2 = oH1 + nh1 + L.hh, oH3 = oH2 + nh2 + L.hh;
+  const float* W = raw + (mat == 0 ? oW2 : (mat == 1 ? oH1 : (mat == 2 ? oH2 : oH3)));
+  float v = mat == 3 && row >= 8 ? 0.f : W[(size_t)row * in + k] * up[row];
+  if (!(__builtin_fabsf(v) <= kSplitLimit)) *reinterpret_cast<int32_t*>(base) = 1;
+  _Float16* dst =
+      reinterpret_cast<_Float16*>(base + (mat == 0 ? L.w2 : (mat == 1 ? L.H1 : (mat == 2 ? L.H2 : L.H3)))) + at;
+  const _Float16 h = (_Float16)v;
+  dst[0] = h;
+  dst[count] = (_Float16)(v - (float)h);
+}
+
+// Chunk sizes: half of what is left over the grid, 32 to 1.
+SplitChunks split_chunks(int n_pairs, int grid) {
+  SplitChunks c{};
+  c.grid = grid;
+  int left = n_pairs, base = 0;
+  for (int l = 0; l < SplitChunks::kLevels; ++l) {
+    int size = left / (2 * grid);
+    int claims = grid;
+    if (size >= kSplitChunk) {
+      size = kSplitChunk;
+      claims = (left - 2 * grid * kSplitChunk) / kSplitChunk + grid;
+    }
+    if (size < 1) size = 1;
+    c.size[l] = size;
+    c.base[l] = base;
+    c.claims[l] = claims;
+    base += size * claims;
+    left -= size * claims;
+    if (left < 0) left = 0;
+  }
+  return c;
+}
+
+template <int H1, int H2>
+hipError_t run_split(const Fp32Net& w, const NetArgs& a, int n_cu, hipStream_t s) {
+  const int slots = n_cu * (H2 >= 256 ? 1 : 2);  // workgroups the register file holds at once
+  const int grid = a.n_pairs < slots ? a.n_pairs : slots;
+  kernel_launch((encoder_split_kernel<H1, H2>), dim3(grid), dim3(2 * H2), 0, s, w, a, split_chunks(a.n_pairs, grid));
+  return hipGetLastError();
+}
+
+template <int Z, int HH, int RT>
+hipError_t run_head(const Fp32Net& w, const NetArgs& a, hipStream_t s) {
+  constexpr size_t smem = sizeof(HeadSmem<Z, HH, RT>);
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&head_split_kernel<Z, HH, RT>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+  if (e != hipSuccess) return e;
+  kernel_launch((head_split_kernel<Z, HH, RT>), dim3((a.n_pairs + 32 * RT - 1) / (32 * RT)), dim3(512), smem, s, w, a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_head_split(const Fp32Net& w, const NetArgs& a, int n_cu, hipStream_t s) {
+  if (a.n_pairs <= 0) return hipSuccess;
+  if (!w.h1s || !w.split_bad) return hipErrorInvalidValue;
+  // One tile per workgroup while every workgroup has a compute unit of its own (the weight stream is the same, the
+  // matrix work half); from there on two tiles halve the streams.
+  const bool two = a.n_pairs > 32 * n_cu;
+  if (w.h2 == 128 && w.hh == 256) return two ? run_head<256, 256, 2>(w, a, s) : run_head<256, 256, 1>(w, a, s);
+  if (w.h2 == 256 && w.hh == 512) return two ? run_head<512, 512, 2>(w, a, s) : run_head<512, 512, 1>(w, a, s);
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_encoder_split(const Fp32Net& w, const NetArgs& a, int n_cu, hipStream_t s) {
+  if (a.n_pairs <= 0) return hipSuccess;
+  if (!w.w2s || !w.split_bad) return hipErrorInvalidValue;
+  if (w.h1 == 64 && w.h2 == 128) return run_split<64, 128>(w, a, n_cu, s);
+  if (w.h1 == 128 && w.h2 == 256) return run_split<128, 256>(w, a, n_cu, s);
+  return hipErrorInvalidValue;
+}
+
+void split_bind(Fp32Net& w, const char* base) {
+  const SplitLayout L = split_layout(w.h1, w.h2, w.hh);
+  w.split_bad = reinterpret_cast<const int32_t*>(base);
+  const float* scale = reinterpret_cast<const float*>(base + L.scale);
+  w.head_bound = scale + 1;
+  w.unscale2 = scale + kSplitScale0 + L.h2 + 2 * L.hh + 8;
+  w.unscale_h1 = w.unscale2 + L.h2;
+  w.unscale_h2 = w.unscale_h1 + L.hh;
+  w.unscale_h3 = w.unscale_h2 + L.hh;
+  w.w1s = reinterpret_cast<const float*>(base + L.w1);
+  w.w2s = reinterpret_cast<const unsigned short*>(base + L.w2);
+  w.h1s = reinterpret_cast<const unsigned short*>(base + L.H1);
+  w.h2s = reinterpret_cast<const unsigned short*>(base + L.H2);
+  w.h3s = reinterpret_cast<const unsigned short*>(base + L.H3);
+}
+
+hipError_t launch_repack(const RepackArgs& a, hipStream_t s) {
+  const int h1 = a.h1, h2 = a.h2, hh = a.hh;
+  const int n = a.pack_n + a.tr_n + 8 * h1 + h2 * h1 + hh * 2 * h2 + hh * hh + 32 * hh;
+  kernel_launch(repack_kernel, dim3((n + 255) / 256), dim3(256), 0, s, a, split_layout(h1, h2, hh));
+  return hipGetLastError();
+}
+
+}  // namespace locc

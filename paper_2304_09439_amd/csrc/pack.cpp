@@ -114,6 +114,72 @@ void fp32_pack(const float* W1, const float* b1, const float* W2, const float* b
 }
 
 
+SplitLayout split_layout(int h1, int h2, int hh) {
+  SplitLayout L{h1, h2, hh, 0, 0, 0, 0, 0, 0, 0};
+  size_t o = 256;
+  L.scale = o; o = align256(o + split_scale_floats(h2, hh) * 4);
+  L.w1 = o; o = align256(o + (size_t)8 * h1 * 4);
+  L.w2 = o; o = align256(o + (size_t)h2 * h1 * 4);
+  L.H1 = o; o = align256(o + (size_t)hh * 2 * h2 * 4);
+  L.H2 = o; o = align256(o + (size_t)hh * hh * 4);
+  L.H3 = o; o = align256(o + (size_t)32 * hh * 4);
+  L.total = o;
+  return L;
+}
+
+void split_scales(const float* flat, int h1, int h2, int hh, float xmax, float nmax, float* scale) {
+  const float* W1 = flat;
+  const float* b1 = W1 + (size_t)h1 * 6;
+  const float* W2 = b1 + h1;
+  const float* H1 = W2 + (size_t)h2 * h1 + h2;
+  const float* c1 = H1 + (size_t)hh * 2 * h2;
+  const float* H2 = c1 + hh;
+  const float* c2 = H2 + (size_t)hh * hh;
+  const float* H3 = c2 + hh;
+  // exponent that takes v to (2^(top - 1), 2^top], within [-most, most]
+  auto shift = [](double v, int top, int most) {
+    if (!(v > 0.0) || !std::isfinite(v)) return 0;
+    int e;
+    if (std::frexp(v, &e) == 0.5) --e;  // v <= 2^e
+    return top - e < -most ? -most : (top - e > most ? most : top - e);
+  };
+  double bound = 0.0;
+  for (int f = 0; f < h1; ++f) {
+    const float* w = W1 + 6 * f;
+    const double b = (std::fabs((double)w[0]) + std::fabs((double)w[1]) + std::fabs((double)w[2])) * xmax +
+                     (std::fabs((double)w[3]) + std::fabs((double)w[4]) + std::fabs((double)w[5])) * nmax +
+                     std::fabs((double)b1[f]);
+    bound = bound > b ? bound : b;
+  }
+  const int s1 = shift(bound, 13, 24);
+  scale[0] = std::ldexp(1.f, s1);
+  auto most = [](const float* W, const float* c, int out, int in, float* at) {  // row sum, bias
+    double sum = 0.0;
+    for (int r = 0; r < out; ++r) {
+      double v = 0.0;
+      for (int k = 0; k < in; ++k) v += std::fabs((double)W[(size_t)r * in + k]);
+      sum = sum > v ? sum : v;
+    }
+    at[0] = (float)sum;
+    at[1] = amax_of(c, out);
+  };
+  most(H1, c1, hh, 2 * h2, scale + 1);
+  most(H2, c2, hh, hh, scale + 3);
+  float* up = scale + kSplitScale0;
+  float* down = up + h2 + 2 * hh + 8;
+  auto rows = [&](const float* W, int out, int in, int s_in) {
+    for (int r = 0; r < out; ++r) {
+      const int t = shift(amax_of(W + (size_t)r * in, in), 8, 100);
+      *up++ = std::ldexp(1.f, t);
+      *down++ = std::ldexp(1.f, -(s_in + t));
+    }
+  };
+  rows(W2, h2, h1, s1);
+  rows(H1, hh, 2 * h2, 0);
+  rows(H2, hh, hh, 0);
+  rows(H3, 8, hh, 0);
+}
+
 // ---------------------------------------------------------------- BF16
 // B operand of 32x32x16: lane l of k-step s of column tile ct holds H[32 ct + l % 32][16 s + 8 (l / 32) + e]
 // (rows from out to out_pad zero)

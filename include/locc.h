@@ -534,7 +534,7 @@ LOCC_API locc_status locc_serve_stop(locc_server* srv);
  * per-dispatch durations a kernel-trace profiler reports, plus event
  * overhead).  locc_profile(ctx, 1) clears the totals and starts recording,
  * locc_profile(ctx, 0) stops.  Kernel names: "crop", "encoder_fp32",
- * "head_fp32" (FP32 per-step path), "fused_bf16" (BF16, one launch),
+ * "head_fp32" (FP32 per-step path), "chain_features" (its gradients), "fused_bf16" (BF16, one launch),
  * "crop" and "encoder_head_bf16" (BF16 split schedule; "encoder_head_bf16_lds"
  * for its one-workgroup-per-CU kernel), "crop" and
  * "encoder_head_fp8" (LOCC_FP8) or "encoder_fp8_head_bf16"

@@ -491,10 +491,9 @@ void locc_destroy(locc_ctx* c) {
   (void)hipFree(c->d_wbf16);
   (void)hipFree(c->d_wfp8);
   (void)hipFree(c->d_wraw);
-  (void)hipFree(c->d_wgrad);
+  (void)hipFree(c->d_wfrag);
   (void)hipFree(c->d_wsplit);
   (void)hipFree(c->d_pack_idx);
-  (void)hipFree(c->d_tr_idx);
   (void)hipFree(c->d_train);
   (void)hipFree(c->d_amax);
   (void)hipFree(c->d_queue);
@@ -526,6 +525,7 @@ locc_status split_repack(locc_ctx* c) {
   ra.h1 = h1;
   ra.h2 = h2;
   ra.hh = hh;
+  ra.frag = c->d_wfrag;
   ra.split = c->d_wsplit;
   HIP_TRY(launch_repack(ra, nullptr));
   HIP_TRY(hipStreamSynchronize(nullptr));
@@ -562,20 +562,9 @@ locc_status locc_upload_weights(locc_ctx* c, const float* h, size_t n) {
   if (!c->d_wfp32) HIP_TRY(hipMalloc(&c->d_wfp32, pack.size() * sizeof(float)));
   HIP_TRY(hipMemcpy(c->d_wfp32, pack.data(), pack.size() * sizeof(float), hipMemcpyHostToDevice));
   if (c->cfg.precision == LOCC_FP32 || c->cfg.precision == LOCC_BF16) {
-    // the pose gradients read the plain weights, the two head matrices transposed and W2 transposed
-    std::vector<float> t((size_t)2 * h2 * hh + (size_t)hh * hh + (size_t)h1 * h2);
-    for (int o = 0; o < hh; ++o)
-      for (int k = 0; k < 2 * h2; ++k) t[(size_t)k * hh + o] = H1[(size_t)o * 2 * h2 + k];
-    float* t2 = t.data() + (size_t)2 * h2 * hh;
-    for (int o = 0; o < hh; ++o)
-      for (int k = 0; k < hh; ++k) t2[(size_t)k * hh + o] = H2[(size_t)o * hh + k];
-    float* t3 = t2 + (size_t)hh * hh;
-    for (int c = 0; c < h2; ++c)
-      for (int k = 0; k < h1; ++k) t3[(size_t)k * h2 + c] = W2[(size_t)c * h1 + k];
     if (!c->d_wraw) HIP_TRY(hipMalloc(&c->d_wraw, n * sizeof(float)));
-    if (!c->d_wgrad) HIP_TRY(hipMalloc(&c->d_wgrad, t.size() * sizeof(float)));
+    if (!c->d_wfrag) HIP_TRY(hipMalloc(&c->d_wfrag, 2 * ((size_t)2 * h2 * hh + (size_t)hh * hh) * sizeof(float)));
     HIP_TRY(hipMemcpy(c->d_wraw, h, n * sizeof(float), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(c->d_wgrad, t.data(), t.size() * sizeof(float), hipMemcpyHostToDevice));
     const SplitLayout SL = split_layout(h1, h2, hh);
     if (!c->d_wsplit) HIP_TRY(hipMalloc(&c->d_wsplit, SL.total));
     c->h_flat.assign(h, h + n);
@@ -592,21 +581,10 @@ locc_status locc_upload_weights(locc_ctx* c, const float* h, size_t n) {
     std::vector<float> pk(pack.size());
     fp32_pack(X, xb1, X + (W2 - W1), X + (b2 - W1), X + (H1 - W1), X + (c1 - W1), X + (H2 - W1),
               X + (c2 - W1), X + (H3 - W1), X + (c3 - W1), h1, h2, hh, pk.data());
-    std::vector<int32_t> pidx(pk.size()), tidx((size_t)2 * h2 * hh + (size_t)hh * hh + (size_t)h1 * h2);
+    std::vector<int32_t> pidx(pk.size());
     for (size_t k = 0; k < pk.size(); ++k) pidx[k] = (int32_t)pk[k] - 1;
-    const size_t oH1 = (size_t)(H1 - W1), oH2 = (size_t)(H2 - W1), oW2 = (size_t)(W2 - W1);
-    for (int o = 0; o < hh; ++o)
-      for (int k = 0; k < 2 * h2; ++k) tidx[(size_t)k * hh + o] = (int32_t)(oH1 + (size_t)o * 2 * h2 + k);
-    int32_t* ti2 = tidx.data() + (size_t)2 * h2 * hh;
-    for (int o = 0; o < hh; ++o)
-      for (int k = 0; k < hh; ++k) ti2[(size_t)k * hh + o] = (int32_t)(oH2 + (size_t)o * hh + k);
-    int32_t* ti3 = ti2 + (size_t)hh * hh;
-    for (int cc = 0; cc < h2; ++cc)
-      for (int k = 0; k < h1; ++k) ti3[(size_t)k * h2 + cc] = (int32_t)(oW2 + (size_t)cc * h1 + k);
     if (!c->d_pack_idx) HIP_TRY(hipMalloc(&c->d_pack_idx, pidx.size() * sizeof(int32_t)));
-    if (!c->d_tr_idx) HIP_TRY(hipMalloc(&c->d_tr_idx, tidx.size() * sizeof(int32_t)));
     HIP_TRY(hipMemcpy(c->d_pack_idx, pidx.data(), pidx.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(c->d_tr_idx, tidx.data(), tidx.size() * sizeof(int32_t), hipMemcpyHostToDevice));
     c->train_t = 0;  // new weights start a new optimisation
     if (c->d_train) HIP_TRY(hipMemset(c->d_train, 0, 3 * n * sizeof(float)));
   }
@@ -1093,8 +1071,9 @@ locc_status locc_pose_gradients(locc_ctx* c, const locc_object* objs, int32_t n_
   const size_t b_rows = align256(P * 2 * K * kRowFloats * sizeof(float)), b_z = align256(P * 2 * h2 * sizeof(float));
   const size_t b_rows16 = bf16 ? align256(P * 2 * K * 8 * sizeof(unsigned short)) : 0;
   const size_t b_idx = align256(P * 2 * K * sizeof(int32_t)), b_amax = align256(P * 2 * h2);
-  const size_t b_dm = align256(P * h2 * sizeof(float));
-  st = ensure_workspace(c, b_meta + b_setup + b_rows + b_z + b_rows16 + b_idx + b_amax + b_dm);
+  const size_t b_dm = align256(P * h2 * sizeof(float)), b_doubt = bf16 ? 0 : align256(P * 2 * (h2 / 32) * 4);
+  const size_t b_dpose = align256(P * 12 * sizeof(float));
+  st = ensure_workspace(c, b_meta + b_setup + b_rows + b_z + b_rows16 + b_idx + b_amax + b_dm + b_dpose + b_doubt);
   if (st != LOCC_OK) return st;
   char* b = static_cast<char*>(c->d_ws);
   PairMeta* meta = reinterpret_cast<PairMeta*>(b);
@@ -1112,11 +1091,15 @@ locc_status locc_pose_gradients(locc_ctx* c, const locc_object* objs, int32_t n_
   uint8_t* amax = reinterpret_cast<uint8_t*>(b);
   b += b_amax;
   float* dm = reinterpret_cast<float*>(b);
+  b += b_dm;
+  float* dpose = reinterpret_cast<float*>(b);
+  b += b_dpose;
+  uint32_t* doubt = bf16 ? nullptr : reinterpret_cast<uint32_t*>(b);
   CropArgs ca{objs, n_objs, pairs, n_pairs, nullptr, c->lib(), K, c->cfg.pad_m,
               idx, nullptr, meta, rows, rows16, c->d_err, setup};
   HIP_TRY(timed(c, "crop", s, [&] { return launch_crop(ca, s, c->sched.crop_unroll); }));
   const Fp32Net net = fp32_net(c);
-  NetArgs na{rows, meta, objs, n_pairs, nullptr, K, z, nullptr, out, amax, c->d_queue};
+  NetArgs na{rows, meta, objs, n_pairs, nullptr, K, z, nullptr, out, amax, c->d_queue, doubt};
   if (bf16) {
     // the BF16 encoder of the split schedule, recording the pooled features and the argmax rows
     FusedArgs fa{};
@@ -1145,11 +1128,14 @@ locc_status locc_pose_gradients(locc_ctx* c, const locc_object* objs, int32_t n_
                     [&] { return launch_encoder_bf16_argmax(fa, h1, h2, hh, grid, s); }));
     }
   } else {
-    if (out) {  // the contacts are locc_detect's, from its own encoder
-      HIP_TRY(timed(c, "encoder_split", s, [&] { return launch_encoder_split(net, na, c->n_cu, s); }));
-      HIP_TRY(timed(c, "head_fp32", s, [&] { return launch_head_split(net, na, c->n_cu, s); }));
-    }
-    HIP_TRY(timed(c, "encoder_fp32", s, [&] { return launch_encoder_fp32(net, na, c->n_cu, s); }));
+    HIP_TRY(timed(c, "encoder_fp32", s, [&] {
+      NetArgs ea = na;
+      if (!out) ea.z = nullptr;  // the chain's features alone are read
+      return launch_encoder_split(net, ea, c->n_cu, s);
+    }));
+    // the contacts are locc_detect's, on the split encoder's features
+    if (out) HIP_TRY(timed(c, "head_fp32", s, [&] { return launch_head_split(net, na, c->n_cu, s); }));
+    HIP_TRY(timed(c, "chain_features", s, [&] { return launch_chain_features(net, na, s); }));
   }
   if (out && bf16) HIP_TRY(timed(c, "head_fp32", s, [&] { return launch_head_split(net, na, c->n_cu, s); }));
   GradArgs ga{};
@@ -1163,6 +1149,7 @@ locc_status locc_pose_gradients(locc_ctx* c, const locc_object* objs, int32_t n_
   ga.z = z;
   ga.amax = amax;
   ga.dm = dm;
+  ga.dpose = dpose;
   ga.grad = grad;
   ga.K = K;
   ga.lib = c->lib();
@@ -1187,9 +1174,7 @@ locc_status locc_pose_gradients(locc_ctx* c, const locc_object* objs, int32_t n_
   ga.off.H3 = o;
   o += (size_t)8 * hh;
   ga.off.c3 = o;
-  ga.H1t = c->d_wgrad;
-  ga.H2t = c->d_wgrad + (size_t)2 * h2 * hh;
-  ga.W2t = ga.H2t + (size_t)hh * hh;
+  ga.frag = c->d_wfrag;
   ga.argmax_b = argmax_b;
   HIP_TRY(timed(c, "pose_grad", s, [&] { return launch_pose_gradients(ga, h1, h2, hh, s); }));
   return LOCC_OK;
@@ -1220,9 +1205,11 @@ locc_status locc_train_step(locc_ctx* c, const locc_object* objs, int32_t n_objs
   const size_t b_dm = align256(P * 2 * h2 * sizeof(float)), b_p = align256(P * 3 * sizeof(float));
   const size_t b_w1 = align256((size_t)kEncSplit * h2 * h1 * 7 * sizeof(float));
   const size_t b_w2 = align256((size_t)kEncSplit * h2 * (h1 + 1) * sizeof(float));
-  const size_t nk = (size_t)(hh > 2 * h2 ? hh : 2 * h2) + 1;
-  const size_t b_op = align256((size_t)kOuterSplit * hh * nk * sizeof(float));
-  st = ensure_workspace(c, base + b_amax + 4 * b_act + b_dm + b_p + b_w1 + b_w2 + b_op);
+  const size_t n_op[3] = {(size_t)kOuterSplit * hh * (hh + 1), (size_t)kOuterSplit * hh * (2 * h2 + 1),
+                          (size_t)kOuterSplit * (hh + 1)};
+  const size_t b_op = align256((n_op[0] + n_op[1] + n_op[2]) * sizeof(float));
+  const size_t b_doubt = align256(P * 2 * (h2 / 32) * sizeof(uint32_t));
+  st = ensure_workspace(c, base + b_amax + 4 * b_act + b_dm + b_p + b_w1 + b_w2 + b_op + b_doubt);
   if (st != LOCC_OK) return st;
   Workspace w{};
   st = carve(c, n_pairs, &w, nullptr);
@@ -1249,13 +1236,20 @@ locc_status locc_train_step(locc_ctx* c, const locc_object* objs, int32_t n_objs
   e += b_w1;
   ta.w2part = reinterpret_cast<float*>(e);
   e += b_w2;
-  ta.opart = reinterpret_cast<float*>(e);
+  float* opart = reinterpret_cast<float*>(e);
+  e += b_op;
+  uint32_t* doubt = reinterpret_cast<uint32_t*>(e);
   CropArgs ca{objs, n_objs, pairs, n_pairs, nullptr, c->lib(), K, c->cfg.pad_m,
               nullptr, nullptr, w.meta, w.rows, nullptr, c->d_err, w.setup};
   HIP_TRY(timed(c, "crop", s, [&] { return launch_crop(ca, s, c->sched.crop_unroll); }));
   const Fp32Net net = fp32_net(c);
-  NetArgs na{w.rows, w.meta, objs, n_pairs, nullptr, K, w.z, nullptr, nullptr, amax};
-  HIP_TRY(timed(c, "encoder_fp32", s, [&] { return launch_encoder_fp32(net, na, c->n_cu, s); }));
+  NetArgs na{w.rows, w.meta, objs, n_pairs, nullptr, K, w.z, nullptr, nullptr, amax, c->d_queue, doubt};
+  HIP_TRY(timed(c, "encoder_fp32", s, [&] {
+    NetArgs ea = na;
+    ea.z = nullptr;
+    return launch_encoder_split(net, ea, c->n_cu, s);
+  }));
+  HIP_TRY(timed(c, "chain_features", s, [&] { return launch_chain_features(net, na, s); }));
   ta.n_pairs = n_pairs;
   ta.meta = w.meta;
   ta.rows = w.rows;
@@ -1285,8 +1279,10 @@ locc_status locc_train_step(locc_ctx* c, const locc_object* objs, int32_t n_objs
   ta.off.H3 = o;
   o += (size_t)8 * hh;
   ta.off.c3 = o;
-  ta.H1t = c->d_wgrad;
-  ta.H2t = c->d_wgrad + (size_t)2 * h2 * hh;
+  ta.outer[0] = OuterJob{ta.du2, hh, hh, ta.g1, hh, hh, opart, ta.off.H2, ta.off.c2};
+  ta.outer[1] = OuterJob{ta.du1, hh, hh, w.z, 2 * h2, 2 * h2, opart + n_op[0], ta.off.H1, ta.off.c1};
+  ta.outer[2] = OuterJob{ta.dx, 1, 1, ta.g2, hh, hh, opart + n_op[0] + n_op[1], ta.off.H3, ta.off.c3};
+  ta.frag = c->d_wfrag;
   ta.grad = c->d_train;
   ta.m = c->d_train + n;
   ta.v = c->d_train + 2 * n;
@@ -1300,7 +1296,7 @@ locc_status locc_train_step(locc_ctx* c, const locc_object* objs, int32_t n_objs
   ta.corr2 = (float)(1.0 / (1.0 - std::pow((double)beta2, (double)t_next)));
   ta.loss = loss;
   ta.repack = RepackArgs{c->d_wraw, h1, h2, hh, c->d_wfp32, c->d_pack_idx, (int32_t)fp32_pack_floats(h1, h2, hh),
-                         c->d_wgrad, c->d_tr_idx, 2 * h2 * hh + hh * hh + h1 * h2, c->d_wsplit};
+                         c->d_wfrag, c->d_wsplit};
   if (argmax) HIP_TRY(hipMemcpyAsync(argmax, amax, P * 2 * h2, hipMemcpyDeviceToDevice, s));
   HIP_TRY(timed(c, "train", s, [&] { return launch_train_step(ta, h1, h2, hh, s); }));
   c->train_t = t_next;

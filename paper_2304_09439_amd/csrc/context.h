@@ -24,14 +24,13 @@ struct locc_ctx {
   unsigned char* d_wbf16 = nullptr;
   unsigned char* d_wfp8 = nullptr;
   float* d_wraw = nullptr;         // FP8 and FP32: the flat FP32 weights (calibration, pose gradients)
-  float* d_wgrad = nullptr;        // FP32: H1^T [2 h2][hh], H2^T [hh][hh], W2^T [h1][h2], for the pose gradients
+  float* d_wfrag = nullptr;        // FP32 and BF16: H1, H2, H2^T, H1^T in the gradient kernels' order
   char* d_wsplit = nullptr;        // FP32 and BF16: the halves of W2, H1, H2 (split_layout())
   std::vector<float> h_flat;       // FP32 and BF16: the weights as uploaded (the halves' scales)
   float lib_xmax = 1.f, lib_nmax = 1.f;  // the library's largest coordinate and normal component
-  // FP32 training: source index of every packed weight (d_wfp32, d_wgrad) in the flat vector (-1: zero),
+  // FP32 training: source index of every packed weight (d_wfp32) in the flat vector (-1: zero),
   // the gradient and the two Adam moments [3][n], and the step count
   int32_t* d_pack_idx = nullptr;
-  int32_t* d_tr_idx = nullptr;
   float* d_train = nullptr;
   int64_t train_t = 0;
   std::vector<float> h_w1b1;       // FP8: W1 then b1 (host), repacked when the activation scale changes

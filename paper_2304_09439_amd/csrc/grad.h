@@ -21,14 +21,13 @@ struct GradArgs {
   const float* z;         // [P][2 h2] pooled features
   const uint8_t* amax;    // [P][2][h2] argmax rows
   float* dm;              // [P][h2] workspace: d logit / d (second object's raw maxima)
+  float* dpose;           // [P][12] workspace: d logit / d (R_ab, t_ab)
   float* grad;            // [P][14] out
   int32_t K;
   DeviceLibrary lib;
   const float* raw;       // flat FP32 weights (device)
   GradOffsets off;
-  const float* H1t;       // [2 h2][hh]
-  const float* H2t;       // [hh][hh]
-  const float* W2t;       // [h1][h2]
+  const float* frag;      // H1, H2, H2^T, H1^T in the order of mfma_rows
   uint8_t* argmax_b;      // [P][h2] copy of the second object's argmax rows, or null
 };
 
@@ -42,6 +41,21 @@ hipError_t launch_pose_gradients(const GradArgs& a, int h1, int h2, int hh, hipS
 constexpr int kEncSplit = 16;    // pair ranges of the encoder weight gradients
 constexpr int kOuterSplit = 64;  // pair ranges of the head weight gradients
 
+// D[o][k] = sum over pairs of X[p][o] Y[p][k] (k < NK), and the plain sum of X[p][o] as column NK: the gradients of the
+// weights at w and the biases at b of the flat vector.
+struct OuterJob {
+  const float* X;
+  int32_t ldx, NO;
+  const float* Y;
+  int32_t ldy, NK;
+  float* part;            // [kOuterSplit][NO][NK + 1] partial sums
+  size_t w, b;
+  __host__ __device__ int nx() const { return (NK + 1 + 63) / 64; }
+  __host__ __device__ int ny() const { return (NO + 63) / 64; }
+  __host__ __device__ int blocks() const { return nx() * ny() * kOuterSplit; }
+  __host__ __device__ int reduce_blocks() const { return (NO * (NK + 1) + 255) / 256; }
+};
+
 struct TrainArgs {
   int32_t n_pairs;
   const PairMeta* meta;   // [P]
@@ -53,8 +67,7 @@ struct TrainArgs {
   float alpha;            // feature-norm weight
   float* raw;             // flat FP32 master weights (updated in place)
   GradOffsets off;
-  const float* H1t;       // [2 h2][hh] (of the weights before the step)
-  const float* H2t;       // [hh][hh]
+  const float* frag;      // H1, H2, H2^T, H1^T in the order of mfma_rows (of the weights before the step)
   // workspace
   float *g1, *g2, *du2, *du1;  // [P][hh]
   float* dmv;             // [P][2 h2]
@@ -62,14 +75,14 @@ struct TrainArgs {
   float* lossp;           // [P][2]: cross-entropy, squared feature norm
   float* w1part;          // [kEncSplit][h2][h1][7]: per pair-range and channel partials of dW1, db1
   float* w2part;          // [kEncSplit][h2][h1 + 1]: partials of dW2 and db2
-  float* opart;           // [kOuterSplit][hh][max(hh, 2 h2) + 1]: partial outer sums
+  OuterJob outer[3];      // H2, H1, the logit's row of H3
   // context state
   float* grad;            // [n] flat, same layout as the weights
   float *m, *v;           // Adam moments [n]
   size_t n;
   float lr, beta1, beta2, eps, corr1, corr2;  // corr = 1 / (1 - beta^t)
   float* loss;            // [2] out: mean cross-entropy, alpha x mean squared feature norm
-  RepackArgs repack;      // every packed form of the weights: the FP32 layout, H1^T, H2^T, W2^T, the halves
+  RepackArgs repack;      // every packed form of the weights
 };
 
 hipError_t launch_train_step(const TrainArgs& a, int h1, int h2, int hh, hipStream_t s);

@@ -3,23 +3,24 @@
 // The paper takes contact force and torque directions from the gradient of
 // the collision network's output with respect to the poses (Sec. II,
 // collision resolution with an object collision network).  After the crop
-// (with its index sets) and the FP32 encoder (recording per object and
-// channel the row of the largest raw layer-2 sum, the first on ties):
+// (with its index sets) and the encoder (recording per object and channel the
+// row of the largest raw layer-2 sum, the first on ties, and the features of
+// one FP32 chain per sum: net_split.hip, or the BF16 encoder):
 //
-//   head_backward_kernel  32 pairs per workgroup: u1 = H1 f + c1, u2 = H2
-//     ReLU(u1) + c2, then du2 = H3[0] (u2 > 0), du1 = (H2^T du2) (u1 > 0), and
-//     for the second object's channels dm = (H1^T du1)[h2 + c] (f > 0): four
-//     products on 16x16x4 FP32 matrix cores, the pairs' activations in LDS,
-//     each wave owning a quarter of the output columns, the weight rows
-//     (row-major [out][in]: H1, H2, H2^T, H1^T) read from L2 as float4.
-//   pose_kernel  one workgroup per pair, one thread per channel c of the
-//     second object: at its argmax row r the layer-1 pre-activation is
-//     recomputed (W1 in LDS), dr = W1^T ((W2[c] dm[c]) (W1 r + b1 > 0)) (W2
-//     read transposed, coalesced over c) gives the point
-//     and normal derivatives, and with the stored point p and normal n of
-//     that row dR_ab += dx p^T + dn n^T, dt_ab += dx; a block reduction, then
-//     one thread applies the chain rule through R_ab = R_a^T R_b, t_ab =
-//     R_a^T (p_b - p_a) and the quaternion polynomial in float64 and writes
+//   head_backward_kernel  32 pairs per workgroup of eight waves: u1 = H1 f +
+//     c1, u2 = H2 ReLU(u1) + c2, then du2 = H3[0] (u2 > 0), du1 = (H2^T du2)
+//     (u1 > 0), and for the second object's channels dm = (H1^T du1)[h2 + c]
+//     (f > 0): four products on 16x16x4 FP32 matrix cores, the pairs'
+//     activations in LDS, each wave owning an eighth of the output columns, the
+//     weights streamed from L2 in operand order.  16,384 pairs at width 512:
+//     0.288 ms, 105 of the 154 TFLOP/s a large FP32 product reaches (0.350 ms
+//     with four waves and row-major weights).
+//   pose_kernel  one workgroup per pair: with dr = W1^T ((W2[c] dm[c]) (W1 r +
+//     b1 > 0)) at channel c's argmax row r, and the stored point p and normal n
+//     of that row, dR_ab += dx p^T + dn n^T, dt_ab += dx.  0.162 ms (0.340 ms
+//     with a thread per channel), bound by the latency of its loads.
+//   pose_chain_kernel  a thread per pair: the chain rule through R_ab = R_a^T
+//     R_b, t_ab = R_a^T (p_b - p_a) and the quaternion polynomial in float64,
 //     the 14 derivatives in the caller's order.
 #include "geometry.h"
 #include "grad.h"
@@ -32,43 +33,55 @@ constexpr int kTT = 16;  // pairs per head-training workgroup (a 4,096-pair batc
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// acc[rt][ct] = In[16 RT rows][K] . W^T for this wave's columns c0 + 16 ct + (0..15), W row-major [out][K]
-// (ldw floats per row), with v_mfma_f32_16x16x4f32: A[i][k], B[k][j] with i, j = lane % 16 and the
-// reduction index permuted so that at k-step 4u + v lane group g = lane / 16 holds k = 16u + 4g + v,
-// which lets A (LDS rows) and B (weight rows) be read as float4.  D[i][j]: row 4g + r, column j.
+// acc[rt][ct] = In[16 RT rows][K] . M^T for the 16-column tiles t0 .. t0 + CT - 1 of M [out][K], with
+// v_mfma_f32_16x16x4f32: A[i][k], B[k][j] with i, j = lane % 16 and the reduction index permuted so that at k-step
+// 4u + v lane group g = lane / 16 holds k = 16u + 4g + v, which lets A (LDS rows) and B be read as float4.  M comes in
+// that order (the repacking writes it so: a load of a wave is 1 KB in a row, where rows of M would be 16 pieces of 64
+// bytes).  D[i][j]: row 4g + r, column j.
 template <int CT, int K, int RT = 2>
-__device__ __forceinline__ void mfma_rows32(const float* In, int IS, const float* __restrict__ W, int ldw, int c0,
-                                            int lane, f32x4 (&acc)[RT][CT]) {
+__device__ __forceinline__ void mfma_rows(const float* In, int IS, const float* __restrict__ M, int t0, int lane,
+                                          f32x4 (&acc)[RT][CT]) {
   const int j = lane & 15, g = lane >> 4;
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // the next step's weights load while this one's products run
+  const float4* wp = reinterpret_cast<const float4*>(M) + (size_t)t0 * (K / 16) * 64 + lane;
+  float4 n[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) n[ct] = wp[ct * (K / 16) * 64];
 #pragma unroll 2
   for (int u = 0; u < K / 16; ++u) {
     float4 b[CT];
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct)
-      b[ct] = *reinterpret_cast<const float4*>(W + (size_t)(c0 + 16 * ct + j) * ldw + 16 * u + 4 * g);
+    for (int ct = 0; ct < CT; ++ct) b[ct] = n[ct];
+    const int un = u + 1 < K / 16 ? u + 1 : u;  // (past the end: a repeated load that nothing uses)
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      const float4 a = *reinterpret_cast<const float4*>(In + (16 * rt + j) * IS + 16 * u + 4 * g);
+    for (int ct = 0; ct < CT; ++ct) n[ct] = wp[(ct * (K / 16) + un) * 64];
+    float4 a[RT];
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct) {
-        acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b[ct].x, acc[rt][ct], 0, 0, 0);
-        acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b[ct].y, acc[rt][ct], 0, 0, 0);
-        acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b[ct].z, acc[rt][ct], 0, 0, 0);
-        acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, b[ct].w, acc[rt][ct], 0, 0, 0);
-      }
-    }
+    for (int rt = 0; rt < RT; ++rt) a[rt] = *reinterpret_cast<const float4*>(In + (16 * rt + j) * IS + 16 * u + 4 * g);
+    // the four steps of a sum one after the other, the sums in turn, so that no product waits for the one before it
+    auto step = [&](auto el) __attribute__((always_inline)) {
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+          acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(el(a[rt]), el(b[ct]), acc[rt][ct], 0, 0, 0);
+    };
+    step([](const float4& v) { return v.x; });
+    step([](const float4& v) { return v.y; });
+    step([](const float4& v) { return v.z; });
+    step([](const float4& v) { return v.w; });
   }
 }
 
 template <int Z, int HH>
-__global__ __launch_bounds__(256) void head_backward_kernel(GradArgs A) {
+__global__ __launch_bounds__(512, 2) void head_backward_kernel(GradArgs A) {
   constexpr int H2 = Z / 2;
-  constexpr int CT = HH / 64;   // 16-column tiles per wave for the HH-wide products (4 waves)
-  constexpr int CT2 = H2 / 64;  // ... for the H2-wide one
+  constexpr int CT = HH / 128;  // 16-column tiles per wave for the HH-wide products (8 waves)
+  constexpr int CT2 = H2 / 128;  // ... for the H2-wide one
   constexpr int LA = (Z > HH ? Z : HH) + 4;  // +4: rows 16 B apart in the LDS banks
   constexpr int LB = HH + 4;
   extern __shared__ __align__(16) float smem[];
@@ -78,22 +91,24 @@ __global__ __launch_bounds__(256) void head_backward_kernel(GradArgs A) {
   const int j = lane & 15, g = lane >> 4;
   const int p0 = blockIdx.x * kGT;
   const int n = A.n_pairs - p0 < kGT ? A.n_pairs - p0 : kGT;
-  for (int e = t; e < kGT * Z; e += 256) {
+  for (int e = t; e < kGT * Z; e += 512) {
     const int r = e / Z, k = e % Z;
     float v = r < n ? A.z[(size_t)(p0 + r) * Z + k] : 0.f;
     As[r * LA + k] = v == v ? v : 0.f;  // invalid pair: NaN features, result discarded
   }
   __syncthreads();
   const float* raw = A.raw;
-  const float* H1 = raw + A.off.H1;  // [hh][2 h2]
+  const float* H1 = A.frag;
   const float* c1 = raw + A.off.c1;
-  const float* H2m = raw + A.off.H2;  // [hh][hh]
+  const float* H2m = H1 + (size_t)HH * Z;
+  const float* H2t = H2m + (size_t)HH * HH;
+  const float* H1t = H2t + (size_t)HH * HH;
   const float* c2 = raw + A.off.c2;
   const float* h3 = raw + A.off.H3;  // row 0: the logit
-  const int c0 = wave * (HH / 4);
+  const int c0 = wave * (HH / 8);
   f32x4 acc[2][CT];
   // u1 = f H1^T + c1 -> ReLU(u1) into B
-  mfma_rows32<CT, Z>(As, LA, H1, Z, c0, lane, acc);
+  mfma_rows<CT, Z>(As, LA, H1, c0 / 16, lane, acc);
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) {
     const int col = c0 + 16 * ct + j;
@@ -108,7 +123,7 @@ __global__ __launch_bounds__(256) void head_backward_kernel(GradArgs A) {
   }
   __syncthreads();
   // u2 = ReLU(u1) H2^T + c2 -> du2 = H3[0] (u2 > 0) into A
-  mfma_rows32<CT, HH>(Bs, LB, H2m, HH, c0, lane, acc);
+  mfma_rows<CT, HH>(Bs, LB, H2m, c0 / 16, lane, acc);
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) {
     const int col = c0 + 16 * ct + j;
@@ -121,7 +136,7 @@ __global__ __launch_bounds__(256) void head_backward_kernel(GradArgs A) {
   __syncthreads();
   // du1 = (du2 H2) (u1 > 0) into B: the weight rows are H2's columns (H2^T row-major); each lane reads
   // and rewrites only its own entries of B
-  mfma_rows32<CT, HH>(As, LA, A.H2t, HH, c0, lane, acc);
+  mfma_rows<CT, HH>(As, LA, H2t, c0 / 16, lane, acc);
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) {
     const int col = c0 + 16 * ct + j;
@@ -136,8 +151,8 @@ __global__ __launch_bounds__(256) void head_backward_kernel(GradArgs A) {
   __syncthreads();
   // dm[c] = (du1 H1)[h2 + c] (f[h2 + c] > 0): the weight rows are H1's columns h2 + c (H1^T rows)
   f32x4 acc2[2][CT2];
-  const int d0 = wave * (H2 / 4);
-  mfma_rows32<CT2, HH>(Bs, LB, A.H1t + (size_t)H2 * HH, HH, d0, lane, acc2);
+  const int d0 = wave * (H2 / 8);
+  mfma_rows<CT2, HH>(Bs, LB, H1t, (H2 + d0) / 16, lane, acc2);
 #pragma unroll
   for (int ct = 0; ct < CT2; ++ct) {
     const int col = d0 + 16 * ct + j;
@@ -154,7 +169,8 @@ __global__ __launch_bounds__(256) void head_backward_kernel(GradArgs A) {
   }
 }
 
-// Block-wide sum of 12 values (256 threads); the result is valid in thread 0.
+// Block-wide sums of 12 values (WAVES waves), into red[0].
+template <int WAVES>
 __device__ __forceinline__ void block_sum12(float (&v)[12], float (*red)[12]) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
 #pragma unroll
@@ -165,9 +181,8 @@ __device__ __forceinline__ void block_sum12(float (&v)[12], float (*red)[12]) {
 #pragma unroll
     for (int q = 0; q < 12; ++q) red[wave][q] = v[q];
   __syncthreads();
-  if (t == 0)
-#pragma unroll
-    for (int q = 0; q < 12; ++q) v[q] = (red[0][q] + red[1][q]) + (red[2][q] + red[3][q]);
+  if (t < 12)
+    for (int w = 1; w < WAVES; ++w) red[0][t] += red[w][t];
 }
 
 // d/dq of sum_ij G[i][j] R(q)[i][j] for the polynomial rotation of q = (w, x, y, z) as given.
@@ -179,57 +194,159 @@ __device__ __forceinline__ void rotation_grad(const float* qf, const double* G, 
   dq[3] = 2.0 * (-2.0 * G[0] * z - G[1] * w + G[2] * x + G[3] * w - 2.0 * G[4] * z + G[5] * y + G[6] * x + G[7] * y);
 }
 
+// One workgroup per pair.  The second object's channels with a gradient are
+// listed by their argmax row (a bitmap of channels per row, so the order does
+// not depend on timing); thread (k, half) owns hidden unit k and half of the
+// list: along a run of channels with the same row it adds up W2[c][k] dm[c],
+// applies the row's layer-1 mask once, and accumulates the sum, and its
+// products with the row's stored point and normal.  W1 enters once per thread
+// at the end.  A channel costs one multiply-add per hidden unit, a row about
+// fifteen; a thread per channel needed fourteen per channel and unit.
 template <int H1, int H2>
-__global__ __launch_bounds__(256) void pose_kernel(GradArgs A) {
-  __shared__ float red[4][12];
-  __shared__ float w1s[H1][8];  // W1 row and bias per hidden unit
-  const int p = blockIdx.x, t = threadIdx.x;
+__global__ __launch_bounds__(H2, 8) void pose_kernel(GradArgs A) {
+  static_assert(H2 == 2 * H1 && H2 % 64 == 0, "two threads per hidden unit, one per channel");
+  constexpr int NW = H2 / 32, WAVES = H2 / 64;
+  __shared__ float red[WAVES][12];
+  __shared__ int2 list[H2];                         // row << 16 | channel, dm
+  extern __shared__ __align__(16) unsigned char rowmem[];   // sized by K
+  float(*rowd)[12] = reinterpret_cast<float(*)[12]>(rowmem);  // per row: (x .. nz), the stored point and normal
+  uint32_t(*bits)[NW] = reinterpret_cast<uint32_t(*)[NW]>(rowmem + (size_t)A.K * 48);  // per row: its channels
+  int* start = reinterpret_cast<int*>(rowmem + (size_t)A.K * (48 + 4 * NW));
+  __shared__ int wsum[WAVES];
+  const int p = blockIdx.x, t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int k = t % H1, half = wave / (H1 / 64);
   const PairMeta mt = A.meta[p];
-  for (int e = t; e < H1 * 7; e += 256) {
-    const int k = e / 7, q = e % 7;
-    w1s[k][q] = q < 6 ? A.raw[A.off.W1 + 6 * k + q] : A.raw[A.off.b1 + k];
-  }
-  __syncthreads();
   float v[12];
 #pragma unroll
   for (int q = 0; q < 12; ++q) v[q] = 0.f;
   const int b = mt.a < 0 ? -1 : (mt.swapped ? A.pairs[2 * p] : A.pairs[2 * p + 1]);
-  if (A.argmax_b && t < H2)  // 255 where the second object has no rows (or the pair is invalid)
-    A.argmax_b[(size_t)p * H2 + t] = mt.a >= 0 && mt.m_b > 0 ? A.amax[((size_t)p * 2 + 1) * H2 + t] : (uint8_t)255;
-  if (mt.a >= 0 && mt.m_b > 0 && t < H2) {
-    const float dm = A.dm[(size_t)p * H2 + t];
-    if (dm != 0.f) {
-      const int r = A.amax[((size_t)p * 2 + 1) * H2 + t];
-      // row r of the second object, stored (x, z, ny, 1 | y, nx, nz, 0)
-      const float* row = A.rows + ((size_t)p * 2 * A.K + A.K + r) * kRowFloats;
-      const float4 lo = *reinterpret_cast<const float4*>(row), hi = *reinterpret_cast<const float4*>(row + 4);
-      const float x[6] = {lo.x, hi.x, lo.y, hi.y, lo.z, hi.z};
-      float dr[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-      for (int k = 0; k < H1; ++k) {
-        const float* wk = w1s[k];
-        const float pre = ((((wk[0] * x[0] + wk[1] * x[1]) + wk[2] * x[2]) + wk[3] * x[3]) + wk[4] * x[4]) +
-                          wk[5] * x[5] + wk[6];
-        const float d = pre > 0.f ? A.W2t[(size_t)k * H2 + t] * dm : 0.f;  // W2[c][k], coalesced over c
+  const int m = mt.a < 0 ? 0 : mt.m_b;
+  int r = 255;
+  float dm = 0.f;
+  if (m > 0) {
+    r = A.amax[((size_t)p * 2 + 1) * H2 + t];
+    dm = A.dm[(size_t)p * H2 + t];
+    if (r >= m) dm = 0.f;  // (no row above -inf: the feature is 0)
+  }
+  if (A.argmax_b)  // 255 where the second object has no rows (or the pair is invalid)
+    A.argmax_b[(size_t)p * H2 + t] = (uint8_t)r;
+  if (m > 0) {  // uniform
+    for (int e = t; e < m * NW; e += H2) (&bits[0][0])[e] = 0;
+    __syncthreads();
+    if (dm != 0.f) atomicOr(&bits[r][t >> 5], 1u << (t & 31));
+    __syncthreads();
+    // list position of each row: prefix of the rows' channel counts, H2 rows at a time
+    int n = 0;
+    for (int r0 = 0; r0 < m; r0 += H2) {
+      int c = 0;
+      if (r0 + t < m)
 #pragma unroll
-        for (int q = 0; q < 6; ++q) dr[q] = fmaf(wk[q], d, dr[q]);
+        for (int w = 0; w < NW; ++w) c += __popc(bits[r0 + t][w]);
+      int at = c;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const int o = __shfl_up(at, d, 64);
+        if (lane >= d) at += o;
       }
-      // the stored point and normal of that row (b's own frame)
-      const int cpos = 1 ^ mt.swapped;
-      const int s = A.idx[((size_t)p * 2 + cpos) * A.K + r];
-      const int pt = A.lib.shapes[A.objs[b].shape].off + s;
-      const float ps[3] = {A.lib.px[pt], A.lib.py[pt], A.lib.pz[pt]};
-      const float ns[3] = {A.lib.nx[pt], A.lib.ny[pt], A.lib.nz[pt]};
+      if (lane == 63) wsum[wave] = at;
+      __syncthreads();
+      int before = n;
 #pragma unroll
-      for (int i = 0; i < 3; ++i) {
+      for (int w = 0; w < WAVES; ++w) {
+        before += w < wave ? wsum[w] : 0;
+        n += wsum[w];
+      }
+      if (r0 + t < m) start[r0 + t] = before + at - c;
+      if (c > 0) {
+        // the row, stored (x, z, ny, 1 | y, nx, nz, 0), and its stored point and normal (b's own frame)
+        const float* row = A.rows + ((size_t)p * 2 * A.K + A.K + r0 + t) * kRowFloats;
+        const float4 lo = *reinterpret_cast<const float4*>(row), hi = *reinterpret_cast<const float4*>(row + 4);
+        const int pt = A.lib.shapes[A.objs[b].shape].off +
+                       A.idx[((size_t)p * 2 + (1 ^ mt.swapped)) * A.K + r0 + t];
+        float4* d = reinterpret_cast<float4*>(rowd[r0 + t]);
+        d[0] = make_float4(lo.x, hi.x, lo.y, hi.y);
+        d[1] = make_float4(lo.z, hi.z, A.lib.px[pt], A.lib.py[pt]);
+        d[2] = make_float4(A.lib.pz[pt], A.lib.nx[pt], A.lib.ny[pt], A.lib.nz[pt]);
+      }
+      __syncthreads();
+    }
+    if (dm != 0.f) {
+      int pos = start[r] + __popc(bits[r][t >> 5] & ((1u << (t & 31)) - 1u));
 #pragma unroll
-        for (int j = 0; j < 3; ++j) v[3 * i + j] = dr[i] * ps[j] + dr[3 + i] * ns[j];
-        v[9 + i] = dr[i];
+      for (int w = 0; w < NW; ++w) pos += w < (t >> 5) ? __popc(bits[r][w]) : 0;
+      list[pos] = make_int2(r << 16 | t, __float_as_int(dm));
+    }
+    __syncthreads();
+    float wk[7];
+#pragma unroll
+    for (int q = 0; q < 6; ++q) wk[q] = A.raw[A.off.W1 + 6 * k + q];
+    wk[6] = A.raw[A.off.b1 + k];
+    const float* __restrict__ w2 = A.raw + A.off.W2 + k;
+    float T[3] = {0.f, 0.f, 0.f}, N[3] = {0.f, 0.f, 0.f}, T0 = 0.f, acc = 0.f;
+    auto finish = [&](int row) __attribute__((always_inline)) {  // a run of channels of one row ends
+      const float4* d = reinterpret_cast<const float4*>(rowd[row]);
+      const float4 d0 = d[0], d1 = d[1], d2 = d[2];
+      // the order of the additions decides the mask of a pre-activation near 0
+      float pre = __builtin_fmaf(wk[0], d0.x, wk[1] * d0.y);
+      pre = __builtin_fmaf(wk[2], d0.z, pre);
+      pre = __builtin_fmaf(wk[3], d0.w, pre);
+      pre = __builtin_fmaf(wk[4], d1.x, pre);
+      pre = __builtin_fmaf(wk[5], d1.y, pre);
+      pre += wk[6];
+      const float val = pre > 0.f ? acc : 0.f;
+      T0 += val;
+      T[0] = __builtin_fmaf(val, d1.z, T[0]);
+      T[1] = __builtin_fmaf(val, d1.w, T[1]);
+      T[2] = __builtin_fmaf(val, d2.x, T[2]);
+      N[0] = __builtin_fmaf(val, d2.y, N[0]);
+      N[1] = __builtin_fmaf(val, d2.z, N[1]);
+      N[2] = __builtin_fmaf(val, d2.w, N[2]);
+      acc = 0.f;
+    };
+    constexpr int U = 8;  // list entries whose weights load together
+    const int mid = (n + 1) / 2, e0 = half ? mid : 0, e1 = half ? n : mid;
+    int row = -1;
+    for (int e = e0; e < e1; e += U) {
+      int code[U];
+      float d[U], w[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int2 en = list[e + u < e1 ? e + u : e1 - 1];
+        code[u] = __builtin_amdgcn_readfirstlane(en.x);
+        d[u] = e + u < e1 ? __int_as_float(en.y) : 0.f;
+        w[u] = w2[(size_t)(code[u] & 0xffff) * H1];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if ((code[u] >> 16) != row) {  // uniform
+          if (row >= 0) finish(row);
+          row = code[u] >> 16;
+        }
+        acc = __builtin_fmaf(w[u], d[u], acc);
       }
     }
+    if (row >= 0) finish(row);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+#pragma unroll
+      for (int j = 0; j < 3; ++j) v[3 * i + j] = wk[i] * T[j] + wk[3 + i] * N[j];
+      v[9 + i] = wk[i] * T0;
+    }
   }
-  block_sum12(v, red);
-  if (t != 0) return;
+  block_sum12<WAVES>(v, red);
+  if (t < 12) A.dpose[(size_t)p * 12 + t] = red[0][t];
+}
+
+// The chain rule from (dR_ab, dt_ab) to the poses, a thread per pair (float64).
+__global__ __launch_bounds__(64) void pose_chain_kernel(GradArgs A) {
+  const int p = blockIdx.x * 64 + threadIdx.x;
+  if (p >= A.n_pairs) return;
+  const PairMeta mt = A.meta[p];
+  const int b = mt.a < 0 ? -1 : (mt.swapped ? A.pairs[2 * p] : A.pairs[2 * p + 1]);
+  const float4* dv = reinterpret_cast<const float4*>(A.dpose + (size_t)p * 12);
+  const float4 v0 = dv[0], v1 = dv[1], v2 = dv[2];
+  const float v[12] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w, v2.x, v2.y, v2.z, v2.w};
   float* out = A.grad + (size_t)p * 14;
   if (mt.a < 0) {
     for (int q = 0; q < 14; ++q) out[q] = __builtin_nanf("");
@@ -282,8 +399,9 @@ hipError_t run(const GradArgs& a, hipStream_t s) {
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&head_backward_kernel<2 * H2, HH>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;
-  kernel_launch((head_backward_kernel<2 * H2, HH>), dim3((a.n_pairs + kGT - 1) / kGT), dim3(256), smem, s, a);
-  kernel_launch((pose_kernel<H1, H2>), dim3(a.n_pairs), dim3(256), 0, s, a);
+  kernel_launch((head_backward_kernel<2 * H2, HH>), dim3((a.n_pairs + kGT - 1) / kGT), dim3(512), smem, s, a);
+  kernel_launch((pose_kernel<H1, H2>), dim3(a.n_pairs), dim3(H2), (uint32_t)(a.K * (48 + H2 / 8 + 4)), s, a);
+  kernel_launch(pose_chain_kernel, dim3((a.n_pairs + 63) / 64), dim3(64), 0, s, a);
   return hipGetLastError();
 }
 
@@ -302,17 +420,18 @@ hipError_t launch_pose_gradients(const GradArgs& a, int h1, int h2, int hh, hipS
 //
 // One step of fitting the FP32 network to collision labels (binary
 // cross-entropy of the logit plus alpha times the squared norm of the pooled
-// features, Adam): head_train_kernel (16 pairs per workgroup, the head
-// forward and backward on matrix cores, keeping per pair g1, g2, du2, du1,
-// the pooled features' gradient dm, dx and the two loss terms);
-// outer_sum_kernel reduces the head's weight and bias gradients over 64
-// ranges of pairs on matrix cores and outer_reduce_kernel sums the ranges;
-// enc_grad_kernel (one workgroup per channel and range of pairs) walks its
-// (pair, object) entries in order, staging 256 argmax rows at a time in LDS,
-// and train_reduce_kernel sums the partials of dW2, db2, dW1, db1 and the
-// loss terms; adam_kernel updates the master weights; one launch
-// repacks them into the layouts the forward and gradient kernels read.  Every
-// reduction has a fixed order, so a step is reproducible bit for bit.
+// features, Adam), four launches after the crop and the encoder:
+// head_train_kernel (16 pairs per workgroup, the head forward and backward on
+// matrix cores, keeping per pair g1, g2, du2, du1, the pooled features'
+// gradient dm, dx and the two loss terms); train_partials_kernel, the head's
+// weight and bias gradients as outer sums over 64 ranges of pairs on matrix
+// cores, and the encoder's (one workgroup per channel and range of pairs walks
+// its (pair, object) entries in order, staging 256 argmax rows at a time in
+// LDS); train_reduce_kernel, which sums the ranges in order and updates each
+// weight where its gradient is complete; and the repacking of the weights into
+// the layouts the kernels read.  Every reduction has a fixed order, so a step is
+// reproducible bit for bit.  4,096 pairs at widths 64 / 128 / 256: 0.247 ms a step,
+// 0.280 ms with eleven launches (137 pairs: 0.156 and 0.165 ms).
 namespace locc {
 namespace {
 
@@ -335,9 +454,11 @@ __global__ __launch_bounds__(256) void head_train_kernel(TrainArgs A, float invB
   }
   __syncthreads();
   const float* raw = A.raw;
-  const float* H1 = raw + A.off.H1;
+  const float* H1 = A.frag;
   const float* c1 = raw + A.off.c1;
-  const float* H2m = raw + A.off.H2;
+  const float* H2m = H1 + (size_t)HH * Z;
+  const float* H2t = H2m + (size_t)HH * HH;
+  const float* H1t = H2t + (size_t)HH * HH;
   const float* c2 = raw + A.off.c2;
   const float* h3 = raw + A.off.H3;
   // squared feature norm per pair (a wave per 8 pairs)
@@ -352,7 +473,7 @@ __global__ __launch_bounds__(256) void head_train_kernel(TrainArgs A, float invB
   const int c0 = wave * (HH / 4);
   f32x4 acc[RT][CT];
   // g1 = ReLU(f H1^T + c1) -> B
-  mfma_rows32<CT, Z, RT>(As, LA, H1, Z, c0, lane, acc);
+  mfma_rows<CT, Z, RT>(As, LA, H1, c0 / 16, lane, acc);
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) {
     const int col = c0 + 16 * ct + j;
@@ -370,7 +491,7 @@ __global__ __launch_bounds__(256) void head_train_kernel(TrainArgs A, float invB
   }
   __syncthreads();
   // g2 = ReLU(g1 H2^T + c2) -> A (f is no longer needed in LDS)
-  mfma_rows32<CT, HH, RT>(Bs, LB, H2m, HH, c0, lane, acc);
+  mfma_rows<CT, HH, RT>(Bs, LB, H2m, c0 / 16, lane, acc);
   __syncthreads();
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) {
@@ -421,7 +542,7 @@ __global__ __launch_bounds__(256) void head_train_kernel(TrainArgs A, float invB
   }
   __syncthreads();
   // du1 = (du2 H2) (g1 > 0) -> B
-  mfma_rows32<CT, HH, RT>(As, LA, A.H2t, HH, c0, lane, acc);
+  mfma_rows<CT, HH, RT>(As, LA, H2t, c0 / 16, lane, acc);
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) {
     const int col = c0 + 16 * ct + j;
@@ -440,7 +561,7 @@ __global__ __launch_bounds__(256) void head_train_kernel(TrainArgs A, float invB
   // dz = du1 H1 + (2 alpha / B) f; dm = dz (f > 0), both objects
   f32x4 accz[RT][CTZ];
   const int d0 = wave * (Z / 4);
-  mfma_rows32<CTZ, HH, RT>(Bs, LB, A.H1t, HH, d0, lane, accz);
+  mfma_rows<CTZ, HH, RT>(Bs, LB, H1t, d0 / 16, lane, accz);
   const float reg = 2.f * A.alpha * invB;
 #pragma unroll
   for (int ct = 0; ct < CTZ; ++ct) {
@@ -464,14 +585,22 @@ __global__ __launch_bounds__(256) void head_train_kernel(TrainArgs A, float invB
 // v_mfma_f32_32x32x2f32 (A[i][q] = X[p + q][o0 + i], B[q][j] = Y[p + q][k0 + j]: lanes 0-31 carry pair
 // p, lanes 32-63 pair p + 1); 32 pairs at a time through LDS, in ascending order within the range.
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-__global__ __launch_bounds__(256) void outer_sum_kernel(const float* X, int ldx, int NO, const float* Y, int ldy,
-                                                        int NK, int P, float* part) {
-  constexpr int PS = 32;        // pairs per stage
+constexpr int kOuterStage = 32;  // pairs per stage
+struct OuterShared {
+  float xs[kOuterStage][64], ys[kOuterStage][64];
+};
+__device__ __forceinline__ void outer_sum(const OuterJob& J, int P, int block, OuterShared& S) {
+  constexpr int PS = kOuterStage;
   constexpr int PT = PS / 4;    // stage rows loaded per thread (one column each of X and Y)
-  __shared__ float xs[PS][64], ys[PS][64];
+  auto& xs = S.xs;
+  auto& ys = S.ys;
+  const float* X = J.X;
+  const float* Y = J.Y;
+  const int ldx = J.ldx, NO = J.NO, ldy = J.ldy, NK = J.NK;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int wo = wave >> 1, wk = wave & 1, l32 = lane & 31, half = lane >> 5;
-  const int o0 = blockIdx.y * 64, k0 = blockIdx.x * 64, z = blockIdx.z;
+  const int nx = J.nx(), ny = J.ny();
+  const int o0 = block / nx % ny * 64, k0 = block % nx * 64, z = block / (nx * ny);
   const int chunk = (P + kOuterSplit - 1) / kOuterSplit;
   const int pa = z * chunk, pe = pa + chunk < P ? pa + chunk : P;
   // thread t loads rows t / 64 + 4 i (i < PT) of column t % 64 of a stage; the next stage's values are
@@ -505,7 +634,7 @@ __global__ __launch_bounds__(256) void outer_sum_kernel(const float* X, int ldx,
                                                  0, 0);
     __syncthreads();
   }
-  float* dst = part + (size_t)z * NO * (NK + 1);
+  float* dst = J.part + (size_t)z * NO * (NK + 1);
   const int k = k0 + 32 * wk + l32;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
@@ -514,32 +643,45 @@ __global__ __launch_bounds__(256) void outer_sum_kernel(const float* X, int ldx,
   }
 }
 
-// D[o][k] = sum_z part[z][o][k] (ranges in order); column NK goes to Dbias[o].
-__global__ __launch_bounds__(256) void outer_reduce_kernel(const float* part, int NO, int NK, float* D, int ldd,
-                                                           float* Dbias) {
-  const int id = blockIdx.x * 256 + threadIdx.x;
-  if (id >= NO * (NK + 1)) return;
-  const int o = id / (NK + 1), k = id % (NK + 1);
+// Adam on weight i with gradient gr (kept for locc_get_weights).
+__device__ __forceinline__ void adam(const TrainArgs& A, size_t i, float gr) {
+  A.grad[i] = gr;
+  const float m = __builtin_fmaf(1.f - A.beta1, gr, A.beta1 * A.m[i]);
+  const float v = __builtin_fmaf((1.f - A.beta2) * gr, gr, A.beta2 * A.v[i]);
+  A.m[i] = m;
+  A.v[i] = v;
+  A.raw[i] -= A.lr * (m * A.corr1) / (sqrtf(v * A.corr2) + A.eps);
+}
+
+// D[o][k] = sum_z part[z][o][k] (ranges in order); column NK is the bias gradient of o.
+__device__ __forceinline__ void outer_reduce(const TrainArgs& A, const OuterJob& J, int block) {
+  const int id = block * 256 + threadIdx.x;
+  if (id >= J.NO * (J.NK + 1)) return;
+  const int o = id / (J.NK + 1), k = id % (J.NK + 1);
   float s = 0.f;
-  for (int z = 0; z < kOuterSplit; ++z) s += part[(size_t)z * NO * (NK + 1) + id];
-  if (k < NK)
-    D[(size_t)o * ldd + k] = s;
-  else
-    Dbias[o] = s;
+#pragma unroll 16
+  for (int z = 0; z < kOuterSplit; ++z) s += J.part[(size_t)z * J.NO * (J.NK + 1) + id];
+  adam(A, k < J.NK ? J.w + (size_t)o * J.NK + k : J.b + o, s);
 }
 
 // Encoder weight-gradient partials: workgroup (c, z) stages the (pair, object) entries of range z, 256
 // at a time, in LDS (channel c's dm and argmax row); thread t handles hidden unit j = t % H1 and the
 // staged entries i = t / H1 (mod 256 / H1) in ascending order, for channel c's dW2 row and db2 and its
 // partials of dW1, db1; the 256 / H1 streams are then added in stream order.
+template <int H1>
+struct EncShared {
+  float srow[256][8];
+  float sdm[256];
+  float red[256 / H1 - 1][H1][9];
+};
 template <int H1, int H2>
-__global__ __launch_bounds__(256) void enc_grad_kernel(TrainArgs A) {
+__device__ __forceinline__ void enc_grad(const TrainArgs& A, int block, EncShared<H1>& S) {
   constexpr int NS = 256 / H1;  // entry streams per hidden unit
-  static_assert(256 % H1 == 0, "hidden width");
-  __shared__ float srow[256][8];
-  __shared__ float sdm[256];
-  __shared__ float red[NS > 1 ? NS - 1 : 1][H1][9];
-  const int c = blockIdx.x, z = blockIdx.y, t = threadIdx.x, j = t % H1, st = t / H1;
+  static_assert(256 % H1 == 0 && NS > 1, "hidden width");
+  auto& srow = S.srow;
+  auto& sdm = S.sdm;
+  auto& red = S.red;
+  const int c = block % H2, z = block / H2, t = threadIdx.x, j = t % H1, st = t / H1;
   float wk[6], bk, w2ck;
 #pragma unroll
   for (int q = 0; q < 6; ++q) wk[q] = A.raw[A.off.W1 + 6 * j + q];
@@ -629,10 +771,7 @@ __device__ __forceinline__ void enc_reduce_w2(const TrainArgs& A, int block) {
   float s = 0.f;
   for (int z = 0; z < kEncSplit; ++z) s += A.w2part[(size_t)z * H2 * (H1 + 1) + id];
   const int c = id / (H1 + 1), k = id % (H1 + 1);
-  if (k < H1)
-    A.grad[A.off.W2 + (size_t)c * H1 + k] = s;
-  else
-    A.grad[A.off.b2 + c] = s;
+  adam(A, k < H1 ? A.off.W2 + (size_t)c * H1 + k : A.off.b2 + c, s);
 }
 
 // dW1, db1: one wave per output (hidden unit k, column q) over the kEncSplit x H2 partials: lane l adds
@@ -647,12 +786,7 @@ __device__ __forceinline__ void enc_reduce_w1(const TrainArgs& A, int block) {
   for (int i = lane; i < NP; i += 64) s += A.w1part[((size_t)i * H1 + k) * 7 + q];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-  if (lane == 0) {
-    if (q < 6)
-      A.grad[A.off.W1 + 6 * k + q] = s;
-    else
-      A.grad[A.off.b1 + k] = s;
-  }
+  if (lane == 0) adam(A, q < 6 ? A.off.W1 + 6 * k + q : A.off.b1 + k, s);
 }
 
 // Mean loss terms, summed in a fixed order by one workgroup.
@@ -680,30 +814,53 @@ __device__ __forceinline__ void loss_sum(const TrainArgs& A, float invB) {
   }
 }
 
-// The reductions after enc_grad_kernel in one launch: blocks [0, B2) reduce dW2 / db2, the next B1 blocks
-// dW1 / db1, the last one the loss terms.
+// Every partial sum of the weight gradients in one launch (none reads another's): the workgroups of the encoder's
+// gradients first, which take longest, then those of the three outer sums.
+template <int H1, int H2>
+__global__ __launch_bounds__(256) void train_partials_kernel(TrainArgs A) {
+  __shared__ union Shared {
+    OuterShared outer;
+    EncShared<H1> enc;
+  } S;
+  int b = blockIdx.x;  // uniform
+  if (b < H2 * kEncSplit) {
+    enc_grad<H1, H2>(A, b, S.enc);
+    return;
+  }
+  b -= H2 * kEncSplit;
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    if (b < A.outer[j].blocks()) {
+      outer_sum(A.outer[j], A.n_pairs, b, S.outer);
+      return;
+    }
+    b -= A.outer[j].blocks();
+  }
+}
+
+// Every reduction, and Adam on each weight by the thread that has its gradient: blocks [0, B2) dW2 / db2, the next B1
+// dW1 / db1, one the loss terms, then the three outer sums.  The weights of the untrained outputs (their rows of H3 and
+// c3) have no gradient and zero moments, and stay as they are.
 template <int H1, int H2>
 __global__ __launch_bounds__(256) void train_reduce_kernel(TrainArgs A, float invB) {
   constexpr int B2 = (H2 * (H1 + 1) + 255) / 256, B1 = (H1 * 7 + 3) / 4;
-  const int b = blockIdx.x;  // uniform
-  if (b < B2)
+  int b = blockIdx.x;  // uniform
+  if (b == 0 && threadIdx.x == 0) *reinterpret_cast<int32_t*>(A.repack.split) = 0;  // set by the repacking that follows
+  if (b < B2) {
     enc_reduce_w2<H1, H2>(A, b);
-  else if (b < B2 + B1)
+  } else if (b < B2 + B1) {
     enc_reduce_w1<H1, H2>(A, b - B2);
-  else
+  } else if (b == B2 + B1) {
     loss_sum(A, invB);
-}
-
-__global__ __launch_bounds__(256) void adam_kernel(TrainArgs A) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= A.n) return;
-  if (i == 0) *reinterpret_cast<int32_t*>(A.repack.split) = 0;  // set by the repacking that follows
-  const float gr = A.grad[i];
-  const float m = A.beta1 * A.m[i] + (1.f - A.beta1) * gr;
-  const float v = A.beta2 * A.v[i] + (1.f - A.beta2) * gr * gr;
-  A.m[i] = m;
-  A.v[i] = v;
-  A.raw[i] -= A.lr * (m * A.corr1) / (sqrtf(v * A.corr2) + A.eps);
+  } else {
+    b -= B2 + B1 + 1;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const int n = A.outer[j].reduce_blocks();
+      if (b >= 0 && b < n) outer_reduce(A, A.outer[j], b);
+      b -= n;
+    }
+  }
 }
 
 template <int H1, int H2, int HH>
@@ -718,21 +875,13 @@ hipError_t run_train(const TrainArgs& a, hipStream_t s) {
   if (e != hipSuccess) return e;
   const int P = a.n_pairs;
   kernel_launch((head_train_kernel<Z, HH>), dim3((P + kTT - 1) / kTT), dim3(256), smem, s, a, invB);
-  const GradOffsets& o = a.off;
-  // dH3[0], dc3[0]; dH2, dc2; dH1, dc1: partial outer sums over pair ranges, then ordered reductions
-  auto outer = [&](const float* X, int ldx, int NO, const float* Y, int ldy, int NK, float* D, float* Db) {
-    kernel_launch(outer_sum_kernel, dim3((NK + 1 + 63) / 64, (NO + 63) / 64, kOuterSplit), dim3(256), 0, s, X,
-                       ldx, NO, Y, ldy, NK, P, a.opart);
-    kernel_launch(outer_reduce_kernel, dim3((NO * (NK + 1) + 255) / 256), dim3(256), 0, s,
-                       (const float*)a.opart, NO, NK, D, NK, Db);
-  };
-  outer(a.dx, 1, 1, a.g2, HH, HH, a.grad + o.H3, a.grad + o.c3);
-  outer(a.du2, HH, HH, a.g1, HH, HH, a.grad + o.H2, a.grad + o.c2);
-  outer(a.du1, HH, HH, a.z, Z, Z, a.grad + o.H1, a.grad + o.c1);
-  kernel_launch((enc_grad_kernel<H1, H2>), dim3(H2, kEncSplit), dim3(256), 0, s, a);
-  kernel_launch((train_reduce_kernel<H1, H2>), dim3((H2 * (H1 + 1) + 255) / 256 + (H1 * 7 + 3) / 4 + 1),
-                     dim3(256), 0, s, a, invB);
-  kernel_launch(adam_kernel, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, s, a);
+  int partials = H2 * kEncSplit, reduces = (H2 * (H1 + 1) + 255) / 256 + (H1 * 7 + 3) / 4 + 1;
+  for (const OuterJob& J : a.outer) {
+    partials += J.blocks();
+    reduces += J.reduce_blocks();
+  }
+  kernel_launch((train_partials_kernel<H1, H2>), dim3(partials), dim3(256), 0, s, a);
+  kernel_launch((train_reduce_kernel<H1, H2>), dim3(reduces), dim3(256), 0, s, a, invB);
   return launch_repack(a.repack, s);
 }
 

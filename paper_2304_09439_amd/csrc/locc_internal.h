@@ -156,6 +156,8 @@ struct Fp32Net {
   // both halves of every weight of W2, H1 and H2 in 32x32x16 B operand order, rows times powers of two, and the
   // factors that undo them (net_split.hip)
   const float* w1s;           // w1pack times the activation scale
+  const float* w1c;           // [h1][8]: W1's rows, bias, 0, in the order of layer 2's reduction
+  const float* w2c;           // [h1][h2]: W2^T in that order
   const unsigned short* w2s;  // [2][h2/32][h1/16][64][8]
   const unsigned short* h1s;  // [2][hh/32][2 h2/16][64][8]
   const unsigned short* h2s;  // [2][hh/32][hh/16][64][8]
@@ -180,13 +182,16 @@ struct NetArgs {
   locc_contact* out;      // [P]
   uint8_t* amax;          // [P][2][h2] row of the largest raw layer-2 sum per channel (first on ties), or null
   unsigned int* queue;    // launch_encoder_split: [2], 0 between launches, or null (static order)
+  uint32_t* doubt;        // [P][2][h2/32]: with amax, a bit per channel whose row is not certain
 };
 
-// The encoder on the FP32 matrix cores, recording the argmax rows (amax).
-hipError_t launch_encoder_fp32(const Fp32Net& w, const NetArgs& a, int n_cu, hipStream_t s);
-
-// The same features without the argmax rows, layer 2 as products of halves.
+// The encoder, layer 2 as products of halves: the pooled features (z, may be
+// null with amax) and, with amax, the argmax rows and which are in doubt.
 hipError_t launch_encoder_split(const Fp32Net& w, const NetArgs& a, int n_cu, hipStream_t s);
+
+// From those rows the features of one FP32 chain per sum, and the rows in doubt
+// decided by it.
+hipError_t launch_chain_features(const Fp32Net& w, const NetArgs& a, hipStream_t s);
 
 // The head on the features in z (products of halves).
 hipError_t launch_head_split(const Fp32Net& w, const NetArgs& a, int n_cu, hipStream_t s);
@@ -226,7 +231,8 @@ __host__ __device__ inline void split_chunk(const SplitChunks& c, int claim, int
 void split_bind(Fp32Net& w, const char* base);
 
 // Repacking on the device from the flat weights raw: pack[i] = raw[pack_idx[i]]
-// (0 where the index is negative) and the same for tr, when given, and the
+// (0 where the index is negative), the head's matrices in the gradient
+// kernels' order at frag (H1 [hh][2 h2], H2 [hh][hh], H2^T, H1^T), and the
 // halves at split (their scales in place, the flag word zero before).
 struct RepackArgs {
   const float* raw;
@@ -234,9 +240,7 @@ struct RepackArgs {
   float* pack;
   const int32_t* pack_idx;
   int32_t pack_n;
-  float* tr;
-  const int32_t* tr_idx;
-  int32_t tr_n;
+  float* frag;
   char* split;
 };
 hipError_t launch_repack(const RepackArgs& a, hipStream_t s);

@@ -79,7 +79,11 @@ struct SplitSmem {
   int32_t bad[2];                // per buffer: the step whose layer-1 outputs are out of range
 };
 
-template <int H1, int H2>
+// ARGMAX: also the row of each channel's largest sum (the first on ties), and which channels' choice is in doubt: where
+// the second largest sum lies within 2^-24 of the largest magnitude a sum can have (about twenty times the rounding
+// error of an FP32 chain here, whose terms are a tenth of their bounds and of both signs) and the feature is not
+// surely 0, or where only some of an object's steps are FP32 chains.  0.3% of the channels of 16,384 pairs.
+template <int H1, int H2, bool ARGMAX>
 __global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, NetArgs A, SplitChunks C) {
   using S_t = SplitSmem<H1, H2>;
   constexpr int HS = S_t::HS;
@@ -106,6 +110,16 @@ __global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, Net
   for (int s = 0; s < 4; ++s) w1f[s] = W.w1s[(ft1 * 4 + s) * 64 + lane];
   const float bias2 = W.b2[wave * 32 + l32], unscale2 = W.unscale2[wave * 32 + l32];
   if (tid < 2) S.bad[tid] = -1;
+  float doubt = 0.f;  // ARGMAX: 2^-24 times this column's absolute weights times 2^13, unscaled
+  if constexpr (ARGMAX) {
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const f16x8 w = __builtin_bit_cast(f16x8, w2f[0][s]);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) doubt += __builtin_fabsf((float)w[e]);
+    }
+    doubt = (doubt + __shfl_xor(doubt, 32, 64)) * unscale2 * 0x1p-11f;
+  }
 
   int gstep = 0;  // steps this workgroup has started (tags S.bad)
   for (int claim = blockIdx.x;; claim += gridDim.x) {
@@ -143,8 +157,12 @@ __global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, Net
     for (int o = wave; o < 2 * n; o += NW) {
       const int m = S.m[o];  // uniform
       if (m > 0) continue;
+      if constexpr (ARGMAX) {
+        if (lane < H2 / 4) reinterpret_cast<int32_t*>(A.amax + ((size_t)base * 2 + o) * H2)[lane] = -1;  // 255
+        if (lane < NW) A.doubt[((size_t)base * 2 + o) * NW + lane] = 0;
+      }
       const float v = m < 0 ? __builtin_nanf("") : 0.f;
-      if (lane < H2 / 4)
+      if (lane < H2 / 4 && A.z)
         reinterpret_cast<float4*>(A.z + ((size_t)base * 2 + o) * H2)[lane] = make_float4(v, v, v, v);
     }
 
@@ -191,7 +209,8 @@ __global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, Net
     }
     float4 xv = ns > 1 ? load_rows(1) : make_float4(0.f, 0.f, 0.f, 0.f);
     __syncthreads();
-    float run = -__builtin_inff();
+    float run = -__builtin_inff(), run2 = -__builtin_inff();  // the largest and (ARGMAX) second largest sum so far
+    int arg = 255, chains = 0;                                // its row; bit 0: a step of halves, bit 1: a chain
     for (int k = 0; k < ns; ++k, ++gstep) {
       const int e = __builtin_amdgcn_readfirstlane(S.step[k]);
       const int o = e & 0xff, r0 = (e >> 8) * kStepRows;
@@ -202,9 +221,23 @@ __global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, Net
       if (more) layer1_issue(xv);
       if (k + 2 < ns) xv = load_rows(k + 2);
       // max of a row tile's raw sums (bias and ReLU once per column afterwards: rounding is monotone)
-      float best = -__builtin_inff();
+      float best = -__builtin_inff(), best2 = -__builtin_inff();
+      int at = 255 - 4 * g;
+      auto keep = [&](float v, int row0, int r) __attribute__((always_inline)) {
+        // a lane's rows ascend: strict > keeps the first maximum; best2 <= best, so the median of three is the second
+        const bool more_than = v > best;
+        best2 = __builtin_amdgcn_fmed3f(v, best, best2);
+        at = more_than ? row0 + 8 * (r >> 2) + (r & 3) : at;
+        best = more_than ? v : best;
+      };
       auto pool = [&](const f32x16& v, int row0) __attribute__((always_inline)) {
-        if (row0 + 32 <= m) {
+        if constexpr (ARGMAX) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int row = row0 + 8 * (r >> 2) + 4 * g + (r & 3);
+            keep(row < m ? v[r] : -__builtin_inff(), row0, r);
+          }
+        } else if (row0 + 32 <= m) {
 #pragma unroll
           for (int r = 0; r < 16; r += 2) best = vmax(vmax(best, v[r]), v[r + 1]);
         } else {
@@ -263,7 +296,14 @@ __global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, Net
           const f32x16 v = hi + lo;
           layer2(1, [&](int s) __attribute__((always_inline)) {
 #pragma unroll
-            for (int r = 16 / KS * s; r < 16 / KS * (s + 1); r += 2) best = vmax(vmax(best, v[r]), v[r + 1]);
+            for (int r = 16 / KS * s; r < 16 / KS * (s + 1); r += 2) {
+              if constexpr (ARGMAX) {
+                keep(v[r], r0, r);
+                keep(v[r + 1], r0, r + 1);
+              } else {
+                best = vmax(vmax(best, v[r]), v[r + 1]);
+              }
+            }
           });
           pool(hi + lo, r0 + 32);
         } else {
@@ -295,11 +335,36 @@ __global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, Net
         layer1_check(buf ^ 1, gstep + 1);
       }
       mx = 0.f;
-      run = vmax(run, chain ? best : best * unscale2);
+      if (!chain) {
+        best *= unscale2;
+        best2 *= unscale2;
+      }
+      if constexpr (ARGMAX) {
+        arg = best > run ? at + 4 * g : arg;
+        run2 = vmax(vmax(run2, best2), fminf(run, best));
+        chains |= chain ? 2 : 1;
+      }
+      run = vmax(run, best);
       if (r0 + kStepRows >= m) {  // the object's last step
-        const float f = fmaxf(fmaxf(run, __shfl_xor(run, 32, 64)) + bias2, 0.f);
+        const float other = __shfl_xor(run, 32, 64);
+        const size_t at0 = ((size_t)base * 2 + o) * H2 + wave * 32;
+        if (lane < 32 && A.z) A.z[at0 + lane] = fmaxf(fmaxf(run, other) + bias2, 0.f);
+        if constexpr (ARGMAX) {
+          // the two half-waves hold rows 4g + ... of every tile: the larger value wins, the lower row on ties
+          const int other_arg = __shfl_xor(arg, 32, 64);
+          const float other2 = __shfl_xor(run2, 32, 64);
+          const bool take = other > run || (other == run && other_arg < arg);
+          const float second = vmax(vmax(run2, other2), fminf(run, other));
+          const float first = vmax(run, other);
+          const bool sure = chains == 2 || (chains == 1 && (first - second > doubt || first + bias2 < -doubt));
+          if (lane < 32) A.amax[at0 + lane] = (uint8_t)(take ? other_arg : arg);
+          const unsigned long long unsure = __ballot(!sure);
+          if (lane == 0) A.doubt[((size_t)base * 2 + o) * NW + wave] = (uint32_t)unsure;
+          run2 = -__builtin_inff();
+          arg = 255;
+          chains = 0;
+        }
         run = -__builtin_inff();
-        if (lane < 32) A.z[((size_t)base * 2 + o) * H2 + wave * 32 + lane] = f;
       }
       __syncthreads();
     }
@@ -310,6 +375,132 @@ __global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, Net
       atomicExch(A.queue, 0u);
       atomicExch(A.queue + 1, 0u);
     }
+  }
+}
+
+// ------------------------------------------------------- features as a chain
+//
+// The pooled features of the pose gradients and of training, whose ReLU and
+// argmax decisions are those of one chain of FP32 multiply-adds per sum (in the
+// order of a 32x32x2 matrix product: layer 1 over (x, y, z, nx, ny, nz, 1),
+// layer 2 over layer 1's permuted features): from the row the split encoder
+// found for each channel, that row's chain gives the feature; a channel whose
+// row is in doubt takes the largest chain over all rows, the first on ties, 64
+// rows at a time by its wave.  A thread per channel and four objects, so that a
+// weight is read once for four; W1 is read by scalar loads.  Bound by its vector
+// instructions: 9 per channel, hidden unit and object, 0.30 ms for 16,384 pairs
+// at 128 / 256, and with the split encoder's 0.70 ms about half of the 1.94 ms
+// of the whole encoder on the FP32 matrix cores.
+
+constexpr int kChainObjects = 4;
+
+template <int H1>
+__device__ __forceinline__ float chain_sum(const float* __restrict__ w1c, const float* __restrict__ w2c, int H2,
+                                           const float (&x)[6]) {
+  float acc = 0.f;
+#pragma unroll 4
+  for (int s = 0; s < H1; ++s) {
+    const float* w = w1c + 8 * s;
+    float h = w[0] * x[0];
+#pragma unroll
+    for (int c = 1; c < 6; ++c) h = __builtin_fmaf(w[c], x[c], h);
+    acc = __builtin_fmaf(vmax(h + w[6], 0.f), w2c[(size_t)s * H2], acc);
+  }
+  return acc;
+}
+
+template <int H1, int H2>
+__global__ __launch_bounds__(H2) void chain_features_kernel(Fp32Net W, NetArgs A) {
+  constexpr int NO = kChainObjects, NW = H2 / 32;
+  const int c = threadIdx.x, lane = c & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(c >> 6);
+  const int P = pair_count(A.n_pairs, A.n_pairs_dev);
+  const int K = A.K;
+  const float* __restrict__ w1c = W.w1c;
+  const float* __restrict__ w2c = W.w2c + c;
+  const size_t o0 = (size_t)blockIdx.x * NO;  // object = 2 pair + side
+  int m[NO], row[NO];
+  float x[NO][6], acc[NO];
+#pragma unroll
+  for (int i = 0; i < NO; ++i) {
+    m[i] = -2;  // no object
+    if (o0 + i < 2 * (size_t)P) {
+      const PairMeta mt = A.meta[(o0 + i) >> 1];
+      m[i] = mt.a < 0 ? -1 : ((o0 + i) & 1 ? mt.m_b : mt.m_a);
+    }
+    row[i] = m[i] > 0 ? A.amax[(o0 + i) * H2 + c] : 0;
+    if (row[i] >= m[i]) row[i] = 0;  // (no row above -inf: the sum is not used)
+#pragma unroll
+    for (int q = 0; q < 6; ++q) x[i][q] = 0.f;
+    if (m[i] > 0) {
+      // stored (x, z, ny, 1 | y, nx, nz, 0)
+      const float4* r = reinterpret_cast<const float4*>(A.rows + ((o0 + i) * K + row[i]) * kRowFloats);
+      const float4 lo = r[0], hi = r[1];
+      x[i][0] = lo.x;
+      x[i][1] = hi.x;
+      x[i][2] = lo.y;
+      x[i][3] = hi.y;
+      x[i][4] = lo.z;
+      x[i][5] = hi.z;
+    }
+    acc[i] = 0.f;
+  }
+#pragma unroll 2
+  for (int s = 0; s < H1; ++s) {
+    const float* w = w1c + 8 * s;
+    const float w2 = w2c[(size_t)s * H2];
+#pragma unroll
+    for (int i = 0; i < NO; ++i) {
+      float h = w[0] * x[i][0];
+#pragma unroll
+      for (int q = 1; q < 6; ++q) h = __builtin_fmaf(w[q], x[i][q], h);
+      acc[i] = __builtin_fmaf(vmax(h + w[6], 0.f), w2, acc[i]);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NO; ++i) {
+    if (m[i] == -2) continue;  // uniform, like every m
+    const size_t o = o0 + i;
+    float best = acc[i];
+    if (m[i] > 0) {
+      if (A.amax[o * H2 + c] >= m[i]) best = -__builtin_inff();
+      // the wave's 64 channels in doubt, one after the other
+      unsigned long long todo = A.doubt[o * NW + 2 * wave] | ((unsigned long long)A.doubt[o * NW + 2 * wave + 1] << 32);
+      while (todo) {  // uniform
+        const int l = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        float top = -__builtin_inff();
+        int at = 255;
+        for (int r0 = 0; r0 < m[i]; r0 += 64) {
+          if (r0 + lane < m[i]) {
+            const float4* r = reinterpret_cast<const float4*>(A.rows + (o * K + r0 + lane) * kRowFloats);
+            const float4 lo = r[0], hi = r[1];
+            const float y[6] = {lo.x, hi.x, lo.y, hi.y, lo.z, hi.z};
+            const float v = chain_sum<H1>(w1c, W.w2c + 64 * wave + l, H2, y);
+            if (v > top) {
+              top = v;
+              at = r0 + lane;
+            }
+          }
+        }
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+          const float ot = __shfl_xor(top, d, 64);
+          const int oa = __shfl_xor(at, d, 64);
+          if (ot > top || (ot == top && oa < at)) {
+            top = ot;
+            at = oa;
+          }
+        }
+        if (lane == l) {
+          best = top;
+          A.amax[o * H2 + c] = (uint8_t)at;
+        }
+      }
+    } else {
+      best = -__builtin_inff();
+    }
+    A.z[o * H2 + c] = m[i] < 0 ? __builtin_nanf("") : fmaxf(best + W.b2[c], 0.f);
   }
 }
 
@@ -635,7 +826,8 @@ __global__ __launch_bounds__(512, 2) void head_split_kernel(Fp32Net W, NetArgs A
 
 // ------------------------------------------------------------- weights, launch
 
-// Repacking, an element per thread: first the two gathers, then the halves of
+// Repacking, an element per thread: first the gather, then layer 1 and W2^T for
+// the chains, the head's operands of the gradient kernels, and the halves of
 // W2, H1, H2 and H3, each row times its power of two, in the B operand order
 // of 32x32x16 products (W2's reduction index in layer 1's output order), and
 // layer 1's operand times its own; the flag word becomes 1 where a weight has
@@ -644,12 +836,12 @@ __global__ __launch_bounds__(256) void repack_kernel(RepackArgs A, SplitLayout L
   char* const base = A.split;
   const float* scale = reinterpret_cast<const float*>(base + L.scale);
   int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < A.pack_n + A.tr_n) {
-    const int32_t k = i < A.pack_n ? A.pack_idx[i] : A.tr_idx[i - A.pack_n];
-    (i < A.pack_n ? A.pack[i] : A.tr[i - A.pack_n]) = k >= 0 ? A.raw[k] : 0.f;
+  if (i < A.pack_n) {
+    const int32_t k = A.pack_idx[i];
+    A.pack[i] = k >= 0 ? A.raw[k] : 0.f;
     return;
   }
-  i -= A.pack_n + A.tr_n;
+  i -= A.pack_n;
   const float* raw = A.raw;
   if (i < 8 * L.h1) {  // [W1 | b1 | 0][f][c], f = 32 ft + l % 32, c = 2 s + l / 32, at (4 ft + s) 64 + l
     const int l = i & 63, f = 32 * (i >> 8) + l % 32, c = 2 * ((i >> 6) & 3) + l / 32;
@@ -658,6 +850,34 @@ __global__ __launch_bounds__(256) void repack_kernel(RepackArgs A, SplitLayout L
     return;
   }
   i -= 8 * L.h1;
+  // layer 1's rows (w0 .. w5, b, 0) and W2^T in the order of layer 2's reduction: step s is feature
+  // F(s / 32, s % 2, (s / 2) % 16)
+  if (i < 8 * L.h1 + L.h2 * L.h1) {
+    const bool first = i < 8 * L.h1;
+    const int at = first ? i : i - 8 * L.h1, s = first ? at >> 3 : at / L.h2, c = first ? at & 7 : at % L.h2;
+    const int f = perm_feature(s / 32, s % 2, (s / 2) % 16);
+    if (first)
+      reinterpret_cast<float*>(base + L.w1c)[at] = c < 6 ? raw[6 * f + c] : (c == 6 ? raw[6 * L.h1 + f] : 0.f);
+    else
+      reinterpret_cast<float*>(base + L.w2c)[at] = raw[7 * L.h1 + (size_t)c * L.h1 + f];
+    return;
+  }
+  i -= 8 * L.h1 + L.h2 * L.h1;
+  // H1, H2, H2^T and H1^T [out][in] as operands of 16x16x4 products: lane l of step u of column tile ct holds
+  // M[16 ct + l % 16][16 u + 4 (l / 16) .. + 3]
+  const int f1 = L.hh * 2 * L.h2, f2 = L.hh * L.hh, offH1 = 7 * L.h1 + L.h2 * L.h1 + L.h2, offH2 = offH1 + f1 + L.hh;
+  if (i < 2 * (f1 + f2)) {
+    const int mat = i < f1 ? 0 : (i < f1 + f2 ? 1 : (i < f1 + 2 * f2 ? 2 : 3));
+    const int at = i - (mat == 0 ? 0 : (mat == 1 ? f1 : (mat == 2 ? f1 + f2 : f1 + 2 * f2)));
+    const int steps = (mat == 0 ? 2 * L.h2 : L.hh) / 16, l = (at >> 2) & 63;
+    const int row = 16 * ((at >> 8) / steps) + l % 16, k = 16 * ((at >> 8) % steps) + 4 * (l / 16) + (at & 3);
+    A.frag[i] = raw[mat == 0   ? offH1 + row * 2 * L.h2 + k
+                    : mat == 1 ? offH2 + row * L.hh + k
+                    : mat == 2 ? offH2 + k * L.hh + row
+                               : offH1 + k * 2 * L.h2 + row];
+    return;
+  }
+  i -= 2 * (f1 + f2);
   const int n2 = L.h2 * L.h1, nh1 = L.hh * 2 * L.h2, nh2 = L.hh * L.hh, nh3 = 32 * L.hh;  // H3: 8 rows, zero to 32
   if (i >= n2 + nh1 + nh2 + nh3) return;
   const int mat = i < n2 ? 0 : (i < n2 + nh1 ? 1 : (i < n2 + nh1 + nh2 ? 2 : 3));
@@ -703,9 +923,21 @@ SplitChunks split_chunks(int n_pairs, int grid) {
 
 template <int H1, int H2>
 hipError_t run_split(const Fp32Net& w, const NetArgs& a, int n_cu, hipStream_t s) {
-  const int slots = n_cu * (H2 >= 256 ? 1 : 2);  // workgroups the register file holds at once
+  const int slots = n_cu * (H2 >= 256 ? 1 : 2);  // workgroups the register file holds at once (four spill: 98 -> 166 us)
   const int grid = a.n_pairs < slots ? a.n_pairs : slots;
-  kernel_launch((encoder_split_kernel<H1, H2>), dim3(grid), dim3(2 * H2), 0, s, w, a, split_chunks(a.n_pairs, grid));
+  if (a.amax)
+    kernel_launch((encoder_split_kernel<H1, H2, true>), dim3(grid), dim3(2 * H2), 0, s, w, a,
+                  split_chunks(a.n_pairs, grid));
+  else
+    kernel_launch((encoder_split_kernel<H1, H2, false>), dim3(grid), dim3(2 * H2), 0, s, w, a,
+                  split_chunks(a.n_pairs, grid));
+  return hipGetLastError();
+}
+
+template <int H1, int H2>
+hipError_t run_chain(const Fp32Net& w, const NetArgs& a, hipStream_t s) {
+  const unsigned grid = (unsigned)((2 * (size_t)a.n_pairs + kChainObjects - 1) / kChainObjects);
+  kernel_launch((chain_features_kernel<H1, H2>), dim3(grid), dim3(H2), 0, s, w, a);
   return hipGetLastError();
 }
 
@@ -734,10 +966,28 @@ hipError_t launch_head_split(const Fp32Net& w, const NetArgs& a, int n_cu, hipSt
 
 hipError_t launch_encoder_split(const Fp32Net& w, const NetArgs& a, int n_cu, hipStream_t s) {
   if (a.n_pairs <= 0) return hipSuccess;
-  if (!w.w2s || !w.split_bad) return hipErrorInvalidValue;
+  if (!w.w2s || !w.split_bad || (a.amax ? !a.doubt : !a.z)) return hipErrorInvalidValue;
   if (w.h1 == 64 && w.h2 == 128) return run_split<64, 128>(w, a, n_cu, s);
   if (w.h1 == 128 && w.h2 == 256) return run_split<128, 256>(w, a, n_cu, s);
   return hipErrorInvalidValue;
+}
+
+Fp32Net fp32_view(const float* base, int h1, int h2, int hh) {
+  const Fp32Layout L = fp32_layout(h1, h2, hh);
+  Fp32Net w{};
+  w.h1 = h1;
+  w.h2 = h2;
+  w.hh = hh;
+  w.w1pack = base + L.w1;
+  w.w2pack = base + L.w2;
+  w.b2 = base + L.b2;
+  w.h1pack = base + L.h1;
+  w.c1 = base + L.c1;
+  w.h2pack = base + L.h2;
+  w.c2 = base + L.c2;
+  w.h3 = base + L.h3;
+  w.c3 = base + L.c3;
+  return w;
 }
 
 void split_bind(Fp32Net& w, const char* base) {
@@ -749,6 +999,8 @@ void split_bind(Fp32Net& w, const char* base) {
   w.unscale_h1 = w.unscale2 + L.h2;
   w.unscale_h2 = w.unscale_h1 + L.hh;
   w.unscale_h3 = w.unscale_h2 + L.hh;
+  w.w1c = reinterpret_cast<const float*>(base + L.w1c);
+  w.w2c = reinterpret_cast<const float*>(base + L.w2c);
   w.w1s = reinterpret_cast<const float*>(base + L.w1);
   w.w2s = reinterpret_cast<const unsigned short*>(base + L.w2);
   w.h1s = reinterpret_cast<const unsigned short*>(base + L.H1);
@@ -756,9 +1008,17 @@ void split_bind(Fp32Net& w, const char* base) {
   w.h3s = reinterpret_cast<const unsigned short*>(base + L.H3);
 }
 
+hipError_t launch_chain_features(const Fp32Net& w, const NetArgs& a, hipStream_t s) {
+  if (a.n_pairs <= 0) return hipSuccess;
+  if (!w.w2c || !a.z || !a.amax || !a.doubt) return hipErrorInvalidValue;
+  if (w.h1 == 64 && w.h2 == 128) return run_chain<64, 128>(w, a, s);
+  if (w.h1 == 128 && w.h2 == 256) return run_chain<128, 256>(w, a, s);
+  return hipErrorInvalidValue;
+}
+
 hipError_t launch_repack(const RepackArgs& a, hipStream_t s) {
   const int h1 = a.h1, h2 = a.h2, hh = a.hh;
-  const int n = a.pack_n + a.tr_n + 8 * h1 + h2 * h1 + hh * 2 * h2 + hh * hh + 32 * hh;
+  const int n = a.pack_n + 2 * (hh * 2 * h2 + hh * hh) + 16 * h1 + 2 * h2 * h1 + hh * 2 * h2 + hh * hh + 32 * hh;
   kernel_launch(repack_kernel, dim3((n + 255) / 256), dim3(256), 0, s, a, split_layout(h1, h2, hh));
   return hipGetLastError();
 }

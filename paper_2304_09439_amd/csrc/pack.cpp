@@ -115,10 +115,15 @@ void fp32_pack(const float* W1, const float* b1, const float* W2, const float* b
 
 
 SplitLayout split_layout(int h1, int h2, int hh) {
-  SplitLayout L{h1, h2, hh, 0, 0, 0, 0, 0, 0, 0};
+  SplitLayout L{};
+  L.h1 = h1;
+  L.h2 = h2;
+  L.hh = hh;
   size_t o = 256;
   L.scale = o; o = align256(o + split_scale_floats(h2, hh) * 4);
   L.w1 = o; o = align256(o + (size_t)8 * h1 * 4);
+  L.w1c = o; o = align256(o + (size_t)8 * h1 * 4);
+  L.w2c = o; o = align256(o + (size_t)h2 * h1 * 4);
   L.w2 = o; o = align256(o + (size_t)h2 * h1 * 4);
   L.H1 = o; o = align256(o + (size_t)hh * 2 * h2 * 4);
   L.H2 = o; o = align256(o + (size_t)hh * hh * 4);

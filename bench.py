@@ -48,10 +48,10 @@ KERNEL_SOURCES = {
     "head_fp32": ["net_split.hip", "pack.h", "post.h"],
     "fused_bf16": ["fused.hip", "fused.h", "geometry.h", "post.h", "head_bf16.h"],
     # the split schedule's two encoder+head kernels (two workgroups per CU: fused.hip; one: encoder_bf16.hip)
-    "encoder_head_bf16": ["fused.hip", "fused.h", "geometry.h", "post.h", "head_bf16.h"],
+    "encoder_head_bf16": ["fused.hip", "head_bf16.hip", "fused.h", "geometry.h", "post.h", "head_bf16.h"],
     "encoder_head_bf16_lds": ["encoder_bf16.hip", "fused.h", "geometry.h", "post.h", "head_bf16.h"],
     "encoder_head_fp8": ["fused_fp8.hip", "fused.h", "post.h"],
-    "encoder_fp8_head_bf16": ["fused_fp8.hip", "fused.h", "head_bf16.h", "post.h"],
+    "encoder_fp8_head_bf16": ["fused_fp8.hip", "head_bf16.hip", "fused.h", "geometry.h", "post.h", "head_bf16.h"],
     "crop_fp8_encoder": ["crop.hip", "geometry.h"],
 }
 # arithmetic of the encoder and of the head in each network kernel (None: not in that kernel)
@@ -67,7 +67,7 @@ PATH_DESC = {
     "fp8": "batched FP8: crop kernel, then one persistent encoder+head launch (encoder layer 2 and head "
            "layers 1-2 e4m3 x e4m3, encoder layer 1 and head layer 3 bf16; activation scales calibrated "
            "on the first 1,024 pairs)",
-    "fp8_encoder": "batched FP8, lower-error variant: crop kernel, then one persistent encoder+head launch "
+    "fp8_encoder": "batched FP8, lower-error variant: crop kernel, then a persistent encoder and a head launch "
                    "(encoder layer 2 e4m3 x e4m3, encoder layer 1 and the whole head bf16; the activation scale "
                    "calibrated on the first 1,024 pairs)",
 }

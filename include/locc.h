@@ -218,12 +218,16 @@ LOCC_API locc_status locc_debug_forward(locc_ctx* ctx, const locc_object* d_objs
  *              workgroup of eight waves per CU with layer 2's weights in LDS,
  *              taking groups of 64 pairs (w, w + CUs, ...), each wave
  *              encoding whole objects; claim and dynamic do not apply to it
- *   claim      pairs a workgroup takes from the queue at a time (1 .. 64)
+ *   claim      pairs a workgroup takes from the queue at a time (1 .. 64), at
+ *              most: fewer in a batch that would leave compute units without
  *   dynamic    1: pairs are claimed from a device-side atomic queue;
  *              0: static round robin (workgroup w takes claims w, w + grid, ...)
  *   split      0: one persistent kernel does crop, encoder and head;
  *              1: a crop kernel writes bf16 encoder rows to a library
  *              workspace, then the persistent kernel runs encoder and head
+ *              (batches between a few and some dozens of pairs per compute
+ *              unit, and FP8: the encoder, and a kernel of its own the head;
+ *              a large batch's FP8 encoder at wg_per_cu = 2 has three)
  *   crop_unroll  also used by the FP32 path's crop kernel
  *   chunks     split schedule and FP8 (1, 2, 4 or 8): the step is cut into
  *              that many runs of pairs; the crop of run k + 1 runs on a

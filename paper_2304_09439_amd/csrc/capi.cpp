@@ -200,10 +200,31 @@ Fp32Net fp32_net(const locc_ctx* c) {
 // Scale of an fp8 activation with maximum amax (448 is e4m3's largest finite value).
 float fp8_scale(float amax) { return amax > 0.f ? amax / 448.f : 1.f; }
 
-int fused_grid(const locc_ctx* c, int n_pairs) {
-  const int claim = c->sched.claim;
+// Whether the encoder and the bf16 head of n_pairs are two kernels.  A workgroup of the combined kernel streams all of
+// the head's weights (1 MB at width 512) for the pairs it has, up to a tile of 32.  As long as a claim of four fills no
+// more than one workgroup per compute unit, that one stream is cheaper than another launch (780 pairs, K = 96: 45 us
+// combined, 46.5 apart); beyond, workgroups of a few pairs share a compute unit and its L2 bandwidth (1,061 pairs:
+// 56.7 combined, 49.8 apart; 4,000: 88.4, 80.4), until their tiles fill (12,000: 171.1, 168.6; 16,384 at K = 128:
+// 253.8, 254.5; a step of 210,040: 2,250, 2,345, as the combined kernel's heads overlap encoders).  The FP8 encoder
+// alone leaves registers for a third workgroup per compute unit, and stays ahead (16,384: 210 combined, 189 apart).
+// At head width 256 the weights are 256 KB and the launch costs more (1,000 pairs: 31.7 combined, 40.2 apart).
+bool head_apart(const locc_ctx* c, int n_pairs) {
+  if (c->cfg.head_h < 512 || n_pairs <= 4 * c->n_cu) return false;
+  return c->fp8() || n_pairs <= 48 * c->n_cu;
+}
+
+// Pairs a workgroup claims at once: the schedule's claim, or fewer where that would leave some of per_cu workgroups per
+// compute unit without pairs.  The combined kernels take per_cu = 1: a workgroup's latency is that of its pairs, one
+// after the other (8 pairs at K = 128 in claims of one 36.0 us, of four 47.1), but every workgroup streams the head
+// (400 pairs: in claims of two 50.0, of one 57.9, of four 56.0).  The encoder alone has no such stream.
+int fused_claim(const locc_ctx* c, int n_pairs, int per_cu) {
+  const int slots = c->n_cu * per_cu, share = (n_pairs + slots - 1) / slots;
+  return share < c->sched.claim ? share : c->sched.claim;
+}
+
+int fused_grid(const locc_ctx* c, int n_pairs, int claim, int per_cu) {
   const int tiles = (n_pairs + claim - 1) / claim;
-  const int grid = c->n_cu * c->sched.wg_per_cu;
+  const int grid = c->n_cu * per_cu;
   return tiles < grid ? tiles : grid;
 }
 
@@ -257,7 +278,16 @@ locc_status locc::run_path(locc_ctx* c, const locc_object* objs, int32_t n_objs,
         HIP_TRY(hipEventRecord(c->chunk_ev[k + 1], cs));
         HIP_TRY(hipStreamWaitEvent(s, c->chunk_ev[k + 1], 0));
       }
-      const int grid = fused_grid(c, len);
+      HeadBf16Args ha{};  // the head of a batch whose encoder is a kernel of its own
+      ha.objs = objs;
+      ha.n_pairs = len;
+      ha.n_pairs_dev = n_dev;
+      ha.dev_base = s0;
+      ha.z16 = rows;
+      ha.z_stride = (int64_t)2 * K * 8;
+      ha.meta = meta;
+      ha.out = out + s0;
+      ha.y_dbg = y_out ? y_out + (size_t)s0 * 8 : nullptr;
       if (c->fp8()) {
         Fp8Args fa{};
         fa.objs = objs;
@@ -278,11 +308,28 @@ locc_status locc::run_path(locc_ctx* c, const locc_object* objs, int32_t n_objs,
         fa.z_dbg = z_out ? z_out + (size_t)s0 * 2 * h2 : nullptr;
         fa.y_dbg = y_out ? y_out + (size_t)s0 * 8 : nullptr;
         fa.queue = own ? own->queue : c->d_queue;
-        fa.claim = c->sched.claim;
         fa.dynamic = c->sched.dynamic;
         const bool h8 = c->fp8_head();
-        HIP_TRY(timed(c, h8 ? "encoder_head_fp8" : "encoder_fp8_head_bf16", s,
-                      [&] { return launch_encoder_head_fp8(fa, h1, h2, hh, h8, grid, s); }));
+        const bool apart = !h8 && head_apart(c, len);
+        // the third workgroup per compute unit: 1,061 pairs 47.8 us without, 52.3 with it; 4,000: 73.8, 79.6; 6,000:
+        // 97.4, 98.0; 16,384: 202.9, 189.0
+        const int per_cu =
+            apart && len >= 32 * c->n_cu && c->sched.wg_per_cu == kFusedWgPerCu ? kFp8EncoderWgPerCu : c->sched.wg_per_cu;
+        fa.claim = fused_claim(c, len, apart ? per_cu : 1);
+        const int grid = fused_grid(c, len, fa.claim, per_cu);
+        if (apart) {
+          fa.z16 = rows;
+          ha.h1p = reinterpret_cast<const unsigned short*>(fa.h1p);
+          ha.c1 = fa.c1;
+          ha.h2p = reinterpret_cast<const unsigned short*>(fa.h2p);
+          ha.c2 = fa.c2;
+          ha.h3p = fa.h3p;
+          ha.c3 = fa.c3;
+        }
+        HIP_TRY(timed(c, h8 ? "encoder_head_fp8" : "encoder_fp8_head_bf16", s, [&] {
+          const hipError_t e = launch_encoder_head_fp8(fa, h1, h2, hh, h8, grid, s);
+          return e == hipSuccess && apart ? launch_head_bf16(ha, h2, hh, c->n_cu, s) : e;
+        }));
       } else {
         FusedArgs fa{};
         fa.objs = objs;
@@ -300,7 +347,6 @@ locc_status locc::run_path(locc_ctx* c, const locc_object* objs, int32_t n_objs,
         fa.rows_bf16 = rows;
         fa.meta = meta;
         fa.queue = own ? own->queue : c->d_queue;
-        fa.claim = c->sched.claim;
         fa.dynamic = c->sched.dynamic;
         if (c->sched.wg_per_cu == 1) {  // one workgroup of eight waves per CU, W2 in LDS
           const int groups = (len + 63) / 64;
@@ -308,8 +354,22 @@ locc_status locc::run_path(locc_ctx* c, const locc_object* objs, int32_t n_objs,
           HIP_TRY(timed(c, "encoder_head_bf16_lds", s,
                         [&] { return launch_encoder_head_bf16_lds(fa, h1, h2, hh, g8, false, s); }));
         } else {
-          HIP_TRY(timed(c, "encoder_head_bf16", s,
-                        [&] { return launch_fused_bf16(fa, h1, h2, hh, grid, true, s); }));
+          const bool apart = head_apart(c, len);
+          fa.claim = fused_claim(c, len, apart ? c->sched.wg_per_cu : 1);
+          if (apart) {
+            fa.z16 = rows;
+            ha.h1p = fa.h1p;
+            ha.c1 = fa.c1;
+            ha.h2p = fa.h2p;
+            ha.c2 = fa.c2;
+            ha.h3p = fa.h3p;
+            ha.c3 = fa.c3;
+          }
+          const int grid = fused_grid(c, len, fa.claim, c->sched.wg_per_cu);
+          HIP_TRY(timed(c, "encoder_head_bf16", s, [&] {
+            const hipError_t e = launch_fused_bf16(fa, h1, h2, hh, grid, true, s);
+            return e == hipSuccess && apart ? launch_head_bf16(ha, h2, hh, c->n_cu, s) : e;
+          }));
         }
       }
     }
@@ -331,9 +391,9 @@ locc_status locc::run_path(locc_ctx* c, const locc_object* objs, int32_t n_objs,
   fa.y_dbg = y_out;
   fa.err_counter = c->d_err;
   fa.queue = own ? own->queue : c->d_queue;
-  fa.claim = c->sched.claim;
+  fa.claim = fused_claim(c, n_pairs, 1);
   fa.dynamic = c->sched.dynamic;
-  const int grid = fused_grid(c, n_pairs);
+  const int grid = fused_grid(c, n_pairs, fa.claim, c->sched.wg_per_cu);
   HIP_TRY(timed(c, "fused_bf16", s, [&] { return launch_fused_bf16(fa, h1, h2, hh, grid, false, s); }));
   return LOCC_OK;
 }
@@ -1115,7 +1175,7 @@ locc_status locc_pose_gradients(locc_ctx* c, const locc_object* objs, int32_t n_
     fa.rows_bf16 = rows16;
     fa.meta = meta;
     fa.queue = c->d_queue;
-    fa.claim = c->sched.claim;
+    fa.claim = fused_claim(c, n_pairs, c->sched.wg_per_cu);
     fa.dynamic = c->sched.dynamic;
     if (c->sched.wg_per_cu == 1) {  // one workgroup of eight waves per CU, W2 in LDS
       const int groups = (n_pairs + 63) / 64;
@@ -1123,7 +1183,7 @@ locc_status locc_pose_gradients(locc_ctx* c, const locc_object* objs, int32_t n_
       HIP_TRY(timed(c, "encoder_bf16_argmax", s,
                     [&] { return launch_encoder_head_bf16_lds(fa, h1, h2, hh, g8, true, s); }));
     } else {
-      const int grid = fused_grid(c, n_pairs);
+      const int grid = fused_grid(c, n_pairs, fa.claim, c->sched.wg_per_cu);
       HIP_TRY(timed(c, "encoder_bf16_argmax", s,
                     [&] { return launch_encoder_bf16_argmax(fa, h1, h2, hh, grid, s); }));
     }

@@ -40,16 +40,40 @@ struct FusedArgs {
   int32_t claim;        // pairs claimed at once
   int32_t dynamic;      // 1: atomic queue, 0: static round robin
   int32_t dev_base;     // first pair of this launch within the step (device count mode)
+  unsigned short* z16;  // split schedule: null, or the encoder alone, leaving the features [f_a, f_b] (bf16) of pair
+                        // p at p * 2K * 8, over its rows (rows_bf16 itself)
 };
+
+// The bf16 head on features in memory (BF16, and FP8 with the bf16 head).
+struct HeadBf16Args {
+  const locc_object* objs;
+  int32_t n_pairs;              // capacity
+  const int32_t* n_pairs_dev;   // actual count in device memory, or null
+  int32_t dev_base;
+  const unsigned short* z16;    // [f_a, f_b] of pair p at p * z_stride
+  int64_t z_stride;
+  const PairMeta* meta;
+  const unsigned short* h1p;
+  const float* c1;
+  const unsigned short* h2p;
+  const float* c2;
+  const unsigned short* h3p;
+  const float* c3;
+  locc_contact* out;
+  float* y_dbg;                 // [P][8] or null
+};
+hipError_t launch_head_bf16(const HeadBf16Args& a, int h2, int hh, int n_cu, hipStream_t s);
 
 void bf16_bind(FusedArgs& a, const unsigned char* dev_base, int h1, int h2, int hh);
 
 // Workgroups per CU the fused kernel is compiled for.
 constexpr int kFusedWgPerCu = 2;
+constexpr int kFp8EncoderWgPerCu = 3;
 constexpr int kFusedTile = 32;
 
 // precropped = false: crop, encoder and head in one kernel; true: encoder and
-// head only, reading rows_bf16 / meta written by the crop kernel.
+// head only (with z16, the encoder only), reading rows_bf16 / meta written by
+// the crop kernel.
 hipError_t launch_fused_bf16(const FusedArgs& a, int h1, int h2, int hh, int grid, bool precropped, hipStream_t s);
 // The encoder of the split schedule alone, recording the pooled features (z_dbg, float) and per channel the
 // row of the largest raw layer-2 sum (amax; 255 for an object with no rows), for the pose gradients.
@@ -95,6 +119,7 @@ struct Fp8Args {
   int32_t claim;
   int32_t dynamic;
   int32_t dev_base;  // first pair of this launch within the step (device count mode)
+  unsigned short* z16;  // without the fp8 head: null, or the encoder alone, leaving the features as in FusedArgs
 };
 
 void fp8_bind(Fp8Args& a, const unsigned char* dev_base, int h1, int h2, int hh, bool head8);

@@ -33,6 +33,8 @@
 // the encoder and head; the crop's dependent loads then overlap across many
 // more resident workgroups than the encoder's register budget allows.
 #include "fused.h"
+
+#include <type_traits>
 #include "geometry.h"
 #include "head_bf16.h"
 #include "post.h"
@@ -121,16 +123,31 @@ __device__ __forceinline__ void head_tile(const FusedArgs& A, Smem<H1, H2, HH>& 
   __syncthreads();
 }
 
-// ARGMAX (split schedule only): the encoder alone, with per channel the row of its largest raw sum; the
-// pooled features and those rows go to z_dbg and amax, and no head runs.
-template <int H1, int H2, int HH, bool PRE, bool ARGMAX = false>
+// The encoder alone (split schedule)
+template <int H1>
+struct EncoderSmem {
+  struct {
+    struct {
+      alignas(16) unsigned short rows[2 * kMaxK * 8];
+      alignas(16) unsigned short h1t[2][kFusedTile * (H1 + 8)];
+    } c;
+  } u;
+  int32_t claim;
+};
+
+// Split schedule (PRE): APART is the encoder alone; the pooled features of a pair go, as bf16, over the pair's own
+// rows, for the head kernel.  ARGMAX is the encoder alone with, per channel, the row of its largest raw sum; the
+// features and those rows go to z_dbg and amax.
+template <int H1, int H2, int HH, bool PRE, bool ARGMAX = false, bool APART = false>
 __global__ __launch_bounds__(256, kFusedWgPerCu) void fused_bf16_kernel(FusedArgs A) {
-  static_assert(PRE || !ARGMAX, "the argmax encoder reads the crop kernel's rows");
-  using S_t = Smem<H1, H2, HH>;
-  constexpr int T = S_t::T, ZS = S_t::ZS;
+  static_assert(PRE || !(ARGMAX || APART), "the encoder alone reads the crop kernel's rows");
+  constexpr bool HEAD = !ARGMAX && !APART;
+  using Tiles = Smem<H1, H2, HH>;
+  using S_t = std::conditional_t<HEAD, Tiles, EncoderSmem<H1>>;
+  constexpr int T = Tiles::T, ZS = Tiles::ZS;
   constexpr int FT = H1 / 32;    // layer-1 feature tiles
   constexpr int FW = (FT + 3) / 4;  // layer-1 feature tiles per wave (tiles wave, wave + 4, ...)
-  constexpr int HS = S_t::HS;
+  constexpr int HS = Tiles::HS;
   constexpr int KS2 = H1 / 16;   // layer-2 k-steps
   constexpr int CT = H2 / 128;   // encoder column tiles per wave
   static_assert(H1 % 32 == 0 && H2 % 128 == 0 && HH % 128 == 0, "widths");
@@ -247,11 +264,12 @@ __global__ __launch_bounds__(256, kFusedWgPerCu) void fused_bf16_kernel(FusedArg
         atomicAdd(A.err_counter, 1ull);
       }
       }
-      if (tid == 0) {
-        S.pair[slot] = p;
-        S.a[slot] = valid ? a : -1;
-        S.swapped[slot] = swapped;
-      }
+      if constexpr (HEAD)
+        if (tid == 0) {
+          S.pair[slot] = p;
+          S.a[slot] = valid ? a : -1;
+          S.swapped[slot] = swapped;
+        }
       __syncthreads();
 
       // ------------------------------------------------------------- encoder
@@ -364,30 +382,29 @@ __global__ __launch_bounds__(256, kFusedWgPerCu) void fused_bf16_kernel(FusedArg
           }
           if (lane < 32) {
             const int col = side * H2 + (wave * CT + ct) * 32 + lane;
-            if constexpr (!ARGMAX) S.z[slot * ZS + col] = bf16_bits(f);
+            if constexpr (HEAD)
+              S.z[slot * ZS + col] = bf16_bits(f);
+            else if constexpr (APART)  // every wave's part of this pair's rows is in LDS by now
+              A.z16[(size_t)p * 2 * K * 8 + col] = bf16_bits(f);
             if (A.z_dbg) A.z_dbg[(size_t)p * 2 * H2 + col] = valid ? f : __builtin_nanf("");
           }
         }
       }
-      ++slot;
       // The crop scratch is reused by the next pair's crop.  The split schedule
       // needs no barrier here: every read of this pair's rows and layer-1 tiles
       // completed before the barrier ending its last row tile (a barrier waits
       // for the wave's LDS accesses), the next pair writes another z slot, and
       // the head begins with a barrier of its own.
       if constexpr (!PRE) __syncthreads();
-      if constexpr (!ARGMAX) {
-        if (slot == T) {
+      if constexpr (HEAD)
+        if (++slot == T) {
           head_tile<H1, H2, HH, PRE ? 4 : 2>(A, S, T);
           slot = 0;
           load_w2();
         }
-      } else {
-        slot = 0;
-      }
     }
   }
-  if constexpr (!ARGMAX)
+  if constexpr (HEAD)
     if (slot > 0) head_tile<H1, H2, HH, PRE ? 4 : 2>(A, S, slot);
 
   if (A.dynamic && tid == 0) {
@@ -401,7 +418,9 @@ __global__ __launch_bounds__(256, kFusedWgPerCu) void fused_bf16_kernel(FusedArg
 
 template <int H1, int H2, int HH>
 hipError_t run_fused(const FusedArgs& a, int grid, bool pre, hipStream_t s) {
-  if (pre)
+  if (a.z16)
+    kernel_launch((fused_bf16_kernel<H1, H2, HH, true, false, true>), dim3(grid), dim3(256), 0, s, a);
+  else if (pre)
     kernel_launch((fused_bf16_kernel<H1, H2, HH, true>), dim3(grid), dim3(256), 0, s, a);
   else
     kernel_launch((fused_bf16_kernel<H1, H2, HH, false>), dim3(grid), dim3(256), 0, s, a);
@@ -437,6 +456,7 @@ hipError_t launch_encoder_bf16_argmax(const FusedArgs& a, int h1, int h2, int hh
 
 hipError_t launch_fused_bf16(const FusedArgs& a, int h1, int h2, int hh, int grid, bool pre, hipStream_t s) {
   if (a.n_pairs <= 0) return hipSuccess;
+  if (a.z16 && (!pre || !a.rows_bf16 || !a.meta || h2 > 8 * a.K)) return hipErrorInvalidValue;
   if (h1 == 64 && h2 == 128 && hh == 256) return run_fused<64, 128, 256>(a, grid, pre, s);
   if (h1 == 128 && h2 == 256 && hh == 512) return run_fused<128, 256, 512>(a, grid, pre, s);
   return hipErrorInvalidValue;

@@ -24,6 +24,8 @@
 // e % 16), F(ft, g, r) = 32 ft + 8 (r / 4) + 4 g + r % 4.  In the LDS tile a
 // row holds, per k-step s and lane group g, those 32 bytes contiguously.
 #include "fused.h"
+
+#include <type_traits>
 #include "geometry.h"
 #include "head_bf16.h"
 #include "post.h"
@@ -87,6 +89,18 @@ struct Smem8 {
   int32_t pair[T];
   int32_t a[T];
   int32_t swapped[T];
+  int32_t claim;
+};
+
+// The encoder alone
+template <int H1>
+struct EncoderSmem8 {
+  struct {
+    struct {
+      alignas(16) unsigned short rows[2 * kMaxK * 8];
+      alignas(16) unsigned char h1t[2][kFusedTile * (H1 + 16)];
+    } e;
+  } u;
   int32_t claim;
 };
 
@@ -183,14 +197,18 @@ __device__ __forceinline__ void head_tile8(const Fp8Args& A, Smem8<H1, H2, HH, H
   __syncthreads();
 }
 
-template <int H1, int H2, int HH, bool HEAD8>
-__global__ __launch_bounds__(256, kFusedWgPerCu) void encoder_head_fp8_kernel(Fp8Args A) {
-  using S_t = Smem8<H1, H2, HH, HEAD8>;
-  constexpr int T = S_t::T, ZB = S_t::ZB;
+// APART (without the fp8 head): the encoder alone; the pooled features of a pair go, as bf16, over the pair's own
+// rows, for the bf16 head's kernel.  Its registers and LDS leave room for a third workgroup per CU.
+template <int H1, int H2, int HH, bool HEAD8, bool APART = false>
+__global__ __launch_bounds__(256, APART ? kFp8EncoderWgPerCu : kFusedWgPerCu) void encoder_head_fp8_kernel(Fp8Args A) {
+  static_assert(!(HEAD8 && APART), "the fp8 head runs inside");
+  using Tiles = Smem8<H1, H2, HH, HEAD8>;
+  using S_t = std::conditional_t<APART, EncoderSmem8<H1>, Tiles>;
+  constexpr int T = Tiles::T, ZB = Tiles::ZB;
   constexpr int FT = H1 / 32;    // layer-1 feature tiles
   constexpr int FW = (FT + 3) / 4;  // layer-1 feature tiles per wave (tiles wave, wave + 4, ...)
   constexpr int KS2 = H1 / 64;   // layer-2 fp8 k-steps (two feature tiles each)
-  constexpr int HB = S_t::HB;
+  constexpr int HB = Tiles::HB;
   constexpr int CT = H2 / 128;   // encoder column tiles per wave
   static_assert(H1 % 64 == 0 && H2 % 128 == 0 && HH % 128 == 0, "widths");
   __shared__ S_t S;
@@ -242,11 +260,12 @@ __global__ __launch_bounds__(256, kFusedWgPerCu) void encoder_head_fp8_kernel(Fp
         if (tid < 2 * K) nxt0 = rows_g[(size_t)(p + 1) * 2 * K + tid];
         if (tid + 256 < 2 * K) nxt1 = rows_g[(size_t)(p + 1) * 2 * K + tid + 256];
       }
-      if (tid == 0) {
-        S.pair[slot] = p;
-        S.a[slot] = valid ? mt.a : -1;
-        S.swapped[slot] = mt.swapped;
-      }
+      if constexpr (!APART)
+        if (tid == 0) {
+          S.pair[slot] = p;
+          S.a[slot] = valid ? mt.a : -1;
+          S.swapped[slot] = mt.swapped;
+        }
       __syncthreads();
       // Row tiles t = 0, 1, ...: this wave's layer-1 features of tile t + 1
       // are computed while layer 2 of tile t runs, then stored to the other
@@ -335,22 +354,25 @@ __global__ __launch_bounds__(256, kFusedWgPerCu) void encoder_head_fp8_kernel(Fp
             if constexpr (HEAD8) {
               const int q = __builtin_amdgcn_cvt_pk_fp8_f32(fminf(f * inv_z, 448.f), 0.f, 0, false);
               S.z[slot * ZB + col] = (unsigned char)(q & 0xff);
+            } else if constexpr (APART) {  // every wave's part of this pair's rows is in LDS by now
+              A.z16[(size_t)p * 2 * K * 8 + col] = head_bf16::bits(f);
             } else {
-              reinterpret_cast<unsigned short*>(S.z)[slot * S_t::ZS + col] = head_bf16::bits(f);
+              reinterpret_cast<unsigned short*>(S.z)[slot * Tiles::ZS + col] = head_bf16::bits(f);
             }
             if (A.z_dbg) A.z_dbg[(size_t)p * 2 * H2 + col] = valid ? f : __builtin_nanf("");
           }
         }
       }
-      ++slot;
       __syncthreads();
-      if (slot == T) {
-        head_tile8<H1, H2, HH, HEAD8>(A, S, T);
-        slot = 0;
-      }
+      if constexpr (!APART)
+        if (++slot == T) {
+          head_tile8<H1, H2, HH, HEAD8>(A, S, T);
+          slot = 0;
+        }
     }
   }
-  if (slot > 0) head_tile8<H1, H2, HH, HEAD8>(A, S, slot);
+  if constexpr (!APART)
+    if (slot > 0) head_tile8<H1, H2, HH, HEAD8>(A, S, slot);
   if (A.dynamic && tid == 0) {
     __threadfence();
     if (atomicAdd(A.queue + 1, 1u) == gridDim.x - 1) {
@@ -449,7 +471,9 @@ void fp8_bind(Fp8Args& a, const unsigned char* base, int h1, int h2, int hh, boo
 
 template <int H1, int H2, int HH>
 void launch_fp8(const Fp8Args& a, bool head8, int grid, hipStream_t s) {
-  if (head8)
+  if (a.z16)
+    kernel_launch((encoder_head_fp8_kernel<H1, H2, HH, false, true>), dim3(grid), dim3(256), 0, s, a);
+  else if (head8)
     kernel_launch((encoder_head_fp8_kernel<H1, H2, HH, true>), dim3(grid), dim3(256), 0, s, a);
   else
     kernel_launch((encoder_head_fp8_kernel<H1, H2, HH, false>), dim3(grid), dim3(256), 0, s, a);
@@ -457,6 +481,7 @@ void launch_fp8(const Fp8Args& a, bool head8, int grid, hipStream_t s) {
 
 hipError_t launch_encoder_head_fp8(const Fp8Args& a, int h1, int h2, int hh, bool head8, int grid, hipStream_t s) {
   if (a.n_pairs <= 0) return hipSuccess;
+  if (a.z16 && (head8 || h2 > 8 * a.K)) return hipErrorInvalidValue;
   if (h1 == 64 && h2 == 128 && hh == 256)
     launch_fp8<64, 128, 256>(a, head8, grid, s);
   else if (h1 == 128 && h2 == 256 && hh == 512)

@@ -547,6 +547,7 @@ void locc_destroy(locc_ctx* c) {
   for (hipEvent_t e : c->event_pool) (void)hipEventDestroy(e);
   (void)hipFree(c->d_shapes);
   (void)hipFree(c->d_points);
+  (void)hipFree(c->d_clusters);
   (void)hipFree(c->d_wfp32);
   (void)hipFree(c->d_wbf16);
   (void)hipFree(c->d_wfp8);
@@ -745,13 +746,33 @@ locc_status locc_calibrate(locc_ctx* c, const locc_object* objs, int32_t n_objs,
   return LOCC_OK;
 }
 
+// The library's spatial clusters, which let the crop skip most of a shape.  Without the memory for them (15 bytes a
+// point next to the points' own 44) the crop tests every point, as it did.
+static hipError_t build_clusters(locc_ctx* c, int32_t n_shapes, int64_t n_points, int max_points) {
+  const size_t count = cluster_count(n_points, n_shapes);
+  const size_t box_bytes = count * 2 * sizeof(float4);
+  hipError_t e = hipMalloc(&c->d_clusters, box_bytes + count * kClusterBytes);
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    c->d_clusters = nullptr;
+    return hipSuccess;
+  }
+  if (e != hipSuccess) return e;
+  c->cluster_boxes = box_bytes;
+  e = launch_clusters(c->d_shapes, n_shapes, max_points, reinterpret_cast<const float4*>(c->d_points),
+                      reinterpret_cast<float4*>(c->d_clusters), c->d_clusters + box_bytes, nullptr);
+  return e == hipSuccess ? hipStreamSynchronize(nullptr) : e;
+}
+
 locc_status locc_upload_shapes(locc_ctx* c, int32_t n_shapes, const int64_t* off, const float* pts) {
   if (!c || !off || !pts) return fail(LOCC_ERR_INVALID_ARG, "null context, offsets or points");
   if (n_shapes <= 0) return fail(LOCC_ERR_INVALID_ARG, "n_shapes=%d", n_shapes);
   if (off[0] != 0) return fail(LOCC_ERR_INVALID_ARG, "offsets[0]=%lld, must be 0", (long long)off[0]);
+  int max_points = 0;
   for (int s = 0; s < n_shapes; ++s) {
     const int64_t n = off[s + 1] - off[s];
     if (n <= 0) return fail(LOCC_ERR_INVALID_ARG, "shape %d has %lld points", s, (long long)n);
+    max_points = n > max_points ? (int)n : max_points;
     if (n > kMaxShapePoints)
       return fail(LOCC_ERR_RANGE, "shape %d has %lld points (max %d)", s, (long long)n, kMaxShapePoints);
   }
@@ -760,7 +781,7 @@ locc_status locc_upload_shapes(locc_ctx* c, int32_t n_shapes, const int64_t* off
   if (c->live_graphs > 0)
     return fail(LOCC_ERR_BUSY, "shape library: %d captured graph(s) read the current one; destroy them first",
                 c->live_graphs);
-  std::vector<float> soa((size_t)total * 6);
+  std::vector<float> soa((size_t)total * 11);  // rows (x, y, z, nx, ny, nz, 0, 0), then x, y and z
   std::vector<ShapeDesc> desc(n_shapes);
   float xmax = 0.f, nmax = 0.f;  // largest coordinate and normal component
   for (int s = 0; s < n_shapes; ++s) {
@@ -776,7 +797,8 @@ locc_status locc_upload_shapes(locc_ctx* c, int32_t n_shapes, const int64_t* off
       for (int k = 0; k < 6; ++k) {
         if (!std::isfinite(row[k]))
           return fail(LOCC_ERR_INVALID_ARG, "shape %d point %lld: non-finite value", s, (long long)(r - off[s]));
-        soa[(size_t)k * total + r] = row[k];
+        soa[(size_t)r * 8 + k] = row[k];
+        if (k < 3) soa[(size_t)(8 + k) * total + r] = row[k];
         float& mx = k < 3 ? xmax : nmax;
         mx = std::fabs(row[k]) > mx ? std::fabs(row[k]) : mx;
       }
@@ -790,14 +812,17 @@ locc_status locc_upload_shapes(locc_ctx* c, int32_t n_shapes, const int64_t* off
   HIP_TRY(hipSetDevice(c->device));
   (void)hipFree(c->d_shapes);
   (void)hipFree(c->d_points);
+  (void)hipFree(c->d_clusters);
   c->d_shapes = nullptr;
   c->d_points = nullptr;
+  c->d_clusters = nullptr;
   c->n_shapes = 0;
   c->n_points = 0;
   HIP_TRY(hipMalloc(&c->d_shapes, sizeof(ShapeDesc) * n_shapes));
   HIP_TRY(hipMalloc(&c->d_points, sizeof(float) * soa.size()));
   HIP_TRY(hipMemcpy(c->d_shapes, desc.data(), sizeof(ShapeDesc) * n_shapes, hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(c->d_points, soa.data(), sizeof(float) * soa.size(), hipMemcpyHostToDevice));
+  HIP_TRY(build_clusters(c, n_shapes, total, max_points));
   c->n_shapes = n_shapes;
   c->n_points = total;
   c->lib_xmax = xmax;

@@ -2,7 +2,8 @@
 // puts it in canonical order and computes its float64 relative pose, crop box
 // and float32 screening constants (geometry.h), so that this work is done
 // once per pair instead of once per wave; then one wave per object of every
-// pair runs the membership scan and the ordered first-K selection, and
+// pair runs the membership scan (by spatial clusters, clusters.hip, or in
+// stored order) and the ordered first-K selection, and
 // writes counts, the optional index sets, the per-pair records and the
 // encoder input rows (float32 for the FP32 path, bf16 for BF16 / FP8).
 #include "geometry.h"
@@ -32,6 +33,8 @@ __global__ __launch_bounds__(kThreads) void pair_setup_kernel(CropArgs A) {
     r.n_a = da.n;
     r.off_b = db.off;
     r.n_b = db.n;
+    r.cl_a = da.off / kClusterPoints + oa.shape;
+    r.cl_b = db.off / kClusterPoints + ob.shape;
   }
   *reinterpret_cast<PairSetup*>(static_cast<char*>(A.setup) + (size_t)p * kPairSetupBytes) = r;
 }
@@ -44,6 +47,8 @@ __global__ __launch_bounds__(kThreads) void pair_setup_kernel(CropArgs A) {
 // resident workgroups does not cap the resident waves.
 struct ObjectShared {
   int32_t sel[kMaxK];
+  uint32_t member[kMaxShapePoints / 32];                // cluster path: a bit per stored point
+  uint16_t alive[kMaxShapePoints / kClusterPoints + 1];  // clusters that may hold members
 };
 
 // LDS written by some lanes of a wave and then read by others of the same
@@ -148,8 +153,105 @@ __device__ __forceinline__ int crop_scan(const PairSetup* __restrict__ rec, cons
   return found;
 }
 
+// The clusters of an object that may hold members, listed in S.alive; returns their number.  An a point lies in the box
+// iff its coordinates lie between the float bounds, so a cluster whose box ends before a bound holds none.  A b cluster
+// is tested in the screen's normalised coordinates: its box maps to an interval u = R' c + t' +- |R'| e (c, e: centre
+// and half-widths of the box), and members have |u| <= 1 up to the error that M bounds (geometry.h): with
+// 2^-21 S' for the map itself, the sums here add less than 2^-21 S', and M is at least 2^-19 S'.  A NaN anywhere keeps
+// the cluster.
+template <bool B>
+__device__ __forceinline__ int crop_alive(const PairScreen& sc, const float4* __restrict__ boxes, int nc, int lane,
+                                          ObjectShared& S) {
+  int alive = 0;  // wave-uniform
+  for (int c0 = 0; c0 < nc; c0 += 64) {
+    const int c = c0 + lane;
+    bool keep = false;
+    if (c < nc) {
+      const float4 lo = boxes[2 * c], hi = boxes[2 * c + 1];
+      if constexpr (B) {
+        const float cx = 0.5f * (lo.x + hi.x), cy = 0.5f * (lo.y + hi.y), cz = 0.5f * (lo.z + hi.z);
+        const float ex = fmaxf(hi.x - cx, cx - lo.x), ey = fmaxf(hi.y - cy, cy - lo.y), ez = fmaxf(hi.z - cz, cz - lo.z);
+        bool out = false;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+          const float* R = sc.R + 3 * i;
+          const float u = __builtin_fmaf(R[2], cz, __builtin_fmaf(R[1], cy, __builtin_fmaf(R[0], cx, sc.t[i])));
+          const float r = __builtin_fmaf(fabsf(R[2]), ez, __builtin_fmaf(fabsf(R[1]), ey, fabsf(R[0]) * ex));
+          out |= fabsf(u) - r > sc.thr_out;
+        }
+        keep = !out;
+      } else {
+        keep = !((lo.x > sc.ahi[0]) | (hi.x < sc.alo[0]) | (lo.y > sc.ahi[1]) | (hi.y < sc.alo[1]) |
+                 (lo.z > sc.ahi[2]) | (hi.z < sc.alo[2]) | (sc.alo[0] > sc.ahi[0]) | (sc.alo[1] > sc.ahi[1]) |
+                 (sc.alo[2] > sc.ahi[2]));
+      }
+    }
+    const unsigned long long m = __ballot(keep);
+    if (keep)
+      S.alive[__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, (unsigned)alive))] =
+          (uint16_t)c;
+    alive += __popcll(m);
+  }
+  return alive;
+}
+
+// Members of one object from its alive clusters: 16 lanes a cluster, four points a lane; a member sets its stored
+// index' bit in LDS, and the first K bits in order are the selection.  Returns all members found.
+template <bool B>
+__device__ __forceinline__ int crop_clusters(const PairSetup* __restrict__ rec, const PairScreen& sc,
+                                             const char* __restrict__ clusters, int alive, int n, int K, int lane,
+                                             ObjectShared& S) {
+  const int words = (n + 31) >> 5;
+  for (int w = lane; w < words; w += 64) S.member[w] = 0u;
+  wave_lds_sync();  // the list of clusters and the cleared bits
+  int found = 0;
+  for (int i0 = 0; i0 < alive; i0 += 4) {
+    const int i = i0 + (lane >> 4);
+    const char* c = clusters + (size_t)S.alive[i < alive ? i : i0] * kClusterBytes;
+    const float4 X = reinterpret_cast<const float4*>(c)[lane & 15];
+    const float4 Y = reinterpret_cast<const float4*>(c + 256)[lane & 15];
+    const float4 Z = reinterpret_cast<const float4*>(c + 512)[lane & 15];
+    const uint2 I = reinterpret_cast<const uint2*>(c + 768)[lane & 15];
+    const float x[4] = {X.x, X.y, X.z, X.w}, y[4] = {Y.x, Y.y, Y.z, Y.w}, z[4] = {Z.x, Z.y, Z.z, Z.w};
+    const unsigned id[4] = {I.x & 0xffffu, I.x >> 16, I.y & 0xffffu, I.y >> 16};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const bool in = (B ? geo_member_b(&rec->g, sc, x[k], y[k], z[k]) : geo_member_a(sc, x[k], y[k], z[k])) &
+                      (i < alive) & (id[k] != kNoPoint);
+      if (in) atomicOr(&S.member[id[k] >> 5], 1u << (id[k] & 31u));
+      found += __popcll(__ballot(in));
+    }
+  }
+  wave_lds_sync();
+  int before = 0;  // members of the words before
+  for (int w0 = 0; w0 < words && before < K; w0 += 64) {
+    unsigned word = w0 + lane < words ? S.member[w0 + lane] : 0u;
+    const int upto = geo_wave_inclusive_scan(__popc(word), lane);
+    int pos = before + upto - __popc(word);
+    while (word && pos < K) {
+      S.sel[pos++] = 32 * (w0 + lane) + __builtin_ctz(word);
+      word &= word - 1;
+    }
+    before += __builtin_amdgcn_readlane(upto, 63);
+  }
+  return found;
+}
+
+// Whether the alive clusters are scanned rather than the stored points in order, which ends once K members are known:
+// at about K n / (32 alive) points, as an alive cluster holds half its points on average.  The clusters cost their own
+// points, and the selection from the bits about as much as 256.  (Half or twice the 32 cost the same to 0.5%; always
+// the clusters: 16,384 pairs of 2,048 points 267.5 us instead of 253.5.)
+__device__ __forceinline__ bool crop_by_clusters(int alive, int n, int K, bool full) {
+  const float scan = full ? (float)n : fminf((float)n, (float)K * (float)n / (float)(32 * alive));
+  return (float)(64 * alive + 256) <= scan;
+}
+
+// Bound by latency (a wave's chain of dependent loads: record, cluster boxes, points, rows) and, with the chip full,
+// by vector issue (half of it used); 80 registers keep six waves per SIMD (84 and five: 1,987 us instead of 1,941 for
+// a step of 210,040 pairs).  The clusters skip most points: half of that step's objects have no member and tested
+// 2,048 points each, now mostly none (crop 616 us before, 330 with them).
 template <int U, int W>
-__global__ __launch_bounds__(64 * W) void crop_kernel(CropArgs A) {
+__global__ __launch_bounds__(64 * W, 6) void crop_kernel(CropArgs A) {
   __shared__ ObjectShared SW[W];
   const int wave = W == 1 ? 0 : wave_index();
   ObjectShared& S = SW[wave];
@@ -186,13 +288,24 @@ __global__ __launch_bounds__(64 * W) void crop_kernel(CropArgs A) {
   const float* __restrict__ px = A.lib.px + off;
   const float* __restrict__ py = A.lib.py + off;
   const float* __restrict__ pz = A.lib.pz + off;
-  int found;
+  const int cl = side ? rec->cl_b : rec->cl_a, nc = (n + kClusterPoints - 1) / kClusterPoints;
+  const float4* boxes = A.lib.boxes && n > A.cluster_min ? A.lib.boxes + 2 * (size_t)cl : nullptr;
+  const char* clusters = A.lib.clusters + (size_t)cl * kClusterBytes;
+  int found, alive = 0;
   if (side) {
 #pragma unroll
     for (int i = 0; i < 3; ++i) sc.t[i] = crop_to_vgpr(sc.t[i]);
-    found = crop_scan<(U >= 8 ? 2 : 1), true>(rec, sc, px, py, pz, n, K, full, lane, S);
+    if (boxes) alive = crop_alive<true>(sc, boxes, nc, lane, S);
+    if (boxes && crop_by_clusters(alive, n, K, full))
+      found = crop_clusters<true>(rec, sc, clusters, alive, n, K, lane, S);
+    else
+      found = crop_scan<(U >= 8 ? 2 : 1), true>(rec, sc, px, py, pz, n, K, full, lane, S);
   } else {
-    found = crop_scan<(U >= 8 ? 2 : 1), false>(rec, sc, px, py, pz, n, K, full, lane, S);
+    if (boxes) alive = crop_alive<false>(sc, boxes, nc, lane, S);
+    if (boxes && crop_by_clusters(alive, n, K, full))
+      found = crop_clusters<false>(rec, sc, clusters, alive, n, K, lane, S);
+    else
+      found = crop_scan<(U >= 8 ? 2 : 1), false>(rec, sc, px, py, pz, n, K, full, lane, S);
   }
   // found: every member when full, else at least min(K, members)
   wave_lds_sync();  // the selected indices are read by other lanes
@@ -254,8 +367,13 @@ __global__ __launch_bounds__(64 * W) void crop_kernel(CropArgs A) {
 
 }  // namespace
 
-hipError_t launch_crop(const CropArgs& a, hipStream_t s, int unroll) {
+hipError_t launch_crop(const CropArgs& args, hipStream_t s, int unroll) {
+  CropArgs a = args;
   if (a.n_pairs <= 0) return hipSuccess;
+  // A few blocks of stored points take a lone wave no longer than the cluster boxes and the selection (80 pairs of 1,024
+  // points with counts: 32.2 us in stored order, 33.7 by clusters); with the chip full the points skipped count
+  // (a step of 210,040 pairs of 1,024 points: 1,847 and 1,782 us; of 512 points: 1,831 and 1,850).
+  a.cluster_min = a.n_pairs < 4096 ? 1024 : 512;
   if (!a.setup || (unroll != 2 && unroll != 4 && unroll != 8)) return hipErrorInvalidValue;
   kernel_launch(pair_setup_kernel, dim3((a.n_pairs + kThreads - 1) / kThreads), dim3(kThreads), 0, s, a);
   constexpr int W = kCropWaves;

@@ -395,16 +395,19 @@ struct PairSetup {
   int32_t valid;          // 0: invalid pair (index out of range, i == j, shape id out of range)
   int32_t a, swapped;     // canonical first object, caller order flag
   int32_t off_a, n_a, off_b, n_b;  // stored points of the two shapes
+  int32_t cl_a, cl_b;              // their first clusters
 };
 static_assert(sizeof(PairSetup) <= kPairSetupBytes, "pair set-up record");
 
 // Encoder input row (x, y, z, nx, ny, nz) in a's frame of stored point gi of
 // object `side` (0 = a as stored, 1 = b transformed in float64, then rounded).
 __device__ __forceinline__ void geo_row(const PairGeom& g, const DeviceLibrary& lib, int gi, int side, float* v) {
+  const float4 u = lib.rows[2 * (size_t)gi];
+  const float2 w = *reinterpret_cast<const float2*>(lib.rows + 2 * (size_t)gi + 1);
   if (side) {
     double q[3], n[3];
-    geo_xform(g, lib.px[gi], lib.py[gi], lib.pz[gi], q);
-    geo_rotate(g, lib.nx[gi], lib.ny[gi], lib.nz[gi], n);
+    geo_xform(g, u.x, u.y, u.z, q);
+    geo_rotate(g, u.w, w.x, w.y, n);
     v[0] = (float)q[0];
     v[1] = (float)q[1];
     v[2] = (float)q[2];
@@ -412,12 +415,12 @@ __device__ __forceinline__ void geo_row(const PairGeom& g, const DeviceLibrary& 
     v[4] = (float)n[1];
     v[5] = (float)n[2];
   } else {
-    v[0] = lib.px[gi];
-    v[1] = lib.py[gi];
-    v[2] = lib.pz[gi];
-    v[3] = lib.nx[gi];
-    v[4] = lib.ny[gi];
-    v[5] = lib.nz[gi];
+    v[0] = u.x;
+    v[1] = u.y;
+    v[2] = u.z;
+    v[3] = u.w;
+    v[4] = w.x;
+    v[5] = w.y;
   }
 }
 

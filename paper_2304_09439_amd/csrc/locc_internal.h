@@ -69,13 +69,26 @@ constexpr int kRowFloats = 8;
 struct DeviceLibrary {
   const ShapeDesc* shapes;
   int32_t n_shapes;
-  const float* px;
+  const float4* rows;  // two a point: x, y, z, nx | ny, nz, 0, 0
+  const float* px;     // the coordinates once more, for the scan in stored order
   const float* py;
   const float* pz;
-  const float* nx;
-  const float* ny;
-  const float* nz;
+  // spatial clusters (clusters.hip), or null: the box of cluster c in boxes[2 c] (lo) and boxes[2 c + 1] (hi), its
+  // points at points + c * kClusterBytes
+  const float4* boxes;
+  const char* clusters;
 };
+
+// A shape's points once more, as clusters of 64 close to each other (the last one padded by copies of a point with
+// index kNoPoint): 64 x, 64 y, 64 z, 64 16-bit indices into the shape's stored points.  Cluster k of shape s, whose
+// stored points begin at off, is number off / 64 + s + k.
+constexpr int kClusterPoints = 64;
+constexpr size_t kClusterBytes = 64 * (3 * 4 + 2);
+constexpr unsigned kNoPoint = 0xffff;
+inline size_t cluster_count(int64_t n_points, int n_shapes) { return (size_t)(n_points / 64) + n_shapes + 1; }
+// The clusters of every shape of a library from its rows (finite); boxes and clusters of cluster_count().
+hipError_t launch_clusters(const ShapeDesc* shapes, int n_shapes, int max_points, const float4* rows, float4* boxes,
+                           char* clusters, hipStream_t s);
 
 // Pair count of a launch: n_pairs is the capacity (grid sizing); when
 // n_pairs_dev is set the kernels read the actual count from device memory
@@ -106,6 +119,7 @@ struct CropArgs {
   unsigned long long* err_counter;
   void* setup;           // [P] records of kPairSetupBytes (library workspace), required
   int32_t dev_base;      // first pair of this launch within the step (device count mode)
+  int32_t cluster_min;   // set by launch_crop: shapes of more points are scanned by clusters where that is less work
 };
 
 // Bytes of the per-pair record (pose, box, screening constants, canonical
@@ -115,7 +129,7 @@ constexpr size_t kPairSetupBytes = 320;
 // Pair set-up (one thread per pair), then the crop (one wave per object of a
 // pair, the two waves of a pair in one workgroup).  unroll (2, 4 or 8): a
 // wave issues the loads of max(1, unroll / 4) blocks of 256 points together.
-hipError_t launch_crop(const CropArgs& a, hipStream_t s, int unroll = 8);
+hipError_t launch_crop(const CropArgs& args, hipStream_t s, int unroll = 8);
 
 // Broad phase over environments: world boxes, then every overlapping pair
 // i < j of objects of the same environment (see broad_phase.hip).

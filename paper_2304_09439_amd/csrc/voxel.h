@@ -33,11 +33,12 @@ static_assert(sizeof(Shape) == 32, "Shape layout");
 
 // Device pointers to every weight array: the flat vector as uploaded, except
 // the point MLP's layers 2-3, used transposed to [in][out] (a coalesced row
-// of outputs per input), and the U-Net's weights, used transposed to
-// [27 taps][in][out], both from a second, packed buffer.
+// of outputs per input), and the U-Net's weights, used as
+// [27 taps][in / 8][2][out][4] (input channel 8 q + 2 v + g at [q][g][.][v]),
+// both from a second, packed buffer.
 struct PackedNet {
   const float *P1, *p1, *P2t, *p2, *P3t, *p3;  // point MLP
-  const float *C[4], *k[4], *D[4], *e[4];      // U-Net convs, transposed convs (C, D: [27][in][128])
+  const float *C[4], *k[4], *D[4], *e[4];      // U-Net convs, transposed convs (C, D: [27][in / 8][2][128][4])
   const float *L, *l;                          // embedding map [16][384]
   const float *A[3], *a[3];                    // per-object MLP [128][28], [128][128] x 2 (row-major)
   const float *Bw[3], *b[4], *B4;              // pair MLP [128][128] x 3, output row [128], b[3] = its bias
@@ -50,16 +51,18 @@ PackedNet packed_view(const float* d_raw, const float* d_packed);
 struct EncoderBuffers {
   int32_t* order; // [n_points]: per shape, its point indices sorted by grid cell
   uint8_t* cell;  // [n_points]: the grid cell of each entry of order
-  float* grid;    // [S][256][216] (cell max of the point features, channel-major)
-  float* c[4];    // [S][128][64]
-  float* d[3];    // [S][128][64]
-  float* d4;      // [S][128][216]
+  // activations, [position][channel / 8][channel % 2][S][(channel % 8) / 2]
+  float* grid;    // 216 positions, 256 channels: cell max of the point features
+  float* c[4];    // 64 positions, 128 channels
+  float* d[3];    // 64 positions, 128 channels
+  float* d4;      // 216 positions, 128 channels
   float* glob;    // [S][256]
 };
+constexpr int kEncodeShapes = 4096;
 size_t encoder_scratch_floats(int n_shapes, int64_t n_points);
 EncoderBuffers encoder_carve(float* base, int n_shapes, int64_t n_points);
 
-// Shape encoder over every shape; grid must be zero (the cell max starts at 0).
+// Shape encoder over n_shapes <= kEncodeShapes shapes; grid must be zero (the cell max starts at 0).
 hipError_t launch_encoder(const PackedNet& w, const Shape* shapes, int n_shapes, int max_points, const float* xyz,
                           int64_t n_points, const EncoderBuffers& b, float* emb, double* consts,
                           hipStream_t s);

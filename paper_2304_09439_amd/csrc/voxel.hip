@@ -26,6 +26,8 @@
 // overwrites after all its reads; every thread owns one output column of a
 // layer for a quarter of the rows, reading the weights [in][out] from L2
 // (coalesced) and the rows from LDS as broadcasts.
+#include <cstring>
+
 #include "geometry.h"
 #include "voxel.h"
 
@@ -34,6 +36,12 @@ namespace vox {
 namespace {
 
 __device__ __forceinline__ float relu(float x) { return x > 0.f ? x : 0.f; }
+
+// Where the U-Net's activations keep channel c of shape s (of S) at grid position x: [x][c / 8][c % 2][s][(c % 8) / 2],
+// so that 16 bytes hold four channels of a column and a half-wave's loads are contiguous.
+__device__ __forceinline__ size_t act_at(int x, int c, int s, int C, int S) {
+  return ((((size_t)x * (C / 8) + c / 8) * 2 + (c & 1)) * S + s) * 4 + ((c & 7) >> 1);
+}
 
 // Grid cell of a stored point (float64, the order of the reading).
 __device__ __forceinline__ int cell_of(float x, float y, float z, const Shape& sh) {
@@ -187,19 +195,20 @@ __global__ __launch_bounds__(256) void point_mlp_kernel(PackedNet w, const Shape
     __syncthreads();
   }
   // max over each run of equal cells (the grid starts at 0 and the outputs are >= 0)
-  unsigned int* gp = reinterpret_cast<unsigned int*>(grid) + ((size_t)s * kH + t) * kCells;
+  unsigned int* gp = reinterpret_cast<unsigned int*>(grid) + act_at(0, t, s, kH, gridDim.y);
+  const size_t cell_stride = (size_t)kH * gridDim.y;
   int cur = cell[0];
   float m = 0.f;
   for (int p = 0; p < np; ++p) {
     const int c = cell[p];  // uniform
     if (c != cur) {
-      atomicMax(gp + cur, __float_as_uint(m));
+      atomicMax(gp + cur * cell_stride, __float_as_uint(m));
       cur = c;
       m = 0.f;
     }
     m = fmaxf(m, HT[t][p]);
   }
-  atomicMax(gp + cur, __float_as_uint(m));
+  atomicMax(gp + cur * cell_stride, __float_as_uint(m));
 }
 
 // Convolutions and transposed convolutions of the U-Net as implicit GEMMs on
@@ -208,121 +217,205 @@ __global__ __launch_bounds__(256) void point_mlp_kernel(PackedNet w, const Shape
 // channels c (the skip concatenation read from two inputs), in(c, u, s, x) =
 // input c of shape s at x + u - pad (conv) or x - u + pad (transposed), 0
 // outside the grid.  A workgroup owns 32 output channels x 32 output
-// positions; its eight waves take an eighth of the channels each, NP pairs
-// of them, over all 27 taps, tap-major: a tap's grid offset and bounds test
-// are formed once per lane and serve its NP steps, and the next tap's
-// operands load while the current tap's NP products issue.  The weights come
-// transposed, Wt[u][c][o], so that a step's A operand is two coalesced rows.
-// The waves' 32 x 32 partial sums meet in LDS and are added in wave order (a
-// fixed order: a launch is reproducible bit for bit).  Lane layouts of
-// 32x32x2: A[i][k] and B[k][j] with i, j = l % 32 and k = l / 32 (here the
-// channel parity); D[i][j] with j = l % 32 and i = 8 (r / 4) + 4 (l / 32) +
-// r % 4 for register r.
+// columns n = p S + s (p: positions, the middle first); its eight waves take an eighth of the channels each, NP
+// pairs of them, over the taps, tap-major.  Columns of a tile are mostly shapes
+// at one position, so that a tap outside the grid is skipped for the whole tile
+// (of the last layer's taps 70%).  The next tap's operands load while the
+// current tap's NP products issue.  The waves' 32 x 32 partial sums meet in LDS
+// and are added in wave order (a fixed order: a launch is reproducible bit for
+// bit).  Lane layouts of 32x32x2: A[i][k] and B[k][j] with i, j = l % 32 and
+// k = l / 32 (here the channel parity); D[i][j] with j = l % 32 and
+// i = 8 (r / 4) + 4 (l / 32) + r % 4 for register r.
+//
+// Both operands lie in memory as a lane reads them: channels 8 q + 2 v + g,
+// v = 0..3, of a weight row or a column in one 16-byte load, which serves four
+// products.  Bound by the products (FP32 matrix cores): 18 us a layer of 128
+// input channels and 32 of 256 at 32 shapes, 46 the last (28 and 56 with a
+// 4-byte load per operand and product, which kept the address units busy
+// longer than the matrix cores, and 180 the last, its outside taps included).
 struct ConvArgs {
-  const float* in1;  // [S][c1][D^3]
+  const float* in1;  // act_at() layout, c1 channels, D^3 positions
   int c1;
-  const float* in2;  // [S][c2][D^3] (the concatenated skip), or null with c2 = 0
+  const float* in2;  // as in1, c2 channels (the concatenated skip), or null with c2 = 0
   int c2;
-  const float* Wt;   // [27][c1 + c2][O]
+  const float* Wt;   // [27][(c1 + c2) / 8][2 g][O][4 v]
   const float* b;    // [O]
-  float* out;        // [S][O][Do^3]
+  float* out;        // act_at() layout, O channels, Do^3 positions
   int O, D, Do, pad, transposed, n_shapes;
 };
 
 constexpr int kConvWaves = 8;
 
+// Position p of n = p S + s: the middle of the grid first, whose taps all lie inside, so that the workgroups with the
+// most work start first.
+__device__ __forceinline__ int conv_axis(int k, int Do) { return (k & 1) ? Do / 2 + (k >> 1) : Do / 2 - 1 - (k >> 1); }
+__device__ __forceinline__ void conv_position(int p, int Do, int& x0, int& x1, int& x2) {
+  x0 = conv_axis(p / (Do * Do), Do);
+  x1 = conv_axis((p / Do) % Do, Do);
+  x2 = conv_axis(p % Do, Do);
+}
+
 template <int NP>  // channel pairs per wave: (c1 + c2) = 16 NP
 __global__ __launch_bounds__(64 * kConvWaves) void conv_kernel(ConvArgs A) {
   __shared__ float part[kConvWaves][32][33];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 5, l32 = lane & 31;
-  const int D = A.D, Do = A.Do, D3 = D * D * D, Do3 = Do * Do * Do;
-  const int N = A.n_shapes * Do3, C = A.c1 + A.c2, O = A.O;
-  const int n0 = blockIdx.x * 32, o0 = blockIdx.y * 32;
-  // this lane's output position (B column)
+  constexpr int NQ = NP / 4;  // 16-byte loads per operand and tap
+  const int lane = threadIdx.x & 63, wave = wave_index(), g = lane >> 5, l32 = lane & 31;
+  const int D = A.D, Do = A.Do, Do3 = Do * Do * Do, S = A.n_shapes;
+  const int N = S * Do3, C = A.c1 + A.c2, O = A.O;
+  const int n0 = blockIdx.y * 32, o0 = blockIdx.x * 32;
+  // this lane's output column (B column)
   const int n = n0 + l32;
   const bool live = n < N;
-  const int sh = live ? n / Do3 : 0, x = live ? n % Do3 : 0;
-  const int x0 = x / (Do * Do), x1 = (x / Do) % Do, x2 = x % Do;
+  const int sh = live ? n % S : 0;
+  int x0, x1, x2;
+  conv_position(live ? n / S : 0, Do, x0, x1, x2);
   // this wave's channels c_begin + 2 j + g, all from one input (c1 is a multiple of 2 NP)
   const int c_begin = wave * 2 * NP;
-  const float* src = c_begin < A.c1 ? A.in1 + ((size_t)sh * A.c1 + c_begin + g) * D3
-                                    : A.in2 + ((size_t)sh * A.c2 + (c_begin - A.c1) + g) * D3;
-  const float* wt = A.Wt + (size_t)(c_begin + g) * O + o0 + l32;
-  const size_t tap_stride = (size_t)C * O;
-  // The loads are unconditional (a tap outside the grid reads the channel's
-  // first value) and the bound test selects 0 at the product, so that no
-  // branch splits the loads of a tap and the waits stay per operand.
-  auto load = [&](int u, float (&a)[NP], float (&b)[NP]) -> bool {
-    const int u0 = u / 9, u1 = (u / 3) % 3, u2 = u % 3;
-    const int y0 = A.transposed ? x0 - u0 + A.pad : x0 + u0 - A.pad;
-    const int y1 = A.transposed ? x1 - u1 + A.pad : x1 + u1 - A.pad;
-    const int y2 = A.transposed ? x2 - u2 + A.pad : x2 + u2 - A.pad;
-    const bool ok = live && y0 >= 0 && y0 < D && y1 >= 0 && y1 < D && y2 >= 0 && y2 < D;
-    const float* sp = src + (ok ? (y0 * D + y1) * D + y2 : 0);
-    const float* wp = wt + (size_t)u * tap_stride;
+  const bool second = c_begin >= A.c1;
+  const int c_in = second ? A.c2 : A.c1, c_own = c_begin - (second ? A.c1 : 0);
+  // raw buffer views of the wave's channels and weights: a load past the end reads zeros and no memory, so that a
+  // column outside the grid needs neither a branch nor a select
+  const float* src = (second ? A.in2 : A.in1) + (size_t)c_own * S;
+  const __amdgpu_buffer_rsrc_t in =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(src), (short)0, (c_in * D * D * D - c_own) * S * 4, 0x00020000);
+  const __amdgpu_buffer_rsrc_t wts =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(A.Wt), (short)0, 27 * C * O * 4, 0x00020000);
+  const unsigned pos_bytes = (unsigned)c_in * S * 4, in_lane = (unsigned)(g * S + sh) * 16;
+  const unsigned tap_bytes = (unsigned)C * O * 4, w_lane = (unsigned)((c_begin / 4 + g) * O + o0 + l32) * 16;
+  // the taps with an input in the grid for some column of the tile: per axis three bits a column, then their product
+  unsigned axis[3];
+  {
+    const int xs[3] = {x0, x1, x2};
 #pragma unroll
-    for (int j = 0; j < NP; ++j) {
-      a[j] = wp[(size_t)2 * j * O];
-      b[j] = sp[2 * j * D3];
+    for (int k = 0; k < 3; ++k) {
+      axis[k] = 0;
+#pragma unroll
+      for (int u = 0; u < 3; ++u) {
+        const int y = A.transposed ? xs[k] - u + A.pad : xs[k] + u - A.pad;
+        axis[k] |= (live & ((unsigned)y < (unsigned)D)) ? 1u << u : 0u;
+      }
     }
-    return ok;
+  }
+  const unsigned row = (axis[1] & 1 ? axis[2] : 0u) | (axis[1] & 2 ? axis[2] << 3 : 0u) | (axis[1] & 4 ? axis[2] << 6 : 0u);
+  const unsigned mine = (axis[0] & 1 ? row : 0u) | (axis[0] & 2 ? row << 9 : 0u) | (axis[0] & 4 ? row << 18 : 0u);
+  unsigned taps = mine;
+#pragma unroll
+  for (int d = 1; d < 32; d <<= 1) taps |= __shfl_xor(taps, d, 64);
+  taps = __builtin_amdgcn_readfirstlane(taps);
+  const int step = A.transposed ? -1 : 1;
+  const int y_base = ((x0 - step * A.pad) * D + (x1 - step * A.pad)) * D + (x2 - step * A.pad);
+  auto load = [&](int u, float4 (&a)[NQ], float4 (&b)[NQ]) {  // u past the last tap: zeros
+    const int u0 = u / 9, u1 = (u / 3) % 3, u2 = u % 3;       // uniform
+    const unsigned y = (unsigned)(y_base + step * ((u0 * D + u1) * D + u2));
+    const unsigned b_at = (mine >> u) & 1u ? y * pos_bytes + in_lane : 0x80000000u, w_at = (unsigned)u * tap_bytes + w_lane;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      a[q] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(wts, w_at + (unsigned)(2 * q * O) * 16, 0, 0));
+      b[q] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(in, b_at + (unsigned)(2 * q * S) * 16, 0, 0));
+    }
   };
   f32x16 acc = f32x16{};
-  float a0[NP], b0[NP], a1[NP], b1[NP];
-  // taps in pairs (u, u + 1) for u = 0, 2, ..., 24, then tap 26; no branch
-  // around a load, so each product waits only for its own operands
-  bool ok0 = load(0, a0, b0);
-  for (int u = 0; u < 26; u += 2) {
-    const bool ok1 = load(u + 1, a1, b1);
+  auto products = [&](const float4 (&a)[NQ], const float4 (&b)[NQ]) {
 #pragma unroll
-    for (int j = 0; j < NP; ++j)
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[j], ok0 ? b0[j] : 0.f, acc, 0, 0, 0);
-    ok0 = load(u + 2, a0, b0);
+    for (int q = 0; q < NQ; ++q) {
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q].x, b[q].x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q].y, b[q].y, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q].z, b[q].z, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q].w, b[q].w, acc, 0, 0, 0);
+    }
+  };
+  // taps in ascending order, the next three loading (counts of taps are mostly multiples of three)
+  auto next = [&]() -> int {
+    const int u = taps ? __builtin_ctz(taps) : 27;
+    taps &= taps - 1;
+    return u;
+  };
+  constexpr int DEPTH = 3;
+  const int rounds = (__builtin_popcount(taps) + DEPTH - 1) / DEPTH;
+  float4 a[DEPTH][NQ], b[DEPTH][NQ];
 #pragma unroll
-    for (int j = 0; j < NP; ++j)
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[j], ok1 ? b1[j] : 0.f, acc, 0, 0, 0);
-  }
+  for (int d = 0; d < DEPTH; ++d) load(next(), a[d], b[d]);
+#pragma unroll 1
+  for (int r = 0; r < rounds; ++r)
 #pragma unroll
-  for (int j = 0; j < NP; ++j)
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[j], ok0 ? b0[j] : 0.f, acc, 0, 0, 0);
+    for (int d = 0; d < DEPTH; ++d) {
+      products(a[d], b[d]);
+      load(next(), a[d], b[d]);
+    }
 #pragma unroll
   for (int r = 0; r < 16; ++r) part[wave][8 * (r >> 2) + 4 * g + (r & 3)][l32] = acc[r];
   __syncthreads();
-  for (int e = threadIdx.x; e < 32 * 32; e += 64 * kConvWaves) {
-    const int i = e >> 5, j = e & 31;   // output channel o0 + i, position n0 + j
+  for (int e = threadIdx.x; e < 8 * 32; e += 64 * kConvWaves) {
+    const int j = e & 31, cg = e >> 5;  // column n0 + j; channels o0 + 8 (cg / 2) + 2 v + cg % 2
     const int nn = n0 + j;
     if (nn >= N) continue;
-    float v = A.b[o0 + i];
+    float4 v4;
+    float* v = reinterpret_cast<float*>(&v4);
 #pragma unroll
-    for (int w = 0; w < kConvWaves; ++w) v += part[w][i][j];
-    const int s2 = nn / Do3, xx = nn % Do3;
-    A.out[((size_t)s2 * O + o0 + i) * Do3 + xx] = relu(v);
+    for (int k = 0; k < 4; ++k) {
+      const int i = 8 * (cg >> 1) + 2 * k + (cg & 1);
+      float w = A.b[o0 + i];
+#pragma unroll
+      for (int q = 0; q < kConvWaves; ++q) w += part[q][i][j];
+      v[k] = relu(w);
+    }
+    int z0, z1, z2;
+    conv_position(nn / S, Do, z0, z1, z2);
+    *reinterpret_cast<float4*>(A.out + act_at((z0 * Do + z1) * Do + z2, o0 + 8 * (cg >> 1) + (cg & 1), nn % S, O, S)) = v4;
   }
 }
 
-__global__ __launch_bounds__(kC) void global_kernel(const float* c4, float* glob) {
-  const int s = blockIdx.x, c = threadIdx.x;
-  const float* src = c4 + ((size_t)s * kC + c) * kB;
+// A lane per (shape, channel) of the bottleneck's channels with one q and g.
+__global__ __launch_bounds__(64) void global_kernel(const float* c4, float* glob, int n_shapes) {
+  const int v = threadIdx.x & 3, s = blockIdx.x * 16 + (threadIdx.x >> 2);
+  const int c = 8 * (blockIdx.y >> 1) + 2 * v + (blockIdx.y & 1);
+  if (s >= n_shapes) return;
+  const float* src = c4 + act_at(0, c, s, kC, n_shapes);
+  const size_t stride = (size_t)kC * n_shapes;
   float m = src[0], sum = 0.f;
+#pragma unroll 8
   for (int x = 0; x < kB; ++x) {
-    m = src[x] > m ? src[x] : m;
-    sum += src[x];
+    const float f = src[x * stride];
+    m = f > m ? f : m;
+    sum += f;
   }
   glob[(size_t)s * 2 * kC + c] = m;
   glob[(size_t)s * 2 * kC + kC + c] = sum / (float)kB;
 }
 
-// E[s][cell][f] = l[f] + L[f] . [d4[s][:][cell], glob[s]]
+// E[s][cell][f] = l[f] + L[f] . [d4[s][:][cell], glob[s]]: a workgroup per shape and 16 cells, a thread per cell and
+// feature, L transposed in LDS; the global feature's part is the same for every cell and summed once (13 us at 32 shapes;
+// 28 with L from memory and that part in every cell).
+constexpr int kEmbedCells = 256 / kF;
 __global__ __launch_bounds__(256) void embed_kernel(PackedNet w, const float* d4, const float* glob, float* emb,
                                                     int n_shapes) {
-  const int id = blockIdx.x * 256 + threadIdx.x;
-  if (id >= n_shapes * kCells * kF) return;
-  const int f = id % kF, cell = (id / kF) % kCells, s = id / (kF * kCells);
-  const float* Lf = w.L + (size_t)f * 3 * kC;
+  __shared__ float L[3 * kC][kF + 1];
+  __shared__ float part[16][kF];
+  const int t = threadIdx.x, f = t % kF, c = t / kF;
+  const int s = blockIdx.x, cell = blockIdx.y * kEmbedCells + c;
+  for (int i = t; i < kF * 3 * kC; i += 256) L[i % (3 * kC)][i / (3 * kC)] = w.L[i];
+  __syncthreads();
+  {
+    const float* gs = glob + (size_t)s * 2 * kC + c * (2 * kC / 16);
+    float v = 0.f;
+#pragma unroll
+    for (int k = 0; k < 2 * kC / 16; ++k) v = fmaf(L[kC + c * (2 * kC / 16) + k][f], gs[k], v);
+    part[c][f] = v;
+  }
+  __syncthreads();
+  if (cell >= kCells) return;
   float acc = w.l[f];
-  for (int k = 0; k < kC; ++k) acc = fmaf(Lf[k], d4[((size_t)s * kC + k) * kCells + cell], acc);
-  for (int k = 0; k < 2 * kC; ++k) acc = fmaf(Lf[kC + k], glob[(size_t)s * 2 * kC + k], acc);
-  emb[id] = acc;
+#pragma unroll 4
+  for (int q = 0; q < kC / 8; ++q) {
+    const float4 e = *reinterpret_cast<const float4*>(d4 + act_at(cell, 8 * q, s, kC, n_shapes));
+    const float4 o = *reinterpret_cast<const float4*>(d4 + act_at(cell, 8 * q + 1, s, kC, n_shapes));
+    const float d[8] = {e.x, o.x, e.y, o.y, e.z, o.z, e.w, o.w};
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc = fmaf(L[8 * q + k][f], d[k], acc);
+  }
+#pragma unroll
+  for (int k = 0; k < 16; ++k) acc += part[k][f];
+  emb[((size_t)s * kCells + cell) * kF + f] = acc;
 }
 
 // Per shape: the cell size s = (hi - lo) / 6 per axis and the margin
@@ -651,7 +744,7 @@ void transpose(const float* src, int rows, int cols, float* dst) {
     for (int c = 0; c < cols; ++c) dst[(size_t)c * rows + r] = src[(size_t)r * cols + c];
 }
 
-// Packed buffer: P2t, P3t, then the U-Net weights transposed to [27][in][out]:
+// Packed buffer: P2t, P3t, then the U-Net weights transposed to [27][in / 8][2][out][4]:
 // C[0..3], D[0..3] (input channels 256, 128, 128, 128, 128, 256, 256, 256).
 constexpr int kConvIn[8] = {kH, kC, kC, kC, kC, 2 * kC, 2 * kC, 2 * kC};
 constexpr size_t kPackSizes[] = {kH * kH, kH * kH,
@@ -659,11 +752,18 @@ constexpr size_t kPackSizes[] = {kH * kH, kH * kH,
                                  (size_t)27 * kC * kC, (size_t)27 * kC * kC, (size_t)27 * 2 * kC * kC,
                                  (size_t)27 * 2 * kC * kC, (size_t)27 * 2 * kC * kC};
 
-// [O][C][27] -> [27][C][O]
+// [O][C][27] -> [27][C / 8][2][O][4]: channel 8 q + 2 v + g at [q][g][.][v]
 void conv_transpose(const float* src, int C, float* dst) {
-  for (int o = 0; o < kC; ++o)
-    for (int c = 0; c < C; ++c)
-      for (int u = 0; u < 27; ++u) dst[((size_t)u * C + c) * kC + o] = src[((size_t)o * C + c) * 27 + u];
+  constexpr int kRow = 4 * kC;  // floats per tap, q and g
+  float tile[27][kRow + 16];  // padded: the taps' rows start in different cache sets
+  for (int qg = 0; qg < C / 4; ++qg) {
+    for (int o = 0; o < kC; ++o)
+      for (int v = 0; v < 4; ++v) {
+        const float* w = src + ((size_t)o * C + 8 * (qg >> 1) + 2 * v + (qg & 1)) * 27;
+        for (int u = 0; u < 27; ++u) tile[u][4 * o + v] = w[u];
+      }
+    for (int u = 0; u < 27; ++u) std::memcpy(dst + ((size_t)u * (C / 4) + qg) * kRow, tile[u], sizeof(float) * kRow);
+  }
 }
 
 }  // namespace
@@ -725,9 +825,12 @@ PackedNet packed_view(const float* raw, const float* packed) {
   return w;
 }
 
+// Floats that order and cell take, to the next 256 bytes (the activations behind them are read 16 bytes at a time).
+static size_t encoder_index_floats(size_t n_points) { return (n_points + (n_points + 3) / 4 + 63) / 64 * 64; }
+
 size_t encoder_scratch_floats(int n_shapes, int64_t n_points) {
   const size_t S = (size_t)n_shapes, P = (size_t)n_points;
-  return P + (P + 3) / 4 + S * kH * kCells + 7 * S * kC * kB + S * kC * kCells + S * 2 * kC;
+  return encoder_index_floats(P) + S * kH * kCells + 7 * S * kC * kB + S * kC * kCells + S * 2 * kC;
 }
 
 EncoderBuffers encoder_carve(float* base, int n_shapes, int64_t n_points) {
@@ -737,7 +840,7 @@ EncoderBuffers encoder_carve(float* base, int n_shapes, int64_t n_points) {
   b.order = reinterpret_cast<int32_t*>(p);
   p += P;
   b.cell = reinterpret_cast<uint8_t*>(p);
-  p += (P + 3) / 4;
+  p = base + encoder_index_floats(P);
   b.grid = p;
   p += S * kH * kCells;
   for (int i = 0; i < 4; ++i) {
@@ -764,7 +867,7 @@ hipError_t conv(const float* in1, int c1, const float* in2, int c2, const float*
   if (C % 16 != 0 || c1 % (C / 8) != 0) return hipErrorInvalidValue;
   ConvArgs a{in1, c1, in2, c2, Wt, bias, out, kC, D, Do, pad, transposed, n_shapes};
   const int N = n_shapes * Do * Do * Do;
-  const dim3 grid((unsigned)((N + 31) / 32), kC / 32), block(64 * kConvWaves);
+  const dim3 grid(kC / 32, (unsigned)((N + 31) / 32)), block(64 * kConvWaves);
   switch (C / 16) {
     case 8: kernel_launch(conv_kernel<8>, grid, block, 0, s, a); break;
     case 16: kernel_launch(conv_kernel<16>, grid, block, 0, s, a); break;
@@ -777,7 +880,7 @@ hipError_t conv(const float* in1, int c1, const float* in2, int c2, const float*
 
 hipError_t launch_encoder(const PackedNet& w, const Shape* shapes, int n_shapes, int max_points, const float* xyz,
                           int64_t n_points, const EncoderBuffers& b, float* emb, double* consts, hipStream_t s) {
-  if (n_shapes <= 0 || max_points <= 0) return hipErrorInvalidValue;
+  if (n_shapes <= 0 || n_shapes > kEncodeShapes || max_points <= 0) return hipErrorInvalidValue;
   kernel_launch(cell_sort_kernel, dim3(n_shapes), dim3(1024), 0, s, shapes, xyz, n_points, b.order, b.cell);
   kernel_launch(point_mlp_kernel, dim3((max_points + kPts - 1) / kPts, n_shapes), dim3(256), 0, s, w, shapes,
                 xyz, n_points, b.order, b.cell, b.grid);
@@ -786,7 +889,7 @@ hipError_t launch_encoder(const PackedNet& w, const Shape* shapes, int n_shapes,
   for (int i = 1; i < 4 && e == hipSuccess; ++i)
     e = conv(b.c[i - 1], kC, nullptr, 0, w.C[i], w.k[i], b.c[i], 4, 4, 1, 0, n_shapes, s);
   if (e == hipSuccess) {
-    kernel_launch(global_kernel, dim3(n_shapes), dim3(kC), 0, s, b.c[3], b.glob);
+    kernel_launch(global_kernel, dim3((n_shapes + 15) / 16, kC / 4), dim3(64), 0, s, b.c[3], b.glob, n_shapes);
     e = hipGetLastError();
   }
   // transposed convs: on the bottleneck, then on [previous, matching conv output]
@@ -795,8 +898,8 @@ hipError_t launch_encoder(const PackedNet& w, const Shape* shapes, int n_shapes,
   if (e == hipSuccess) e = conv(b.d[1], kC, b.c[1], kC, w.D[2], w.e[2], b.d[2], 4, 4, 1, 1, n_shapes, s);
   if (e == hipSuccess) e = conv(b.d[2], kC, b.c[0], kC, w.D[3], w.e[3], b.d4, 4, kM, 0, 1, n_shapes, s);
   if (e == hipSuccess) {
-    const int n = n_shapes * kCells * kF;
-    kernel_launch(embed_kernel, dim3((n + 255) / 256), dim3(256), 0, s, w, b.d4, b.glob, emb, n_shapes);
+    kernel_launch(embed_kernel, dim3(n_shapes, (kCells + kEmbedCells - 1) / kEmbedCells), dim3(256), 0, s, w, b.d4,
+                  b.glob, emb, n_shapes);
     kernel_launch(consts_kernel, dim3((n_shapes + 63) / 64), dim3(64), 0, s, shapes, n_shapes, consts);
     e = hipGetLastError();
   }

@@ -48,19 +48,24 @@ void free_shapes(locc_voxel_ctx* c) {
   c->have_embeddings = false;
 }
 
-// Runs the shape encoder over every resident shape (synchronous).
+// Runs the shape encoder over every resident shape (synchronous), kEncodeShapes at a time (the scratch of so many stays
+// within a buffer view's 2 GiB).
 locc_status encode(locc_voxel_ctx* c) {
   c->have_embeddings = false;
   if (!c->have_weights || c->n_shapes == 0) return LOCC_OK;
-  const int S = c->n_shapes;
+  const int S = c->n_shapes < kEncodeShapes ? c->n_shapes : kEncodeShapes;
   float* scratch = nullptr;
   const size_t n = encoder_scratch_floats(S, c->n_points);
   HIP_TRY(hipMalloc(&scratch, n * sizeof(float)));
   const EncoderBuffers b = encoder_carve(scratch, S, c->n_points);
-  hipError_t e = hipMemset(b.grid, 0, (size_t)S * kH * kCells * sizeof(float));
-  if (e == hipSuccess)
-    e = launch_encoder(packed_view(c->d_raw, c->d_packed), c->d_shapes, S, c->max_points, c->d_xyz, c->n_points, b,
-                       c->d_emb, c->d_consts, nullptr);
+  hipError_t e = hipSuccess;
+  for (int s0 = 0; s0 < c->n_shapes && e == hipSuccess; s0 += S) {
+    const int m = c->n_shapes - s0 < S ? c->n_shapes - s0 : S;
+    e = hipMemset(b.grid, 0, (size_t)m * kH * kCells * sizeof(float));
+    if (e == hipSuccess)
+      e = launch_encoder(packed_view(c->d_raw, c->d_packed), c->d_shapes + s0, m, c->max_points, c->d_xyz, c->n_points,
+                         b, c->d_emb + (size_t)s0 * kCells * kF, c->d_consts + (size_t)s0 * 4, nullptr);
+  }
   if (e == hipSuccess) e = hipDeviceSynchronize();
   (void)hipFree(scratch);
   if (e != hipSuccess) return fail(LOCC_ERR_HIP, "shape encoder: %s", hipGetErrorString(e));

@@ -97,6 +97,25 @@ def test_ragged_and_degenerate_shapes_match_the_oracle(torch, setup):
     ctx.close()
 
 
+@pytest.mark.parametrize("n_shapes", [2, 31, 33, 70])
+def test_embeddings_do_not_depend_on_the_shapes_beside_them(torch, setup, n_shapes):
+    """The U-Net's tiles of 32 columns hold shapes of one position, of several, or a rest of either: a shape's embedding
+    is the same bit for bit as in a library of its own, and the oracle's."""
+    lib, w, emb = setup
+    clouds = [lib.pts[lib.offsets[s % 8]:lib.offsets[s % 8 + 1]] for s in range(n_shapes)]
+    clouds = [c if s < 8 else c[s:] for s, c in enumerate(clouds)]
+    offsets = np.concatenate([[0], np.cumsum([len(c) for c in clouds])]).astype(np.int64)
+    ctx = B.VoxelContext()
+    ctx.upload_weights(w)
+    ctx.upload_shapes(offsets, np.concatenate(clouds).astype(np.float32))
+    E = ctx.embeddings().cpu().numpy()
+    assert max(_normwise(E[s], emb[s]) for s in range(min(8, n_shapes))) < TOL
+    for s in {0, 1, n_shapes // 2, n_shapes - 1}:
+        ctx.upload_shapes(np.array([0, len(clouds[s])], np.int64), np.ascontiguousarray(clouds[s], np.float32))
+        np.testing.assert_array_equal(ctx.embeddings().cpu().numpy()[0], E[s])
+    ctx.close()
+
+
 def _scene(lib, n_objs=64, n_pairs=3000, seed=21, spread=0.06):
     rng = np.random.default_rng(seed)
     pos = (rng.standard_normal((n_objs, 3)) * spread).astype(np.float32)

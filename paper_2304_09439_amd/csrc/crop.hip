@@ -1,7 +1,8 @@
 // Crop step: a set-up kernel with one thread per pair validates the pair,
 // puts it in canonical order and computes its float64 relative pose, crop box
 // and float32 screening constants (geometry.h), so that this work is done
-// once per pair instead of once per wave; then one wave per object of every
+// once per pair instead of once per wave (in small batches the waves do it
+// themselves); then one wave per object of every
 // pair runs the membership scan (by spatial clusters, clusters.hip, or in
 // stored order) and the ordered first-K selection, and
 // writes counts, the optional index sets, the per-pair records and the
@@ -14,11 +15,10 @@ namespace {
 // one thread per pair, 64 per workgroup: a batch of 16384 pairs spreads over
 // 256 workgroups, one per compute unit, for this latency-bound float64 work
 constexpr int kThreads = 64;
+constexpr int kInlinePairs = 2048;
 constexpr int kCropWaves = 2;  // object waves per workgroup of the crop kernel (1, 2, 4, 8 measured: 2 fastest)
 
-__global__ __launch_bounds__(kThreads) void pair_setup_kernel(CropArgs A) {
-  const int p = blockIdx.x * kThreads + threadIdx.x;
-  if (p >= pair_count(A.n_pairs, A.n_pairs_dev, A.dev_base)) return;
+__device__ __forceinline__ PairSetup pair_setup(const CropArgs& A, int p) {
   PairSetup r{};
   locc_object oa, ob;
   ShapeDesc da, db;
@@ -36,7 +36,13 @@ __global__ __launch_bounds__(kThreads) void pair_setup_kernel(CropArgs A) {
     r.cl_a = da.off / kClusterPoints + oa.shape;
     r.cl_b = db.off / kClusterPoints + ob.shape;
   }
-  *reinterpret_cast<PairSetup*>(static_cast<char*>(A.setup) + (size_t)p * kPairSetupBytes) = r;
+  return r;
+}
+
+__global__ __launch_bounds__(kThreads) void pair_setup_kernel(CropArgs A) {
+  const int p = blockIdx.x * kThreads + threadIdx.x;
+  if (p >= pair_count(A.n_pairs, A.n_pairs_dev, A.dev_base)) return;
+  *reinterpret_cast<PairSetup*>(static_cast<char*>(A.setup) + (size_t)p * kPairSetupBytes) = pair_setup(A, p);
 }
 
 // One wave per object of a pair: wave item = 2p + side scans, selects and
@@ -250,9 +256,12 @@ __device__ __forceinline__ bool crop_by_clusters(int alive, int n, int K, bool f
 // by vector issue (half of it used); 80 registers keep six waves per SIMD (84 and five: 1,987 us instead of 1,941 for
 // a step of 210,040 pairs).  The clusters skip most points: half of that step's objects have no member and tested
 // 2,048 points each, now mostly none (crop 616 us before, 330 with them).
-template <int U, int W>
-__global__ __launch_bounds__(64 * W, 6) void crop_kernel(CropArgs A) {
+//
+// INLINE: the pair's set-up is done here, by both of its waves, instead of by a kernel of its own.
+template <int U, int W, bool INLINE>
+__global__ __launch_bounds__(64 * W, INLINE ? 4 : 6) void crop_kernel(CropArgs A) {
   __shared__ ObjectShared SW[W];
+  __shared__ PairSetup RW[INLINE ? W : 1];
   const int wave = W == 1 ? 0 : wave_index();
   ObjectShared& S = SW[wave];
   const int item = blockIdx.x * W + wave;
@@ -265,7 +274,14 @@ __global__ __launch_bounds__(64 * W, 6) void crop_kernel(CropArgs A) {
   // the pair's record: the same address for the whole wave (scalar loads)
   const PairSetup* __restrict__ rec =
       reinterpret_cast<const PairSetup*>(static_cast<const char*>(A.setup) + (size_t)p * kPairSetupBytes);
-  if (!rec->valid) {  // uniform; object 0's wave reports the pair
+  if constexpr (INLINE) {
+    const PairSetup r = pair_setup(A, p);
+    if (lane == 0) RW[wave] = r;
+    wave_lds_sync();
+    rec = &RW[wave];
+  }
+  auto uniform = [](int v) -> int { return INLINE ? __builtin_amdgcn_readfirstlane(v) : v; };
+  if (!uniform(rec->valid)) {  // uniform; object 0's wave reports the pair
     if (side == 0) {
       if (A.idx_out)
         for (int e = lane; e < 2 * K; e += 64) A.idx_out[(size_t)p * 2 * K + e] = -1;
@@ -280,15 +296,27 @@ __global__ __launch_bounds__(64 * W, 6) void crop_kernel(CropArgs A) {
     }
     return;
   }
-  const int swapped = rec->swapped;
-  const int n = side ? rec->n_b : rec->n_a;
-  const int off = side ? rec->off_b : rec->off_a;
+  const int swapped = uniform(rec->swapped);
+  const int n = uniform(side ? rec->n_b : rec->n_a);
+  const int off = uniform(side ? rec->off_b : rec->off_a);
   PairScreen sc = rec->sc;
+  if constexpr (INLINE) {  // wave-uniform: scalar registers
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      sc.alo[i] = geo_uniform(sc.alo[i]);
+      sc.ahi[i] = geo_uniform(sc.ahi[i]);
+      sc.t[i] = geo_uniform(sc.t[i]);
+    }
+#pragma unroll
+    for (int k = 0; k < 9; ++k) sc.R[k] = geo_uniform(sc.R[k]);
+    sc.thr_in = geo_uniform(sc.thr_in);
+    sc.thr_out = geo_uniform(sc.thr_out);
+  }
   const bool full = A.counts_out != nullptr;  // else stop once K members are known
   const float* __restrict__ px = A.lib.px + off;
   const float* __restrict__ py = A.lib.py + off;
   const float* __restrict__ pz = A.lib.pz + off;
-  const int cl = side ? rec->cl_b : rec->cl_a, nc = (n + kClusterPoints - 1) / kClusterPoints;
+  const int cl = uniform(side ? rec->cl_b : rec->cl_a), nc = (n + kClusterPoints - 1) / kClusterPoints;
   const float4* boxes = A.lib.boxes && n > A.cluster_min ? A.lib.boxes + 2 * (size_t)cl : nullptr;
   const char* clusters = A.lib.clusters + (size_t)cl * kClusterBytes;
   int found, alive = 0;
@@ -375,14 +403,23 @@ hipError_t launch_crop(const CropArgs& args, hipStream_t s, int unroll) {
   // (a step of 210,040 pairs of 1,024 points: 1,847 and 1,782 us; of 512 points: 1,831 and 1,850).
   a.cluster_min = a.n_pairs < 4096 ? 1024 : 512;
   if (!a.setup || (unroll != 2 && unroll != 4 && unroll != 8)) return hipErrorInvalidValue;
-  kernel_launch(pair_setup_kernel, dim3((a.n_pairs + kThreads - 1) / kThreads), dim3(kThreads), 0, s, a);
   constexpr int W = kCropWaves;
   const dim3 grid((2 * a.n_pairs + W - 1) / W), block(64 * W);
+  // A small batch saves the set-up kernel's launch (8 pairs: 32.4 us with it, 30.1 without; 1,500: 63.7, 61.5; 2,000: 59.8,
+  // 59.0); in a larger one the float64 set-up of every wave costs more (3,000: 73.4, 75.5; 16,384: 250, 262).
+  if (a.n_pairs <= kInlinePairs) {
+    switch (unroll) {
+      case 2: kernel_launch((crop_kernel<2, W, true>), grid, block, 0, s, a); break;
+      case 4: kernel_launch((crop_kernel<4, W, true>), grid, block, 0, s, a); break;
+      default: kernel_launch((crop_kernel<8, W, true>), grid, block, 0, s, a); break;
+    }
+    return hipGetLastError();
+  }
+  kernel_launch(pair_setup_kernel, dim3((a.n_pairs + kThreads - 1) / kThreads), dim3(kThreads), 0, s, a);
   switch (unroll) {
-    case 2: kernel_launch((crop_kernel<2, W>), grid, block, 0, s, a); break;
-    case 4: kernel_launch((crop_kernel<4, W>), grid, block, 0, s, a); break;
-    case 8: kernel_launch((crop_kernel<8, W>), grid, block, 0, s, a); break;
-    default: return hipErrorInvalidValue;
+    case 2: kernel_launch((crop_kernel<2, W, false>), grid, block, 0, s, a); break;
+    case 4: kernel_launch((crop_kernel<4, W, false>), grid, block, 0, s, a); break;
+    default: kernel_launch((crop_kernel<8, W, false>), grid, block, 0, s, a); break;
   }
   return hipGetLastError();
 }

@@ -1,4 +1,5 @@
-"""BF16 and FP8 detect at the batch sizes where the launches change: one pair per workgroup, shares, the encoder and the
+"""BF16 and FP8 detect at the batch sizes where the launches change: one pair per workgroup, shares, the pair set-up inside
+or ahead of the crop, the encoder and the
 head as kernels of their own (scale widths), two row tiles per head workgroup.  Every pair is computed on its own with
 the same operations whatever the batch, so a batch must equal its parts, computed in small batches, bit for bit."""
 
@@ -23,7 +24,7 @@ def torch():
 
 @pytest.mark.parametrize("precision", ["bf16", "fp8_encoder"])
 @pytest.mark.parametrize("net,K,sizes", [("small", 32, (1, 257, 1025)),
-                                         ("scale", 32, (1, 1023, 1025, 4097)),
+                                         ("scale", 32, (1, 1023, 1025, 2048, 2049, 4097)),
                                          ("scale", 96, (31, 1024, 1055, 4095, 12289))])
 def test_batches_equal_their_parts(torch, precision, net, K, sizes):
     w = NETS[net]

@@ -38,12 +38,24 @@ static_assert(sizeof(Shape) == 32, "Shape layout");
 // both from a second, packed buffer.
 struct PackedNet {
   const float *P1, *p1, *P2t, *p2, *P3t, *p3;  // point MLP
+  const unsigned short *P2s, *P3s;             // layers 2-3 as halves (point_halves_kernel), with their rows'
+  const float *u2, *u3;                        // inverse scales
   const float *C[4], *k[4], *D[4], *e[4];      // U-Net convs, transposed convs (C, D: [27][in / 8][2][128][4])
   const float *L, *l;                          // embedding map [16][384]
   const float *A[3], *a[3];                    // per-object MLP [128][28], [128][128] x 2 (row-major)
   const float *Bw[3], *b[4], *B4;              // pair MLP [128][128] x 3, output row [128], b[3] = its bias
 };
 size_t packed_floats();
+// Largest absolute row sum and bias of the point MLP's layers: a layer's outputs are at most amp * (its largest input) +
+// off.
+struct PointBounds {
+  float amp1, off1, amp2, off2, amp3, off3;
+};
+PointBounds point_bounds(const float* flat);
+// Whether layers 2 and 3 can be computed as products of halves for shapes with coordinates up to xmax.
+bool point_halves(const PointBounds& B, float xmax);
+// Their halves, from the uploaded weights into the packed buffer.
+hipError_t launch_point_halves(const float* d_raw, float* d_packed, hipStream_t s);
 // Host-side transposition of the flat weights into dst (packed_floats() floats).
 void pack_transposed(const float* flat, float* dst);
 PackedNet packed_view(const float* d_raw, const float* d_packed);
@@ -63,9 +75,10 @@ size_t encoder_scratch_floats(int n_shapes, int64_t n_points);
 EncoderBuffers encoder_carve(float* base, int n_shapes, int64_t n_points);
 
 // Shape encoder over n_shapes <= kEncodeShapes shapes; grid must be zero (the cell max starts at 0).
+// bounds: the point MLP's layers 2 and 3 as products of halves; null: as FP32 products.
 hipError_t launch_encoder(const PackedNet& w, const Shape* shapes, int n_shapes, int max_points, const float* xyz,
                           int64_t n_points, const EncoderBuffers& b, float* emb, double* consts,
-                          hipStream_t s);
+                          const PointBounds* bounds, hipStream_t s);
 
 struct PairArgs {
   const locc_object* objs;

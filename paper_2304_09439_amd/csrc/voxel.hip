@@ -20,12 +20,14 @@
 // residue mod 16, the float4 loads of both objects issued together, summed
 // across the residues by shuffles), and writes both objects' predictor input
 // rows to the workspace; with small register use many waves are in flight
-// to hide the load latency.  mlp_kernel: 32 pairs per workgroup of eight waves run the
+// to hide the load latency (80, six waves per SIMD: 70.5 us both launches at
+// 16,384 pairs; 86: 71.9).  mlp_kernel: 32 pairs per workgroup of eight waves run the
 // per-object MLP on the 64 rows, the pair max, the pair MLP and the output
 // layer in float32, activations in one LDS buffer that each layer
 // overwrites after all its reads; every thread owns one output column of a
 // layer for a quarter of the rows, reading the weights [in][out] from L2
 // (coalesced) and the rows from LDS as broadcasts.
+#include <cmath>
 #include <cstring>
 
 #include "geometry.h"
@@ -100,6 +102,8 @@ __global__ __launch_bounds__(1024) void cell_sort_kernel(const Shape* shapes, co
 constexpr int kPts = 64;  // points per workgroup of the point MLP
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 // Per-point MLP 3 -> 256 -> 256 -> 256 over 64 points, taken in cell order,
 // and the cell max.
@@ -209,6 +213,191 @@ __global__ __launch_bounds__(256) void point_mlp_kernel(PackedNet w, const Shape
     m = fmaxf(m, HT[t][p]);
   }
   atomicMax(gp + cur * cell_stride, __float_as_uint(m));
+}
+
+// The same with layers 2 and 3 as products of halves on the 16-bit matrix cores: a float is x0 + x1, halves of 11 bits
+// each, and a product x0 y0 + x0 y1 + x1 y0 (v_mfma_f32_32x32x16_f16, FP32 accumulation; what is left out is below
+// 2^-22 of the product).  A weight row is scaled by a power of two to a largest magnitude in [2^7, 2^8), the
+// activations of a shape by one that keeps their bound (PointBounds) below 2^15; both are undone exactly on the sums.
+// Three 16-bit products of 16 steps take 96 cycles where FP32 takes 512: 70 us at 32 shapes of 2,048 points, 168 with
+// the FP32 products, which stay for weights and coordinates near the ends of the exponents (point_halves()).
+struct PointShared {
+  union {
+    unsigned short h[2][kPts][kH + 8];  // activations: [part][point][channel], 16 bytes past a multiple of 128
+    float out[kH][kPts + 1];            // the last layer's, for the pooling walk
+  };
+};
+
+__device__ __forceinline__ float point_scale(float bound) {  // a power of two: bound * it in [2^14, 2^15)
+  const int e = (int)((__float_as_uint(fmaxf(bound, 0x1p-100f)) >> 23) & 255u) - 127;
+  return __uint_as_float((unsigned)(127 + 14 - e) << 23);
+}
+__device__ __forceinline__ unsigned half_bits(float a) { return __builtin_bit_cast(unsigned short, (_Float16)a); }
+__device__ __forceinline__ float half_rest(float a) { return a - (float)(_Float16)a; }
+
+__global__ __launch_bounds__(256, 2) void point_mlp_split_kernel(PackedNet w, PointBounds B, const Shape* shapes,
+                                                                 const float* xyz, int64_t n_points,
+                                                                 const int32_t* order, const uint8_t* cells,
+                                                                 float* grid) {
+  constexpr int KS = kH / 16, kAhead = 4;
+  __shared__ PointShared S;
+  const int s = blockIdx.y;
+  const Shape sh = shapes[s];
+  const int base = blockIdx.x * kPts;
+  if (base >= sh.n) return;  // uniform
+  const int np = sh.n - base < kPts ? sh.n - base : kPts;
+  const int t = threadIdx.x, lane = t & 63, wave = wave_index(), g = lane >> 5, l32 = lane & 31;
+  float xmax = 0.f;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) xmax = fmaxf(xmax, fmaxf(fabsf(sh.lo[k]), fabsf(sh.hi[k])));
+  const float bound1 = B.amp1 * xmax + B.off1, bound2 = B.amp2 * bound1 + B.off2;
+  const float scale1 = point_scale(bound1), scale2 = point_scale(bound2);  // of layer 1's and layer 2's outputs
+  // lane = point, in every wave
+  float x = 0.f, y = 0.f, z = 0.f;
+  int cell = -1;
+  if (lane < np) {
+    const int64_t q = (int64_t)sh.off + base + lane;
+    const int64_t r = (int64_t)sh.off + order[q];
+    x = xyz[r];
+    y = xyz[n_points + r];
+    z = xyz[2 * n_points + r];
+    cell = cells[q];
+  }
+  {  // layer 1: the wave's 64 channels, whose weights the lanes hold, four at a time
+    const int own = wave * 64 + lane;
+    const float c0 = w.P1[3 * own], c1 = w.P1[3 * own + 1], c2 = w.P1[3 * own + 2], cb = w.p1[own];
+    auto of = [](float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
+#pragma unroll
+    for (int k = 0; k < 64; k += 4) {
+      unsigned hi[4], lo[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float v = relu(((of(c0, k + e) * x + of(c1, k + e) * y) + of(c2, k + e) * z) + of(cb, k + e)) * scale1;
+        hi[e] = half_bits(v);
+        lo[e] = half_bits(half_rest(v));
+      }
+      *reinterpret_cast<uint2*>(&S.h[0][lane][wave * 64 + k]) = make_uint2(hi[0] | hi[1] << 16, hi[2] | hi[3] << 16);
+      *reinterpret_cast<uint2*>(&S.h[1][lane][wave * 64 + k]) = make_uint2(lo[0] | lo[1] << 16, lo[2] | lo[3] << 16);
+    }
+  }
+  __syncthreads();
+#pragma unroll 1
+  for (int layer = 0; layer < 2; ++layer) {
+    // A operands: [k-step][part][channel tile][lane][8]
+    const u32x4* Wt = reinterpret_cast<const u32x4*>(layer ? w.P3s : w.P2s) + wave * 2 * 64 + lane;
+    const float* bias = (layer ? w.p3 : w.p2) + wave * 64 + 4 * g;
+    const float* unscale = (layer ? w.u3 : w.u2) + wave * 64 + 4 * g;
+    u32x4 ar[kAhead][2][2];  // [ahead][part][channel tile]
+    auto fetch = [&](int ks, u32x4 (&a)[2][2]) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int ot = 0; ot < 2; ++ot) a[q][ot] = Wt[(size_t)((ks * 2 + q) * (kH / 32) + ot) * 64];
+    };
+#pragma unroll
+    for (int d = 0; d < kAhead; ++d) fetch(d, ar[d]);
+    f32x16 acc[2][2];  // [channel tile][point tile]
+#pragma unroll
+    for (int ot = 0; ot < 2; ++ot) acc[ot][0] = acc[ot][1] = f32x16{};
+#pragma unroll 1
+    for (int k0 = 0; k0 < KS; k0 += kAhead) {
+#pragma unroll
+      for (int d = 0; d < kAhead; ++d) {
+        const int ks = k0 + d;
+        f16x8 b[2][2];  // [part][point tile]
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int pt = 0; pt < 2; ++pt)
+            b[q][pt] = *reinterpret_cast<const f16x8*>(&S.h[q][32 * pt + l32][16 * ks + 8 * g]);
+#pragma unroll
+        for (int part = 2; part >= 0; --part)  // the small products first
+#pragma unroll
+          for (int ot = 0; ot < 2; ++ot)
+#pragma unroll
+            for (int pt = 0; pt < 2; ++pt)
+              acc[ot][pt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, ar[d][part == 2][ot]),
+                                                                   b[part == 1][pt], acc[ot][pt], 0, 0, 0);
+        fetch(ks + kAhead < KS ? ks + kAhead : 0, ar[d]);  // past the end: loaded, not used
+      }
+    }
+    __syncthreads();  // every wave has read the activations
+    const float down = 1.f / (layer ? scale2 : scale1);
+#pragma unroll
+    for (int ot = 0; ot < 2; ++ot)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float4 u4 = *reinterpret_cast<const float4*>(unscale + 32 * ot + 8 * q);
+        const float4 b4 = *reinterpret_cast<const float4*>(bias + 32 * ot + 8 * q);
+        const float u[4] = {u4.x, u4.y, u4.z, u4.w}, b[4] = {b4.x, b4.y, b4.z, b4.w};
+        const int c = wave * 64 + 32 * ot + 8 * q + 4 * g;
+#pragma unroll
+        for (int pt = 0; pt < 2; ++pt) {
+          float v[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = relu(fmaf(acc[ot][pt][4 * q + e], u[e] * down, b[e]));
+          if (layer) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) S.out[c + e][32 * pt + l32] = v[e];
+          } else {
+            unsigned hi[4], lo[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              v[e] *= scale2;
+              hi[e] = half_bits(v[e]);
+              lo[e] = half_bits(half_rest(v[e]));
+            }
+            *reinterpret_cast<uint2*>(&S.h[0][32 * pt + l32][c]) = make_uint2(hi[0] | hi[1] << 16, hi[2] | hi[3] << 16);
+            *reinterpret_cast<uint2*>(&S.h[1][32 * pt + l32][c]) = make_uint2(lo[0] | lo[1] << 16, lo[2] | lo[3] << 16);
+          }
+        }
+      }
+    __syncthreads();
+  }
+  // max over each run of equal cells (the grid starts at 0 and the outputs are >= 0)
+  unsigned int* gp = reinterpret_cast<unsigned int*>(grid) + act_at(0, t, s, kH, gridDim.y);
+  const size_t cell_stride = (size_t)kH * gridDim.y;
+  int cur = __builtin_amdgcn_readlane(cell, 0);
+  float m = 0.f;
+  for (int p0 = 0; p0 < np; p0 += 8) {
+    float v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = S.out[t][p0 + k];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if (p0 + k >= np) break;  // uniform
+      const int c = __builtin_amdgcn_readlane(cell, p0 + k);
+      if (c != cur) {  // uniform
+        atomicMax(gp + cur * cell_stride, __float_as_uint(m));
+        cur = c;
+        m = 0.f;
+      }
+      m = fmaxf(m, v[k]);
+    }
+  }
+  atomicMax(gp + cur * cell_stride, __float_as_uint(m));
+}
+
+// The halves of P2 and P3 (a wave per row): dst[k-step][part][channel tile][lane][8], lane l of k-step ks of tile ot
+// holding row 32 ot + l % 32, columns 16 ks + 8 (l / 32) + e; unscale[row] the inverse of the row's power of two.
+__global__ __launch_bounds__(64) void point_halves_kernel(const float* P, unsigned short* dst, float* unscale) {
+  const int row = blockIdx.x, lane = threadIdx.x;
+  const float4 v4 = reinterpret_cast<const float4*>(P + (size_t)row * kH)[lane];  // columns 4 lane ..
+  const float v[4] = {v4.x, v4.y, v4.z, v4.w};
+  float mx = fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) mx = fmaxf(mx, __shfl_xor(mx, d, 64));
+  const float up = point_scale(mx) * 0x1p-7f;
+  if (lane == 0) unscale[row] = 1.f / up;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int col = 4 * lane + e, ks = col / 16, l = 32 * ((col % 16) / 8) + row % 32;
+    const float x = v[e] * up;
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      dst[((size_t)((ks * 2 + q) * (kH / 32) + row / 32) * 64 + l) * 8 + col % 8] =
+          (unsigned short)(q ? half_bits(half_rest(x)) : half_bits(x));
+  }
 }
 
 // Convolutions and transposed convolutions of the U-Net as implicit GEMMs on
@@ -443,7 +632,7 @@ __global__ __launch_bounds__(64) void consts_kernel(const Shape* shapes, int n_s
 // wave-uniform; both objects' cell tests and embedding loads are then issued
 // together, and each object's predictor input row [mean (16), pose in the
 // other object's frame (12)] goes to the workspace.
-__global__ __launch_bounds__(64) void select_kernel(PairArgs A) {
+__global__ __launch_bounds__(64, 6) void select_kernel(PairArgs A) {
   const int q = blockIdx.x, lane = threadIdx.x;
   if (q >= A.n_pairs) return;
   float* zrow = A.z + (size_t)q * 2 * kIn;
@@ -750,7 +939,8 @@ constexpr int kConvIn[8] = {kH, kC, kC, kC, kC, 2 * kC, 2 * kC, 2 * kC};
 constexpr size_t kPackSizes[] = {kH * kH, kH * kH,
                                  (size_t)27 * kH * kC, (size_t)27 * kC * kC, (size_t)27 * kC * kC,
                                  (size_t)27 * kC * kC, (size_t)27 * kC * kC, (size_t)27 * 2 * kC * kC,
-                                 (size_t)27 * 2 * kC * kC, (size_t)27 * 2 * kC * kC};
+                                 (size_t)27 * 2 * kC * kC, (size_t)27 * 2 * kC * kC,
+                                 (size_t)kH * kH, kH, (size_t)kH * kH, kH};  // halves of P2 and P3, their rows' scales
 
 // [O][C][27] -> [27][C / 8][2][O][4]: channel 8 q + 2 v + g at [q][g][.][v]
 void conv_transpose(const float* src, int C, float* dst) {
@@ -789,6 +979,44 @@ void pack_transposed(const float* flat, float* dst) {
   }
 }
 
+PointBounds point_bounds(const float* flat) {
+  size_t off[kArrays];
+  offsets(off);
+  PointBounds B{};
+  auto layer = [&](int w, int in, float* amp, float* bias) {
+    double a = 0.0, b = 0.0;
+    for (int o = 0; o < kH; ++o) {
+      double sum = 0.0;
+      for (int c = 0; c < in; ++c) sum += std::fabs((double)flat[off[w] + (size_t)o * in + c]);
+      a = std::fmax(a, sum);
+      b = std::fmax(b, std::fabs((double)flat[off[w + 1] + o]));
+    }
+    *amp = (float)(a * (1.0 + 0x1p-20));
+    *bias = (float)(b * (1.0 + 0x1p-20));
+  };
+  layer(0, 3, &B.amp1, &B.off1);
+  layer(2, kH, &B.amp2, &B.off2);
+  layer(4, kH, &B.amp3, &B.off3);
+  return B;
+}
+
+bool point_halves(const PointBounds& B, float xmax) {
+  // the bounds, and with them every weight that is not 0, far from the ends of the exponents
+  const double b1 = (double)B.amp1 * xmax + B.off1, b2 = B.amp2 * b1 + B.off2;
+  return B.amp2 < 0x1p90 && B.amp3 < 0x1p90 && b1 < 0x1p90 && b2 < 0x1p90;
+}
+
+hipError_t launch_point_halves(const float* raw, float* packed, hipStream_t s) {
+  size_t off[kArrays];
+  offsets(off);
+  const PackedNet w = packed_view(raw, packed);
+  kernel_launch(point_halves_kernel, dim3(kH), dim3(64), 0, s, raw + off[2], const_cast<unsigned short*>(w.P2s),
+                const_cast<float*>(w.u2));
+  kernel_launch(point_halves_kernel, dim3(kH), dim3(64), 0, s, raw + off[4], const_cast<unsigned short*>(w.P3s),
+                const_cast<float*>(w.u3));
+  return hipGetLastError();
+}
+
 PackedNet packed_view(const float* raw, const float* packed) {
   size_t off[kArrays];
   offsets(off);
@@ -818,6 +1046,13 @@ PackedNet packed_view(const float* raw, const float* packed) {
     (i < 4 ? w.C[i] : w.D[i - 4]) = d;
     d += (size_t)27 * kConvIn[i] * kC;
   }
+  w.P2s = reinterpret_cast<const unsigned short*>(d);
+  d += kH * kH;
+  w.u2 = d;
+  d += kH;
+  w.P3s = reinterpret_cast<const unsigned short*>(d);
+  d += kH * kH;
+  w.u3 = d;
   for (int i = 0; i < 3; ++i) {
     w.A[i] = raw + off[24 + 2 * i];
     w.Bw[i] = raw + off[30 + 2 * i];
@@ -879,11 +1114,16 @@ hipError_t conv(const float* in1, int c1, const float* in2, int c2, const float*
 }  // namespace
 
 hipError_t launch_encoder(const PackedNet& w, const Shape* shapes, int n_shapes, int max_points, const float* xyz,
-                          int64_t n_points, const EncoderBuffers& b, float* emb, double* consts, hipStream_t s) {
+                          int64_t n_points, const EncoderBuffers& b, float* emb, double* consts,
+                          const PointBounds* bounds, hipStream_t s) {
   if (n_shapes <= 0 || n_shapes > kEncodeShapes || max_points <= 0) return hipErrorInvalidValue;
   kernel_launch(cell_sort_kernel, dim3(n_shapes), dim3(1024), 0, s, shapes, xyz, n_points, b.order, b.cell);
-  kernel_launch(point_mlp_kernel, dim3((max_points + kPts - 1) / kPts, n_shapes), dim3(256), 0, s, w, shapes,
-                xyz, n_points, b.order, b.cell, b.grid);
+  const dim3 points((max_points + kPts - 1) / kPts, n_shapes);
+  if (bounds)
+    kernel_launch(point_mlp_split_kernel, points, dim3(256), 0, s, w, *bounds, shapes, xyz, n_points, b.order, b.cell,
+                  b.grid);
+  else
+    kernel_launch(point_mlp_kernel, points, dim3(256), 0, s, w, shapes, xyz, n_points, b.order, b.cell, b.grid);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = conv(b.grid, kH, nullptr, 0, w.C[0], w.k[0], b.c[0], kM, 4, 0, 0, n_shapes, s);
   for (int i = 1; i < 4 && e == hipSuccess; ++i)

@@ -19,11 +19,13 @@ struct locc_voxel_ctx {
   int32_t n_shapes = 0;
   int max_points = 0;
   int64_t n_points = 0;
+  float xmax = 0.f;  // largest coordinate
   Shape* d_shapes = nullptr;
   float* d_xyz = nullptr;
   // weights
   float* d_raw = nullptr;
   float* d_packed = nullptr;
+  PointBounds bounds{};
   // per-shape results of the encoder
   float* d_emb = nullptr;       // [S][216][16]
   double* d_consts = nullptr;   // [S][4] cell size and margin
@@ -64,7 +66,8 @@ locc_status encode(locc_voxel_ctx* c) {
     e = hipMemset(b.grid, 0, (size_t)m * kH * kCells * sizeof(float));
     if (e == hipSuccess)
       e = launch_encoder(packed_view(c->d_raw, c->d_packed), c->d_shapes + s0, m, c->max_points, c->d_xyz, c->n_points,
-                         b, c->d_emb + (size_t)s0 * kCells * kF, c->d_consts + (size_t)s0 * 4, nullptr);
+                         b, c->d_emb + (size_t)s0 * kCells * kF, c->d_consts + (size_t)s0 * 4,
+                         point_halves(c->bounds, c->xmax) ? &c->bounds : nullptr, nullptr);
   }
   if (e == hipSuccess) e = hipDeviceSynchronize();
   (void)hipFree(scratch);
@@ -122,6 +125,8 @@ locc_status locc_voxel_upload_weights(locc_voxel_ctx* c, const float* h, size_t 
   if (!c->d_packed) HIP_TRY(hipMalloc(&c->d_packed, packed.size() * sizeof(float)));
   HIP_TRY(hipMemcpy(c->d_raw, h, n * sizeof(float), hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(c->d_packed, packed.data(), packed.size() * sizeof(float), hipMemcpyHostToDevice));
+  HIP_TRY(launch_point_halves(c->d_raw, c->d_packed, nullptr));
+  c->bounds = point_bounds(h);
   c->have_weights = true;
   return encode(c);
 }
@@ -141,6 +146,7 @@ locc_status locc_voxel_upload_shapes(locc_voxel_ctx* c, int32_t n_shapes, const 
   if (total >= (int64_t)INT32_MAX) return fail(LOCC_ERR_RANGE, "%lld points in total", (long long)total);
   std::vector<float> xyz((size_t)total * 3);
   std::vector<Shape> shapes(n_shapes);
+  float xmax = 0.f;
   for (int s = 0; s < n_shapes; ++s) {
     Shape d{};
     d.off = (int32_t)off[s];
@@ -159,6 +165,7 @@ locc_status locc_voxel_upload_shapes(locc_voxel_ctx* c, int32_t n_shapes, const 
         d.hi[k] = row[k] > d.hi[k] ? row[k] : d.hi[k];
       }
     }
+    for (int k = 0; k < 3; ++k) xmax = std::fmax(xmax, std::fmax(std::fabs(d.lo[k]), std::fabs(d.hi[k])));
     shapes[s] = d;
   }
   HIP_TRY(hipSetDevice(c->device));
@@ -172,6 +179,7 @@ locc_status locc_voxel_upload_shapes(locc_voxel_ctx* c, int32_t n_shapes, const 
   HIP_TRY(hipMemcpy(c->d_xyz, xyz.data(), sizeof(float) * xyz.size(), hipMemcpyHostToDevice));
   c->n_shapes = n_shapes;
   c->max_points = max_points;
+  c->xmax = xmax;
   c->n_points = total;
   return encode(c);
 }

@@ -116,6 +116,45 @@ def test_embeddings_do_not_depend_on_the_shapes_beside_them(torch, setup, n_shap
     ctx.close()
 
 
+def _scaled(w, p1=0, p2=0, p3=0):
+    """The weights with the point MLP's layers 1-3 (and their biases) times powers of two."""
+    w = w.copy()
+    n1, n2 = 256 * 3 + 256, 256 * 256 + 256
+    for (a, b), k in zip(((0, n1), (n1, n1 + n2), (n1 + n2, n1 + 2 * n2)), (p1, p2, p3)):
+        w[a:b] *= np.float32(2.0) ** k
+    return w
+
+
+@pytest.mark.parametrize("k", [20, -20])
+def test_coordinates_scaled_by_powers_of_two_give_the_same_embeddings(torch, setup, k):
+    """Layer 1's products are the same bits when the coordinates are scaled by 2^k and its matrix by 2^-k, and the
+    halves' scales follow the bounds."""
+    lib, w, _ = setup
+    ref = _ctx(lib, w).embeddings().cpu().numpy()
+    ws = w.copy()
+    ws[:256 * 3] *= np.float32(2.0) ** -k
+    pts = lib.pts.copy()
+    pts[:, :3] *= np.float32(2.0) ** k
+    ctx = B.VoxelContext()
+    ctx.upload_weights(ws)
+    ctx.upload_shapes(lib.offsets, pts)
+    np.testing.assert_array_equal(ctx.embeddings().cpu().numpy(), ref)
+    ctx.close()
+
+
+def test_point_weights_past_the_halves_take_fp32(torch, setup):
+    """Layer 2 times 2^95 and layer 3's matrix times 2^-95: the bounds leave the halves' range, the sums do not leave
+    float32's, and the embeddings are the oracle's for the weights given."""
+    lib, w, emb = setup
+    ws = _scaled(w, p2=95)
+    n = 256 * 3 + 256 + 256 * 256 + 256
+    ws[n:n + 256 * 256] *= np.float32(2.0) ** -95
+    ctx = _ctx(lib, ws)
+    E = ctx.embeddings().cpu().numpy()
+    assert max(_normwise(E[s], emb[s]) for s in range(lib.n_shapes)) < TOL
+    ctx.close()
+
+
 def _scene(lib, n_objs=64, n_pairs=3000, seed=21, spread=0.06):
     rng = np.random.default_rng(seed)
     pos = (rng.standard_normal((n_objs, 3)) * spread).astype(np.float32)

@@ -38,8 +38,10 @@ static_assert(sizeof(Shape) == 32, "Shape layout");
 // both from a second, packed buffer.
 struct PackedNet {
   const float *P1, *p1, *P2t, *p2, *P3t, *p3;  // point MLP
-  const unsigned short *P2s, *P3s;             // layers 2-3 as halves (point_halves_kernel), with their rows'
+  const unsigned short *P2s, *P3s;             // layers 2-3 as halves (halves_kernel), with their rows'
   const float *u2, *u3;                        // inverse scales
+  const unsigned short *As[3], *Bs[3];         // the predictor's MLPs as halves, with their rows' inverse scales
+  const float* us[6];
   const float *C[4], *k[4], *D[4], *e[4];      // U-Net convs, transposed convs (C, D: [27][in / 8][2][128][4])
   const float *L, *l;                          // embedding map [16][384]
   const float *A[3], *a[3];                    // per-object MLP [128][28], [128][128] x 2 (row-major)
@@ -54,8 +56,8 @@ struct PointBounds {
 PointBounds point_bounds(const float* flat);
 // Whether layers 2 and 3 can be computed as products of halves for shapes with coordinates up to xmax.
 bool point_halves(const PointBounds& B, float xmax);
-// Their halves, from the uploaded weights into the packed buffer.
-hipError_t launch_point_halves(const float* d_raw, float* d_packed, hipStream_t s);
+// The halves of the point MLP and of the predictor, from the uploaded weights into the packed buffer.
+hipError_t launch_halves(const float* d_raw, float* d_packed, hipStream_t s);
 // Host-side transposition of the flat weights into dst (packed_floats() floats).
 void pack_transposed(const float* flat, float* dst);
 PackedNet packed_view(const float* d_raw, const float* d_packed);

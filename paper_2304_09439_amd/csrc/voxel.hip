@@ -20,13 +20,11 @@
 // residue mod 16, the float4 loads of both objects issued together, summed
 // across the residues by shuffles), and writes both objects' predictor input
 // rows to the workspace; with small register use many waves are in flight
-// to hide the load latency (80, six waves per SIMD: 70.5 us both launches at
-// 16,384 pairs; 86: 71.9).  mlp_kernel: 32 pairs per workgroup of eight waves run the
-// per-object MLP on the 64 rows, the pair max, the pair MLP and the output
-// layer in float32, activations in one LDS buffer that each layer
-// overwrites after all its reads; every thread owns one output column of a
-// layer for a quarter of the rows, reading the weights [in][out] from L2
-// (coalesced) and the rows from LDS as broadcasts.
+// to hide the load latency (80 registers, six waves per SIMD: 70.5 us both
+// launches at 16,384 pairs; 86: 71.9).  mlp_kernel: 32 pairs per workgroup of
+// eight waves run the per-object MLP on the 64 rows, the pair max, the pair
+// MLP and the output layer as products of halves on the 16-bit matrix cores,
+// activations in LDS, each layer in place.
 #include <cmath>
 #include <cstring>
 
@@ -378,24 +376,24 @@ __global__ __launch_bounds__(256, 2) void point_mlp_split_kernel(PackedNet w, Po
   atomicMax(gp + cur * cell_stride, __float_as_uint(m));
 }
 
-// The halves of P2 and P3 (a wave per row): dst[k-step][part][channel tile][lane][8], lane l of k-step ks of tile ot
-// holding row 32 ot + l % 32, columns 16 ks + 8 (l / 32) + e; unscale[row] the inverse of the row's power of two.
-__global__ __launch_bounds__(64) void point_halves_kernel(const float* P, unsigned short* dst, float* unscale) {
-  const int row = blockIdx.x, lane = threadIdx.x;
-  const float4 v4 = reinterpret_cast<const float4*>(P + (size_t)row * kH)[lane];  // columns 4 lane ..
-  const float v[4] = {v4.x, v4.y, v4.z, v4.w};
-  float mx = fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));
+// The halves of a weight matrix P [out][in] (a wave per row): dst[k-step][part][row tile][lane][8], lane l of k-step ks
+// of tile ot holding row 32 ot + l % 32, columns 16 ks + 8 (l / 32) + e (0 past in); unscale[row] the inverse of the
+// row's power of two.
+__global__ __launch_bounds__(64) void halves_kernel(const float* P, int in, int k_steps, unsigned short* dst,
+                                                    float* unscale) {
+  const int row = blockIdx.x, lane = threadIdx.x, tiles = gridDim.x / 32;
+  float mx = 0.f;
+  for (int c = lane; c < in; c += 64) mx = fmaxf(mx, fabsf(P[(size_t)row * in + c]));
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) mx = fmaxf(mx, __shfl_xor(mx, d, 64));
   const float up = point_scale(mx) * 0x1p-7f;
   if (lane == 0) unscale[row] = 1.f / up;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int col = 4 * lane + e, ks = col / 16, l = 32 * ((col % 16) / 8) + row % 32;
-    const float x = v[e] * up;
+  for (int c = lane; c < 16 * k_steps; c += 64) {
+    const int ks = c / 16, l = 32 * ((c % 16) / 8) + row % 32;
+    const float x = c < in ? P[(size_t)row * in + c] * up : 0.f;
 #pragma unroll
     for (int q = 0; q < 2; ++q)
-      dst[((size_t)((ks * 2 + q) * (kH / 32) + row / 32) * 64 + l) * 8 + col % 8] =
+      dst[((size_t)((ks * 2 + q) * tiles + row / 32) * 64 + l) * 8 + c % 8] =
           (unsigned short)(q ? half_bits(half_rest(x)) : half_bits(x));
   }
 }
@@ -792,7 +790,6 @@ constexpr int kZS = 36;                  // LDS row strides (floats): the inputs
 constexpr int kHS = kHP + 4;             // +4 so that 8 consecutive rows start in different banks
 
 struct MlpShared {
-  int valid[kTP];
   alignas(16) float Z[2 * kTP][kZS];
   alignas(16) float H[2 * kTP][kHS];     // activations, overwritten layer by layer
 };
@@ -839,13 +836,9 @@ __device__ __forceinline__ void mfma_layer(const float* In, float* Out, const fl
   __syncthreads();
 }
 
-// Predictor MLPs: 32 pairs per workgroup; the 64 object rows come from the workspace.
-__global__ __launch_bounds__(kThreads) void mlp_kernel(PairArgs A) {
-  __shared__ MlpShared S;
+// The predictor MLPs of a tile as FP32 products; writes the outputs of the pairs wanted.
+__device__ __forceinline__ void mlp_fp32(const PairArgs& A, MlpShared& S, int q0, int n, const int32_t* wanted) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int q0 = blockIdx.x * kTP;
-  const int n = A.n_pairs - q0 < kTP ? A.n_pairs - q0 : kTP;  // pairs of this workgroup
-  if (t < kTP) S.valid[t] = t < n ? A.valid[q0 + t] : 0;
   for (int id = t; id < 2 * kTP * 8; id += kThreads) {  // 64 rows x 8 float4 (28 inputs, zero to 32)
     const int row = id >> 3, c4 = id & 7;
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -886,11 +879,214 @@ __global__ __launch_bounds__(kThreads) void mlp_kernel(PairArgs A) {
     float v = fmaf(w_lo, S.H[q][lane], w_hi * S.H[q][lane + 64]);
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-    if (lane == 0 && S.valid[q]) {
+    if (lane == 0 && wanted[q]) {
       const float logit = v + b4;
       A.out[2 * (q0 + q)] = logit;
       A.out[2 * (q0 + q) + 1] = 1.f / (1.f + expf(-logit));
     }
+  }
+}
+
+
+// Predictor MLPs: 32 pairs per workgroup; the 64 object rows come from the workspace.  The layers are products of
+// halves as in point_mlp_split_kernel, weights x rows, so that a lane has one row: every row has its own scale at every
+// layer, from its largest value (a bound of it through six layers cost the logits half a digit).  A wave has one 32 x 32 tile of a layer (of the pair layers'
+// 32 rows only four waves), the maximum over a pair's objects is taken between neighbouring lanes, and the weights of a
+// layer load while the one before it ends.  A pair with a value past kHalvesMost, or NaN inputs, is computed as FP32
+// products after the others.  24.5 us at 16,384 pairs, 13.8 at 8 (as FP32 products on 16x16x4 tiles,
+// bound by them, 43 and 21.9); at most 128 registers keep two workgroups per compute unit (134: 32 us).
+constexpr float kHalvesMost = 0x1p90f;
+struct MlpSplitShared {
+  unsigned short h[2][2 * kTP][kHP + 8];  // object rows: [part][row][channel]
+  unsigned short p[2][kTP][kHP + 8];      // pairs
+  float top[4][2 * kTP];                  // a layer's largest output per row and column tile
+  float pscale[kTP];                      // the scale of a pair's maximum
+  float part[4][kTP];
+};
+
+// The products of one 32 x 32 tile: weights (tile ct of the packed halves) x rows 32 rt + l32 of h.
+template <int KS>
+struct TileWeights {
+  u32x4 w[KS][2];
+};
+template <int KS>
+__device__ __forceinline__ void load_tile(const unsigned short* __restrict__ pack, int ct, int lane,
+                                          TileWeights<KS>& T) {
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      T.w[ks][q] = reinterpret_cast<const u32x4*>(pack)[(size_t)((ks * 2 + q) * (kHP / 32) + ct) * 64 + lane];
+}
+template <int KS, int ROWS>
+__device__ __forceinline__ f32x16 tile_products(const TileWeights<KS>& T, const unsigned short (&h)[2][ROWS][kHP + 8],
+                                                int row, int g) {
+  f32x16 acc = f32x16{};
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    f16x8 b[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) b[q] = *reinterpret_cast<const f16x8*>(&h[q][row][16 * ks + 8 * g]);
+#pragma unroll
+    for (int part = 2; part >= 0; --part)  // the small products first
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, T.w[ks][part == 2]), b[part == 1], acc, 0, 0, 0);
+  }
+  return acc;
+}
+// Four outputs of a lane's row, channels c .. c + 3, as halves of v * scale.
+template <int ROWS>
+__device__ __forceinline__ void put_halves(unsigned short (&h)[2][ROWS][kHP + 8], int row, int c, const float (&v)[4],
+                                           float scale) {
+  unsigned hi[4], lo[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float x = v[e] * scale;
+    hi[e] = half_bits(x);
+    lo[e] = half_bits(half_rest(x));
+  }
+  *reinterpret_cast<uint2*>(&h[0][row][c]) = make_uint2(hi[0] | hi[1] << 16, hi[2] | hi[3] << 16);
+  *reinterpret_cast<uint2*>(&h[1][row][c]) = make_uint2(lo[0] | lo[1] << 16, lo[2] | lo[3] << 16);
+}
+
+__global__ __launch_bounds__(kThreads, 4) void mlp_kernel(PairArgs A) {
+  __shared__ union {
+    MlpSplitShared split;
+    MlpShared fp32;
+  } U;
+  __shared__ int32_t valid[kTP], again[kTP], any_again;  // again: valid pairs for the FP32 products
+  MlpSplitShared& S = U.split;
+  const int t = threadIdx.x, lane = t & 63, wave = wave_index(), g = lane >> 5, l32 = lane & 31;
+  const int q0 = blockIdx.x * kTP;
+  const int n = A.n_pairs - q0 < kTP ? A.n_pairs - q0 : kTP;  // pairs of this workgroup
+  const int ct = wave & 3, rt = wave >> 2;  // this wave's tile of an object layer; waves 0-3 have the pair layers'
+  TileWeights<2> w0;
+  TileWeights<kHP / 16> w1;
+  load_tile<2>(A.w.As[0], ct, lane, w0);
+  if (t < kTP) {
+    valid[t] = t < n ? A.valid[q0 + t] : 0;
+    again[t] = 0;
+  }
+  if (t == 0) any_again = 0;
+  __syncthreads();
+  {  // 64 rows x 8 float4 (28 inputs, zero to 32); a row's eight lanes find its scales
+    const int row = t >> 3, c4 = t & 7;
+    float4 v4 = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (row < 2 * n && c4 < kIn / 4) v4 = *reinterpret_cast<const float4*>(A.z + ((size_t)q0 * 2 + row) * kIn + 4 * c4);
+    const float v[4] = {v4.x, v4.y, v4.z, v4.w};
+    float top = 0.f, sum = 0.f;  // sum: NaN or inf where an input is
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      top = fmaxf(top, fabsf(v[e]));
+      sum += fabsf(v[e]);
+    }
+#pragma unroll
+    for (int d = 1; d < 8; d <<= 1) {
+      top = fmaxf(top, __shfl_xor(top, d, 64));
+      sum += __shfl_xor(sum, d, 64);
+    }
+    if (c4 == 0) S.top[0][row] = top;
+    if (!(sum < kHalvesMost) && c4 == 0 && valid[row >> 1]) again[row >> 1] = any_again = 1;
+    put_halves(S.h, row, 4 * c4, v, point_scale(top));
+  }
+  __syncthreads();
+  const int row = 32 * rt + l32;
+  float v[4][4];  // a layer's outputs of this lane's row: channels 32 ct + 8 q + 4 g + e
+  auto outputs = [&](const f32x16& acc, int layer, float down) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int c = 32 * ct + 8 * q + 4 * g;
+      const float4 u4 = *reinterpret_cast<const float4*>(A.w.us[layer] + c);
+      const float4 b4 = *reinterpret_cast<const float4*>((layer < 3 ? A.w.a[layer] : A.w.b[layer - 3]) + c);
+      const float u[4] = {u4.x, u4.y, u4.z, u4.w}, b[4] = {b4.x, b4.y, b4.z, b4.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[q][e] = relu(fmaf(acc[4 * q + e], u[e] * down, b[e]));
+    }
+  };
+  // the largest of v in row r, over the column tiles' waves (a barrier, before which every wave has read the inputs)
+  auto row_top = [&](int r, bool mine) -> float {
+    float top = 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) top = fmaxf(top, v[q][e]);
+    top = fmaxf(top, __shfl_xor(top, 32, 64));
+    if (mine && lane < 32) S.top[ct][r] = top;
+    __syncthreads();
+    return fmaxf(fmaxf(S.top[0][r], S.top[1][r]), fmaxf(S.top[2][r], S.top[3][r]));
+  };
+  auto check = [&](float top, int pair) {
+    if (!(top < kHalvesMost) && valid[pair]) again[pair] = any_again = 1;
+  };
+  float scale = point_scale(S.top[0][row]);
+  f32x16 acc = tile_products<2>(w0, S.h, row, g);
+  load_tile<kHP / 16>(A.w.As[1], ct, lane, w1);
+  __syncthreads();  // every wave has read the inputs' scales, which the first layer's largest outputs replace
+#pragma unroll 1
+  for (int layer = 0; layer < 2; ++layer) {
+    outputs(acc, layer, 1.f / scale);
+    const float top = row_top(row, true);
+    check(top, row >> 1);
+    scale = point_scale(top);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) put_halves(S.h, row, 32 * ct + 8 * q + 4 * g, v[q], scale);
+    __syncthreads();
+    acc = tile_products<kHP / 16>(w1, S.h, row, g);
+    load_tile<kHP / 16>(layer ? A.w.Bs[0] : A.w.As[2], ct, lane, w1);
+  }
+  outputs(acc, 2, 1.f / scale);
+#pragma unroll
+  for (int q = 0; q < 4; ++q)  // the maximum over the pair's two rows, lanes 2 k and 2 k + 1
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[q][e] = fmaxf(v[q][e], __shfl_xor(v[q][e], 1, 64));
+  {
+    const float top = row_top(row, true);
+    check(top, row >> 1);
+    if (!(lane & 1)) {
+      if (ct == 0 && g == 0) S.pscale[row >> 1] = point_scale(top);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) put_halves(S.p, row >> 1, 32 * ct + 8 * q + 4 * g, v[q], point_scale(top));
+    }
+  }
+  __syncthreads();
+  // pair layers, in place, by waves 0-3 (a lane per pair)
+  scale = S.pscale[l32];
+#pragma unroll 1
+  for (int layer = 0; layer < 2; ++layer) {
+    if (wave < 4) {
+      acc = tile_products<kHP / 16>(w1, S.p, l32, g);
+      load_tile<kHP / 16>(A.w.Bs[layer + 1], ct, lane, w1);
+      outputs(acc, 3 + layer, 1.f / scale);
+    }
+    const float top = row_top(l32, wave < 4);
+    if (wave < 4) {
+      check(top, l32);
+      scale = point_scale(top);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) put_halves(S.p, l32, 32 * ct + 8 * q + 4 * g, v[q], scale);
+    }
+    __syncthreads();
+  }
+  if (wave < 4) {  // the last pair layer and the output row's products
+    acc = tile_products<kHP / 16>(w1, S.p, l32, g);
+    outputs(acc, 5, 1.f / scale);
+    float sum = 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float4 o4 = *reinterpret_cast<const float4*>(A.w.B4 + 32 * ct + 8 * q + 4 * g);
+      sum = fmaf(v[q][0], o4.x, fmaf(v[q][1], o4.y, fmaf(v[q][2], o4.z, fmaf(v[q][3], o4.w, sum))));
+    }
+    sum += __shfl_xor(sum, 32, 64);
+    if (lane < 32) S.part[ct][lane] = sum;
+  }
+  __syncthreads();
+  if (t < kTP && valid[t] && !again[t]) {
+    const float logit = ((S.part[0][t] + S.part[1][t]) + S.part[2][t]) + S.part[3][t] + A.w.b[3][0];
+    A.out[2 * (q0 + t)] = logit;
+    A.out[2 * (q0 + t) + 1] = 1.f / (1.f + expf(-logit));
+  }
+  if (any_again) {  // uniform
+    __syncthreads();
+    mlp_fp32(A, U.fp32, q0, n, again);
   }
 }
 
@@ -940,7 +1136,9 @@ constexpr size_t kPackSizes[] = {kH * kH, kH * kH,
                                  (size_t)27 * kH * kC, (size_t)27 * kC * kC, (size_t)27 * kC * kC,
                                  (size_t)27 * kC * kC, (size_t)27 * kC * kC, (size_t)27 * 2 * kC * kC,
                                  (size_t)27 * 2 * kC * kC, (size_t)27 * 2 * kC * kC,
-                                 (size_t)kH * kH, kH, (size_t)kH * kH, kH};  // halves of P2 and P3, their rows' scales
+                                 (size_t)kH * kH, kH, (size_t)kH * kH, kH,  // halves of P2 and P3, their rows' scales
+                                 (size_t)kHP * 32, kHP, (size_t)kHP * kHP, kHP, (size_t)kHP * kHP, kHP,
+                                 (size_t)kHP * kHP, kHP, (size_t)kHP * kHP, kHP, (size_t)kHP * kHP, kHP};  // predictor's
 
 // [O][C][27] -> [27][C / 8][2][O][4]: channel 8 q + 2 v + g at [q][g][.][v]
 void conv_transpose(const float* src, int C, float* dst) {
@@ -979,24 +1177,25 @@ void pack_transposed(const float* flat, float* dst) {
   }
 }
 
+static void layer_bounds(const float* W, const float* b, int out, int in, float* amp, float* bias) {
+  double a = 0.0, m = 0.0;
+  for (int o = 0; o < out; ++o) {
+    double sum = 0.0;
+    for (int c = 0; c < in; ++c) sum += std::fabs((double)W[(size_t)o * in + c]);
+    a = std::fmax(a, sum);
+    m = std::fmax(m, std::fabs((double)b[o]));
+  }
+  *amp = (float)(a * (1.0 + 0x1p-20));
+  *bias = (float)(m * (1.0 + 0x1p-20));
+}
+
 PointBounds point_bounds(const float* flat) {
   size_t off[kArrays];
   offsets(off);
   PointBounds B{};
-  auto layer = [&](int w, int in, float* amp, float* bias) {
-    double a = 0.0, b = 0.0;
-    for (int o = 0; o < kH; ++o) {
-      double sum = 0.0;
-      for (int c = 0; c < in; ++c) sum += std::fabs((double)flat[off[w] + (size_t)o * in + c]);
-      a = std::fmax(a, sum);
-      b = std::fmax(b, std::fabs((double)flat[off[w + 1] + o]));
-    }
-    *amp = (float)(a * (1.0 + 0x1p-20));
-    *bias = (float)(b * (1.0 + 0x1p-20));
-  };
-  layer(0, 3, &B.amp1, &B.off1);
-  layer(2, kH, &B.amp2, &B.off2);
-  layer(4, kH, &B.amp3, &B.off3);
+  layer_bounds(flat + off[0], flat + off[1], kH, 3, &B.amp1, &B.off1);
+  layer_bounds(flat + off[2], flat + off[3], kH, kH, &B.amp2, &B.off2);
+  layer_bounds(flat + off[4], flat + off[5], kH, kH, &B.amp3, &B.off3);
   return B;
 }
 
@@ -1006,14 +1205,17 @@ bool point_halves(const PointBounds& B, float xmax) {
   return B.amp2 < 0x1p90 && B.amp3 < 0x1p90 && b1 < 0x1p90 && b2 < 0x1p90;
 }
 
-hipError_t launch_point_halves(const float* raw, float* packed, hipStream_t s) {
+hipError_t launch_halves(const float* raw, float* packed, hipStream_t s) {
+  const PackedNet w = packed_view(raw, packed);
   size_t off[kArrays];
   offsets(off);
-  const PackedNet w = packed_view(raw, packed);
-  kernel_launch(point_halves_kernel, dim3(kH), dim3(64), 0, s, raw + off[2], const_cast<unsigned short*>(w.P2s),
-                const_cast<float*>(w.u2));
-  kernel_launch(point_halves_kernel, dim3(kH), dim3(64), 0, s, raw + off[4], const_cast<unsigned short*>(w.P3s),
-                const_cast<float*>(w.u3));
+  auto pack = [&](int array, int out, int in, const unsigned short* dst, const float* unscale) {
+    kernel_launch(halves_kernel, dim3(out), dim3(64), 0, s, raw + off[array], in, (in + 15) / 16,
+                  const_cast<unsigned short*>(dst), const_cast<float*>(unscale));
+  };
+  pack(2, kH, kH, w.P2s, w.u2);
+  pack(4, kH, kH, w.P3s, w.u3);
+  for (int i = 0; i < 6; ++i) pack(24 + 2 * i, kHP, i ? kHP : kIn, i < 3 ? w.As[i] : w.Bs[i - 3], w.us[i]);
   return hipGetLastError();
 }
 
@@ -1053,6 +1255,13 @@ PackedNet packed_view(const float* raw, const float* packed) {
   w.P3s = reinterpret_cast<const unsigned short*>(d);
   d += kH * kH;
   w.u3 = d;
+  d += kH;
+  for (int i = 0; i < 6; ++i) {
+    (i < 3 ? w.As[i] : w.Bs[i - 3]) = reinterpret_cast<const unsigned short*>(d);
+    d += kHP * (i ? kHP : 32);
+    w.us[i] = d;
+    d += kHP;
+  }
   for (int i = 0; i < 3; ++i) {
     w.A[i] = raw + off[24 + 2 * i];
     w.Bw[i] = raw + off[30 + 2 * i];

@@ -125,7 +125,7 @@ locc_status locc_voxel_upload_weights(locc_voxel_ctx* c, const float* h, size_t 
   if (!c->d_packed) HIP_TRY(hipMalloc(&c->d_packed, packed.size() * sizeof(float)));
   HIP_TRY(hipMemcpy(c->d_raw, h, n * sizeof(float), hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(c->d_packed, packed.data(), packed.size() * sizeof(float), hipMemcpyHostToDevice));
-  HIP_TRY(launch_point_halves(c->d_raw, c->d_packed, nullptr));
+  HIP_TRY(launch_halves(c->d_raw, c->d_packed, nullptr));
   c->bounds = point_bounds(h);
   c->have_weights = true;
   return encode(c);

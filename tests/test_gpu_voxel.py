@@ -219,6 +219,24 @@ def test_swapped_pairs_and_batch_invariance(torch, setup):
     ctx.close()
 
 
+def test_pairs_past_the_halves_take_fp32(torch, setup):
+    """Pairs with an object 1e28 away: their rows' bounds leave the halves' range, their sums do not leave float32's; the
+    other pairs of their tiles keep their bits."""
+    lib, w, emb = setup
+    pos, quat, shape, pairs = _scene(lib, n_pairs=200, seed=23)
+    pos[7] = [1e28, -2e28, 0.0]
+    far = (pairs == 7).any(axis=1) & (pairs != 9).all(axis=1) & (pairs < 64).all(axis=1) & (pairs[:, 0] != pairs[:, 1])
+    assert 3 <= far.sum() < 40
+    ref = V.detect(lib.pts, lib.offsets, pos, quat, shape, pairs, w, emb=emb)
+    ctx = _ctx(lib, w)
+    objs = torch.from_numpy(B.pack_objects(pos, quat, shape)).cuda()
+    out = ctx.detect(objs, torch.from_numpy(pairs).cuda())[0].cpu().numpy()
+    assert _normwise(out[far, 0], ref["logit"][far]) < TOL
+    near = ctx.detect(objs, torch.from_numpy(np.ascontiguousarray(pairs[~far])).cuda())[0].cpu().numpy()
+    np.testing.assert_array_equal(near, out[~far])
+    ctx.close()
+
+
 def test_upload_and_argument_errors(torch, setup):
     lib, w, _ = setup
     ctx = B.VoxelContext()

@@ -181,12 +181,19 @@ __global__ __launch_bounds__(256, kFusedWgPerCu) void fused_bf16_kernel(FusedArg
     w1f[i] = wave + 4 * i < FT ? reinterpret_cast<const s16x4*>(A.w1p)[(size_t)(wave + 4 * i) * 64 + lane] : s16x4{};
 
   int slot = 0;
+  // The first claim is the workgroup's index; the queue has those past the grid's, so that a batch of one claim a
+  // workgroup does without its atomics: hundreds at once on one address cost 5 us (400 pairs of 128 + 128 points with
+  // counts 43.2 -> 38.5 us, 1,061 of 96 + 96 48.0 -> 43.3; the FP8 encoder at 500 pairs 40.9 -> 34.7).
+  const int queued = (int)gridDim.x * A.claim;
   for (int iter = 0;; ++iter) {
-    if (tid == 0)
-      S.claim = A.dynamic ? (int)atomicAdd(A.queue, (unsigned)A.claim) : (blockIdx.x + iter * gridDim.x) * A.claim;
-    __syncthreads();
-    const int base = S.claim;
-    __syncthreads();  // S.claim is rewritten by the next claim
+    int base = (blockIdx.x + iter * (int)gridDim.x) * A.claim;
+    if (A.dynamic && iter > 0) {
+      if (queued >= P) break;
+      if (tid == 0) S.claim = queued + (int)atomicAdd(A.queue, (unsigned)A.claim);
+      __syncthreads();
+      base = S.claim;
+      __syncthreads();  // S.claim is rewritten by the next claim
+    }
     if (base >= P) break;
     const int n_claim = P - base < A.claim ? P - base : A.claim;
 
@@ -407,7 +414,7 @@ __global__ __launch_bounds__(256, kFusedWgPerCu) void fused_bf16_kernel(FusedArg
   if constexpr (HEAD)
     if (slot > 0) head_tile<H1, H2, HH, PRE ? 4 : 2>(A, S, slot);
 
-  if (A.dynamic && tid == 0) {
+  if (A.dynamic && queued < P && tid == 0) {
     __threadfence();
     if (atomicAdd(A.queue + 1, 1u) == gridDim.x - 1) {  // last workgroup out resets the queue
       atomicExch(A.queue, 0u);

@@ -232,12 +232,16 @@ __global__ __launch_bounds__(256, APART ? kFp8EncoderWgPerCu : kFusedWgPerCu) vo
     w1f[i] = wave + 4 * i < FT ? reinterpret_cast<const s16x4*>(A.w1p)[(size_t)(wave + 4 * i) * 64 + lane] : s16x4{};
 
   int slot = 0;
+  const int queued = (int)gridDim.x * A.claim;
   for (int iter = 0;; ++iter) {
-    if (tid == 0)
-      S.claim = A.dynamic ? (int)atomicAdd(A.queue, (unsigned)A.claim) : (blockIdx.x + iter * gridDim.x) * A.claim;
-    __syncthreads();
-    const int base = S.claim;
-    __syncthreads();
+    int base = (blockIdx.x + iter * (int)gridDim.x) * A.claim;
+    if (A.dynamic && iter > 0) {
+      if (queued >= P) break;
+      if (tid == 0) S.claim = queued + (int)atomicAdd(A.queue, (unsigned)A.claim);
+      __syncthreads();
+      base = S.claim;
+      __syncthreads();  // S.claim is rewritten by the next claim
+    }
     if (base >= P) break;
     const int n_claim = P - base < A.claim ? P - base : A.claim;
     // the next pair's record and rows are carried in registers (two named
@@ -373,7 +377,7 @@ __global__ __launch_bounds__(256, APART ? kFp8EncoderWgPerCu : kFusedWgPerCu) vo
   }
   if constexpr (!APART)
     if (slot > 0) head_tile8<H1, H2, HH, HEAD8>(A, S, slot);
-  if (A.dynamic && tid == 0) {
+  if (A.dynamic && queued < P && tid == 0) {
     __threadfence();
     if (atomicAdd(A.queue + 1, 1u) == gridDim.x - 1) {
       atomicExch(A.queue, 0u);

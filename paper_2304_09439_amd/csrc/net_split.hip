@@ -122,11 +122,22 @@ __global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, Net
   }
 
   int gstep = 0;  // steps this workgroup has started (tags S.bad)
-  for (int claim = blockIdx.x;; claim += gridDim.x) {
-    if (A.queue) {
-      if (tid == 0) S.claim = (int)atomicAdd(A.queue, 1u);
-      __syncthreads();
-      claim = S.claim;
+  // The first claim is the workgroup's index; the queue has those past the grid's, so that a batch of one claim a
+  // workgroup does without its atomics: hundreds at once on one address (500 pairs of 64 + 64 points at 64 / 128 with
+  // counts 49.0 -> 36.2 us, 80 pairs 29.6 -> 26.9).
+  int claim = blockIdx.x, queued_base, queued_n;
+  split_chunk(C, gridDim.x, queued_base, queued_n);
+  const bool queued = A.queue && queued_base < P;
+  for (int iter = 0;; ++iter) {
+    if (iter > 0) {
+      if (A.queue) {
+        if (!queued) break;
+        if (tid == 0) S.claim = (int)(gridDim.x + atomicAdd(A.queue, 1u));
+        __syncthreads();
+        claim = S.claim;
+      } else {
+        claim += gridDim.x;
+      }
     }
     int base, n;
     split_chunk(C, claim, base, n);
@@ -369,7 +380,7 @@ __global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, Net
       __syncthreads();
     }
   }
-  if (A.queue && tid == 0) {
+  if (queued && tid == 0) {
     __threadfence();
     if (atomicAdd(A.queue + 1, 1u) == gridDim.x - 1) {  // last workgroup out resets the queue
       atomicExch(A.queue, 0u);
@@ -392,6 +403,10 @@ __global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, Net
 // at 128 / 256, and with the split encoder's 0.70 ms about half of the 1.94 ms
 // of the whole encoder on the FP32 matrix cores.
 
+// Four objects a workgroup read W2 once for four; up to 2,048 pairs the chip has room for every object alone, and the
+// chain of one is the shorter one (pose gradients of 40 pairs at 64 / 128 89.0 -> 83.2 us, 150 pairs at 128 / 256
+// 263.5 -> 245.9; 3,000 pairs go the other way, 436.7 against 444.0).
+constexpr int kChainLonePairs = 2048;
 constexpr int kChainObjects = 4;
 
 template <int H1>
@@ -409,9 +424,9 @@ __device__ __forceinline__ float chain_sum(const float* __restrict__ w1c, const 
   return acc;
 }
 
-template <int H1, int H2>
+template <int H1, int H2, int NO>
 __global__ __launch_bounds__(H2) void chain_features_kernel(Fp32Net W, NetArgs A) {
-  constexpr int NO = kChainObjects, NW = H2 / 32;
+  constexpr int NW = H2 / 32;
   const int c = threadIdx.x, lane = c & 63;
   const int wave = __builtin_amdgcn_readfirstlane(c >> 6);
   const int P = pair_count(A.n_pairs, A.n_pairs_dev);
@@ -898,8 +913,13 @@ __global__ __launch_bounds__(256) void repack_kernel(RepackArgs A, SplitLayout L
   dst[count] = (_Float16)(v - (float)h);
 }
 
-// Chunk sizes: half of what is left over the grid, 32 to 1.
-SplitChunks split_chunks(int n_pairs, int grid) {
+// Chunk sizes: half of what is left over the grid, 32 to 1. A batch of up to `lone` pairs a workgroup is dealt out
+// evenly in one claim each, without the queue: the pairs of a call cost nearly the same, and the halving levels' claims
+// cost more than the even split loses. At 64 / 128 (two workgroups a CU, grid 512) 2,000 pairs 66.4 -> 49.8 us, 8,000
+// 117.0 -> 105.2, 12,000 157.5 -> 147.6, but with the argmax 16,000 389.7 -> 396.1; at 128 / 256 (grid 256), whose
+// pairs are four times as long, 1,000 pairs 102.6 -> 96.9, but 2,000 137.3 -> 138.5. A batch whose length the device holds may be far shorter than
+// n_pairs, and one claim of its capacity's share would leave workgroups without work.
+SplitChunks split_chunks(int n_pairs, int grid, int lone) {
   SplitChunks c{};
   c.grid = grid;
   int left = n_pairs, base = 0;
@@ -910,6 +930,7 @@ SplitChunks split_chunks(int n_pairs, int grid) {
       size = kSplitChunk;
       claims = (left - 2 * grid * kSplitChunk) / kSplitChunk + grid;
     }
+    if (l == 0 && n_pairs <= (long long)lone * grid) size = (n_pairs + grid - 1) / grid;
     if (size < 1) size = 1;
     c.size[l] = size;
     c.base[l] = base;
@@ -925,19 +946,24 @@ template <int H1, int H2>
 hipError_t run_split(const Fp32Net& w, const NetArgs& a, int n_cu, hipStream_t s) {
   const int slots = n_cu * (H2 >= 256 ? 1 : 2);  // workgroups the register file holds at once (four spill: 98 -> 166 us)
   const int grid = a.n_pairs < slots ? a.n_pairs : slots;
+  const int lone = a.n_pairs_dev ? 0 : (H2 >= 256 ? 4 : 24);
   if (a.amax)
     kernel_launch((encoder_split_kernel<H1, H2, true>), dim3(grid), dim3(2 * H2), 0, s, w, a,
-                  split_chunks(a.n_pairs, grid));
+                  split_chunks(a.n_pairs, grid, lone));
   else
     kernel_launch((encoder_split_kernel<H1, H2, false>), dim3(grid), dim3(2 * H2), 0, s, w, a,
-                  split_chunks(a.n_pairs, grid));
+                  split_chunks(a.n_pairs, grid, lone));
   return hipGetLastError();
 }
 
 template <int H1, int H2>
 hipError_t run_chain(const Fp32Net& w, const NetArgs& a, hipStream_t s) {
-  const unsigned grid = (unsigned)((2 * (size_t)a.n_pairs + kChainObjects - 1) / kChainObjects);
-  kernel_launch((chain_features_kernel<H1, H2>), dim3(grid), dim3(H2), 0, s, w, a);
+  const size_t objects = 2 * (size_t)a.n_pairs;
+  if (a.n_pairs <= kChainLonePairs)
+    kernel_launch((chain_features_kernel<H1, H2, 1>), dim3((unsigned)objects), dim3(H2), 0, s, w, a);
+  else
+    kernel_launch((chain_features_kernel<H1, H2, kChainObjects>),
+                  dim3((unsigned)((objects + kChainObjects - 1) / kChainObjects)), dim3(H2), 0, s, w, a);
   return hipGetLastError();
 }
 

@@ -58,3 +58,31 @@ def test_batches_equal_their_parts(torch, precision, net, K, sizes):
     # bf16 rounds inputs, weights and activations of five layers to 2^-9 each, e4m3 one layer to 2^-4
     err = np.abs(whole[2][rows] - ref["z"]).max() / np.abs(ref["z"]).max()
     assert err < (0.02 if precision == "bf16" else 0.1)
+
+
+@pytest.mark.parametrize("net,K,sizes", [("small", 32, (511, 513, 2048, 2049, 12288, 12289)),
+                                         ("scale", 32, (255, 257, 1024, 1025, 2049))])
+def test_fp32_batches_equal_their_parts(torch, net, K, sizes):
+    """One claim per workgroup or the queue's; argmax chains of one object or of four per workgroup."""
+    w = NETS[net]
+    wd = (w.h1, w.h2, w.hh)
+    weights = I.flatten_weights(I.gaussian_weights(w, seed=4, bias_std=0.1))
+    scene = _scene(max(sizes), K + 9)
+    ctx = B.context_for_scene(scene, K, wd, weights)
+    objs, pairs = B.scene_tensors(scene)
+    whole = [t.cpu().numpy() for t in ctx.detect(objs, pairs)]
+    grad, out, arg = ctx.pose_gradients(objs, pairs, want_contacts=True, want_argmax=True)
+    grads = [t.cpu().numpy() for t in (grad, out, arg)]
+    for n in sizes[:-1]:
+        part = pairs[:n].contiguous()
+        for a, b in zip(ctx.detect(objs, part), whole):
+            np.testing.assert_array_equal(a.cpu().numpy(), b[:n])
+        for a, b in zip(ctx.pose_gradients(objs, part, want_contacts=True, want_argmax=True), grads):
+            np.testing.assert_array_equal(a.cpu().numpy().reshape(-1), b.reshape(len(pairs), -1)[:n].reshape(-1))
+    out = torch.full((max(sizes), 8), 7.0, device=objs.device)
+    n_dev = torch.tensor([max(sizes) - 33], dtype=torch.int32, device=objs.device)
+    ctx.detect_device_count(objs, pairs, n_dev, out)
+    got = out.cpu().numpy()
+    np.testing.assert_array_equal(got[:-33], whole[0][:-33])
+    assert (got[-33:] == 7.0).all()
+    ctx.close()

@@ -232,6 +232,7 @@ __global__ __launch_bounds__(256, APART ? kFp8EncoderWgPerCu : kFusedWgPerCu) vo
     w1f[i] = wave + 4 * i < FT ? reinterpret_cast<const s16x4*>(A.w1p)[(size_t)(wave + 4 * i) * 64 + lane] : s16x4{};
 
   int slot = 0;
+  // the first claim is the workgroup's index, as in the BF16 kernel: 500 pairs 40.9 -> 34.7 us
   const int queued = (int)gridDim.x * A.claim;
   for (int iter = 0;; ++iter) {
     int base = (blockIdx.x + iter * (int)gridDim.x) * A.claim;

@@ -124,7 +124,8 @@ __global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, Net
   int gstep = 0;  // steps this workgroup has started (tags S.bad)
   // The first claim is the workgroup's index; the queue has those past the grid's, so that a batch of one claim a
   // workgroup does without its atomics: hundreds at once on one address (500 pairs of 64 + 64 points at 64 / 128 with
-  // counts 49.0 -> 36.2 us, 80 pairs 29.6 -> 26.9).
+  // counts 49.0 -> 36.2 us, 80 pairs 29.6 -> 26.9).  A caller without a queue (the no-allocation detect) has the
+  // claims in static order.
   int claim = blockIdx.x, queued_base, queued_n;
   split_chunk(C, gridDim.x, queued_base, queued_n);
   const bool queued = A.queue && queued_base < P;

@@ -210,8 +210,9 @@ hipError_t launch_chain_features(const Fp32Net& w, const NetArgs& a, hipStream_t
 // The head on the features in z (products of halves).
 hipError_t launch_head_split(const Fp32Net& w, const NetArgs& a, int n_cu, hipStream_t s);
 
-// Largest finite half: a float up to it has finite halves.
+// Largest finite half: a float up to it has finite halves.  Both halves of one from kHalvesLeast on keep all their bits.
 constexpr float kSplitLimit = 65504.f;
+constexpr float kHalvesLeast = 0x1p-2f;
 
 // Chunks of pairs a workgroup of the split encoder claims: level l holds
 // claims[l] chunks of size[l] pairs from pair base[l] on (the last level as
@@ -247,7 +248,8 @@ void split_bind(Fp32Net& w, const char* base);
 // Repacking on the device from the flat weights raw: pack[i] = raw[pack_idx[i]]
 // (0 where the index is negative), the head's matrices in the gradient
 // kernels' order at frag (H1 [hh][2 h2], H2 [hh][hh], H2^T, H1^T), and the
-// halves at split (their scales in place, the flag word zero before).
+// halves and their rows' factors at split (layer 1's factor in place, the flag
+// word zero before).
 struct RepackArgs {
   const float* raw;
   int32_t h1, h2, hh;

@@ -20,7 +20,7 @@
 // Halves span 2^-14 to 2^16 with all their bits, so layer 1's weights come
 // multiplied by a power of two that puts the largest output any row of the
 // library can give at 2^13, W2's rows by one that puts their largest weight at
-// 2^8, and the pooled sum is scaled back (all exact).  A step of rows whose
+// 2^14 to 2^15, and the pooled sum is scaled back (all exact).  A step of rows whose
 // layer-1 outputs are not all finite and in the range of a half, and every
 // step when a weight is not, is computed as net_fp32.hip's FP32 chain.
 //
@@ -842,35 +842,118 @@ __global__ __launch_bounds__(512, 2) void head_split_kernel(Fp32Net W, NetArgs A
 
 // ------------------------------------------------------------- weights, launch
 
-// Repacking, an element per thread: first the gather, then layer 1 and W2^T for
-// the chains, the head's operands of the gradient kernels, and the halves of
-// W2, H1, H2 and H3, each row times its power of two, in the B operand order
-// of 32x32x16 products (W2's reduction index in layer 1's output order), and
-// layer 1's operand times its own; the flag word becomes 1 where a weight has
-// no halves.  One launch: training runs it every step.
-__global__ __launch_bounds__(256) void repack_kernel(RepackArgs A, SplitLayout L) {
+// Repacking.  The first workgroups, an element per thread: the gather, layer 1 and W2^T for the chains, the head's
+// operands of the gradient kernels, and layer 1's operand times its factor.  The others, eight inputs of a row per
+// thread: the halves of W2, H1, H2 and H3 (8 rows, zero to 32) in the B operand order of 32x32x16 products (W2's
+// reduction index in layer 1's output order), each row times the power of two that puts its largest weight at 2^14 to
+// 2^15, found here by the row's threads, so that the halves follow the weights through training.  A weight 2^-16 of its
+// row's largest or less keeps fewer bits than a float.  A few in a row do not matter beside the others; where they are
+// more than a 64th of the row's and one (as when the largest weight is that of a unit which is always 0), or a weight is
+// not finite, the flag word becomes 1 and every pair takes the FP32 chains.  One launch: training runs it every step.
+struct RepackSizes {
+  int pack, w1, w1c, w2c, frag;  // elements, in this order
+  int halves[4];                 // rows' eighths of W2, H1, H2, H3: multiples of 256
+  __host__ __device__ int elements() const { return pack + w1 + w1c + w2c + frag; }
+  __host__ __device__ int element_blocks() const { return (elements() + 255) / 256; }
+};
+RepackSizes repack_sizes(int pack_n, int h1, int h2, int hh) {
+  return RepackSizes{pack_n,
+                     8 * h1,
+                     8 * h1,
+                     h2 * h1,
+                     2 * (hh * 2 * h2 + hh * hh),
+                     {h2 * h1 / 8, hh * 2 * h2 / 8, hh * hh / 8, 32 * hh / 8}};
+}
+
+// A power of two: v times it in [2^14, 2^15) (v at least 2^-100).
+__device__ __forceinline__ float halves_scale(float v) {
+  const int e = (int)((__float_as_uint(fmaxf(v, 0x1p-100f)) >> 23) & 255u) - 127;
+  return __uint_as_float((unsigned)(127 + 14 - e) << 23);
+}
+
+__device__ __forceinline__ void repack_halves(const RepackArgs& A, const SplitLayout& L, const RepackSizes& Z, int i) {
+  int mat = 0;
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+    if (mat == k && i >= Z.halves[k]) {
+      i -= Z.halves[k];
+      mat = k + 1;
+    }
   char* const base = A.split;
-  const float* scale = reinterpret_cast<const float*>(base + L.scale);
+  const int in = mat == 0 ? L.h1 : (mat == 1 ? 2 * L.h2 : L.hh), lanes = in / 8;  // 8 to 64 lanes of a wave a row
+  const int row = i / lanes, j = i % lanes, s = j >> 1, g = j & 1;
+  const int oW2 = 7 * L.h1, oH1 = oW2 + L.h2 * L.h1 + L.h2, oH2 = oH1 + L.hh * 2 * L.h2 + L.hh,
+            oH3 = oH2 + L.hh * L.hh + L.hh;
+  const float* W = A.raw + (mat == 0 ? oW2 : (mat == 1 ? oH1 : (mat == 2 ? oH2 : oH3)));
+  const bool zero = mat == 3 && row >= 8;
+  float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (!zero) {
+    const float* src = W + (size_t)row * in + 16 * s + (mat == 0 ? 4 : 8) * g;
+    const float4 a = *reinterpret_cast<const float4*>(src), b = *reinterpret_cast<const float4*>(src + (mat == 0 ? 8 : 4));
+    v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w, v[4] = b.x, v[5] = b.y, v[6] = b.z, v[7] = b.w;
+  }
+  float mx = 0.f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) mx = fmaxf(mx, __builtin_fabsf(v[e]));
+  for (int d = 1; d < lanes; d <<= 1) mx = fmaxf(mx, __shfl_xor(mx, d, 64));
+  const float up = halves_scale(mx);
+  int lost = 0, some = 0;
+  bool bad = false;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const bool any = v[e] != 0.f;
+    v[e] *= up;
+    some += any;
+    lost += any && __builtin_fabsf(v[e]) < kHalvesLeast;
+    bad |= !(__builtin_fabsf(v[e]) <= kSplitLimit);
+  }
+  int count = some << 16 | lost;
+  for (int d = 1; d < lanes; d <<= 1) count += __shfl_xor(count, d, 64);
+  if (bad || (count & 0xffff) > 1 + (count >> 16) / 64) *reinterpret_cast<int32_t*>(base) = 1;
+  u32x4 part[2];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    part[0][e] = split_part(v[2 * e], v[2 * e + 1]);
+    part[1][e] = last_part(v[2 * e], v[2 * e + 1]);
+  }
+  const size_t at = ((size_t)(row / 32) * (in / 16) + s) * 64 + row % 32 + 32 * g;
+  const size_t stride = (size_t)(mat == 0 ? Z.halves[0] : (mat == 1 ? Z.halves[1] : (mat == 2 ? Z.halves[2] : Z.halves[3])));
+  u32x4* dst = reinterpret_cast<u32x4*>(base + (mat == 0 ? L.w2 : (mat == 1 ? L.H1 : (mat == 2 ? L.H2 : L.H3)))) + at;
+  dst[0] = part[0];
+  dst[stride] = part[1];
+  if (j == 0 && !zero) {
+    float* scale = reinterpret_cast<float*>(base + L.scale);
+    const int first = mat == 0 ? 0 : (mat == 1 ? L.h2 : (mat == 2 ? L.h2 + L.hh : L.h2 + 2 * L.hh));
+    scale[kSplitScale0 + first + row] = 1.f / up * (mat == 0 ? 1.f / scale[0] : 1.f);
+  }
+}
+
+__global__ __launch_bounds__(256) void repack_kernel(RepackArgs A, SplitLayout L, RepackSizes Z) {
+  char* const base = A.split;
   int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < A.pack_n) {
+  if ((int)blockIdx.x >= Z.element_blocks()) {
+    repack_halves(A, L, Z, i - Z.element_blocks() * 256);
+    return;
+  }
+  if (i < Z.pack) {
     const int32_t k = A.pack_idx[i];
     A.pack[i] = k >= 0 ? A.raw[k] : 0.f;
     return;
   }
-  i -= A.pack_n;
+  i -= Z.pack;
   const float* raw = A.raw;
-  if (i < 8 * L.h1) {  // [W1 | b1 | 0][f][c], f = 32 ft + l % 32, c = 2 s + l / 32, at (4 ft + s) 64 + l
+  if (i < Z.w1) {  // [W1 | b1 | 0][f][c], f = 32 ft + l % 32, c = 2 s + l / 32, at (4 ft + s) 64 + l
     const int l = i & 63, f = 32 * (i >> 8) + l % 32, c = 2 * ((i >> 6) & 3) + l / 32;
     reinterpret_cast<float*>(base + L.w1)[i] =
-        (c < 6 ? raw[6 * f + c] : (c == 6 ? raw[6 * L.h1 + f] : 0.f)) * scale[0];
+        (c < 6 ? raw[6 * f + c] : (c == 6 ? raw[6 * L.h1 + f] : 0.f)) * *reinterpret_cast<const float*>(base + L.scale);
     return;
   }
-  i -= 8 * L.h1;
+  i -= Z.w1;
   // layer 1's rows (w0 .. w5, b, 0) and W2^T in the order of layer 2's reduction: step s is feature
   // F(s / 32, s % 2, (s / 2) % 16)
-  if (i < 8 * L.h1 + L.h2 * L.h1) {
-    const bool first = i < 8 * L.h1;
-    const int at = first ? i : i - 8 * L.h1, s = first ? at >> 3 : at / L.h2, c = first ? at & 7 : at % L.h2;
+  if (i < Z.w1c + Z.w2c) {
+    const bool first = i < Z.w1c;
+    const int at = first ? i : i - Z.w1c, s = first ? at >> 3 : at / L.h2, c = first ? at & 7 : at % L.h2;
     const int f = perm_feature(s / 32, s % 2, (s / 2) % 16);
     if (first)
       reinterpret_cast<float*>(base + L.w1c)[at] = c < 6 ? raw[6 * f + c] : (c == 6 ? raw[6 * L.h1 + f] : 0.f);
@@ -878,40 +961,19 @@ __global__ __launch_bounds__(256) void repack_kernel(RepackArgs A, SplitLayout L
       reinterpret_cast<float*>(base + L.w2c)[at] = raw[7 * L.h1 + (size_t)c * L.h1 + f];
     return;
   }
-  i -= 8 * L.h1 + L.h2 * L.h1;
+  i -= Z.w1c + Z.w2c;
   // H1, H2, H2^T and H1^T [out][in] as operands of 16x16x4 products: lane l of step u of column tile ct holds
   // M[16 ct + l % 16][16 u + 4 (l / 16) .. + 3]
+  if (i >= Z.frag) return;
   const int f1 = L.hh * 2 * L.h2, f2 = L.hh * L.hh, offH1 = 7 * L.h1 + L.h2 * L.h1 + L.h2, offH2 = offH1 + f1 + L.hh;
-  if (i < 2 * (f1 + f2)) {
-    const int mat = i < f1 ? 0 : (i < f1 + f2 ? 1 : (i < f1 + 2 * f2 ? 2 : 3));
-    const int at = i - (mat == 0 ? 0 : (mat == 1 ? f1 : (mat == 2 ? f1 + f2 : f1 + 2 * f2)));
-    const int steps = (mat == 0 ? 2 * L.h2 : L.hh) / 16, l = (at >> 2) & 63;
-    const int row = 16 * ((at >> 8) / steps) + l % 16, k = 16 * ((at >> 8) % steps) + 4 * (l / 16) + (at & 3);
-    A.frag[i] = raw[mat == 0   ? offH1 + row * 2 * L.h2 + k
-                    : mat == 1 ? offH2 + row * L.hh + k
-                    : mat == 2 ? offH2 + k * L.hh + row
-                               : offH1 + k * 2 * L.h2 + row];
-    return;
-  }
-  i -= 2 * (f1 + f2);
-  const int n2 = L.h2 * L.h1, nh1 = L.hh * 2 * L.h2, nh2 = L.hh * L.hh, nh3 = 32 * L.hh;  // H3: 8 rows, zero to 32
-  if (i >= n2 + nh1 + nh2 + nh3) return;
-  const int mat = i < n2 ? 0 : (i < n2 + nh1 ? 1 : (i < n2 + nh1 + nh2 ? 2 : 3));
-  const int at = i - (mat == 0 ? 0 : (mat == 1 ? n2 : (mat == 2 ? n2 + nh1 : n2 + nh1 + nh2)));
-  const int count = mat == 0 ? n2 : (mat == 1 ? nh1 : (mat == 2 ? nh2 : nh3));
-  const int in = mat == 0 ? L.h1 : (mat == 1 ? 2 * L.h2 : L.hh), ks = in / 16;
-  const int e = at & 7, l = (at >> 3) & 63, s = (at >> 9) % ks, row = 32 * ((at >> 9) / ks) + l % 32;
-  const int k = mat == 0 ? perm_feature(s / 2, l / 32, 8 * (s % 2) + e) : 16 * s + 8 * (l / 32) + e;
-  const float* up = scale + kSplitScale0 + (mat == 0 ? 0 : (mat == 1 ? L.h2 : (mat == 2 ? L.h2 + L.hh : L.h2 + 2 * L.hh)));
-  const int oW2 = 7 * L.h1, oH1 = oW2 + n2 + L.h2, oH2 = oH1 + nh1 + L.hh, oH3 = oH2 + nh2 + L.hh;
-  const float* W = raw + (mat == 0 ? oW2 : (mat == 1 ? oH1 : (mat == 2 ? oH2 : oH3)));
-  float v = mat == 3 && row >= 8 ? 0.f : W[(size_t)row * in + k] * up[row];
-  if (!(__builtin_fabsf(v) <= kSplitLimit)) *reinterpret_cast<int32_t*>(base) = 1;
-  _Float16* dst =
-      reinterpret_cast<_Float16*>(base + (mat == 0 ? L.w2 : (mat == 1 ? L.H1 : (mat == 2 ? L.H2 : L.H3)))) + at;
-  const _Float16 h = (_Float16)v;
-  dst[0] = h;
-  dst[count] = (_Float16)(v - (float)h);
+  const int mat = i < f1 ? 0 : (i < f1 + f2 ? 1 : (i < f1 + 2 * f2 ? 2 : 3));
+  const int at = i - (mat == 0 ? 0 : (mat == 1 ? f1 : (mat == 2 ? f1 + f2 : f1 + 2 * f2)));
+  const int steps = (mat == 0 ? 2 * L.h2 : L.hh) / 16, l = (at >> 2) & 63;
+  const int row = 16 * ((at >> 8) / steps) + l % 16, k = 16 * ((at >> 8) % steps) + 4 * (l / 16) + (at & 3);
+  A.frag[i] = raw[mat == 0   ? offH1 + row * 2 * L.h2 + k
+                  : mat == 1 ? offH2 + row * L.hh + k
+                  : mat == 2 ? offH2 + k * L.hh + row
+                             : offH1 + k * 2 * L.h2 + row];
 }
 
 // Chunk sizes: half of what is left over the grid, 32 to 1. A batch of up to `lone` pairs a workgroup is dealt out
@@ -1022,7 +1084,7 @@ void split_bind(Fp32Net& w, const char* base) {
   w.split_bad = reinterpret_cast<const int32_t*>(base);
   const float* scale = reinterpret_cast<const float*>(base + L.scale);
   w.head_bound = scale + 1;
-  w.unscale2 = scale + kSplitScale0 + L.h2 + 2 * L.hh + 8;
+  w.unscale2 = scale + kSplitScale0;
   w.unscale_h1 = w.unscale2 + L.h2;
   w.unscale_h2 = w.unscale_h1 + L.hh;
   w.unscale_h3 = w.unscale_h2 + L.hh;
@@ -1044,9 +1106,9 @@ hipError_t launch_chain_features(const Fp32Net& w, const NetArgs& a, hipStream_t
 }
 
 hipError_t launch_repack(const RepackArgs& a, hipStream_t s) {
-  const int h1 = a.h1, h2 = a.h2, hh = a.hh;
-  const int n = a.pack_n + 2 * (hh * 2 * h2 + hh * hh) + 16 * h1 + 2 * h2 * h1 + hh * 2 * h2 + hh * hh + 32 * hh;
-  kernel_launch(repack_kernel, dim3((n + 255) / 256), dim3(256), 0, s, a, split_layout(h1, h2, hh));
+  const RepackSizes z = repack_sizes(a.pack_n, a.h1, a.h2, a.hh);
+  const int halves = (z.halves[0] + z.halves[1] + z.halves[2] + z.halves[3]) / 256;
+  kernel_launch(repack_kernel, dim3(z.element_blocks() + halves), dim3(256), 0, s, a, split_layout(a.h1, a.h2, a.hh), z);
   return hipGetLastError();
 }
 

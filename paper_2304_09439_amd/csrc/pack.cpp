@@ -140,7 +140,6 @@ void split_scales(const float* flat, int h1, int h2, int hh, float xmax, float n
   const float* c1 = H1 + (size_t)hh * 2 * h2;
   const float* H2 = c1 + hh;
   const float* c2 = H2 + (size_t)hh * hh;
-  const float* H3 = c2 + hh;
   // exponent that takes v to (2^(top - 1), 2^top], within [-most, most]
   auto shift = [](double v, int top, int most) {
     if (!(v > 0.0) || !std::isfinite(v)) return 0;
@@ -170,19 +169,6 @@ void split_scales(const float* flat, int h1, int h2, int hh, float xmax, float n
   };
   most(H1, c1, hh, 2 * h2, scale + 1);
   most(H2, c2, hh, hh, scale + 3);
-  float* up = scale + kSplitScale0;
-  float* down = up + h2 + 2 * hh + 8;
-  auto rows = [&](const float* W, int out, int in, int s_in) {
-    for (int r = 0; r < out; ++r) {
-      const int t = shift(amax_of(W + (size_t)r * in, in), 8, 100);
-      *up++ = std::ldexp(1.f, t);
-      *down++ = std::ldexp(1.f, -(s_in + t));
-    }
-  };
-  rows(W2, h2, h1, s1);
-  rows(H1, hh, 2 * h2, 0);
-  rows(H2, hh, hh, 0);
-  rows(H3, 8, hh, 0);
 }
 
 // ---------------------------------------------------------------- BF16

@@ -1,0 +1,85 @@
+"""The FP32 network on the half-precision matrix cores where the magnitudes of a network, of a library or of a scene lie
+far apart: margins and coordinates far above the other values, one large shape in a library, hidden units scaled
+against the weights that read them, units that large biases keep at 0, and weights that training has made from zeros.
+Against the float64 oracle within 1e-5 per field, the FP32 tolerance of the other tests."""
+
+import numpy as np
+import pytest
+
+from helpers import field_errors
+from oracle import locc_oracle as O
+from paper_2304_09439_amd import binding as B
+from paper_2304_09439_amd import inputs as I
+from test_gpu_split import NETS, TOL, _scene
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    assert t.cuda.is_available(), "GPU tests need a GPU"
+    B.load()
+    return t
+
+
+def _layers(net, seed=2):
+    return [a.copy() for a in I.gaussian_weights(NETS[net], seed=seed, bias_std=0.1)]
+
+
+def _errors(torch, scene, net, layers, K, pad=O.PAD_M, rows=None):
+    """Errors of detect's contacts, and of the contacts beside the pose gradients, over the pairs `rows`."""
+    w = NETS[net]
+    wd = (w.h1, w.h2, w.hh)
+    flat = I.flatten_weights(layers)
+    ctx = B.context_for_scene(scene, K, wd, flat, pad=pad)
+    objs, pairs = B.scene_tensors(scene)
+    out, counts = (t.cpu().numpy() for t in ctx.detect(objs, pairs))
+    beside = ctx.pose_gradients(objs, pairs, want_contacts=True)[1].cpu().numpy()
+    ctx.close()
+    np.testing.assert_array_equal(beside, out)
+    rows = np.arange(len(scene.pairs)) if rows is None else rows
+    ref = O.detect_scene(scene, flat, wd, K, pad=pad, rows=rows)
+    np.testing.assert_array_equal(counts[rows], ref["counts"])
+    errs = field_errors(out[rows], ref["contacts"])
+    print(net, pad, {k: f"{v:.1e}" for k, v in errs.items()}, flush=True)
+    return max(errs.values())
+
+
+@pytest.mark.parametrize("net", ["small", "scale"])
+@pytest.mark.parametrize("layer", [1, 2, 3, 4])
+def test_a_large_weight_of_an_idle_unit(torch, net, layer):
+    """Every row of a matrix has one weight far above the others, of a unit that is always 0."""
+    L = _layers(net)
+    L[2 * layer - 2][7] = 0.0
+    L[2 * layer - 1][7] = -1.0
+    L[2 * layer][:, 7] = 1e6
+    assert _errors(torch, _scene(40, 90), net, L, 96) < TOL
+
+
+@pytest.mark.parametrize("net", ["small", "scale"])
+def test_weights_trained_from_zero_and_shrunk(torch, net):
+    """Rows that are zero at the upload and grow in training, and rows that shrink: the halves follow the weights."""
+    w = NETS[net]
+    wd = (w.h1, w.h2, w.hh)
+    L = _layers(net, seed=4)
+    L[2][3] = 0.0                # a row of the encoder's second layer,
+    L[8][0], L[9][0] = 0.0, 0.0  # the logit's
+    L[6][5] = 0.0                # and one of the head's
+    L[4][9] *= np.float32(1e-4)  # weights of the size of one step, which may shrink to nothing
+    scene = _scene(64, 200)
+    ctx = B.context_for_scene(scene, 64, wd, I.flatten_weights(L))
+    objs, pairs = B.scene_tensors(scene)
+    labels = torch.from_numpy((np.arange(64) % 2).astype(np.float32)).cuda()
+    for lr in (1e-4, 1e-5, 1e-6):
+        for _ in range(3):
+            ctx.train_step(objs, pairs, labels, lr=lr)
+        out = ctx.detect(objs, pairs)[0].cpu().numpy()
+        ref = O.detect_scene(scene, ctx.get_weights(0), wd, 64)
+        errs = field_errors(out, ref["contacts"])
+        print(net, lr, errs, flush=True)
+        assert max(errs.values()) < TOL
+    # a library uploaded after training does not bring the old weights' scales back
+    ctx.upload_shapes(scene.lib.offsets, scene.lib.pts)
+    np.testing.assert_array_equal(ctx.detect(objs, pairs)[0].cpu().numpy(), out)
+    ctx.close()

@@ -577,9 +577,8 @@ locc_status split_repack(locc_ctx* c) {
   const int h1 = c->cfg.enc_h1, h2 = c->cfg.enc_h2, hh = c->cfg.head_h;
   const SplitLayout L = split_layout(h1, h2, hh);
   // a b row lies in the crop box (a's box widened by the margin); a rotation keeps a normal's length
-  std::vector<float> head(L.scale / 4 + kSplitScale0, 0.f);  // the flag word, then the scales
-  split_scales(c->h_flat.data(), h1, h2, hh, c->lib_xmax + (float)c->cfg.pad_m, 1.75f * c->lib_nmax,
-               head.data() + L.scale / 4);
+  std::vector<float> head(L.scale / 4 + 1, 0.f);  // the flag word, then layer 1's factor
+  head.back() = split_layer1_scale(c->h_flat.data(), h1, c->lib_xmax + (float)c->cfg.pad_m, 1.75f * c->lib_nmax);
   HIP_TRY(hipMemcpy(c->d_wsplit, head.data(), head.size() * sizeof(float), hipMemcpyHostToDevice));
   RepackArgs ra{};
   ra.raw = c->d_wraw;

@@ -176,7 +176,6 @@ struct Fp32Net {
   const unsigned short* h1s;  // [2][hh/32][2 h2/16][64][8]
   const unsigned short* h2s;  // [2][hh/32][hh/16][64][8]
   const unsigned short* h3s;  // [2][hh/16][64][8] (8 rows, zero to 32)
-  const float* head_bound;    // of layers 1 and 2: the largest row sum of absolute weights, the largest bias
   const float* unscale2;      // [h2], the activation scale included
   const float* unscale_h1;    // [hh]
   const float* unscale_h2;    // [hh]

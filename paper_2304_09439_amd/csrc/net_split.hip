@@ -529,12 +529,14 @@ __global__ __launch_bounds__(H2) void chain_features_kernel(Fp32Net W, NetArgs A
 // columns of layers 1 and 2 and streams their weight halves from L2 two steps
 // ahead, each fragment serving all row tiles; layer 3 splits its reduction
 // over the waves.  A pair's row is scaled by the power of two that puts its
-// largest feature (layer 1's input), or the bound its weights give from there
-// (layers 2 and 3), at 2^13.  16,384 pairs at width 512: 66 us (0.350 ms as FP32
-// products, 32 pairs and four waves per workgroup); 80 pairs at width 256: 14 us
-// (40 us).  Bound by the 2 MB of weights each workgroup streams from L2 (RT = 1)
-// or by the matrix cores (RT = 2).  A pair with a value out of range gets the FP32
-// chain's result instead.
+// largest input at 2^14 to 2^15, in every layer (a bound of it through the layers
+// would leave the bits to one unit with a large bias or large weights).  The
+// weights are the products' first operand, so that a lane's outputs belong to one
+// pair.  16,384 pairs at width 512: 69 us (0.350 ms as FP32 products, 32 pairs and
+// four waves per workgroup); 80 pairs at width 256: 14 us (40 us).  Bound by the 2 MB
+// of weights each workgroup streams from L2 (RT = 1) or by the matrix cores (RT = 2).
+// A pair with a value out of range, or with too many inputs of a layer so far below its
+// largest that their halves are short of bits, gets the FP32 chain's result instead.
 
 template <int Z, int HH, int RT>
 struct HeadSmem {
@@ -546,22 +548,24 @@ struct HeadSmem {
     alignas(16) unsigned short a[2][T * AS];   // activations: [part][row][feature]
     float chain[2][32 * LZ];                   // the FP32 chain's input and output of a layer, 32 pairs
   } u;
-  alignas(16) float unscale[T];   // per row: undoes the scale of the current input
-  alignas(16) float top[T];       // per row: the largest absolute input, later its bound
+  float unscale[T];               // per row: undoes the scale of the current input
+  float top[8][T];                // per wave and row: a layer's largest output
+  int32_t count[8][T];            // per wave and row: the outputs that are not 0, and those short of bits
   float part[8][T][8];            // layer 3: each wave's part
   int32_t bad[T];                 // per row: a value out of range
   int32_t any_bad;
 };
 
-// 2^(13 - e) for v in (2^(e - 1), 2^e], within 2^+-100; 1 for 0.
-__device__ __forceinline__ float row_scale(float v) {
-  const int e = (int)((__float_as_uint(v) + 0x007fffffu) >> 23) - 127;  // ceil(log2 v)
-  int t = 13 - e;
-  t = t > 100 ? 100 : (t < -100 ? -100 : t);
-  return v > 0.f ? __uint_as_float((unsigned)(t + 127) << 23) : 1.f;
+// A power of two: v times it in [2^14, 2^15) (v at least 2^-100).
+__device__ __forceinline__ float halves_scale(float v) {
+  const int e = (int)((__float_as_uint(fmaxf(v, 0x1p-100f)) >> 23) & 255u) - 127;
+  return __uint_as_float((unsigned)(127 + 14 - e) << 23);
 }
+// Whether too many of a row's values have halves short of bits: one may, and a 64th of those that are not 0 (`count`:
+// those that are not 0 << 16 | those short of bits).  By chance 3e-5 of the values are.
+__device__ __forceinline__ bool halves_short(int count) { return (count & 0xffff) > 1 + (count >> 16) / 64; }
 
-// acc[c][t] = rows of tile t times the wave's column tile c, over KDIM inputs
+// acc[c][t] = the wave's column tile c times the rows of tile t, over KDIM inputs: a lane has 16 outputs of row l32
 template <int KDIM, int AS, int CT, int RT>
 __device__ __forceinline__ void head_products(const unsigned short* __restrict__ pack, size_t part_stride,
                                               const unsigned short* a, size_t a_part, int wave, int lane,
@@ -612,9 +616,9 @@ __device__ __forceinline__ void head_products(const unsigned short* __restrict__
       for (int c = 0; c < CT; ++c)
 #pragma unroll
         for (int t = 0; t < RT; ++t) {
-          lo(c, t) = mfma_k16(x1[t], q0[d][c], lo(c, t));
-          lo(c, t) = mfma_k16(x0[t], q1[d][c], lo(c, t));
-          acc[c][t] = mfma_k16(x0[t], q0[d][c], acc[c][t]);
+          lo(c, t) = mfma_k16(q0[d][c], x1[t], lo(c, t));
+          lo(c, t) = mfma_k16(q1[d][c], x0[t], lo(c, t));
+          acc[c][t] = mfma_k16(q0[d][c], x0[t], acc[c][t]);
         }
       const int n = s + D < KS ? s + D : s;  // (past the end: a repeated load that nothing uses)
 #pragma unroll
@@ -704,8 +708,9 @@ __global__ __launch_bounds__(512, 2) void head_split_kernel(Fp32Net W, NetArgs A
 
   // the features of a pair per wave at a time: 4 consecutive ones per lane and load
   constexpr int NL = (Z + 255) / 256;
-  for (int r = wave; r < T; r += 8) {
-    const int p = p0 + r;
+#pragma unroll 4
+  for (int i = 0; i < T / 8; ++i) {
+    const int r = wave + 8 * i, p = p0 + r;
     float4 v[NL];
     float mx = 0.f;
 #pragma unroll
@@ -721,11 +726,19 @@ __global__ __launch_bounds__(512, 2) void head_split_kernel(Fp32Net W, NetArgs A
     }
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) mx = fmaxf(mx, __shfl_xor(mx, d, 64));
-    const float sc = row_scale(mx);
+    const float sc = halves_scale(mx);
+    int some = 0, lost = 0;
+#pragma unroll
+    for (int k = 0; k < NL; ++k)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float x = fabsf(e == 0 ? v[k].x : (e == 1 ? v[k].y : (e == 2 ? v[k].z : v[k].w)));
+        some += __popcll(__ballot(x > 0.f));
+        lost += __popcll(__ballot((x > 0.f) & (x * sc < kHalvesLeast)));
+      }
     if (lane == 0) {
-      S.top[r] = mx;
       S.unscale[r] = 1.f / sc;
-      if (!(mx <= 0x1p100f)) S.bad[r] = S.any_bad = 1;
+      if (!(mx <= 0x1p100f) || halves_short(some << 16 | lost)) S.bad[r] = S.any_bad = 1;
     }
 #pragma unroll
     for (int k = 0; k < NL; ++k) {
@@ -743,61 +756,93 @@ __global__ __launch_bounds__(512, 2) void head_split_kernel(Fp32Net W, NetArgs A
   __syncthreads();
 
   f32x16 acc[CT][RT];
+  float down[RT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t) down[t] = S.unscale[32 * t + l32];
 #pragma unroll
   for (int layer = 0; layer < 2; ++layer) {
+    const float* bias = (layer ? W.c2 : W.c1) + wave * CT * 32 + 4 * g;
+    const float* un = (layer ? W.unscale_h2 : W.unscale_h1) + wave * CT * 32 + 4 * g;
+    float4 u4[CT][4], b4[CT][4];  // (loaded ahead of the products, not after them)
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        u4[c][q] = *reinterpret_cast<const float4*>(un + 32 * c + 8 * q);
+        b4[c][q] = *reinterpret_cast<const float4*>(bias + 32 * c + 8 * q);
+      }
     if (layer == 0)
       head_products<Z, AS, CT, RT>(W.h1s, (size_t)HH * Z, S.u.a[0], AP, wave, lane, acc);
     else
       head_products<HH, AS, CT, RT>(W.h2s, (size_t)HH * HH, S.u.a[0], AP, wave, lane, acc);
-    __syncthreads();  // every wave has read the layer's inputs
-    const float* bias = layer ? W.c2 : W.c1;
-    const float* un = layer ? W.unscale_h2 : W.unscale_h1;
-    const float amp = W.head_bound[2 * layer], off = W.head_bound[2 * layer + 1];
-    float mx = 0.f;
+    float top[RT];
 #pragma unroll
-    for (int t = 0; t < RT; ++t)
+    for (int t = 0; t < RT; ++t) top[t] = 0.f;
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int r0 = 32 * t + 8 * q + 4 * g;
-        const float4 u4 = *reinterpret_cast<const float4*>(&S.unscale[r0]);
-        const float4 t4 = *reinterpret_cast<const float4*>(&S.top[r0]);
-        const float us[4] = {u4.x, u4.y, u4.z, u4.w}, tp[4] = {t4.x, t4.y, t4.z, t4.w};
+        const float u[4] = {u4[c][q].x, u4[c][q].y, u4[c][q].z, u4[c][q].w};
+        const float b[4] = {b4[c][q].x, b4[c][q].y, b4[c][q].z, b4[c][q].w};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float sc = row_scale(__builtin_fmaf(tp[e], amp, off));
+        for (int t = 0; t < RT; ++t)
 #pragma unroll
-          for (int c = 0; c < CT; ++c) {
-            const int col = (wave * CT + c) * 32 + l32;
-            const float v = vmax(__builtin_fmaf(acc[c][t][4 * q + e], us[e] * un[col], bias[col]), 0.f) * sc;
-            mx = vmax(mx, v);
-            const _Float16 h = (_Float16)v;
-            const _Float16 l = (_Float16)(v - (float)h);
-            unsigned short* dst = &S.u.a[0][(r0 + e) * AS + col];
-            dst[0] = __builtin_bit_cast(unsigned short, h);
-            dst[AP] = __builtin_bit_cast(unsigned short, l);
+          for (int e = 0; e < 4; ++e) {
+            const float v = vmax(__builtin_fmaf(acc[c][t][4 * q + e], down[t] * u[e], b[e]), 0.f);
+            acc[c][t][4 * q + e] = v;
+            top[t] = vmax(top[t], v);
           }
-        }
       }
-    if (__ballot(!(mx <= kSplitLimit)) != 0) {  // rare: mark the rows
-#pragma unroll 1
-      for (int r = 0; r < T; ++r) {
-        float top = 0.f;
 #pragma unroll
-        for (int c = 0; c < CT; ++c) {
-          const unsigned short h = S.u.a[0][r * AS + (wave * CT + c) * 32 + l32];
-          top = vmax(top, (float)__builtin_bit_cast(_Float16, h));  // infinite or NaN past the range
-        }
-        if (__ballot(!(top <= kSplitLimit)) != 0 && lane == 0) S.bad[r] = S.any_bad = 1;
+    for (int t = 0; t < RT; ++t) {
+      top[t] = vmax(top[t], __shfl_xor(top[t], 32, 64));
+      if (lane < 32) S.top[wave][32 * t + lane] = top[t];
+    }
+    __syncthreads();  // every wave has read the layer's inputs
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      const int row = 32 * t + l32;
+      float mx = 0.f;
+#pragma unroll
+      for (int w = 0; w < 8; ++w) mx = vmax(mx, S.top[w][row]);
+      const float sc = halves_scale(mx);
+      down[t] = 1.f / sc;
+      if (tid < 32) {
+        S.unscale[row] = down[t];
+        if (!(mx <= 0x1p100f)) S.bad[row] = S.any_bad = 1;
       }
+      int some = 0, lost = 0;
+#pragma unroll
+      for (int c = 0; c < CT; ++c)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          float v[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            v[e] = acc[c][t][4 * q + e] * sc;
+            some += acc[c][t][4 * q + e] > 0.f;
+            lost += v[e] < kHalvesLeast;
+          }
+          uint2 h, l;
+          h.x = split_part(v[0], v[1]);
+          h.y = split_part(v[2], v[3]);
+          l.x = last_part(v[0], v[1]);
+          l.y = last_part(v[2], v[3]);
+          unsigned short* dst = &S.u.a[0][row * AS + (wave * CT + c) * 32 + 8 * q + 4 * g];
+          *reinterpret_cast<uint2*>(dst) = h;
+          *reinterpret_cast<uint2*>(dst + AP) = l;
+        }
+      int count = some << 16 | (lost - (16 * CT - some));  // the zeros are not short of bits
+      count += __shfl_xor(count, 32, 64);
+      if (lane < 32) S.count[wave][row] = count;
     }
     __syncthreads();
-    if (tid < T) {  // the scale just used, and what bounds the next layer's input
-      const float b = __builtin_fmaf(S.top[tid], amp, off);
-      S.unscale[tid] = 1.f / row_scale(b);
-      S.top[tid] = b;
-      if (!(b <= 0x1p100f)) S.bad[tid] = S.any_bad = 1;
+    if (tid < T) {
+      int count = 0;
+#pragma unroll
+      for (int w = 0; w < 8; ++w) count += S.count[w][tid];
+      if (halves_short(count)) S.bad[tid] = S.any_bad = 1;
     }
-    __syncthreads();
   }
 
   // layer 3: 8 outputs padded to 32 columns, the reduction split over the waves
@@ -865,12 +910,6 @@ RepackSizes repack_sizes(int pack_n, int h1, int h2, int hh) {
                      {h2 * h1 / 8, hh * 2 * h2 / 8, hh * hh / 8, 32 * hh / 8}};
 }
 
-// A power of two: v times it in [2^14, 2^15) (v at least 2^-100).
-__device__ __forceinline__ float halves_scale(float v) {
-  const int e = (int)((__float_as_uint(fmaxf(v, 0x1p-100f)) >> 23) & 255u) - 127;
-  return __uint_as_float((unsigned)(127 + 14 - e) << 23);
-}
-
 __device__ __forceinline__ void repack_halves(const RepackArgs& A, const SplitLayout& L, const RepackSizes& Z, int i) {
   int mat = 0;
 #pragma unroll
@@ -909,7 +948,7 @@ __device__ __forceinline__ void repack_halves(const RepackArgs& A, const SplitLa
   }
   int count = some << 16 | lost;
   for (int d = 1; d < lanes; d <<= 1) count += __shfl_xor(count, d, 64);
-  if (bad || (count & 0xffff) > 1 + (count >> 16) / 64) *reinterpret_cast<int32_t*>(base) = 1;
+  if (bad || halves_short(count)) *reinterpret_cast<int32_t*>(base) = 1;
   u32x4 part[2];
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
@@ -1083,7 +1122,6 @@ void split_bind(Fp32Net& w, const char* base) {
   const SplitLayout L = split_layout(w.h1, w.h2, w.hh);
   w.split_bad = reinterpret_cast<const int32_t*>(base);
   const float* scale = reinterpret_cast<const float*>(base + L.scale);
-  w.head_bound = scale + 1;
   w.unscale2 = scale + kSplitScale0;
   w.unscale_h1 = w.unscale2 + L.h2;
   w.unscale_h2 = w.unscale_h1 + L.hh;

@@ -132,14 +132,9 @@ SplitLayout split_layout(int h1, int h2, int hh) {
   return L;
 }
 
-void split_scales(const float* flat, int h1, int h2, int hh, float xmax, float nmax, float* scale) {
+float split_layer1_scale(const float* flat, int h1, float xmax, float nmax) {
   const float* W1 = flat;
   const float* b1 = W1 + (size_t)h1 * 6;
-  const float* W2 = b1 + h1;
-  const float* H1 = W2 + (size_t)h2 * h1 + h2;
-  const float* c1 = H1 + (size_t)hh * 2 * h2;
-  const float* H2 = c1 + hh;
-  const float* c2 = H2 + (size_t)hh * hh;
   // exponent that takes v to (2^(top - 1), 2^top], within [-most, most]
   auto shift = [](double v, int top, int most) {
     if (!(v > 0.0) || !std::isfinite(v)) return 0;
@@ -155,20 +150,7 @@ void split_scales(const float* flat, int h1, int h2, int hh, float xmax, float n
                      std::fabs((double)b1[f]);
     bound = bound > b ? bound : b;
   }
-  const int s1 = shift(bound, 13, 24);
-  scale[0] = std::ldexp(1.f, s1);
-  auto most = [](const float* W, const float* c, int out, int in, float* at) {  // row sum, bias
-    double sum = 0.0;
-    for (int r = 0; r < out; ++r) {
-      double v = 0.0;
-      for (int k = 0; k < in; ++k) v += std::fabs((double)W[(size_t)r * in + k]);
-      sum = sum > v ? sum : v;
-    }
-    at[0] = (float)sum;
-    at[1] = amax_of(c, out);
-  };
-  most(H1, c1, hh, 2 * h2, scale + 1);
-  most(H2, c2, hh, hh, scale + 3);
+  return std::ldexp(1.f, shift(bound, 13, 24));
 }
 
 // ---------------------------------------------------------------- BF16

@@ -46,6 +46,35 @@ def _errors(torch, scene, net, layers, K, pad=O.PAD_M, rows=None):
     return max(errs.values())
 
 
+UNITS = {"one": np.s_[3:4], "few": np.s_[0::9], "half": np.s_[0::2], "most": np.s_[4:]}
+
+
+@pytest.mark.parametrize("net", ["small", "scale"])
+@pytest.mark.parametrize("layer", [1, 2, 3])
+@pytest.mark.parametrize("k", [-30, -16, 20])
+@pytest.mark.parametrize("units", list(UNITS))
+def test_units_scaled_against_their_readers(torch, net, layer, k, units):
+    """Hidden units times 2^k and the weights that read them times 2^-k: the same function."""
+    L, u = _layers(net), UNITS[units]
+    s = np.float32(2.0) ** k
+    L[2 * layer][u] *= s
+    L[2 * layer + 1][u] *= s
+    reads = L[2 * layer + 2]
+    if layer == 1:    # the features of both objects
+        reads = reads.reshape(len(reads), 2, -1)
+    reads[..., u] /= s
+    assert _errors(torch, _scene(40, 90), net, L, 96) < TOL
+
+
+@pytest.mark.parametrize("net", ["small", "scale"])
+@pytest.mark.parametrize("layer", [1, 2, 3])
+@pytest.mark.parametrize("bias", [1e4, 1e7, 1e12])
+def test_units_off_by_a_large_bias(torch, net, layer, bias):
+    L = _layers(net)
+    L[2 * layer + 1][1::5] = -bias
+    assert _errors(torch, _scene(40, 90), net, L, 96) < TOL
+
+
 @pytest.mark.parametrize("net", ["small", "scale"])
 @pytest.mark.parametrize("layer", [1, 2, 3, 4])
 def test_a_large_weight_of_an_idle_unit(torch, net, layer):

@@ -2,6 +2,7 @@
 // weights, workspace, and the launch sequence of the path.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -572,14 +573,10 @@ void locc_destroy(locc_ctx* c) {
 
 namespace {
 
-// The halves of the FP32 weights, with scales for the weights and the library as they are (synchronous).
+// The packed forms of the FP32 weights that the device makes from the flat ones (synchronous).
 locc_status split_repack(locc_ctx* c) {
   const int h1 = c->cfg.enc_h1, h2 = c->cfg.enc_h2, hh = c->cfg.head_h;
-  const SplitLayout L = split_layout(h1, h2, hh);
-  // a b row lies in the crop box (a's box widened by the margin); a rotation keeps a normal's length
-  std::vector<float> head(L.scale / 4 + 1, 0.f);  // the flag word, then layer 1's factor
-  head.back() = split_layer1_scale(c->h_flat.data(), h1, c->lib_xmax + (float)c->cfg.pad_m, 1.75f * c->lib_nmax);
-  HIP_TRY(hipMemcpy(c->d_wsplit, head.data(), head.size() * sizeof(float), hipMemcpyHostToDevice));
+  HIP_TRY(hipMemset(c->d_wsplit, 0, sizeof(int32_t)));  // the flag word
   RepackArgs ra{};
   ra.raw = c->d_wraw;
   ra.h1 = h1;
@@ -587,6 +584,7 @@ locc_status split_repack(locc_ctx* c) {
   ra.hh = hh;
   ra.frag = c->d_wfrag;
   ra.split = c->d_wsplit;
+  ra.unit = c->unit;
   HIP_TRY(launch_repack(ra, nullptr));
   HIP_TRY(hipStreamSynchronize(nullptr));
   return LOCC_OK;
@@ -627,7 +625,6 @@ locc_status locc_upload_weights(locc_ctx* c, const float* h, size_t n) {
     HIP_TRY(hipMemcpy(c->d_wraw, h, n * sizeof(float), hipMemcpyHostToDevice));
     const SplitLayout SL = split_layout(h1, h2, hh);
     if (!c->d_wsplit) HIP_TRY(hipMalloc(&c->d_wsplit, SL.total));
-    c->h_flat.assign(h, h + n);
     const locc_status ss = split_repack(c);
     if (ss != LOCC_OK) return ss;
   }
@@ -745,6 +742,14 @@ locc_status locc_calibrate(locc_ctx* c, const locc_object* objs, int32_t n_objs,
   return LOCC_OK;
 }
 
+// A power of two of about twice a coordinate, 2^-100 to 2^100; 1 for 0.
+static float library_unit(float x) {
+  if (!(x > 0.f)) return 1.f;
+  int e;
+  (void)std::frexp(x, &e);  // x in [2^(e - 1), 2^e)
+  return std::ldexp(1.f, e + 1 < -100 ? -100 : (e + 1 > 100 ? 100 : e + 1));
+}
+
 // The library's spatial clusters, which let the crop skip most of a shape.  Without the memory for them (15 bytes a
 // point next to the points' own 44) the crop tests every point, as it did.
 static hipError_t build_clusters(locc_ctx* c, int32_t n_shapes, int64_t n_points, int max_points) {
@@ -782,7 +787,7 @@ locc_status locc_upload_shapes(locc_ctx* c, int32_t n_shapes, const int64_t* off
                 c->live_graphs);
   std::vector<float> soa((size_t)total * 11);  // rows (x, y, z, nx, ny, nz, 0, 0), then x, y and z
   std::vector<ShapeDesc> desc(n_shapes);
-  float xmax = 0.f, nmax = 0.f;  // largest coordinate and normal component
+  std::vector<float> reach(n_shapes, 0.f);  // each shape's largest coordinate
   for (int s = 0; s < n_shapes; ++s) {
     ShapeDesc d{};
     d.off = (int32_t)off[s];
@@ -798,14 +803,13 @@ locc_status locc_upload_shapes(locc_ctx* c, int32_t n_shapes, const int64_t* off
           return fail(LOCC_ERR_INVALID_ARG, "shape %d point %lld: non-finite value", s, (long long)(r - off[s]));
         soa[(size_t)r * 8 + k] = row[k];
         if (k < 3) soa[(size_t)(8 + k) * total + r] = row[k];
-        float& mx = k < 3 ? xmax : nmax;
-        mx = std::fabs(row[k]) > mx ? std::fabs(row[k]) : mx;
       }
       for (int k = 0; k < 3; ++k) {
         d.lo[k] = row[k] < d.lo[k] ? row[k] : d.lo[k];
         d.hi[k] = row[k] > d.hi[k] ? row[k] : d.hi[k];
       }
     }
+    for (int k = 0; k < 3; ++k) reach[s] = std::fmax(reach[s], std::fmax(std::fabs(d.lo[k]), std::fabs(d.hi[k])));
     desc[s] = d;
   }
   HIP_TRY(hipSetDevice(c->device));
@@ -824,10 +828,11 @@ locc_status locc_upload_shapes(locc_ctx* c, int32_t n_shapes, const int64_t* off
   HIP_TRY(build_clusters(c, n_shapes, total, max_points));
   c->n_shapes = n_shapes;
   c->n_points = total;
-  c->lib_xmax = xmax;
-  c->lib_nmax = nmax;
-  if (c->d_wsplit && c->cfg.precision == LOCC_FP32) return split_repack(c);  // layer 1's scale depends on them
-  return LOCC_OK;
+  std::nth_element(reach.begin(), reach.begin() + n_shapes / 2, reach.end());
+  const float unit = library_unit(reach[n_shapes / 2]);
+  if (unit == c->unit) return LOCC_OK;
+  c->unit = unit;
+  return c->cfg.precision == LOCC_FP32 && c->d_wsplit ? split_repack(c) : LOCC_OK;
 }
 
 locc_status locc_detect(locc_ctx* c, const locc_object* objs, int32_t n_objs, const int32_t* pairs,
@@ -1380,7 +1385,7 @@ locc_status locc_train_step(locc_ctx* c, const locc_object* objs, int32_t n_objs
   ta.corr2 = (float)(1.0 / (1.0 - std::pow((double)beta2, (double)t_next)));
   ta.loss = loss;
   ta.repack = RepackArgs{c->d_wraw, h1, h2, hh, c->d_wfp32, c->d_pack_idx, (int32_t)fp32_pack_floats(h1, h2, hh),
-                         c->d_wfrag, c->d_wsplit};
+                         c->d_wfrag, c->d_wsplit, c->unit};
   if (argmax) HIP_TRY(hipMemcpyAsync(argmax, amax, P * 2 * h2, hipMemcpyDeviceToDevice, s));
   HIP_TRY(timed(c, "train", s, [&] { return launch_train_step(ta, h1, h2, hh, s); }));
   c->train_t = t_next;

@@ -21,6 +21,7 @@ struct locc_ctx {
   float* d_points = nullptr;  // rows (x, y, z, nx, ny, nz, 0, 0), then x, y and z, each n_points floats
   char* d_clusters = nullptr;  // the points once more as spatial clusters (boxes, then clusters); null: no memory for it
   size_t cluster_boxes = 0;    // bytes of the boxes
+  float unit = 1.f;            // a power of two: twice most shapes' largest coordinate, for the halves' scales
   // weights
   float* d_wfp32 = nullptr;
   unsigned char* d_wbf16 = nullptr;
@@ -28,8 +29,6 @@ struct locc_ctx {
   float* d_wraw = nullptr;         // FP8 and FP32: the flat FP32 weights (calibration, pose gradients)
   float* d_wfrag = nullptr;        // FP32 and BF16: H1, H2, H2^T, H1^T in the gradient kernels' order
   char* d_wsplit = nullptr;        // FP32 and BF16: the halves of W2, H1, H2 (split_layout())
-  std::vector<float> h_flat;       // FP32 and BF16: the weights as uploaded (the halves' scales)
-  float lib_xmax = 1.f, lib_nmax = 1.f;  // the library's largest coordinate and normal component
   // FP32 training: source index of every packed weight (d_wfp32) in the flat vector (-1: zero),
   // the gradient and the two Adam moments [3][n], and the step count
   int32_t* d_pack_idx = nullptr;
@@ -80,7 +79,8 @@ struct locc_ctx {
     const size_t n = (size_t)n_points;
     const float* x = b + 8 * n;
     return locc::DeviceLibrary{d_shapes, n_shapes, reinterpret_cast<const float4*>(b), x, x + n, x + 2 * n,
-                               reinterpret_cast<const float4*>(d_clusters), d_clusters ? d_clusters + cluster_boxes : nullptr};
+                               reinterpret_cast<const float4*>(d_clusters), d_clusters ? d_clusters + cluster_boxes : nullptr,
+                               1.f / unit};
   }
 };
 

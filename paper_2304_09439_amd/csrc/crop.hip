@@ -159,6 +159,12 @@ __device__ __forceinline__ int crop_scan(const PairSetup* __restrict__ rec, cons
   return found;
 }
 
+// The power of two that takes magnitudes up to top (at least 1) to at most 1; 0 for NaN and past 2^100.
+__device__ __forceinline__ float row_power(float top) {
+  const unsigned e = (__float_as_uint(top) + 0x007fffffu) >> 23;  // 127 + ceil(log2 top)
+  return top <= 0x1p100f ? __uint_as_float((254u - e) << 23) : 0.f;
+}
+
 // The clusters of an object that may hold members, listed in S.alive; returns their number.  An a point lies in the box
 // iff its coordinates lie between the float bounds, so a cluster whose box ends before a bound holds none.  A b cluster
 // is tested in the screen's normalised coordinates: its box maps to an interval u = R' c + t' +- |R'| e (c, e: centre
@@ -355,19 +361,33 @@ __global__ __launch_bounds__(64 * W, INLINE ? 4 : 6) void crop_kernel(CropArgs A
     for (int r = lane; r < K; r += 64) A.idx_out[((size_t)p * 2 + caller) * K + r] = r < m ? S.sel[r] : -1;
   if (A.rows) {
     // rows (x, y, z, nx, ny, nz, 1, 0) stored permuted as (e0, e2, e4, e6, e1, e3, e5, e7);
-    // zero rows past the valid count
+    // zero rows past the valid count; e7 is the object's power of two
     const PairGeom g = rec->g;
+    float top = 0.f, top_n = 1.f;  // the largest coordinate and normal component in this lane's rows
     for (int r = lane; r < K; r += 64) {
       float4 lo4 = make_float4(0.f, 0.f, 0.f, 0.f), hi4 = lo4;
       if (r < m) {
         float v[6];
         geo_row(g, A.lib, off + S.sel[r], side, v);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          top = __builtin_elementwise_maximum(top, fabsf(v[k]));
+          top_n = __builtin_elementwise_maximum(top_n, fabsf(v[3 + k]));
+        }
         lo4 = make_float4(v[0], v[2], v[4], 1.0f);
-        hi4 = make_float4(v[1], v[3], v[5], 0.0f);
+        hi4 = make_float4(v[1], v[3], v[5], 1.0f);
       }
       float4* dst = reinterpret_cast<float4*>(A.rows + ((size_t)p * 2 * K + side * K + r) * kRowFloats);
       dst[0] = lo4;
       dst[1] = hi4;
+    }
+    top = __builtin_elementwise_maximum(top * A.lib.per_unit, top_n);
+    if (__ballot(!(top <= 1.f)) != 0) {  // a coordinate past the unit, or a normal longer than 1
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) top = __builtin_elementwise_maximum(top, __shfl_xor(top, d, 64));
+      const float power = row_power(top);
+      for (int r = lane; r < m; r += 64)  // (each lane's own rows: behind its stores above)
+        A.rows[((size_t)p * 2 * K + side * K + r) * kRowFloats + kRowFloats - 1] = power;
     }
   }
   if (A.rows_bf16) {

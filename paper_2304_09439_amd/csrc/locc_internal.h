@@ -63,7 +63,10 @@ constexpr int kMaxShapePoints = 16384;
 constexpr int kMaxK = 256;
 // Encoder input rows: 8 floats (x, y, z, nx, ny, nz, 1, 0) stored in the
 // order (e0, e2, e4, e6, e1, e3, e5, e7) so that each half-wave of a 32x32x2
-// MFMA operand load reads one float4.
+// MFMA operand load reads one float4.  e7, which layer 1 gives a zero weight,
+// is in the rows of an object the power of two, at most 1, that takes all their
+// normals, and coordinates in the library's unit, into [-1, 1] (0: none does),
+// for the products of halves.
 constexpr int kRowFloats = 8;
 
 struct DeviceLibrary {
@@ -77,6 +80,7 @@ struct DeviceLibrary {
   // points at points + c * kClusterBytes
   const float4* boxes;
   const char* clusters;
+  float per_unit;  // a power of two: most shapes' coordinates times it lie in [-1/2, 1/2]
 };
 
 // A shape's points once more, as clusters of 64 close to each other (the last one padded by copies of a point with
@@ -169,14 +173,14 @@ struct Fp32Net {
   const float* c3;      // [8]
   // both halves of every weight of W2, H1 and H2 in 32x32x16 B operand order, rows times powers of two, and the
   // factors that undo them (net_split.hip)
-  const float* w1s;           // w1pack times the activation scale
+  const float* w1s;           // w1pack, rows times powers of two
   const float* w1c;           // [h1][8]: W1's rows, bias, 0, in the order of layer 2's reduction
   const float* w2c;           // [h1][h2]: W2^T in that order
   const unsigned short* w2s;  // [2][h2/32][h1/16][64][8]
   const unsigned short* h1s;  // [2][hh/32][2 h2/16][64][8]
   const unsigned short* h2s;  // [2][hh/32][hh/16][64][8]
   const unsigned short* h3s;  // [2][hh/16][64][8] (8 rows, zero to 32)
-  const float* unscale2;      // [h2], the activation scale included
+  const float* unscale2;      // [h2]
   const float* unscale_h1;    // [hh]
   const float* unscale_h2;    // [hh]
   const float* unscale_h3;    // [8]
@@ -247,8 +251,7 @@ void split_bind(Fp32Net& w, const char* base);
 // Repacking on the device from the flat weights raw: pack[i] = raw[pack_idx[i]]
 // (0 where the index is negative), the head's matrices in the gradient
 // kernels' order at frag (H1 [hh][2 h2], H2 [hh][hh], H2^T, H1^T), and the
-// halves and their rows' factors at split (layer 1's factor in place, the flag
-// word zero before).
+// halves and their rows' factors at split (its flag word zero before).
 struct RepackArgs {
   const float* raw;
   int32_t h1, h2, hh;
@@ -257,6 +260,7 @@ struct RepackArgs {
   int32_t pack_n;
   float* frag;
   char* split;
+  float unit;  // of the library's coordinates (1 / DeviceLibrary::per_unit)
 };
 hipError_t launch_repack(const RepackArgs& a, hipStream_t s);
 

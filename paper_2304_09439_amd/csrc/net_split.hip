@@ -4,9 +4,9 @@
 //   h1 = ReLU(W1 r + b1), h2 = ReLU(W2 h1 + b2), f = max over the valid rows
 // of each object (0 when none; Sec. III, appendix).  Layer 1 runs on the FP32
 // matrix cores.  Layer 2, 97% of the work, runs on 16-bit ones: a float x is
-// the sum of two halves, x0 = half(x) and x1 = half(x - x0), to 2^-24 of x,
-// and of the four products of two such sums all but x1 y1 (below 2^-24 of the
-// product) are accumulated in FP32.  x0 y0 has a sum of its own, so that the
+// the sum of two halves, x0 = half(x) and x1 = half(x - x0), to 2^-23 of x
+// (three floats in four exactly), and of the four products of two such sums all
+// but x1 y1 (at most 2^-22 of the product) are accumulated in FP32.  x0 y0 has a sum of its own, so that the
 // large partial sums round 8 times per output where a chain of FP32
 // multiply-adds rounds 128 times; the result is as near the 64-bit one as
 // that chain's.  Three 32x32x16 products take 96 cycles for the 1024 that
@@ -17,12 +17,19 @@
 // clock falls to 1.93 GHz.  Six products of three bf16 parts (no scales
 // needed) took 0.98 ms.
 //
-// Halves span 2^-14 to 2^16 with all their bits, so layer 1's weights come
-// multiplied by a power of two that puts the largest output any row of the
-// library can give at 2^13, W2's rows by one that puts their largest weight at
-// 2^14 to 2^15, and the pooled sum is scaled back (all exact).  A step of rows whose
-// layer-1 outputs are not all finite and in the range of a half, and every
-// step when a weight is not, is computed as net_fp32.hip's FP32 chain.
+// Two halves keep all their bits from 2^-2 to 2^16, so everything is multiplied
+// by powers of two, and the pooled sums divided by them (all exact): an object's
+// rows by the one, at most 1, that takes them into [-1, 1] (the crop finds it; the
+// coordinates in a unit of about most shapes' size, so that it is mostly 1);
+// a hidden unit's weights and bias by one that then keeps its outputs below 2^15,
+// the weights that read it by the inverse; W2's rows by one that puts their
+// largest weight at 2^14 to 2^15.  So neither a wide margin, a large shape elsewhere
+// in the library, a unit far from the others nor training costs bits.  What falls
+// below 2^-2 all the same (by chance 2e-5 of the outputs) matters only where it is
+// not beside larger ones: a step with a row that has too many such outputs in a tile
+// of 32 units (halves_short), an object whose rows have no power of two, and every
+// step when a row of W2 has too many or a weight is not finite, is computed as an
+// FP32 chain.
 //
 // A persistent workgroup of h2 / 32 waves takes chunks of pairs from a queue
 // (chunk sizes fall from 32 to 1 towards the end of the batch, so that the
@@ -64,6 +71,20 @@ __device__ __forceinline__ unsigned last_part(float a, float b) {
   return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a, b}, f16x2));
 }
 
+// A power of two: v times it in [2^14, 2^15) (v at least 2^-100).
+__device__ __forceinline__ float halves_scale(float v) {
+  const int e = (int)((__float_as_uint(fmaxf(v, 0x1p-100f)) >> 23) & 255u) - 127;
+  return __uint_as_float((unsigned)(127 + 14 - e) << 23);
+}
+// Whether too many of a row's values have halves short of bits: one may, and a `share`-th of those that are not 0
+// (`count`: those that are not 0 << 16 | those short of bits).  By chance 2e-5 of the values are, so that three of 32
+// activations, or three of 64 weights, are not: both limits leave out what the other catches, since few activations
+// far below the others matter only with weights as far above the others'.
+__device__ __forceinline__ bool halves_short(int count, int share) {
+  return (count & 0xffff) > 1 + (count >> 16) / share;
+}
+constexpr int kShortWeights = 64, kShortActivations = 16;
+
 constexpr int kStepRows = 64;
 constexpr int kMaxSteps = kSplitChunk * 2 * (kMaxK / kStepRows);
 static_assert(kSplitChunk == 32, "one lane per object of a chunk");
@@ -76,13 +97,14 @@ struct SplitSmem {
   int32_t m[2 * kSplitChunk];    // rows per object; -1: invalid pair
   int32_t n_steps;
   int32_t claim;
-  int32_t bad[2];                // per buffer: the step whose layer-1 outputs are out of range
+  int32_t bad[2];                // per buffer: the step whose layer-1 outputs are short of bits
 };
 
 // ARGMAX: also the row of each channel's largest sum (the first on ties), and which channels' choice is in doubt: where
-// the second largest sum lies within 2^-24 of the largest magnitude a sum can have (about twenty times the rounding
-// error of an FP32 chain here, whose terms are a tenth of their bounds and of both signs) and the feature is not
-// surely 0, or where only some of an object's steps are FP32 chains.  0.3% of the channels of 16,384 pairs.
+// the second largest sum lies within 2^-24 of the largest magnitude a sum of the object's rows can have and the feature
+// is not surely 0.  That margin is about ten times the usual rounding error of an FP32 chain here (whose terms are a
+// tenth of their bounds and of both signs), not a bound of it (which is over a hundred times as large): a chain that
+// rounds worse than that may have its maximum in another row.  0.3% of the channels of 16,384 pairs.
 template <int H1, int H2, bool ARGMAX>
 __global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, NetArgs A, SplitChunks C) {
   using S_t = SplitSmem<H1, H2>;
@@ -110,7 +132,7 @@ __global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, Net
   for (int s = 0; s < 4; ++s) w1f[s] = W.w1s[(ft1 * 4 + s) * 64 + lane];
   const float bias2 = W.b2[wave * 32 + l32], unscale2 = W.unscale2[wave * 32 + l32];
   if (tid < 2) S.bad[tid] = -1;
-  float doubt = 0.f;  // ARGMAX: 2^-24 times this column's absolute weights times 2^13, unscaled
+  float doubt = 0.f;  // ARGMAX: 2^-24 times this column's absolute weights times 2^15, unscaled
   if constexpr (ARGMAX) {
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
@@ -118,7 +140,7 @@ __global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, Net
 #pragma unroll
       for (int e = 0; e < 8; ++e) doubt += __builtin_fabsf((float)w[e]);
     }
-    doubt = (doubt + __shfl_xor(doubt, 32, 64)) * unscale2 * 0x1p-11f;
+    doubt = (doubt + __shfl_xor(doubt, 32, 64)) * unscale2 * 0x1p-9f;
   }
 
   int gstep = 0;  // steps this workgroup has started (tags S.bad)
@@ -178,28 +200,37 @@ __global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, Net
         reinterpret_cast<float4*>(A.z + ((size_t)base * 2 + o) * H2)[lane] = make_float4(v, v, v, v);
     }
 
-    // this lane's layer-1 input of step k (rows past the object's count are not needed and may not exist)
-    auto load_rows = [&](int k) __attribute__((always_inline)) -> float4 {
+    // a step's layer-1 input in this lane (rows past the object's count are zeros), and how many rows of the wave's row
+    // tile the object has; a wave whose tile it does not reach has the step's first tile again, whose outputs are not read
+    struct Input {
+      float4 x;
+      int live;
+    };
+    auto load_rows = [&](int k) __attribute__((always_inline)) -> Input {
       const int e = __builtin_amdgcn_readfirstlane(S.step[k]);
       const int o = e & 0xff, r0 = (e >> 8) * kStepRows + 32 * rt1;
-      if (r0 >= __builtin_amdgcn_readfirstlane(S.m[o])) return make_float4(0.f, 0.f, 0.f, 0.f);
-      return *reinterpret_cast<const float4*>(A.rows + (((size_t)base * 2 + o) * K + r0 + l32) * kRowFloats + 4 * g);
+      const int live = __builtin_amdgcn_readfirstlane(S.m[o]) - r0;
+      const size_t row = ((size_t)base * 2 + o) * K + (live > 0 ? r0 : r0 - 32 * rt1) + l32;
+      return Input{*reinterpret_cast<const float4*>(A.rows + row * kRowFloats + 4 * g), live};
     };
     f32x16 acc1 = f32x16{};
-    auto layer1_issue = [&](float4 x) __attribute__((always_inline)) {
-      acc1 = mfma32x32x2(w1f[0], x.x, f32x16{});
-      acc1 = mfma32x32x2(w1f[1], x.y, acc1);
-      acc1 = mfma32x32x2(w1f[2], x.z, acc1);
-      acc1 = mfma32x32x2(w1f[3], x.w, acc1);
+    // issues layer 1 and returns the rows' power of two, which comes with the tile's first row
+    auto layer1_issue = [&](const float4& x) __attribute__((always_inline)) -> float {
+      const float up = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x.w), 32));
+      acc1 = mfma32x32x2(w1f[0], x.x * up, f32x16{});
+      acc1 = mfma32x32x2(w1f[1], x.y * up, acc1);
+      acc1 = mfma32x32x2(w1f[2], x.z * up, acc1);
+      acc1 = mfma32x32x2(w1f[3], x.w * up, acc1);
+      return up;
     };
     // One of the eight pairs of layer-1 outputs of this lane to their parts (h = pair / 4, e = pair % 4); the
     // fourth of a half writes the half's 16 bytes of each part.
     u32x4 q0, q1;
-    float mx = 0.f;
+    unsigned least = ~0u;  // bits of the smallest output that is not negative (of a live row: 0 is rare)
     auto layer1_pair = [&](int pair, int buf) __attribute__((always_inline)) {
       const int hf = pair >> 2, e = pair & 3;
       float a = vmax(acc1[2 * pair], 0.f), b = vmax(acc1[2 * pair + 1], 0.f);
-      mx = vmax(vmax(mx, a), b);
+      least = min(least, min(__float_as_uint(acc1[2 * pair]), __float_as_uint(acc1[2 * pair + 1])));
       q0[e] = split_part(a, b);
       q1[e] = last_part(a, b);
       if (e == 3) {
@@ -208,18 +239,32 @@ __global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, Net
         *reinterpret_cast<u32x4*>(dst + kStepRows * HS) = q1;
       }
     };
-    auto layer1_check = [&](int buf, int tag) __attribute__((always_inline)) {
-      if (__ballot(!(mx <= kSplitLimit)) != 0 && lane == 0) S.bad[buf] = tag;
+    // Whether a row of the step has too many outputs short of bits in this wave's 32 units (both lanes of a row).
+    auto layer1_check = [&](int buf, int tag, int live) __attribute__((always_inline)) {
+      if (__ballot((least < __float_as_uint(kHalvesLeast)) & (l32 < live)) != 0) {  // a step in five, in one of its waves
+        int some = 0, lost = 0;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          some += acc1[r] > 0.f;
+          lost += acc1[r] > 0.f && acc1[r] < kHalvesLeast;
+        }
+        int count = some << 16 | lost;
+        count += __shfl_xor(count, 32, 64);
+        if (__ballot(halves_short(count, kShortActivations) & (l32 < live)) != 0 && lane == 0) S.bad[buf] = tag;
+      }
+      least = ~0u;
     };
 
+    float up = 1.f;  // of the current step
     if (ns > 0) {
-      layer1_issue(load_rows(0));
+      const Input in = load_rows(0);
+      up = layer1_issue(in.x);
 #pragma unroll
       for (int q = 0; q < 8; ++q) layer1_pair(q, 0);
-      layer1_check(0, gstep);
-      mx = 0.f;
+      layer1_check(0, gstep, in.live);
     }
-    float4 xv = ns > 1 ? load_rows(1) : make_float4(0.f, 0.f, 0.f, 0.f);
+    Input next{make_float4(0.f, 0.f, 0.f, 0.f), 0};
+    if (ns > 1) next = load_rows(1);
     __syncthreads();
     float run = -__builtin_inff(), run2 = -__builtin_inff();  // the largest and (ARGMAX) second largest sum so far
     int arg = 255, chains = 0;                                // its row; bit 0: a step of halves, bit 1: a chain
@@ -229,9 +274,11 @@ __global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, Net
       const int m = __builtin_amdgcn_readfirstlane(S.m[o]);
       const bool more = k + 1 < ns;
       const int buf = k & 1;
-      const bool chain = slow || __builtin_amdgcn_readfirstlane(S.bad[buf]) == gstep;
-      if (more) layer1_issue(xv);
-      if (k + 2 < ns) xv = load_rows(k + 2);
+      const bool chain = slow || up == 0.f || __builtin_amdgcn_readfirstlane(S.bad[buf]) == gstep;
+      const int live = next.live;
+      float next_up = 1.f;
+      if (more) next_up = layer1_issue(next.x);
+      if (k + 2 < ns) next = load_rows(k + 2);
       // max of a row tile's raw sums (bias and ReLU once per column afterwards: rounding is monotone)
       float best = -__builtin_inff(), best2 = -__builtin_inff();
       int at = 255 - 4 * g;
@@ -344,12 +391,14 @@ __global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, Net
         if (chain)
 #pragma unroll
           for (int q = 0; q < 8; ++q) layer1_pair(q, buf ^ 1);
-        layer1_check(buf ^ 1, gstep + 1);
+        layer1_check(buf ^ 1, gstep + 1, live);
       }
-      mx = 0.f;
+      least = ~0u;
+      const float down = __uint_as_float((254u << 23) - __float_as_uint(up));  // 1 / up
+      up = next_up;
       if (!chain) {
-        best *= unscale2;
-        best2 *= unscale2;
+        best = best * unscale2 * down;
+        best2 = best2 * unscale2 * down;
       }
       if constexpr (ARGMAX) {
         arg = best > run ? at + 4 * g : arg;
@@ -368,7 +417,8 @@ __global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, Net
           const bool take = other > run || (other == run && other_arg < arg);
           const float second = vmax(vmax(run2, other2), fminf(run, other));
           const float first = vmax(run, other);
-          const bool sure = chains == 2 || (chains == 1 && (first - second > doubt || first + bias2 < -doubt));
+          const float margin = doubt * down;
+          const bool sure = chains == 2 || first - second > margin || first + bias2 < -margin;
           if (lane < 32) A.amax[at0 + lane] = (uint8_t)(take ? other_arg : arg);
           const unsigned long long unsure = __ballot(!sure);
           if (lane == 0) A.doubt[((size_t)base * 2 + o) * NW + wave] = (uint32_t)unsure;
@@ -550,20 +600,10 @@ struct HeadSmem {
   } u;
   float unscale[T];               // per row: undoes the scale of the current input
   float top[8][T];                // per wave and row: a layer's largest output
-  int32_t count[8][T];            // per wave and row: the outputs that are not 0, and those short of bits
   float part[8][T][8];            // layer 3: each wave's part
   int32_t bad[T];                 // per row: a value out of range
   int32_t any_bad;
 };
-
-// A power of two: v times it in [2^14, 2^15) (v at least 2^-100).
-__device__ __forceinline__ float halves_scale(float v) {
-  const int e = (int)((__float_as_uint(fmaxf(v, 0x1p-100f)) >> 23) & 255u) - 127;
-  return __uint_as_float((unsigned)(127 + 14 - e) << 23);
-}
-// Whether too many of a row's values have halves short of bits: one may, and a 64th of those that are not 0 (`count`:
-// those that are not 0 << 16 | those short of bits).  By chance 3e-5 of the values are.
-__device__ __forceinline__ bool halves_short(int count) { return (count & 0xffff) > 1 + (count >> 16) / 64; }
 
 // acc[c][t] = the wave's column tile c times the rows of tile t, over KDIM inputs: a lane has 16 outputs of row l32
 template <int KDIM, int AS, int CT, int RT>
@@ -726,19 +766,28 @@ __global__ __launch_bounds__(512, 2) void head_split_kernel(Fp32Net W, NetArgs A
     }
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) mx = fmaxf(mx, __shfl_xor(mx, d, 64));
-    const float sc = halves_scale(mx);
-    int some = 0, lost = 0;
+    const float sc = halves_scale(mx), short_below = kHalvesLeast / sc;
+    unsigned least = ~0u;  // bits of the smallest feature that is not 0, minus 1 (a 0: the largest)
 #pragma unroll
     for (int k = 0; k < NL; ++k)
+      least = min(min(least, min(__float_as_uint(v[k].x) - 1u, __float_as_uint(v[k].y) - 1u)),
+                  min(__float_as_uint(v[k].z) - 1u, __float_as_uint(v[k].w) - 1u));
+    bool bad = !(mx <= 0x1p100f);
+    if (__ballot(least < __float_as_uint(short_below) - 1u) != 0) {  // rare
+      int some = 0, lost = 0;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float x = fabsf(e == 0 ? v[k].x : (e == 1 ? v[k].y : (e == 2 ? v[k].z : v[k].w)));
-        some += __popcll(__ballot(x > 0.f));
-        lost += __popcll(__ballot((x > 0.f) & (x * sc < kHalvesLeast)));
-      }
+      for (int k = 0; k < NL; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float x = e == 0 ? v[k].x : (e == 1 ? v[k].y : (e == 2 ? v[k].z : v[k].w));
+          some += __popcll(__ballot(x > 0.f));
+          lost += __popcll(__ballot((x > 0.f) & (x < short_below)));
+        }
+      bad |= halves_short(some << 16 | lost, kShortActivations);
+    }
     if (lane == 0) {
       S.unscale[r] = 1.f / sc;
-      if (!(mx <= 0x1p100f) || halves_short(some << 16 | lost)) S.bad[r] = S.any_bad = 1;
+      if (bad) S.bad[r] = S.any_bad = 1;
     }
 #pragma unroll
     for (int k = 0; k < NL; ++k) {
@@ -776,8 +825,12 @@ __global__ __launch_bounds__(512, 2) void head_split_kernel(Fp32Net W, NetArgs A
     else
       head_products<HH, AS, CT, RT>(W.h2s, (size_t)HH * HH, S.u.a[0], AP, wave, lane, acc);
     float top[RT];
+    unsigned least[RT];  // bits of the smallest output that is not negative
 #pragma unroll
-    for (int t = 0; t < RT; ++t) top[t] = 0.f;
+    for (int t = 0; t < RT; ++t) {
+      top[t] = 0.f;
+      least[t] = ~0u;
+    }
 #pragma unroll
     for (int c = 0; c < CT; ++c)
 #pragma unroll
@@ -788,9 +841,10 @@ __global__ __launch_bounds__(512, 2) void head_split_kernel(Fp32Net W, NetArgs A
         for (int t = 0; t < RT; ++t)
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const float v = vmax(__builtin_fmaf(acc[c][t][4 * q + e], down[t] * u[e], b[e]), 0.f);
+            const float v = __builtin_fmaf(acc[c][t][4 * q + e], down[t] * u[e], b[e]);
             acc[c][t][4 * q + e] = v;
             top[t] = vmax(top[t], v);
+            least[t] = min(least[t], __float_as_uint(v));
           }
       }
 #pragma unroll
@@ -811,18 +865,27 @@ __global__ __launch_bounds__(512, 2) void head_split_kernel(Fp32Net W, NetArgs A
         S.unscale[row] = down[t];
         if (!(mx <= 0x1p100f)) S.bad[row] = S.any_bad = 1;
       }
-      int some = 0, lost = 0;
+      const float short_below = kHalvesLeast * down[t];
+      if (__ballot((least[t] < __float_as_uint(short_below)) & (mx > 0.f)) != 0) {  // rare: in the wave's columns
+        int some = 0, lost = 0;
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            some += acc[c][t][r] > 0.f;
+            lost += acc[c][t][r] > 0.f && acc[c][t][r] < short_below;
+          }
+        int count = some << 16 | lost;
+        count += __shfl_xor(count, 32, 64);
+        if (lane < 32 && halves_short(count, kShortActivations)) S.bad[row] = S.any_bad = 1;
+      }
 #pragma unroll
       for (int c = 0; c < CT; ++c)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           float v[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            v[e] = acc[c][t][4 * q + e] * sc;
-            some += acc[c][t][4 * q + e] > 0.f;
-            lost += v[e] < kHalvesLeast;
-          }
+          for (int e = 0; e < 4; ++e) v[e] = vmax(acc[c][t][4 * q + e], 0.f) * sc;
           uint2 h, l;
           h.x = split_part(v[0], v[1]);
           h.y = split_part(v[2], v[3]);
@@ -832,17 +895,8 @@ __global__ __launch_bounds__(512, 2) void head_split_kernel(Fp32Net W, NetArgs A
           *reinterpret_cast<uint2*>(dst) = h;
           *reinterpret_cast<uint2*>(dst + AP) = l;
         }
-      int count = some << 16 | (lost - (16 * CT - some));  // the zeros are not short of bits
-      count += __shfl_xor(count, 32, 64);
-      if (lane < 32) S.count[wave][row] = count;
     }
     __syncthreads();
-    if (tid < T) {
-      int count = 0;
-#pragma unroll
-      for (int w = 0; w < 8; ++w) count += S.count[w][tid];
-      if (halves_short(count)) S.bad[tid] = S.any_bad = 1;
-    }
   }
 
   // layer 3: 8 outputs padded to 32 columns, the reduction split over the waves
@@ -891,10 +945,22 @@ __global__ __launch_bounds__(512, 2) void head_split_kernel(Fp32Net W, NetArgs A
 // operands of the gradient kernels, and layer 1's operand times its factor.  The others, eight inputs of a row per
 // thread: the halves of W2, H1, H2 and H3 (8 rows, zero to 32) in the B operand order of 32x32x16 products (W2's
 // reduction index in layer 1's output order), each row times the power of two that puts its largest weight at 2^14 to
-// 2^15, found here by the row's threads, so that the halves follow the weights through training.  A weight 2^-16 of its
-// row's largest or less keeps fewer bits than a float.  A few in a row do not matter beside the others; where they are
+// 2^15, found here by the row's threads, and W2's columns times what undoes the powers of two of layer 1's units, so that
+// the halves follow the weights through training.  A weight 2^-16 of its row's largest or less keeps fewer bits than a float.  A few in a row do not matter beside the others; where they are
 // more than a 64th of the row's and one (as when the largest weight is that of a unit which is always 0), or a weight is
 // not finite, the flag word becomes 1 and every pair takes the FP32 chains.  One launch: training runs it every step.
+// A hidden unit's largest output for normals in [-1, 1] and coordinates in the library's unit in [-1, 1] is its weights'
+// and bias' absolute sum (the coordinates' times the unit); unit_power is the power of two that takes it to (2^14, 2^15]
+// (of a sum of at least 2^-100; 0 for a unit without weights; NaN past 2^100 and for weights that are not finite).
+__device__ __forceinline__ float unit_power(const float* __restrict__ raw, int h1, float unit, int f) {
+  float sum = __builtin_fabsf(raw[6 * h1 + f]);
+#pragma unroll
+  for (int c = 0; c < 6; ++c) sum += __builtin_fabsf(raw[6 * f + c]) * (c < 3 ? unit : 1.f);
+  if (!(sum <= 0x1p100f)) return __builtin_nanf("");
+  const int e = (int)((__float_as_uint(fmaxf(sum, 0x1p-100f)) + 0x007fffffu) >> 23) - 127;  // ceil(log2 sum)
+  return sum == 0.f ? 0.f : __uint_as_float((unsigned)(127 + 15 - e) << 23);
+}
+
 struct RepackSizes {
   int pack, w1, w1c, w2c, frag;  // elements, in this order
   int halves[4];                 // rows' eighths of W2, H1, H2, H3: multiples of 256
@@ -921,6 +987,14 @@ __device__ __forceinline__ void repack_halves(const RepackArgs& A, const SplitLa
   char* const base = A.split;
   const int in = mat == 0 ? L.h1 : (mat == 1 ? 2 * L.h2 : L.hh), lanes = in / 8;  // 8 to 64 lanes of a wave a row
   const int row = i / lanes, j = i % lanes, s = j >> 1, g = j & 1;
+  __shared__ float unit[128];  // W2's inputs: what undoes their units' powers of two
+  if (mat == 0) {              // uniform
+    for (int f = threadIdx.x; f < in; f += 256) {
+      const float up = unit_power(A.raw, L.h1, A.unit, f);
+      unit[f] = up > 0.f ? 1.f / up : 0.f;
+    }
+    __syncthreads();
+  }
   const int oW2 = 7 * L.h1, oH1 = oW2 + L.h2 * L.h1 + L.h2, oH2 = oH1 + L.hh * 2 * L.h2 + L.hh,
             oH3 = oH2 + L.hh * L.hh + L.hh;
   const float* W = A.raw + (mat == 0 ? oW2 : (mat == 1 ? oH1 : (mat == 2 ? oH2 : oH3)));
@@ -930,6 +1004,9 @@ __device__ __forceinline__ void repack_halves(const RepackArgs& A, const SplitLa
     const float* src = W + (size_t)row * in + 16 * s + (mat == 0 ? 4 : 8) * g;
     const float4 a = *reinterpret_cast<const float4*>(src), b = *reinterpret_cast<const float4*>(src + (mat == 0 ? 8 : 4));
     v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w, v[4] = b.x, v[5] = b.y, v[6] = b.z, v[7] = b.w;
+    if (mat == 0)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] *= unit[16 * s + 4 * g + e + (e < 4 ? 0 : 4)];
   }
   float mx = 0.f;
 #pragma unroll
@@ -948,7 +1025,7 @@ __device__ __forceinline__ void repack_halves(const RepackArgs& A, const SplitLa
   }
   int count = some << 16 | lost;
   for (int d = 1; d < lanes; d <<= 1) count += __shfl_xor(count, d, 64);
-  if (bad || halves_short(count)) *reinterpret_cast<int32_t*>(base) = 1;
+  if (bad || halves_short(count, kShortWeights)) *reinterpret_cast<int32_t*>(base) = 1;
   u32x4 part[2];
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
@@ -960,11 +1037,8 @@ __device__ __forceinline__ void repack_halves(const RepackArgs& A, const SplitLa
   u32x4* dst = reinterpret_cast<u32x4*>(base + (mat == 0 ? L.w2 : (mat == 1 ? L.H1 : (mat == 2 ? L.H2 : L.H3)))) + at;
   dst[0] = part[0];
   dst[stride] = part[1];
-  if (j == 0 && !zero) {
-    float* scale = reinterpret_cast<float*>(base + L.scale);
-    const int first = mat == 0 ? 0 : (mat == 1 ? L.h2 : (mat == 2 ? L.h2 + L.hh : L.h2 + 2 * L.hh));
-    scale[kSplitScale0 + first + row] = 1.f / up * (mat == 0 ? 1.f / scale[0] : 1.f);
-  }
+  if (j == 0 && !zero)
+    reinterpret_cast<float*>(base + L.scale)[(mat == 0 ? 0 : (mat == 1 ? L.h2 : L.h2 + (mat - 1) * L.hh)) + row] = 1.f / up;
 }
 
 __global__ __launch_bounds__(256) void repack_kernel(RepackArgs A, SplitLayout L, RepackSizes Z) {
@@ -983,8 +1057,10 @@ __global__ __launch_bounds__(256) void repack_kernel(RepackArgs A, SplitLayout L
   const float* raw = A.raw;
   if (i < Z.w1) {  // [W1 | b1 | 0][f][c], f = 32 ft + l % 32, c = 2 s + l / 32, at (4 ft + s) 64 + l
     const int l = i & 63, f = 32 * (i >> 8) + l % 32, c = 2 * ((i >> 6) & 3) + l / 32;
-    reinterpret_cast<float*>(base + L.w1)[i] =
-        (c < 6 ? raw[6 * f + c] : (c == 6 ? raw[6 * L.h1 + f] : 0.f)) * *reinterpret_cast<const float*>(base + L.scale);
+    const float up = unit_power(raw, L.h1, A.unit, f), w = c < 6 ? raw[6 * f + c] : (c == 6 ? raw[6 * L.h1 + f] : 0.f);
+    const float v = up == 0.f && c == 6 ? -1.f : w * up;  // (a unit without weights, which W2 does not read: below 0)
+    if (!(__builtin_fabsf(v) <= 0x1p126f)) *reinterpret_cast<int32_t*>(base) = 1;
+    reinterpret_cast<float*>(base + L.w1)[i] = v;
     return;
   }
   i -= Z.w1;
@@ -1122,7 +1198,7 @@ void split_bind(Fp32Net& w, const char* base) {
   const SplitLayout L = split_layout(w.h1, w.h2, w.hh);
   w.split_bad = reinterpret_cast<const int32_t*>(base);
   const float* scale = reinterpret_cast<const float*>(base + L.scale);
-  w.unscale2 = scale + kSplitScale0;
+  w.unscale2 = scale;
   w.unscale_h1 = w.unscale2 + L.h2;
   w.unscale_h2 = w.unscale_h1 + L.hh;
   w.unscale_h3 = w.unscale_h2 + L.hh;

@@ -120,7 +120,7 @@ SplitLayout split_layout(int h1, int h2, int hh) {
   L.h2 = h2;
   L.hh = hh;
   size_t o = 256;
-  L.scale = o; o = align256(o + split_scale_floats(h2, hh) * 4);
+  L.scale = o; o = align256(o + ((size_t)h2 + 2 * (size_t)hh + 8) * 4);
   L.w1 = o; o = align256(o + (size_t)8 * h1 * 4);
   L.w1c = o; o = align256(o + (size_t)8 * h1 * 4);
   L.w2c = o; o = align256(o + (size_t)h2 * h1 * 4);
@@ -130,27 +130,6 @@ SplitLayout split_layout(int h1, int h2, int hh) {
   L.H3 = o; o = align256(o + (size_t)32 * hh * 4);
   L.total = o;
   return L;
-}
-
-float split_layer1_scale(const float* flat, int h1, float xmax, float nmax) {
-  const float* W1 = flat;
-  const float* b1 = W1 + (size_t)h1 * 6;
-  // exponent that takes v to (2^(top - 1), 2^top], within [-most, most]
-  auto shift = [](double v, int top, int most) {
-    if (!(v > 0.0) || !std::isfinite(v)) return 0;
-    int e;
-    if (std::frexp(v, &e) == 0.5) --e;  // v <= 2^e
-    return top - e < -most ? -most : (top - e > most ? most : top - e);
-  };
-  double bound = 0.0;
-  for (int f = 0; f < h1; ++f) {
-    const float* w = W1 + 6 * f;
-    const double b = (std::fabs((double)w[0]) + std::fabs((double)w[1]) + std::fabs((double)w[2])) * xmax +
-                     (std::fabs((double)w[3]) + std::fabs((double)w[4]) + std::fabs((double)w[5])) * nmax +
-                     std::fabs((double)b1[f]);
-    bound = bound > b ? bound : b;
-  }
-  return std::ldexp(1.f, shift(bound, 13, 24));
 }
 
 // ---------------------------------------------------------------- BF16

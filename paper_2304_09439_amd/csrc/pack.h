@@ -25,19 +25,14 @@ void fp32_pack(const float* W1, const float* b1, const float* W2, const float* b
                int h2, int hh, float* dst);
 
 // Byte offsets of the halves of the FP32 weights (net_split.hip): a flag word,
-// the scales (layer 1's factor; the factors that undo those of W2's, H1's, H2's
-// and H3's rows), layer 1 scaled, layer 1's rows and W2^T in the order of layer
-// 2's reduction, both halves of W2, H1, H2 and H3 (8 rows, padded to 32).
-constexpr int kSplitScale0 = 4;  // floats before the rows' factors, which are read 16 bytes at a time
+// the factors that undo the powers of two of W2's, H1's, H2's and H3's rows,
+// layer 1 scaled, layer 1's rows and W2^T in the order of layer 2's reduction,
+// both halves of W2, H1, H2 and H3 (8 rows, padded to 32).
 struct SplitLayout {
   int h1, h2, hh;
   size_t scale, w1, w1c, w2c, w2, H1, H2, H3, total;
 };
 SplitLayout split_layout(int h1, int h2, int hh);
-inline size_t split_scale_floats(int h2, int hh) { return kSplitScale0 + (size_t)h2 + 2 * (size_t)hh + 8; }
-// A power of two: layer 1's outputs for coordinates up to xmax and normals up to nmax in absolute value stay below 2^13.
-// flat: the weights in locc_upload_weights' order.
-float split_layer1_scale(const float* flat, int h1, float xmax, float nmax);
 
 // ---------------------------------------------------------------- BF16
 // Byte offsets of the packed BF16 weights inside one device buffer.

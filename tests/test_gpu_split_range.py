@@ -46,11 +46,44 @@ def _errors(torch, scene, net, layers, K, pad=O.PAD_M, rows=None):
     return max(errs.values())
 
 
+@pytest.mark.parametrize("net", ["small", "scale"])
+@pytest.mark.parametrize("pad", [1e3, 1e6, 1e9, 1e30])
+def test_wide_margins(torch, net, pad):
+    assert _errors(torch, _scene(64, 90), net, _layers(net), 96, pad) < TOL
+
+
+@pytest.mark.parametrize("net", ["small", "scale"])
+@pytest.mark.parametrize("distance", [3e2, 1e5, 1e9])
+def test_far_objects_within_a_wide_margin(torch, net, distance):
+    """The second object's rows have coordinates of the distance, the first's of its own size."""
+    scene = _scene(64, 90)
+    scene.pos[1::2] += (np.random.default_rng(5).normal(size=(64, 3)) * distance).astype(np.float32)
+    assert _errors(torch, scene, net, _layers(net), 96, 100 * distance) < TOL
+
+
+@pytest.mark.parametrize("net", ["small", "scale"])
+@pytest.mark.parametrize("size", [1e3, 1e6, 1e12])
+def test_one_large_shape_in_the_library(torch, net, size):
+    """Shape 0 is larger than the others by far; half of the pairs have it, and one of its points is near them."""
+    scene = _scene(64, 90)
+    pts = scene.lib.pts.reshape(12, 90, 6)
+    pts[0, 1:, :3] *= np.float32(size)
+    rng = np.random.default_rng(6)
+    pts[0, 5:40, :3] = rng.normal(0.0, 0.1, (35, 3))    # near points and far ones in one cloud
+    scene.shape[:] = rng.integers(1, 12, 128)
+    scene.shape[1:64:2] = 0
+    scene.shape[64:96:2] = 0
+    has = (scene.shape.reshape(-1, 2) == 0).any(axis=1)
+    net_layers = _layers(net)
+    assert _errors(torch, scene, net, net_layers, 96, rows=np.flatnonzero(~has)) < TOL
+    assert _errors(torch, scene, net, net_layers, 96, rows=np.flatnonzero(has)) < TOL
+
+
 UNITS = {"one": np.s_[3:4], "few": np.s_[0::9], "half": np.s_[0::2], "most": np.s_[4:]}
 
 
 @pytest.mark.parametrize("net", ["small", "scale"])
-@pytest.mark.parametrize("layer", [1, 2, 3])
+@pytest.mark.parametrize("layer", [0, 1, 2, 3])
 @pytest.mark.parametrize("k", [-30, -16, 20])
 @pytest.mark.parametrize("units", list(UNITS))
 def test_units_scaled_against_their_readers(torch, net, layer, k, units):
@@ -67,7 +100,7 @@ def test_units_scaled_against_their_readers(torch, net, layer, k, units):
 
 
 @pytest.mark.parametrize("net", ["small", "scale"])
-@pytest.mark.parametrize("layer", [1, 2, 3])
+@pytest.mark.parametrize("layer", [0, 1, 2, 3])
 @pytest.mark.parametrize("bias", [1e4, 1e7, 1e12])
 def test_units_off_by_a_large_bias(torch, net, layer, bias):
     L = _layers(net)
@@ -112,3 +145,25 @@ def test_weights_trained_from_zero_and_shrunk(torch, net):
     ctx.upload_shapes(scene.lib.offsets, scene.lib.pts)
     np.testing.assert_array_equal(ctx.detect(objs, pairs)[0].cpu().numpy(), out)
     ctx.close()
+
+
+@pytest.mark.parametrize("net", ["small", "scale"])
+@pytest.mark.parametrize("k", [12, -12])
+def test_a_library_in_another_unit(torch, net, k):
+    """Shapes, poses and margin times 2^k and the weights of the coordinates times 2^-k: layer 1's products are the same
+    bits, and so is what does not depend on the poses, whatever the unit: the halves', not the FP32 chains'."""
+    w = NETS[net]
+    wd = (w.h1, w.h2, w.hh)
+    L, s = _layers(net), np.float32(2.0) ** k
+    scene = _scene(64, 90)
+    out = []
+    for _ in range(2):
+        ctx = B.context_for_scene(scene, 96, wd, I.flatten_weights(L), pad=0.01 if not out else 0.01 * float(s))
+        objs, pairs = B.scene_tensors(scene)
+        got, counts = (t.cpu().numpy() for t in ctx.detect(objs, pairs))
+        out.append(np.concatenate([got[:, :1], got[:, 7:], counts], 1))
+        ctx.close()
+        scene.lib.pts[:, :3] *= s
+        scene.pos *= s
+        L[0][:, :3] /= s
+    np.testing.assert_array_equal(out[0], out[1])

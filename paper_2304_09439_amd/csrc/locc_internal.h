@@ -213,9 +213,8 @@ hipError_t launch_chain_features(const Fp32Net& w, const NetArgs& a, hipStream_t
 // The head on the features in z (products of halves).
 hipError_t launch_head_split(const Fp32Net& w, const NetArgs& a, int n_cu, hipStream_t s);
 
-// Largest finite half: a float up to it has finite halves.  Both halves of one from kHalvesLeast on keep all their bits.
+// Largest finite half: a float up to it has finite halves.
 constexpr float kSplitLimit = 65504.f;
-constexpr float kHalvesLeast = 0x1p-2f;
 
 // Chunks of pairs a workgroup of the split encoder claims: level l holds
 // claims[l] chunks of size[l] pairs from pair base[l] on (the last level as

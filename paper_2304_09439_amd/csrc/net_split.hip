@@ -38,6 +38,7 @@
 // both parts in registers; layer 1 of the next step is computed one 32 x 32
 // tile per wave, split, and written to the other of two LDS buffers while
 // layer 2 of the current step runs (one barrier per step).
+#include "halves.h"
 #include "locc_internal.h"
 #include "post.h"
 
@@ -45,8 +46,6 @@ namespace locc {
 namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
@@ -59,31 +58,6 @@ __device__ __forceinline__ f32x16 mfma_k16(u32x4 a, u32x4 b, f32x16 c) {
                                                 0);
 }
 __device__ __forceinline__ int perm_feature(int ft, int g, int r) { return 32 * ft + 8 * (r / 4) + 4 * g + r % 4; }
-
-// Two floats to halves (round to nearest even), packed; the floats become the exact remainders.
-__device__ __forceinline__ unsigned split_part(float& a, float& b) {
-  const f16x2 h = __builtin_convertvector((f32x2){a, b}, f16x2);
-  a = __builtin_fmaf((float)h[0], -1.f, a);
-  b = __builtin_fmaf((float)h[1], -1.f, b);
-  return __builtin_bit_cast(unsigned, h);
-}
-__device__ __forceinline__ unsigned last_part(float a, float b) {
-  return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a, b}, f16x2));
-}
-
-// A power of two: v times it in [2^14, 2^15) (v at least 2^-100).
-__device__ __forceinline__ float halves_scale(float v) {
-  const int e = (int)((__float_as_uint(fmaxf(v, 0x1p-100f)) >> 23) & 255u) - 127;
-  return __uint_as_float((unsigned)(127 + 14 - e) << 23);
-}
-// Whether too many of a row's values have halves short of bits: one may, and a `share`-th of those that are not 0
-// (`count`: those that are not 0 << 16 | those short of bits).  By chance 2e-5 of the values are, so that three of 32
-// activations, or three of 64 weights, are not: both limits leave out what the other catches, since few activations
-// far below the others matter only with weights as far above the others'.
-__device__ __forceinline__ bool halves_short(int count, int share) {
-  return (count & 0xffff) > 1 + (count >> 16) / share;
-}
-constexpr int kShortWeights = 64, kShortActivations = 16;
 
 constexpr int kStepRows = 64;
 constexpr int kMaxSteps = kSplitChunk * 2 * (kMaxK / kStepRows);
@@ -394,7 +368,7 @@ __global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, Net
         layer1_check(buf ^ 1, gstep + 1, live);
       }
       least = ~0u;
-      const float down = __uint_as_float((254u << 23) - __float_as_uint(up));  // 1 / up
+      const float down = halves_unscale(up);
       up = next_up;
       if (!chain) {
         best = best * unscale2 * down;
@@ -766,7 +740,7 @@ __global__ __launch_bounds__(512, 2) void head_split_kernel(Fp32Net W, NetArgs A
     }
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) mx = fmaxf(mx, __shfl_xor(mx, d, 64));
-    const float sc = halves_scale(mx), short_below = kHalvesLeast / sc;
+    const float sc = halves_scale(mx), short_below = kHalvesLeast * halves_unscale(sc);
     unsigned least = ~0u;  // bits of the smallest feature that is not 0, minus 1 (a 0: the largest)
 #pragma unroll
     for (int k = 0; k < NL; ++k)
@@ -786,7 +760,7 @@ __global__ __launch_bounds__(512, 2) void head_split_kernel(Fp32Net W, NetArgs A
       bad |= halves_short(some << 16 | lost, kShortActivations);
     }
     if (lane == 0) {
-      S.unscale[r] = 1.f / sc;
+      S.unscale[r] = halves_unscale(sc);
       if (bad) S.bad[r] = S.any_bad = 1;
     }
 #pragma unroll
@@ -860,7 +834,7 @@ __global__ __launch_bounds__(512, 2) void head_split_kernel(Fp32Net W, NetArgs A
 #pragma unroll
       for (int w = 0; w < 8; ++w) mx = vmax(mx, S.top[w][row]);
       const float sc = halves_scale(mx);
-      down[t] = 1.f / sc;
+      down[t] = halves_unscale(sc);
       if (tid < 32) {
         S.unscale[row] = down[t];
         if (!(mx <= 0x1p100f)) S.bad[row] = S.any_bad = 1;

@@ -48,14 +48,9 @@ struct PackedNet {
   const float *Bw[3], *b[4], *B4;              // pair MLP [128][128] x 3, output row [128], b[3] = its bias
 };
 size_t packed_floats();
-// Largest absolute row sum and bias of the point MLP's layers: a layer's outputs are at most amp * (its largest input) +
-// off.
-struct PointBounds {
-  float amp1, off1, amp2, off2, amp3, off3;
-};
-PointBounds point_bounds(const float* flat);
-// Whether layers 2 and 3 can be computed as products of halves for shapes with coordinates up to xmax.
-bool point_halves(const PointBounds& B, float xmax);
+// Whether the point MLP's layers 2 and 3, and the predictor's hidden layers, can be products of halves (host weights).
+bool point_halves(const float* flat);
+bool pair_halves(const float* flat);
 // The halves of the point MLP and of the predictor, from the uploaded weights into the packed buffer.
 hipError_t launch_halves(const float* d_raw, float* d_packed, hipStream_t s);
 // Host-side transposition of the flat weights into dst (packed_floats() floats).
@@ -77,10 +72,10 @@ size_t encoder_scratch_floats(int n_shapes, int64_t n_points);
 EncoderBuffers encoder_carve(float* base, int n_shapes, int64_t n_points);
 
 // Shape encoder over n_shapes <= kEncodeShapes shapes; grid must be zero (the cell max starts at 0).
-// bounds: the point MLP's layers 2 and 3 as products of halves; null: as FP32 products.
+// fp32: the point MLP's layers 2 and 3 as FP32 products, not as products of halves.
 hipError_t launch_encoder(const PackedNet& w, const Shape* shapes, int n_shapes, int max_points, const float* xyz,
                           int64_t n_points, const EncoderBuffers& b, float* emb, double* consts,
-                          const PointBounds* bounds, hipStream_t s);
+                          bool fp32, hipStream_t s);
 
 struct PairArgs {
   const locc_object* objs;
@@ -96,6 +91,7 @@ struct PairArgs {
   int32_t* counts;        // [P][2] or null
   float* pooled;          // [P][2][16] or null
   unsigned long long* err;
+  int32_t fp32;           // 1: the predictor's layers as FP32 products, not as products of halves
   float* z;               // workspace [P][2][28]: per-object predictor inputs (canonical order)
   int32_t* valid;         // workspace [P]
 };

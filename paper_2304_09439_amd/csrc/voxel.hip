@@ -29,6 +29,7 @@
 #include <cstring>
 
 #include "geometry.h"
+#include "halves.h"
 #include "voxel.h"
 
 namespace locc {
@@ -103,52 +104,29 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-// Per-point MLP 3 -> 256 -> 256 -> 256 over 64 points, taken in cell order,
-// and the cell max.
+struct PointShared {
+  union {
+    unsigned short h[2][kPts][kH + 8];  // activations: [part][point][channel], 16 bytes past a multiple of 128
+    float out[kH][kPts + 1];            // the last layer's, for the pooling walk; as FP32 products every layer's
+  };
+  float top[4][kPts];                   // per wave and point: a layer's largest output
+  int32_t again;                        // a point whose layers are FP32 products
+};
+
+// Layers 1 to 3 of the per-point MLP 3 -> 256 -> 256 -> 256 for 64 points (a lane's in x, y, z) as FP32 products.
 // Layer 1 on the vector units (a wave per 64 channels, a lane per point);
 // layers 2 and 3 on the matrix cores (v_mfma_f32_32x32x2f32, bias as the
 // accumulator's start): wave w owns output channels [64 w, 64 w + 64), two
 // 32-channel tiles over the two 32-point tiles, its A operands the rows of
 // the transposed weights Wt[in][out] (coalesced, four steps ahead), its B
 // operands the activations, kept channel-major in LDS (HT[c][p]: a step
-// reads two rows of 32 points).  The last layer's outputs go to LDS too;
-// a thread per channel then walks the 64 points, whose cells come in runs,
-// and issues one atomic max per run.  Lane layouts as in conv_kernel below.
-__global__ __launch_bounds__(256) void point_mlp_kernel(PackedNet w, const Shape* shapes, const float* xyz,
-                                                         int64_t n_points, const int32_t* order,
-                                                         const uint8_t* cells, float* grid) {
-  __shared__ float X[kPts][4];
-  __shared__ int cell[kPts];
-  __shared__ float HT[kH][kPts + 1];  // padded: the pooling walk reads a column
-  const int s = blockIdx.y;
-  const Shape sh = shapes[s];
-  const int base = blockIdx.x * kPts;
-  if (base >= sh.n) return;  // uniform
-  const int np = sh.n - base < kPts ? sh.n - base : kPts;
+// reads two rows of 32 points).  The last layer's outputs go to LDS too.
+// Lane layouts as in conv_kernel below.
+__device__ __forceinline__ void point_fp32(const PackedNet& w, float x, float y, float z, float (&HT)[kH][kPts + 1]) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6, g = lane >> 5, l32 = lane & 31;
-  if (t < kPts) {
-    float x = 0.f, y = 0.f, z = 0.f;
-    int c = -1;
-    if (t < np) {
-      const int64_t q = (int64_t)sh.off + base + t;
-      const int64_t r = (int64_t)sh.off + order[q];
-      x = xyz[r];
-      y = xyz[n_points + r];
-      z = xyz[2 * n_points + r];
-      c = cells[q];
-    }
-    X[t][0] = x;
-    X[t][1] = y;
-    X[t][2] = z;
-    cell[t] = c;
-  }
-  __syncthreads();
-  {  // layer 1: lane = point, the wave's 64 channels in turn
-    const float x = X[lane][0], y = X[lane][1], z = X[lane][2];
-    for (int k = 0; k < 64; ++k) {
-      const int o = wave * 64 + k;
-      HT[o][lane] = relu(((w.P1[3 * o] * x + w.P1[3 * o + 1] * y) + w.P1[3 * o + 2] * z) + w.p1[o]);
-    }
+  for (int k = 0; k < 64; ++k) {  // lane = point, the wave's 64 channels in turn
+    const int o = wave * 64 + k;
+    HT[o][lane] = relu(((w.P1[3 * o] * x + w.P1[3 * o + 1] * y) + w.P1[3 * o + 2] * z) + w.p1[o]);
   }
   __syncthreads();
   f32x16 acc[2][2];  // [channel tile][point tile]
@@ -196,47 +174,33 @@ __global__ __launch_bounds__(256) void point_mlp_kernel(PackedNet w, const Shape
           HT[wave * 64 + 32 * ot + 8 * (r >> 2) + 4 * g + (r & 3)][32 * pt + l32] = relu(acc[ot][pt][r]);
     __syncthreads();
   }
-  // max over each run of equal cells (the grid starts at 0 and the outputs are >= 0)
-  unsigned int* gp = reinterpret_cast<unsigned int*>(grid) + act_at(0, t, s, kH, gridDim.y);
-  const size_t cell_stride = (size_t)kH * gridDim.y;
-  int cur = cell[0];
-  float m = 0.f;
-  for (int p = 0; p < np; ++p) {
-    const int c = cell[p];  // uniform
-    if (c != cur) {
-      atomicMax(gp + cur * cell_stride, __float_as_uint(m));
-      cur = c;
-      m = 0.f;
-    }
-    m = fmaxf(m, HT[t][p]);
-  }
-  atomicMax(gp + cur * cell_stride, __float_as_uint(m));
 }
 
-// The same with layers 2 and 3 as products of halves on the 16-bit matrix cores: a float is x0 + x1, halves of 11 bits
-// each, and a product x0 y0 + x0 y1 + x1 y0 (v_mfma_f32_32x32x16_f16, FP32 accumulation; what is left out is below
-// 2^-22 of the product).  A weight row is scaled by a power of two to a largest magnitude in [2^7, 2^8), the
-// activations of a shape by one that keeps their bound (PointBounds) below 2^15; both are undone exactly on the sums.
+// v * scale as halves, four in a row of each part.
+__device__ __forceinline__ void put_halves(unsigned short* part0, unsigned short* part1, const float (&v)[4],
+                                           float scale) {
+  float a = v[0] * scale, b = v[1] * scale, c = v[2] * scale, d = v[3] * scale;
+  uint2 h, l;
+  h.x = split_part(a, b);
+  h.y = split_part(c, d);
+  l.x = last_part(a, b);
+  l.y = last_part(c, d);
+  *reinterpret_cast<uint2*>(part0) = h;
+  *reinterpret_cast<uint2*>(part1) = l;
+}
+
+// The per-point MLP over 64 points, taken in cell order, and the cell max: a thread per channel walks the 64 points,
+// whose cells come in runs, and issues one atomic max per run.
+// Layers 2 and 3 are products of halves (halves.h) on the 16-bit matrix cores (v_mfma_f32_32x32x16_f16, FP32
+// accumulation).  A weight row is scaled by a power of two to a largest magnitude in [2^14, 2^15), and so are a point's
+// inputs of a layer, by their own largest; both are undone exactly on the sums.
 // Three 16-bit products of 16 steps take 96 cycles where FP32 takes 512: 70 us at 32 shapes of 2,048 points, 168 with
-// the FP32 products, which stay for weights and coordinates near the ends of the exponents (point_halves()).
-struct PointShared {
-  union {
-    unsigned short h[2][kPts][kH + 8];  // activations: [part][point][channel], 16 bytes past a multiple of 128
-    float out[kH][kPts + 1];            // the last layer's, for the pooling walk
-  };
-};
-
-__device__ __forceinline__ float point_scale(float bound) {  // a power of two: bound * it in [2^14, 2^15)
-  const int e = (int)((__float_as_uint(fmaxf(bound, 0x1p-100f)) >> 23) & 255u) - 127;
-  return __uint_as_float((unsigned)(127 + 14 - e) << 23);
-}
-__device__ __forceinline__ unsigned half_bits(float a) { return __builtin_bit_cast(unsigned short, (_Float16)a); }
-__device__ __forceinline__ float half_rest(float a) { return a - (float)(_Float16)a; }
-
-__global__ __launch_bounds__(256, 2) void point_mlp_split_kernel(PackedNet w, PointBounds B, const Shape* shapes,
-                                                                 const float* xyz, int64_t n_points,
-                                                                 const int32_t* order, const uint8_t* cells,
-                                                                 float* grid) {
+// the FP32 products.  Those stay for weights that have not all the bits they need as halves (fp32), and for 64 points
+// one of which has a value near the end of the exponents or too many inputs of a layer short of bits.
+constexpr float kHalvesMost = 0x1p90f;
+__global__ __launch_bounds__(256, 2) void point_mlp_kernel(PackedNet w, int fp32, const Shape* shapes, const float* xyz,
+                                                           int64_t n_points, const int32_t* order,
+                                                           const uint8_t* cells, float* grid) {
   constexpr int KS = kH / 16, kAhead = 4;
   __shared__ PointShared S;
   const int s = blockIdx.y;
@@ -245,11 +209,6 @@ __global__ __launch_bounds__(256, 2) void point_mlp_split_kernel(PackedNet w, Po
   if (base >= sh.n) return;  // uniform
   const int np = sh.n - base < kPts ? sh.n - base : kPts;
   const int t = threadIdx.x, lane = t & 63, wave = wave_index(), g = lane >> 5, l32 = lane & 31;
-  float xmax = 0.f;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) xmax = fmaxf(xmax, fmaxf(fabsf(sh.lo[k]), fabsf(sh.hi[k])));
-  const float bound1 = B.amp1 * xmax + B.off1, bound2 = B.amp2 * bound1 + B.off2;
-  const float scale1 = point_scale(bound1), scale2 = point_scale(bound2);  // of layer 1's and layer 2's outputs
   // lane = point, in every wave
   float x = 0.f, y = 0.f, z = 0.f;
   int cell = -1;
@@ -261,96 +220,161 @@ __global__ __launch_bounds__(256, 2) void point_mlp_split_kernel(PackedNet w, Po
     z = xyz[2 * n_points + r];
     cell = cells[q];
   }
-  {  // layer 1: the wave's 64 channels, whose weights the lanes hold, four at a time
-    const int own = wave * 64 + lane;
-    const float c0 = w.P1[3 * own], c1 = w.P1[3 * own + 1], c2 = w.P1[3 * own + 2], cb = w.p1[own];
-    auto of = [](float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
+  // marks the points whose inputs of a layer (largest: top) are out of range, or whose `least` says that some are short
+  // of bits and count(below) that too many of a wave's 64 channels are
+  auto check = [&](float top, unsigned least, bool mine, auto count) {
+    const float below = kHalvesLeast * halves_unscale(halves_scale(top));
+    bool bad = !(top < kHalvesMost);
+    if (__ballot((least < __float_as_uint(below)) & (top > 0.f)) != 0)
+      bad |= halves_short(count(below), kShortActivations);
+    if (bad && mine) S.again = 1;
+  };
+  if (!fp32) {
+    if (t == 0) S.again = 0;
+    float scale[2];  // of the inputs of this lane's columns, points 32 pt + l32
+    {                // layer 1: the wave's 64 channels, whose weights the lanes hold
+      const int own = wave * 64 + lane;
+      const float c0 = w.P1[3 * own], c1 = w.P1[3 * own + 1], c2 = w.P1[3 * own + 2], cb = w.p1[own];
+      auto of = [](float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
+      float v[64], top = 0.f;
+      unsigned least = ~0u;  // bits of the smallest output that is not negative
 #pragma unroll
-    for (int k = 0; k < 64; k += 4) {
-      unsigned hi[4], lo[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float v = relu(((of(c0, k + e) * x + of(c1, k + e) * y) + of(c2, k + e) * z) + of(cb, k + e)) * scale1;
-        hi[e] = half_bits(v);
-        lo[e] = half_bits(half_rest(v));
+      for (int k = 0; k < 64; ++k) {
+        v[k] = ((of(c0, k) * x + of(c1, k) * y) + of(c2, k) * z) + of(cb, k);
+        top = fmaxf(top, v[k]);
+        least = min(least, __float_as_uint(v[k]));
       }
-      *reinterpret_cast<uint2*>(&S.h[0][lane][wave * 64 + k]) = make_uint2(hi[0] | hi[1] << 16, hi[2] | hi[3] << 16);
-      *reinterpret_cast<uint2*>(&S.h[1][lane][wave * 64 + k]) = make_uint2(lo[0] | lo[1] << 16, lo[2] | lo[3] << 16);
+      S.top[wave][lane] = top;
+      __syncthreads();
+      top = fmaxf(fmaxf(S.top[0][lane], S.top[1][lane]), fmaxf(S.top[2][lane], S.top[3][lane]));
+      check(top, least, lane < np, [&](float below) {
+        int some = 0, lost = 0;
+#pragma unroll
+        for (int k = 0; k < 64; ++k) {
+          some += v[k] > 0.f;
+          lost += v[k] > 0.f && v[k] < below;
+        }
+        return some << 16 | lost;
+      });
+      const float up = halves_scale(top);
+#pragma unroll
+      for (int k = 0; k < 64; k += 4) {
+        float a[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a[e] = relu(v[k + e]);
+        put_halves(&S.h[0][lane][wave * 64 + k], &S.h[1][lane][wave * 64 + k], a, up);
+      }
+#pragma unroll
+      for (int pt = 0; pt < 2; ++pt) scale[pt] = __shfl(up, 32 * pt + l32, 64);
     }
-  }
-  __syncthreads();
+    __syncthreads();
 #pragma unroll 1
-  for (int layer = 0; layer < 2; ++layer) {
-    // A operands: [k-step][part][channel tile][lane][8]
-    const u32x4* Wt = reinterpret_cast<const u32x4*>(layer ? w.P3s : w.P2s) + wave * 2 * 64 + lane;
-    const float* bias = (layer ? w.p3 : w.p2) + wave * 64 + 4 * g;
-    const float* unscale = (layer ? w.u3 : w.u2) + wave * 64 + 4 * g;
-    u32x4 ar[kAhead][2][2];  // [ahead][part][channel tile]
-    auto fetch = [&](int ks, u32x4 (&a)[2][2]) {
-#pragma unroll
-      for (int q = 0; q < 2; ++q)
-#pragma unroll
-        for (int ot = 0; ot < 2; ++ot) a[q][ot] = Wt[(size_t)((ks * 2 + q) * (kH / 32) + ot) * 64];
-    };
-#pragma unroll
-    for (int d = 0; d < kAhead; ++d) fetch(d, ar[d]);
-    f32x16 acc[2][2];  // [channel tile][point tile]
-#pragma unroll
-    for (int ot = 0; ot < 2; ++ot) acc[ot][0] = acc[ot][1] = f32x16{};
-#pragma unroll 1
-    for (int k0 = 0; k0 < KS; k0 += kAhead) {
-#pragma unroll
-      for (int d = 0; d < kAhead; ++d) {
-        const int ks = k0 + d;
-        f16x8 b[2][2];  // [part][point tile]
+    for (int layer = 0; layer < 2; ++layer) {
+      // A operands: [k-step][part][channel tile][lane][8]
+      const u32x4* Wt = reinterpret_cast<const u32x4*>(layer ? w.P3s : w.P2s) + wave * 2 * 64 + lane;
+      const float* bias = (layer ? w.p3 : w.p2) + wave * 64 + 4 * g;
+      const float* unscale = (layer ? w.u3 : w.u2) + wave * 64 + 4 * g;
+      u32x4 ar[kAhead][2][2];  // [ahead][part][channel tile]
+      auto fetch = [&](int ks, u32x4 (&a)[2][2]) {
 #pragma unroll
         for (int q = 0; q < 2; ++q)
 #pragma unroll
-          for (int pt = 0; pt < 2; ++pt)
-            b[q][pt] = *reinterpret_cast<const f16x8*>(&S.h[q][32 * pt + l32][16 * ks + 8 * g]);
+          for (int ot = 0; ot < 2; ++ot) a[q][ot] = Wt[(size_t)((ks * 2 + q) * (kH / 32) + ot) * 64];
+      };
 #pragma unroll
-        for (int part = 2; part >= 0; --part)  // the small products first
+      for (int d = 0; d < kAhead; ++d) fetch(d, ar[d]);
+      f32x16 acc[2][2];  // [channel tile][point tile]
 #pragma unroll
-          for (int ot = 0; ot < 2; ++ot)
+      for (int ot = 0; ot < 2; ++ot) acc[ot][0] = acc[ot][1] = f32x16{};
+#pragma unroll 1
+      for (int k0 = 0; k0 < KS; k0 += kAhead) {
+#pragma unroll
+        for (int d = 0; d < kAhead; ++d) {
+          const int ks = k0 + d;
+          f16x8 b[2][2];  // [part][point tile]
+#pragma unroll
+          for (int q = 0; q < 2; ++q)
 #pragma unroll
             for (int pt = 0; pt < 2; ++pt)
-              acc[ot][pt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, ar[d][part == 2][ot]),
-                                                                   b[part == 1][pt], acc[ot][pt], 0, 0, 0);
-        fetch(ks + kAhead < KS ? ks + kAhead : 0, ar[d]);  // past the end: loaded, not used
-      }
-    }
-    __syncthreads();  // every wave has read the activations
-    const float down = 1.f / (layer ? scale2 : scale1);
+              b[q][pt] = *reinterpret_cast<const f16x8*>(&S.h[q][32 * pt + l32][16 * ks + 8 * g]);
 #pragma unroll
-    for (int ot = 0; ot < 2; ++ot)
+          for (int part = 2; part >= 0; --part)  // the small products first
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float4 u4 = *reinterpret_cast<const float4*>(unscale + 32 * ot + 8 * q);
-        const float4 b4 = *reinterpret_cast<const float4*>(bias + 32 * ot + 8 * q);
-        const float u[4] = {u4.x, u4.y, u4.z, u4.w}, b[4] = {b4.x, b4.y, b4.z, b4.w};
-        const int c = wave * 64 + 32 * ot + 8 * q + 4 * g;
+            for (int ot = 0; ot < 2; ++ot)
 #pragma unroll
-        for (int pt = 0; pt < 2; ++pt) {
-          float v[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = relu(fmaf(acc[ot][pt][4 * q + e], u[e] * down, b[e]));
-          if (layer) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) S.out[c + e][32 * pt + l32] = v[e];
-          } else {
-            unsigned hi[4], lo[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              v[e] *= scale2;
-              hi[e] = half_bits(v[e]);
-              lo[e] = half_bits(half_rest(v[e]));
-            }
-            *reinterpret_cast<uint2*>(&S.h[0][32 * pt + l32][c]) = make_uint2(hi[0] | hi[1] << 16, hi[2] | hi[3] << 16);
-            *reinterpret_cast<uint2*>(&S.h[1][32 * pt + l32][c]) = make_uint2(lo[0] | lo[1] << 16, lo[2] | lo[3] << 16);
-          }
+              for (int pt = 0; pt < 2; ++pt)
+                acc[ot][pt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, ar[d][part == 2][ot]),
+                                                                     b[part == 1][pt], acc[ot][pt], 0, 0, 0);
+          fetch(ks + kAhead < KS ? ks + kAhead : 0, ar[d]);  // past the end: loaded, not used
         }
       }
+      float top[2] = {0.f, 0.f};
+      unsigned least[2] = {~0u, ~0u};
+#pragma unroll
+      for (int ot = 0; ot < 2; ++ot)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float4 u4 = *reinterpret_cast<const float4*>(unscale + 32 * ot + 8 * q);
+          const float4 b4 = *reinterpret_cast<const float4*>(bias + 32 * ot + 8 * q);
+          const float u[4] = {u4.x, u4.y, u4.z, u4.w}, b[4] = {b4.x, b4.y, b4.z, b4.w};
+#pragma unroll
+          for (int pt = 0; pt < 2; ++pt)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const float v = fmaf(acc[ot][pt][4 * q + e], u[e] * halves_unscale(scale[pt]), b[e]);
+              acc[ot][pt][4 * q + e] = v;
+              top[pt] = fmaxf(top[pt], v);
+              least[pt] = min(least[pt], __float_as_uint(v));
+            }
+        }
+      if (!layer)
+#pragma unroll
+        for (int pt = 0; pt < 2; ++pt) {
+          top[pt] = fmaxf(top[pt], __shfl_xor(top[pt], 32, 64));
+          if (lane < 32) S.top[wave][32 * pt + lane] = top[pt];
+        }
+      __syncthreads();  // every wave has read the activations
+#pragma unroll
+      for (int pt = 0; pt < 2; ++pt) {
+        const int point = 32 * pt + l32;
+        if (!layer) {
+          const float mx = fmaxf(fmaxf(S.top[0][point], S.top[1][point]), fmaxf(S.top[2][point], S.top[3][point]));
+          check(mx, least[pt], point < np, [&](float below) {
+            int some = 0, lost = 0;
+#pragma unroll
+            for (int ot = 0; ot < 2; ++ot)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) {
+                some += acc[ot][pt][r] > 0.f;
+                lost += acc[ot][pt][r] > 0.f && acc[ot][pt][r] < below;
+              }
+            const int count = some << 16 | lost;
+            return count + __shfl_xor(count, 32, 64);
+          });
+          scale[pt] = halves_scale(mx);
+        }
+#pragma unroll
+        for (int ot = 0; ot < 2; ++ot)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int c = wave * 64 + 32 * ot + 8 * q + 4 * g;
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = relu(acc[ot][pt][4 * q + e]);
+            if (layer) {
+#pragma unroll
+              for (int e = 0; e < 4; ++e) S.out[c + e][point] = v[e];
+            } else {
+              put_halves(&S.h[0][point][c], &S.h[1][point][c], v, scale[pt]);
+            }
+          }
+      }
+      __syncthreads();
+    }
+  }
+  if (fp32 || S.again) {  // uniform
     __syncthreads();
+    point_fp32(w, x, y, z, S.out);
   }
   // max over each run of equal cells (the grid starts at 0 and the outputs are >= 0)
   unsigned int* gp = reinterpret_cast<unsigned int*>(grid) + act_at(0, t, s, kH, gridDim.y);
@@ -386,7 +410,7 @@ __global__ __launch_bounds__(64) void halves_kernel(const float* P, int in, int 
   for (int c = lane; c < in; c += 64) mx = fmaxf(mx, fabsf(P[(size_t)row * in + c]));
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) mx = fmaxf(mx, __shfl_xor(mx, d, 64));
-  const float up = point_scale(mx) * 0x1p-7f;
+  const float up = halves_scale(mx);
   if (lane == 0) unscale[row] = 1.f / up;
   for (int c = lane; c < 16 * k_steps; c += 64) {
     const int ks = c / 16, l = 32 * ((c % 16) / 8) + row % 32;
@@ -394,7 +418,7 @@ __global__ __launch_bounds__(64) void halves_kernel(const float* P, int in, int 
 #pragma unroll
     for (int q = 0; q < 2; ++q)
       dst[((size_t)((ks * 2 + q) * tiles + row / 32) * 64 + l) * 8 + c % 8] =
-          (unsigned short)(q ? half_bits(half_rest(x)) : half_bits(x));
+          __builtin_bit_cast(unsigned short, (_Float16)(q ? x - (float)(_Float16)x : x));
   }
 }
 
@@ -889,13 +913,12 @@ __device__ __forceinline__ void mlp_fp32(const PairArgs& A, MlpShared& S, int q0
 
 
 // Predictor MLPs: 32 pairs per workgroup; the 64 object rows come from the workspace.  The layers are products of
-// halves as in point_mlp_split_kernel, weights x rows, so that a lane has one row: every row has its own scale at every
-// layer, from its largest value (a bound of it through six layers cost the logits half a digit).  A wave has one 32 x 32 tile of a layer (of the pair layers'
-// 32 rows only four waves), the maximum over a pair's objects is taken between neighbouring lanes, and the weights of a
-// layer load while the one before it ends.  A pair with a value past kHalvesMost, or NaN inputs, is computed as FP32
-// products after the others.  24.5 us at 16,384 pairs, 13.8 at 8 (as FP32 products on 16x16x4 tiles,
+// halves as in point_mlp_kernel, weights x rows, so that a lane has one row: every row has its own scale at every
+// layer, from its largest value (a bound of it through six layers cost the logits half a digit).  A wave has one 32 x 32
+// tile of a layer (of the pair layers' 32 rows only four waves), the maximum over a pair's objects is taken between neighbouring lanes, and the weights of a
+// layer load while the one before it ends.  A pair with a value past kHalvesMost, NaN inputs, or too many inputs of a
+// layer short of bits, is computed as FP32 products after the others, and every pair where the weights are (A.fp32).  24.5 us at 16,384 pairs, 13.8 at 8 (as FP32 products on 16x16x4 tiles,
 // bound by them, 43 and 21.9); at most 128 registers keep two workgroups per compute unit (134: 32 us).
-constexpr float kHalvesMost = 0x1p90f;
 struct MlpSplitShared {
   unsigned short h[2][2 * kTP][kHP + 8];  // object rows: [part][row][channel]
   unsigned short p[2][kTP][kHP + 8];      // pairs
@@ -933,21 +956,6 @@ __device__ __forceinline__ f32x16 tile_products(const TileWeights<KS>& T, const 
   }
   return acc;
 }
-// Four outputs of a lane's row, channels c .. c + 3, as halves of v * scale.
-template <int ROWS>
-__device__ __forceinline__ void put_halves(unsigned short (&h)[2][ROWS][kHP + 8], int row, int c, const float (&v)[4],
-                                           float scale) {
-  unsigned hi[4], lo[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const float x = v[e] * scale;
-    hi[e] = half_bits(x);
-    lo[e] = half_bits(half_rest(x));
-  }
-  *reinterpret_cast<uint2*>(&h[0][row][c]) = make_uint2(hi[0] | hi[1] << 16, hi[2] | hi[3] << 16);
-  *reinterpret_cast<uint2*>(&h[1][row][c]) = make_uint2(lo[0] | lo[1] << 16, lo[2] | lo[3] << 16);
-}
-
 __global__ __launch_bounds__(kThreads, 4) void mlp_kernel(PairArgs A) {
   __shared__ union {
     MlpSplitShared split;
@@ -968,6 +976,10 @@ __global__ __launch_bounds__(kThreads, 4) void mlp_kernel(PairArgs A) {
   }
   if (t == 0) any_again = 0;
   __syncthreads();
+  if (A.fp32) {  // uniform
+    mlp_fp32(A, U.fp32, q0, n, valid);
+    return;
+  }
   {  // 64 rows x 8 float4 (28 inputs, zero to 32); a row's eight lanes find its scales
     const int row = t >> 3, c4 = t & 7;
     float4 v4 = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -985,13 +997,31 @@ __global__ __launch_bounds__(kThreads, 4) void mlp_kernel(PairArgs A) {
       sum += __shfl_xor(sum, d, 64);
     }
     if (c4 == 0) S.top[0][row] = top;
-    if (!(sum < kHalvesMost) && c4 == 0 && valid[row >> 1]) again[row >> 1] = any_again = 1;
-    put_halves(S.h, row, 4 * c4, v, point_scale(top));
+    bool bad = !(sum < kHalvesMost);
+    const float below = kHalvesLeast * halves_unscale(halves_scale(top));
+    bool some_short = false;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) some_short |= (v[e] != 0.f) & (fabsf(v[e]) < below);
+    if (__ballot(some_short) != 0) {
+      // (the embedding, the offset and the rotation's entries are of different sizes by nature: half of them may be short)
+      int count = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        count += (v[e] != 0.f ? 1 << 16 : 0) + ((v[e] != 0.f) & (fabsf(v[e]) < below) ? 1 : 0);
+#pragma unroll
+      for (int d = 1; d < 8; d <<= 1) count += __shfl_xor(count, d, 64);
+      bad |= halves_short(count, 2);
+    }
+    if (bad && c4 == 0 && valid[row >> 1]) again[row >> 1] = any_again = 1;
+    put_halves(&S.h[0][row][4 * c4], &S.h[1][row][4 * c4], v, halves_scale(top));
   }
   __syncthreads();
   const int row = 32 * rt + l32;
-  float v[4][4];  // a layer's outputs of this lane's row: channels 32 ct + 8 q + 4 g + e
-  auto outputs = [&](const f32x16& acc, int layer, float down) {
+  float v[4][4];          // a layer's outputs of this lane's row: channels 32 ct + 8 q + 4 g + e
+  unsigned least = ~0u;   // bits of the smallest that is not negative (before the ReLU)
+  auto outputs = [&](const f32x16& acc, int layer, float scale) {
+    const float down = halves_unscale(scale);
+    least = ~0u;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int c = 32 * ct + 8 * q + 4 * g;
@@ -999,7 +1029,11 @@ __global__ __launch_bounds__(kThreads, 4) void mlp_kernel(PairArgs A) {
       const float4 b4 = *reinterpret_cast<const float4*>((layer < 3 ? A.w.a[layer] : A.w.b[layer - 3]) + c);
       const float u[4] = {u4.x, u4.y, u4.z, u4.w}, b[4] = {b4.x, b4.y, b4.z, b4.w};
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[q][e] = relu(fmaf(acc[4 * q + e], u[e] * down, b[e]));
+      for (int e = 0; e < 4; ++e) {
+        v[q][e] = fmaf(acc[4 * q + e], u[e] * down, b[e]);
+        least = min(least, __float_as_uint(v[q][e]));
+        v[q][e] = relu(v[q][e]);
+      }
     }
   };
   // the largest of v in row r, over the column tiles' waves (a barrier, before which every wave has read the inputs)
@@ -1015,36 +1049,55 @@ __global__ __launch_bounds__(kThreads, 4) void mlp_kernel(PairArgs A) {
     return fmaxf(fmaxf(S.top[0][r], S.top[1][r]), fmaxf(S.top[2][r], S.top[3][r]));
   };
   auto check = [&](float top, int pair) {
-    if (!(top < kHalvesMost) && valid[pair]) again[pair] = any_again = 1;
+    const float below = kHalvesLeast * halves_unscale(halves_scale(top));
+    bool bad = !(top < kHalvesMost);
+    if (__ballot((least < __float_as_uint(below)) & (top > 0.f)) != 0) {  // rare: of the wave's 32 channels
+      int some = 0, lost = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          some += v[q][e] > 0.f;
+          lost += v[q][e] > 0.f && v[q][e] < below;
+        }
+      int count = some << 16 | lost;
+      count += __shfl_xor(count, 32, 64);
+      bad |= halves_short(count, kShortActivations);
+    }
+    if (bad && valid[pair]) again[pair] = any_again = 1;
   };
-  float scale = point_scale(S.top[0][row]);
+  float scale = halves_scale(S.top[0][row]);
   f32x16 acc = tile_products<2>(w0, S.h, row, g);
   load_tile<kHP / 16>(A.w.As[1], ct, lane, w1);
   __syncthreads();  // every wave has read the inputs' scales, which the first layer's largest outputs replace
 #pragma unroll 1
   for (int layer = 0; layer < 2; ++layer) {
-    outputs(acc, layer, 1.f / scale);
+    outputs(acc, layer, scale);
     const float top = row_top(row, true);
     check(top, row >> 1);
-    scale = point_scale(top);
+    scale = halves_scale(top);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) put_halves(S.h, row, 32 * ct + 8 * q + 4 * g, v[q], scale);
+    for (int q = 0; q < 4; ++q) put_halves(&S.h[0][row][32 * ct + 8 * q + 4 * g], &S.h[1][row][32 * ct + 8 * q + 4 * g], v[q], scale);
     __syncthreads();
     acc = tile_products<kHP / 16>(w1, S.h, row, g);
     load_tile<kHP / 16>(layer ? A.w.Bs[0] : A.w.As[2], ct, lane, w1);
   }
-  outputs(acc, 2, 1.f / scale);
+  outputs(acc, 2, scale);
+  least = ~0u;
 #pragma unroll
   for (int q = 0; q < 4; ++q)  // the maximum over the pair's two rows, lanes 2 k and 2 k + 1
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[q][e] = fmaxf(v[q][e], __shfl_xor(v[q][e], 1, 64));
+    for (int e = 0; e < 4; ++e) {
+      v[q][e] = fmaxf(v[q][e], __shfl_xor(v[q][e], 1, 64));
+      least = min(least, v[q][e] > 0.f ? __float_as_uint(v[q][e]) : ~0u);
+    }
   {
     const float top = row_top(row, true);
     check(top, row >> 1);
     if (!(lane & 1)) {
-      if (ct == 0 && g == 0) S.pscale[row >> 1] = point_scale(top);
+      if (ct == 0 && g == 0) S.pscale[row >> 1] = halves_scale(top);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) put_halves(S.p, row >> 1, 32 * ct + 8 * q + 4 * g, v[q], point_scale(top));
+      for (int q = 0; q < 4; ++q) put_halves(&S.p[0][row >> 1][32 * ct + 8 * q + 4 * g], &S.p[1][row >> 1][32 * ct + 8 * q + 4 * g], v[q], halves_scale(top));
     }
   }
   __syncthreads();
@@ -1055,20 +1108,20 @@ __global__ __launch_bounds__(kThreads, 4) void mlp_kernel(PairArgs A) {
     if (wave < 4) {
       acc = tile_products<kHP / 16>(w1, S.p, l32, g);
       load_tile<kHP / 16>(A.w.Bs[layer + 1], ct, lane, w1);
-      outputs(acc, 3 + layer, 1.f / scale);
+      outputs(acc, 3 + layer, scale);
     }
     const float top = row_top(l32, wave < 4);
     if (wave < 4) {
       check(top, l32);
-      scale = point_scale(top);
+      scale = halves_scale(top);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) put_halves(S.p, l32, 32 * ct + 8 * q + 4 * g, v[q], scale);
+      for (int q = 0; q < 4; ++q) put_halves(&S.p[0][l32][32 * ct + 8 * q + 4 * g], &S.p[1][l32][32 * ct + 8 * q + 4 * g], v[q], scale);
     }
     __syncthreads();
   }
   if (wave < 4) {  // the last pair layer and the output row's products
     acc = tile_products<kHP / 16>(w1, S.p, l32, g);
-    outputs(acc, 5, 1.f / scale);
+    outputs(acc, 5, scale);
     float sum = 0.f;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -1177,32 +1230,35 @@ void pack_transposed(const float* flat, float* dst) {
   }
 }
 
-static void layer_bounds(const float* W, const float* b, int out, int in, float* amp, float* bias) {
-  double a = 0.0, m = 0.0;
-  for (int o = 0; o < out; ++o) {
-    double sum = 0.0;
-    for (int c = 0; c < in; ++c) sum += std::fabs((double)W[(size_t)o * in + c]);
-    a = std::fmax(a, sum);
-    m = std::fmax(m, std::fabs((double)b[o]));
+// Whether the halves of a matrix have the bits its products need, row by row (halves_kernel scales a row to [2^14, 2^15)).
+static bool matrix_halves(const float* W, int out, int in) {
+  for (int o = 0; o < out; ++o, W += in) {
+    float mx = 0.f;
+    for (int c = 0; c < in; ++c) mx = std::fmax(mx, std::fabs(W[c]));
+    if (!(mx < 0x1p90f)) return false;
+    const float below = std::ldexp(kHalvesLeast, std::ilogb(std::fmax(mx, 0x1p-100f)) - 14);
+    int some = 0, lost = 0;
+    for (int c = 0; c < in; ++c) {
+      some += W[c] != 0.f;
+      lost += W[c] != 0.f && std::fabs(W[c]) < below;
+    }
+    if (halves_short(some << 16 | lost, kShortWeights)) return false;
   }
-  *amp = (float)(a * (1.0 + 0x1p-20));
-  *bias = (float)(m * (1.0 + 0x1p-20));
+  return true;
 }
 
-PointBounds point_bounds(const float* flat) {
+bool point_halves(const float* flat) {
   size_t off[kArrays];
   offsets(off);
-  PointBounds B{};
-  layer_bounds(flat + off[0], flat + off[1], kH, 3, &B.amp1, &B.off1);
-  layer_bounds(flat + off[2], flat + off[3], kH, kH, &B.amp2, &B.off2);
-  layer_bounds(flat + off[4], flat + off[5], kH, kH, &B.amp3, &B.off3);
-  return B;
+  return matrix_halves(flat + off[2], kH, kH) && matrix_halves(flat + off[4], kH, kH);
 }
 
-bool point_halves(const PointBounds& B, float xmax) {
-  // the bounds, and with them every weight that is not 0, far from the ends of the exponents
-  const double b1 = (double)B.amp1 * xmax + B.off1, b2 = B.amp2 * b1 + B.off2;
-  return B.amp2 < 0x1p90 && B.amp3 < 0x1p90 && b1 < 0x1p90 && b2 < 0x1p90;
+bool pair_halves(const float* flat) {
+  size_t off[kArrays];
+  offsets(off);
+  for (int i = 0; i < 6; ++i)
+    if (!matrix_halves(flat + off[24 + 2 * i], kHP, i ? kHP : kIn)) return false;
+  return true;
 }
 
 hipError_t launch_halves(const float* raw, float* packed, hipStream_t s) {
@@ -1324,15 +1380,11 @@ hipError_t conv(const float* in1, int c1, const float* in2, int c2, const float*
 
 hipError_t launch_encoder(const PackedNet& w, const Shape* shapes, int n_shapes, int max_points, const float* xyz,
                           int64_t n_points, const EncoderBuffers& b, float* emb, double* consts,
-                          const PointBounds* bounds, hipStream_t s) {
+                          bool fp32, hipStream_t s) {
   if (n_shapes <= 0 || n_shapes > kEncodeShapes || max_points <= 0) return hipErrorInvalidValue;
   kernel_launch(cell_sort_kernel, dim3(n_shapes), dim3(1024), 0, s, shapes, xyz, n_points, b.order, b.cell);
-  const dim3 points((max_points + kPts - 1) / kPts, n_shapes);
-  if (bounds)
-    kernel_launch(point_mlp_split_kernel, points, dim3(256), 0, s, w, *bounds, shapes, xyz, n_points, b.order, b.cell,
-                  b.grid);
-  else
-    kernel_launch(point_mlp_kernel, points, dim3(256), 0, s, w, shapes, xyz, n_points, b.order, b.cell, b.grid);
+  kernel_launch(point_mlp_kernel, dim3((max_points + kPts - 1) / kPts, n_shapes), dim3(256), 0, s, w, (int)fp32, shapes, xyz,
+                n_points, b.order, b.cell, b.grid);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = conv(b.grid, kH, nullptr, 0, w.C[0], w.k[0], b.c[0], kM, 4, 0, 0, n_shapes, s);
   for (int i = 1; i < 4 && e == hipSuccess; ++i)

@@ -19,13 +19,12 @@ struct locc_voxel_ctx {
   int32_t n_shapes = 0;
   int max_points = 0;
   int64_t n_points = 0;
-  float xmax = 0.f;  // largest coordinate
   Shape* d_shapes = nullptr;
   float* d_xyz = nullptr;
   // weights
   float* d_raw = nullptr;
   float* d_packed = nullptr;
-  PointBounds bounds{};
+  bool point_fp32 = false, pair_fp32 = false;  // the weights do not go into halves
   // per-shape results of the encoder
   float* d_emb = nullptr;       // [S][216][16]
   double* d_consts = nullptr;   // [S][4] cell size and margin
@@ -67,7 +66,7 @@ locc_status encode(locc_voxel_ctx* c) {
     if (e == hipSuccess)
       e = launch_encoder(packed_view(c->d_raw, c->d_packed), c->d_shapes + s0, m, c->max_points, c->d_xyz, c->n_points,
                          b, c->d_emb + (size_t)s0 * kCells * kF, c->d_consts + (size_t)s0 * 4,
-                         point_halves(c->bounds, c->xmax) ? &c->bounds : nullptr, nullptr);
+                         c->point_fp32, nullptr);
   }
   if (e == hipSuccess) e = hipDeviceSynchronize();
   (void)hipFree(scratch);
@@ -126,7 +125,8 @@ locc_status locc_voxel_upload_weights(locc_voxel_ctx* c, const float* h, size_t 
   HIP_TRY(hipMemcpy(c->d_raw, h, n * sizeof(float), hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(c->d_packed, packed.data(), packed.size() * sizeof(float), hipMemcpyHostToDevice));
   HIP_TRY(launch_halves(c->d_raw, c->d_packed, nullptr));
-  c->bounds = point_bounds(h);
+  c->point_fp32 = !point_halves(h);
+  c->pair_fp32 = !pair_halves(h);
   c->have_weights = true;
   return encode(c);
 }
@@ -146,7 +146,6 @@ locc_status locc_voxel_upload_shapes(locc_voxel_ctx* c, int32_t n_shapes, const 
   if (total >= (int64_t)INT32_MAX) return fail(LOCC_ERR_RANGE, "%lld points in total", (long long)total);
   std::vector<float> xyz((size_t)total * 3);
   std::vector<Shape> shapes(n_shapes);
-  float xmax = 0.f;
   for (int s = 0; s < n_shapes; ++s) {
     Shape d{};
     d.off = (int32_t)off[s];
@@ -165,7 +164,6 @@ locc_status locc_voxel_upload_shapes(locc_voxel_ctx* c, int32_t n_shapes, const 
         d.hi[k] = row[k] > d.hi[k] ? row[k] : d.hi[k];
       }
     }
-    for (int k = 0; k < 3; ++k) xmax = std::fmax(xmax, std::fmax(std::fabs(d.lo[k]), std::fabs(d.hi[k])));
     shapes[s] = d;
   }
   HIP_TRY(hipSetDevice(c->device));
@@ -179,7 +177,6 @@ locc_status locc_voxel_upload_shapes(locc_voxel_ctx* c, int32_t n_shapes, const 
   HIP_TRY(hipMemcpy(c->d_xyz, xyz.data(), sizeof(float) * xyz.size(), hipMemcpyHostToDevice));
   c->n_shapes = n_shapes;
   c->max_points = max_points;
-  c->xmax = xmax;
   c->n_points = total;
   return encode(c);
 }
@@ -216,6 +213,7 @@ locc_status locc_voxel_detect(locc_voxel_ctx* c, const locc_object* objs, int32_
   a.counts = counts;
   a.pooled = pooled;
   a.err = c->d_err;
+  a.fp32 = c->pair_fp32;
   const size_t need = pair_workspace_bytes(n_pairs);
   if (need > c->ws_bytes) {  // synchronous growth
     if (c->d_ws) HIP_TRY(hipFree(c->d_ws));

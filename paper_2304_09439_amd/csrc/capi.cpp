@@ -750,12 +750,17 @@ static float library_unit(float x) {
   return std::ldexp(1.f, e + 1 < -100 ? -100 : (e + 1 > 100 ? 100 : e + 1));
 }
 
-// The library's spatial clusters, which let the crop skip most of a shape.  Without the memory for them (15 bytes a
-// point next to the points' own 44) the crop tests every point, as it did.
+// The library's spatial clusters, which let the crop skip most of a shape.  They take 15 bytes a point next to the
+// points' own 24; a library that would leave them more than an eighth of the free memory does without, and the crop
+// tests every point.
 static hipError_t build_clusters(locc_ctx* c, int32_t n_shapes, int64_t n_points, int max_points) {
   const size_t count = cluster_count(n_points, n_shapes);
   const size_t box_bytes = count * 2 * sizeof(float4);
-  hipError_t e = hipMalloc(&c->d_clusters, box_bytes + count * kClusterBytes);
+  size_t room = 0, all = 0;
+  hipError_t e = hipMemGetInfo(&room, &all);
+  if (e != hipSuccess) return e;
+  e = box_bytes + count * kClusterBytes <= room / 8 ? hipMalloc(&c->d_clusters, box_bytes + count * kClusterBytes)
+                                                    : hipErrorOutOfMemory;
   if (e == hipErrorOutOfMemory) {
     (void)hipGetLastError();
     c->d_clusters = nullptr;
@@ -763,7 +768,7 @@ static hipError_t build_clusters(locc_ctx* c, int32_t n_shapes, int64_t n_points
   }
   if (e != hipSuccess) return e;
   c->cluster_boxes = box_bytes;
-  e = launch_clusters(c->d_shapes, n_shapes, max_points, reinterpret_cast<const float4*>(c->d_points),
+  e = launch_clusters(c->d_shapes, n_shapes, max_points, c->d_points, n_points,
                       reinterpret_cast<float4*>(c->d_clusters), c->d_clusters + box_bytes, nullptr);
   return e == hipSuccess ? hipStreamSynchronize(nullptr) : e;
 }
@@ -785,7 +790,7 @@ locc_status locc_upload_shapes(locc_ctx* c, int32_t n_shapes, const int64_t* off
   if (c->live_graphs > 0)
     return fail(LOCC_ERR_BUSY, "shape library: %d captured graph(s) read the current one; destroy them first",
                 c->live_graphs);
-  std::vector<float> soa((size_t)total * 11);  // rows (x, y, z, nx, ny, nz, 0, 0), then x, y and z
+  std::vector<float> points((size_t)total * 6);  // x, y and z, then the normals' rows
   std::vector<ShapeDesc> desc(n_shapes);
   std::vector<float> reach(n_shapes, 0.f);  // each shape's largest coordinate
   for (int s = 0; s < n_shapes; ++s) {
@@ -801,8 +806,7 @@ locc_status locc_upload_shapes(locc_ctx* c, int32_t n_shapes, const int64_t* off
       for (int k = 0; k < 6; ++k) {
         if (!std::isfinite(row[k]))
           return fail(LOCC_ERR_INVALID_ARG, "shape %d point %lld: non-finite value", s, (long long)(r - off[s]));
-        soa[(size_t)r * 8 + k] = row[k];
-        if (k < 3) soa[(size_t)(8 + k) * total + r] = row[k];
+        points[k < 3 ? (size_t)k * total + r : (size_t)(total + r) * 3 + (k - 3)] = row[k];
       }
       for (int k = 0; k < 3; ++k) {
         d.lo[k] = row[k] < d.lo[k] ? row[k] : d.lo[k];
@@ -822,9 +826,9 @@ locc_status locc_upload_shapes(locc_ctx* c, int32_t n_shapes, const int64_t* off
   c->n_shapes = 0;
   c->n_points = 0;
   HIP_TRY(hipMalloc(&c->d_shapes, sizeof(ShapeDesc) * n_shapes));
-  HIP_TRY(hipMalloc(&c->d_points, sizeof(float) * soa.size()));
+  HIP_TRY(hipMalloc(&c->d_points, sizeof(float) * points.size()));
   HIP_TRY(hipMemcpy(c->d_shapes, desc.data(), sizeof(ShapeDesc) * n_shapes, hipMemcpyHostToDevice));
-  HIP_TRY(hipMemcpy(c->d_points, soa.data(), sizeof(float) * soa.size(), hipMemcpyHostToDevice));
+  HIP_TRY(hipMemcpy(c->d_points, points.data(), sizeof(float) * points.size(), hipMemcpyHostToDevice));
   HIP_TRY(build_clusters(c, n_shapes, total, max_points));
   c->n_shapes = n_shapes;
   c->n_points = total;

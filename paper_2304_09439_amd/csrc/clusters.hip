@@ -25,10 +25,8 @@ struct ClusterShared {
   uint16_t axis[kMaxClusters];                        // a segment's widest axis
 };
 
-__device__ __forceinline__ float row_axis(const float4& u, int k) { return k == 0 ? u.x : k == 1 ? u.y : u.z; }
-
 __global__ __launch_bounds__(kClusterThreads) void cluster_kernel(const ShapeDesc* __restrict__ shapes,
-                                                                  const float4* __restrict__ rows,
+                                                                  const float* __restrict__ xyz, int64_t n_points,
                                                                   float4* __restrict__ boxes,
                                                                   char* __restrict__ clusters) {
   __shared__ ClusterShared S;
@@ -39,7 +37,7 @@ __global__ __launch_bounds__(kClusterThreads) void cluster_kernel(const ShapeDes
   const int nc = (n + kClusterPoints - 1) / kClusterPoints;
   int n2 = kClusterPoints;
   while (n2 < n) n2 *= 2;
-  const float4* pts = rows + 2 * (size_t)off;
+  auto axis_of = [&](int p, int k) { return xyz[(size_t)k * n_points + off + p]; };
 
   for (int i = tid; i < n2; i += NT) key[i] = i < n ? (unsigned long long)i : ~0ull;
   for (int c = tid; c < nc; c += NT) {
@@ -56,11 +54,12 @@ __global__ __launch_bounds__(kClusterThreads) void cluster_kernel(const ShapeDes
     __syncthreads();
     for (int i = tid; i < n; i += NT) {
       const int st = S.start[i / kClusterPoints];
-      const float4 u = pts[2 * (int)(key[i] & 0x3fff)];
+      const int p = (int)(key[i] & 0x3fff);
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
-        atomicMin(&S.lo[st][k], float_key(row_axis(u, k)));
-        atomicMax(&S.hi[st][k], float_key(row_axis(u, k)));
+        const unsigned x = float_key(axis_of(p, k));
+        atomicMin(&S.lo[st][k], x);
+        atomicMax(&S.hi[st][k], x);
       }
     }
     __syncthreads();
@@ -78,7 +77,7 @@ __global__ __launch_bounds__(kClusterThreads) void cluster_kernel(const ShapeDes
     for (int i = tid; i < n; i += NT) {
       const int st = S.start[i / kClusterPoints];
       const int p = (int)(key[i] & 0x3fff);
-      key[i] = (unsigned long long)st << 46 | (unsigned long long)float_key(row_axis(pts[2 * p], S.axis[st])) << 14 |
+      key[i] = (unsigned long long)st << 46 | (unsigned long long)float_key(axis_of(p, S.axis[st])) << 14 |
                (unsigned long long)p;
     }
     __syncthreads();
@@ -109,15 +108,18 @@ __global__ __launch_bounds__(kClusterThreads) void cluster_kernel(const ShapeDes
   for (int c = wave_index(); c < nc; c += NT / 64) {
     const int i = c * kClusterPoints + lane;
     const int p = (int)(key[i < n ? i : c * kClusterPoints] & 0x3fff);
-    const float4 u = pts[2 * p];
+    float x[3];
     char* dst = clusters + (first + c) * kClusterBytes;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) reinterpret_cast<float*>(dst)[64 * k + lane] = row_axis(u, k);
+    for (int k = 0; k < 3; ++k) {
+      x[k] = axis_of(p, k);
+      reinterpret_cast<float*>(dst)[64 * k + lane] = x[k];
+    }
     reinterpret_cast<uint16_t*>(dst + 768)[lane] = (uint16_t)(i < n ? p : kNoPoint);
     float lo[3], hi[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      lo[k] = hi[k] = row_axis(u, k);
+      lo[k] = hi[k] = x[k];
 #pragma unroll
       for (int d = 1; d < 64; d <<= 1) {
         lo[k] = fminf(lo[k], __shfl_xor(lo[k], d, 64));
@@ -133,8 +135,8 @@ __global__ __launch_bounds__(kClusterThreads) void cluster_kernel(const ShapeDes
 
 }  // namespace
 
-hipError_t launch_clusters(const ShapeDesc* shapes, int n_shapes, int max_points, const float4* rows, float4* boxes,
-                           char* clusters, hipStream_t s) {
+hipError_t launch_clusters(const ShapeDesc* shapes, int n_shapes, int max_points, const float* xyz, int64_t n_points,
+                           float4* boxes, char* clusters, hipStream_t s) {
   if (n_shapes <= 0 || max_points <= 0 || max_points > kMaxShapePoints) return hipErrorInvalidValue;
   size_t n2 = kClusterPoints;
   while (n2 < (size_t)max_points) n2 *= 2;
@@ -143,7 +145,8 @@ hipError_t launch_clusters(const ShapeDesc* shapes, int n_shapes, int max_points
   const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&cluster_kernel),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;
-  kernel_launch(cluster_kernel, dim3(n_shapes), dim3(kClusterThreads), smem, s, shapes, rows, boxes, clusters);
+  kernel_launch(cluster_kernel, dim3(n_shapes), dim3(kClusterThreads), smem, s, shapes, xyz, n_points, boxes,
+                clusters);
   return hipGetLastError();
 }
 

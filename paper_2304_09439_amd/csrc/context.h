@@ -18,7 +18,7 @@ struct locc_ctx {
   int32_t n_shapes = 0;
   int64_t n_points = 0;
   locc::ShapeDesc* d_shapes = nullptr;
-  float* d_points = nullptr;  // rows (x, y, z, nx, ny, nz, 0, 0), then x, y and z, each n_points floats
+  float* d_points = nullptr;  // x, y and z, each n_points floats, then the normals (nx, ny, nz)
   char* d_clusters = nullptr;  // the points once more as spatial clusters (boxes, then clusters); null: no memory for it
   size_t cluster_boxes = 0;    // bytes of the boxes
   float unit = 1.f;            // a power of two: twice most shapes' largest coordinate, for the halves' scales
@@ -77,8 +77,7 @@ struct locc_ctx {
   locc::DeviceLibrary lib() const {
     const float* b = d_points;
     const size_t n = (size_t)n_points;
-    const float* x = b + 8 * n;
-    return locc::DeviceLibrary{d_shapes, n_shapes, reinterpret_cast<const float4*>(b), x, x + n, x + 2 * n,
+    return locc::DeviceLibrary{d_shapes, n_shapes, b, b + n, b + 2 * n, reinterpret_cast<const float3*>(b + 3 * n),
                                reinterpret_cast<const float4*>(d_clusters), d_clusters ? d_clusters + cluster_boxes : nullptr,
                                1.f / unit};
   }

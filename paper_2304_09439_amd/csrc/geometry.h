@@ -402,12 +402,11 @@ static_assert(sizeof(PairSetup) <= kPairSetupBytes, "pair set-up record");
 // Encoder input row (x, y, z, nx, ny, nz) in a's frame of stored point gi of
 // object `side` (0 = a as stored, 1 = b transformed in float64, then rounded).
 __device__ __forceinline__ void geo_row(const PairGeom& g, const DeviceLibrary& lib, int gi, int side, float* v) {
-  const float4 u = lib.rows[2 * (size_t)gi];
-  const float2 w = *reinterpret_cast<const float2*>(lib.rows + 2 * (size_t)gi + 1);
+  const float3 u = make_float3(lib.px[gi], lib.py[gi], lib.pz[gi]), w = lib.normals[gi];
   if (side) {
     double q[3], n[3];
     geo_xform(g, u.x, u.y, u.z, q);
-    geo_rotate(g, u.w, w.x, w.y, n);
+    geo_rotate(g, w.x, w.y, w.z, n);
     v[0] = (float)q[0];
     v[1] = (float)q[1];
     v[2] = (float)q[2];
@@ -418,9 +417,9 @@ __device__ __forceinline__ void geo_row(const PairGeom& g, const DeviceLibrary& 
     v[0] = u.x;
     v[1] = u.y;
     v[2] = u.z;
-    v[3] = u.w;
-    v[4] = w.x;
-    v[5] = w.y;
+    v[3] = w.x;
+    v[4] = w.y;
+    v[5] = w.z;
   }
 }
 

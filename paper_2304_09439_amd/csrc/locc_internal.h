@@ -72,10 +72,10 @@ constexpr int kRowFloats = 8;
 struct DeviceLibrary {
   const ShapeDesc* shapes;
   int32_t n_shapes;
-  const float4* rows;  // two a point: x, y, z, nx | ny, nz, 0, 0
-  const float* px;     // the coordinates once more, for the scan in stored order
+  const float* px;       // coordinates
   const float* py;
   const float* pz;
+  const float3* normals;
   // spatial clusters (clusters.hip), or null: the box of cluster c in boxes[2 c] (lo) and boxes[2 c + 1] (hi), its
   // points at points + c * kClusterBytes
   const float4* boxes;
@@ -90,9 +90,10 @@ constexpr int kClusterPoints = 64;
 constexpr size_t kClusterBytes = 64 * (3 * 4 + 2);
 constexpr unsigned kNoPoint = 0xffff;
 inline size_t cluster_count(int64_t n_points, int n_shapes) { return (size_t)(n_points / 64) + n_shapes + 1; }
-// The clusters of every shape of a library from its rows (finite); boxes and clusters of cluster_count().
-hipError_t launch_clusters(const ShapeDesc* shapes, int n_shapes, int max_points, const float4* rows, float4* boxes,
-                           char* clusters, hipStream_t s);
+// The clusters of every shape of a library from its coordinates (finite; xyz: all x, all y, all z); boxes and clusters
+// of cluster_count().
+hipError_t launch_clusters(const ShapeDesc* shapes, int n_shapes, int max_points, const float* xyz, int64_t n_points,
+                           float4* boxes, char* clusters, hipStream_t s);
 
 // Pair count of a launch: n_pairs is the capacity (grid sizing); when
 // n_pairs_dev is set the kernels read the actual count from device memory

@@ -59,3 +59,17 @@ def test_clusters_match_oracle(torch, sizes, n_pairs, K):
     without, _ = ctx.detect(objs, pairs, want_counts=False)
     np.testing.assert_array_equal(without.cpu().numpy(), with_counts.cpu().numpy())
     ctx.close()
+
+
+def test_library_memory(torch):
+    """A stored point takes 24 bytes on the device, and its share of the clusters 15 more."""
+    rng = np.random.default_rng(3)
+    pts = rng.uniform(-0.2, 0.2, (256 * 16384, 6)).astype(np.float32)
+    ctx = B.Context(32, WD, 0.01, "bf16")
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    ctx.upload_shapes(np.arange(257, dtype=np.int64) * 16384, pts)
+    used = free - torch.cuda.mem_get_info()[0]
+    ctx.close()
+    print(f"{used / len(pts):.1f} bytes a point", flush=True)
+    assert used < 39.1 * len(pts) + 8 * 2 ** 20   # allocations are rounded up to a few MiB

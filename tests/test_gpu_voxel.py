@@ -257,3 +257,25 @@ def test_upload_and_argument_errors(torch, setup):
     out, _, _ = ctx.detect(objs, torch.zeros((0, 2), dtype=torch.int32, device="cuda"))
     assert out.shape == (0, 2)
     ctx.close()
+
+
+def test_libraries_past_the_encoders_parts(torch, setup):
+    """4,101 shapes are encoded 4,096 at a time: the shapes at the seam and in the second part have the embeddings of a
+    library of their own."""
+    _, w, _ = setup
+    rng = np.random.default_rng(8)
+    counts = rng.integers(1, 4, 4101)
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int64)
+    pts = rng.uniform(-0.2, 0.2, (offsets[-1], 6)).astype(np.float32)
+    ctx = B.VoxelContext()
+    ctx.upload_weights(w)
+    ctx.upload_shapes(offsets, pts)
+    E = ctx.embeddings().cpu().numpy()
+    assert E.shape[0] == 4101 and np.isfinite(E).all()
+    rows = [0, 4094, 4095, 4096, 4097, 4100]
+    for s in rows:
+        ctx.upload_shapes(np.array([0, counts[s]], np.int64), np.ascontiguousarray(pts[offsets[s]:offsets[s + 1]]))
+        np.testing.assert_array_equal(ctx.embeddings().cpu().numpy()[0], E[s])
+    ref = V.library_embeddings(pts[offsets[4095]:offsets[4098]], offsets[4095:4099] - offsets[4095], w)
+    assert max(_normwise(E[4095 + k], ref[k]) for k in range(3)) < TOL
+    ctx.close()

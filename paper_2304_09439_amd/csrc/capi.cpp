@@ -210,7 +210,7 @@ float fp8_scale(float amax) { return amax > 0.f ? amax / 448.f : 1.f; }
 // alone leaves registers for a third workgroup per compute unit, and stays ahead (16,384: 210 combined, 189 apart).
 // At head width 256 the weights are 256 KB and the launch costs more (1,000 pairs: 31.7 combined, 40.2 apart).
 bool head_apart(const locc_ctx* c, int n_pairs) {
-  if (c->cfg.head_h < 512 || n_pairs <= 4 * c->n_cu) return false;
+  if (c->cfg.head_h < kApartHead || n_pairs <= 4 * c->n_cu) return false;
   return c->fp8() || n_pairs <= 48 * c->n_cu;
 }
 

@@ -69,6 +69,8 @@ void bf16_bind(FusedArgs& a, const unsigned char* dev_base, int h1, int h2, int 
 // Workgroups per CU the fused kernel is compiled for.
 constexpr int kFusedWgPerCu = 2;
 constexpr int kFp8EncoderWgPerCu = 3;
+// Head widths whose head may be a kernel of its own (the head alone is compiled for them).
+constexpr int kApartHead = 512;
 constexpr int kFusedTile = 32;
 
 // precropped = false: crop, encoder and head in one kernel; true: encoder and

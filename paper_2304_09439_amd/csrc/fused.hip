@@ -425,9 +425,12 @@ __global__ __launch_bounds__(256, kFusedWgPerCu) void fused_bf16_kernel(FusedArg
 
 template <int H1, int H2, int HH>
 hipError_t run_fused(const FusedArgs& a, int grid, bool pre, hipStream_t s) {
-  if (a.z16)
-    kernel_launch((fused_bf16_kernel<H1, H2, HH, true, false, true>), dim3(grid), dim3(256), 0, s, a);
-  else if (pre)
+  if constexpr (HH >= kApartHead)
+    if (a.z16) {
+      kernel_launch((fused_bf16_kernel<H1, H2, HH, true, false, true>), dim3(grid), dim3(256), 0, s, a);
+      return hipGetLastError();
+    }
+  if (pre)
     kernel_launch((fused_bf16_kernel<H1, H2, HH, true>), dim3(grid), dim3(256), 0, s, a);
   else
     kernel_launch((fused_bf16_kernel<H1, H2, HH, false>), dim3(grid), dim3(256), 0, s, a);
@@ -463,7 +466,7 @@ hipError_t launch_encoder_bf16_argmax(const FusedArgs& a, int h1, int h2, int hh
 
 hipError_t launch_fused_bf16(const FusedArgs& a, int h1, int h2, int hh, int grid, bool pre, hipStream_t s) {
   if (a.n_pairs <= 0) return hipSuccess;
-  if (a.z16 && (!pre || !a.rows_bf16 || !a.meta || h2 > 8 * a.K)) return hipErrorInvalidValue;
+  if (a.z16 && (!pre || !a.rows_bf16 || !a.meta || h2 > 8 * a.K || hh < kApartHead)) return hipErrorInvalidValue;
   if (h1 == 64 && h2 == 128 && hh == 256) return run_fused<64, 128, 256>(a, grid, pre, s);
   if (h1 == 128 && h2 == 256 && hh == 512) return run_fused<128, 256, 512>(a, grid, pre, s);
   return hipErrorInvalidValue;

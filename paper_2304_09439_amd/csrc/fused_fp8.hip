@@ -476,9 +476,12 @@ void fp8_bind(Fp8Args& a, const unsigned char* base, int h1, int h2, int hh, boo
 
 template <int H1, int H2, int HH>
 void launch_fp8(const Fp8Args& a, bool head8, int grid, hipStream_t s) {
-  if (a.z16)
-    kernel_launch((encoder_head_fp8_kernel<H1, H2, HH, false, true>), dim3(grid), dim3(256), 0, s, a);
-  else if (head8)
+  if constexpr (HH >= kApartHead)
+    if (a.z16) {
+      kernel_launch((encoder_head_fp8_kernel<H1, H2, HH, false, true>), dim3(grid), dim3(256), 0, s, a);
+      return;
+    }
+  if (head8)
     kernel_launch((encoder_head_fp8_kernel<H1, H2, HH, true>), dim3(grid), dim3(256), 0, s, a);
   else
     kernel_launch((encoder_head_fp8_kernel<H1, H2, HH, false>), dim3(grid), dim3(256), 0, s, a);
@@ -486,7 +489,7 @@ void launch_fp8(const Fp8Args& a, bool head8, int grid, hipStream_t s) {
 
 hipError_t launch_encoder_head_fp8(const Fp8Args& a, int h1, int h2, int hh, bool head8, int grid, hipStream_t s) {
   if (a.n_pairs <= 0) return hipSuccess;
-  if (a.z16 && (head8 || h2 > 8 * a.K)) return hipErrorInvalidValue;
+  if (a.z16 && (head8 || h2 > 8 * a.K || hh < kApartHead)) return hipErrorInvalidValue;
   if (h1 == 64 && h2 == 128 && hh == 256)
     launch_fp8<64, 128, 256>(a, head8, grid, s);
   else if (h1 == 128 && h2 == 256 && hh == 512)

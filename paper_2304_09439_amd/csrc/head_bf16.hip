@@ -152,7 +152,6 @@ hipError_t pick(const HeadBf16Args& a, int n_cu, hipStream_t s) {
 
 hipError_t launch_head_bf16(const HeadBf16Args& a, int h2, int hh, int n_cu, hipStream_t s) {
   if (a.n_pairs <= 0) return hipSuccess;
-  if (h2 == 128 && hh == 256) return pick<128, 256>(a, n_cu, s);
   if (h2 == 256 && hh == 512) return pick<256, 512>(a, n_cu, s);
   return hipErrorInvalidValue;
 }

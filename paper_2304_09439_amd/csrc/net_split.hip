@@ -556,9 +556,11 @@ __global__ __launch_bounds__(H2) void chain_features_kernel(Fp32Net W, NetArgs A
 // largest input at 2^14 to 2^15, in every layer (a bound of it through the layers
 // would leave the bits to one unit with a large bias or large weights).  The
 // weights are the products' first operand, so that a lane's outputs belong to one
-// pair.  16,384 pairs at width 512: 69 us (0.350 ms as FP32 products, 32 pairs and
-// four waves per workgroup); 80 pairs at width 256: 14 us (40 us).  Bound by the 2 MB
-// of weights each workgroup streams from L2 (RT = 1) or by the matrix cores (RT = 2).
+// pair.  16,384 pairs at width 512: 55 us (0.350 ms as FP32 products, 32 pairs and
+// four waves per workgroup), 1,000: 30 us; 80 pairs at width 256: 12.4 us (40 us).
+// Bound by the 2 MB of weights each workgroup streams from L2 (RT = 1), or by the
+// matrix cores (RT = 2).  Left to itself the compiler moves those loads to their
+// use (42 us at 1,000 pairs).
 // A pair with a value out of range, or with too many inputs of a layer so far below its
 // largest that their halves are short of bits, gets the FP32 chain's result instead.
 
@@ -640,6 +642,7 @@ __device__ __forceinline__ void head_products(const unsigned short* __restrict__
         q0[d][c] = b0[(c * KS + n) * 64];
         q1[d][c] = b1[(c * KS + n) * 64];
       }
+      __builtin_amdgcn_sched_barrier(0);  // the loads stay here, D steps ahead of their use
     }
   }
   if constexpr (APART)
@@ -786,18 +789,22 @@ __global__ __launch_bounds__(512, 2) void head_split_kernel(Fp32Net W, NetArgs A
   for (int layer = 0; layer < 2; ++layer) {
     const float* bias = (layer ? W.c2 : W.c1) + wave * CT * 32 + 4 * g;
     const float* un = (layer ? W.unscale_h2 : W.unscale_h1) + wave * CT * 32 + 4 * g;
-    float4 u4[CT][4], b4[CT][4];  // (loaded ahead of the products, not after them)
+    float4 u4[CT][4], b4[CT][4];
+    auto load_scales = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int c = 0; c < CT; ++c)
+      for (int c = 0; c < CT; ++c)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        u4[c][q] = *reinterpret_cast<const float4*>(un + 32 * c + 8 * q);
-        b4[c][q] = *reinterpret_cast<const float4*>(bias + 32 * c + 8 * q);
-      }
+        for (int q = 0; q < 4; ++q) {
+          u4[c][q] = *reinterpret_cast<const float4*>(un + 32 * c + 8 * q);
+          b4[c][q] = *reinterpret_cast<const float4*>(bias + 32 * c + 8 * q);
+        }
+    };
+    if (RT > 1) load_scales();
     if (layer == 0)
       head_products<Z, AS, CT, RT>(W.h1s, (size_t)HH * Z, S.u.a[0], AP, wave, lane, acc);
     else
       head_products<HH, AS, CT, RT>(W.h2s, (size_t)HH * HH, S.u.a[0], AP, wave, lane, acc);
+    if (RT == 1) load_scales();
     float top[RT];
     unsigned least[RT];  // bits of the smallest output that is not negative
 #pragma unroll

@@ -191,7 +191,7 @@ locc_status locc::check_call(locc_ctx* c, const locc_object* objs, int32_t n_obj
 
 namespace {
 
-// Device views of the FP32 weights and of their bf16 parts.
+// Device views of the FP32 weights and of their halves.
 Fp32Net fp32_net(const locc_ctx* c) {
   Fp32Net w = fp32_view(c->d_wfp32, c->cfg.enc_h1, c->cfg.enc_h2, c->cfg.head_h);
   split_bind(w, c->d_wsplit);
@@ -202,22 +202,24 @@ Fp32Net fp32_net(const locc_ctx* c) {
 float fp8_scale(float amax) { return amax > 0.f ? amax / 448.f : 1.f; }
 
 // Whether the encoder and the bf16 head of n_pairs are two kernels.  A workgroup of the combined kernel streams all of
-// the head's weights (1 MB at width 512) for the pairs it has, up to a tile of 32.  As long as a claim of four fills no
-// more than one workgroup per compute unit, that one stream is cheaper than another launch (780 pairs, K = 96: 45 us
-// combined, 46.5 apart); beyond, workgroups of a few pairs share a compute unit and its L2 bandwidth (1,061 pairs:
-// 56.7 combined, 49.8 apart; 4,000: 88.4, 80.4), until their tiles fill (12,000: 171.1, 168.6; 16,384 at K = 128:
-// 253.8, 254.5; a step of 210,040: 2,250, 2,345, as the combined kernel's heads overlap encoders).  The FP8 encoder
-// alone leaves registers for a third workgroup per compute unit, and stays ahead (16,384: 210 combined, 189 apart).
-// At head width 256 the weights are 256 KB and the launch costs more (1,000 pairs: 31.7 combined, 40.2 apart).
+// the head's weights (1 MB at width 512) for the pairs it has, up to a tile of 32; apart, the encoder's claims are shared
+// out over every workgroup, and the head has one stream a tile.  For a handful of pairs the second launch costs as much as
+// that gains (64 pairs, K = 128: 28.5 us combined, 29.0 apart; 128: 29.1, 29.2); from there on it is cheaper (256: 30.5,
+// 29.5; 400: 34.3, 31.6; 1,000: 44.1, 40.8; 1,061 with K = 96: 48.4, 41.6; 4,000: 97.1, 88.7), but for batches of one
+// pair more than four a compute unit (1,025: 44.6, 45.6), until the tiles fill (12,000: 198.6, 195.5; 16,384: 250.4,
+// 249.4; a step of 210,040: 2,250, 2,345, as the combined kernel's heads overlap encoders).  The FP8 encoder alone
+// leaves registers for a third workgroup per compute unit, and stays ahead (16,384: 199.4 combined, 178.4 apart).  At
+// head width 256 the weights are 256 KB (1,000 pairs: 23.1 combined, 23.2 apart; 2,000: 28.2, 29.9).
 bool head_apart(const locc_ctx* c, int n_pairs) {
-  if (c->cfg.head_h < kApartHead || n_pairs <= 4 * c->n_cu) return false;
+  if (c->cfg.head_h < kApartHead || 2 * n_pairs <= c->n_cu) return false;
   return c->fp8() || n_pairs <= 48 * c->n_cu;
 }
 
 // Pairs a workgroup claims at once: the schedule's claim, or fewer where that would leave some of per_cu workgroups per
 // compute unit without pairs.  The combined kernels take per_cu = 1: a workgroup's latency is that of its pairs, one
-// after the other (8 pairs at K = 128 in claims of one 36.0 us, of four 47.1), but every workgroup streams the head
-// (400 pairs: in claims of two 50.0, of one 57.9, of four 56.0).  The encoder alone has no such stream.
+// after the other (8 pairs at K = 128 in claims of one 27.3 us, of four 39.1), but every workgroup streams the head (FP8,
+// 400 pairs: in claims of one 29.5, of two 28.7, of four 35.2; 1,000: 47.1, 34.8, 36.3).  The encoder alone has no such
+// stream.
 int fused_claim(const locc_ctx* c, int n_pairs, int per_cu) {
   const int slots = c->n_cu * per_cu, share = (n_pairs + slots - 1) / slots;
   return share < c->sched.claim ? share : c->sched.claim;
@@ -312,10 +314,9 @@ locc_status locc::run_path(locc_ctx* c, const locc_object* objs, int32_t n_objs,
         fa.dynamic = c->sched.dynamic;
         const bool h8 = c->fp8_head();
         const bool apart = !h8 && head_apart(c, len);
-        // the third workgroup per compute unit: 1,061 pairs 47.8 us without, 52.3 with it; 4,000: 73.8, 79.6; 6,000:
-        // 97.4, 98.0; 16,384: 202.9, 189.0
-        const int per_cu =
-            apart && len >= 32 * c->n_cu && c->sched.wg_per_cu == kFusedWgPerCu ? kFp8EncoderWgPerCu : c->sched.wg_per_cu;
+        // the third workgroup per compute unit: 600 pairs 34.6 us without, 31.5 with it; 1,061: 40.9, 39.5; 3,000: 68.8,
+        // 57.6; 6,000: 100.0, 96.5; 16,384: 191.8, 178.4 (but 4,000, whose claims come out uneven: 75.5, 77.5)
+        const int per_cu = apart && c->sched.wg_per_cu == kFusedWgPerCu ? kFp8EncoderWgPerCu : c->sched.wg_per_cu;
         fa.claim = fused_claim(c, len, apart ? per_cu : 1);
         const int grid = fused_grid(c, len, fa.claim, per_cu);
         if (apart) {

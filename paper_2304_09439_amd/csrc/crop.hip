@@ -418,10 +418,13 @@ __global__ __launch_bounds__(64 * W, INLINE ? 4 : 6) void crop_kernel(CropArgs A
 hipError_t launch_crop(const CropArgs& args, hipStream_t s, int unroll) {
   CropArgs a = args;
   if (a.n_pairs <= 0) return hipSuccess;
-  // A few blocks of stored points take a lone wave no longer than the cluster boxes and the selection (80 pairs of 1,024
-  // points with counts: 32.2 us in stored order, 33.7 by clusters); with the chip full the points skipped count
-  // (a step of 210,040 pairs of 1,024 points: 1,847 and 1,782 us; of 512 points: 1,831 and 1,850).
-  a.cluster_min = a.n_pairs < 4096 ? 1024 : 512;
+  // A few blocks of stored points take a lone wave no longer than the cluster boxes and the selection, and more of them
+  // where it needs every member and may load ahead (80 pairs with counts: of 1,024 points 26.7 us in stored order, 27.5 by
+  // clusters; of 2,048 28.7 and 30.1; of 3,072 30.7 and 32.1; 2,000 pairs: 46.1 and 47.2, 49.6 and 53.0, 54.9 and 55.8; of
+  // 4,096 59.5 and 58.5) than where it stops at K (80 pairs: 26.6 and 26.9, 28.3 and 28.5, 30.5 and 27.1).  With the chip
+  // full the points skipped count (a step of 210,040 pairs of 1,024 points: 1,847 and 1,782 us; of 512 points: 1,831
+  // and 1,850).
+  a.cluster_min = a.n_pairs >= 4096 ? 512 : (a.counts_out && a.n_pairs <= kInlinePairs ? 3072 : 1024);
   if (!a.setup || (unroll != 2 && unroll != 4 && unroll != 8)) return hipErrorInvalidValue;
   constexpr int W = kCropWaves;
   const dim3 grid((2 * a.n_pairs + W - 1) / W), block(64 * W);

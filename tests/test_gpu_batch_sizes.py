@@ -86,3 +86,9 @@ def test_fp32_batches_equal_their_parts(torch, net, K, sizes):
     np.testing.assert_array_equal(got[:-33], whole[0][:-33])
     assert (got[-33:] == 7.0).all()
     ctx.close()
+
+
+@pytest.mark.parametrize("precision", ["bf16", "fp8_encoder"])
+def test_small_batches_equal_their_parts(torch, precision):
+    """The head as a kernel of its own from one pair in two compute units on; the FP8 encoder's third workgroup."""
+    test_batches_equal_their_parts(torch, precision, "scale", 64, (127, 128, 129, 256, 257, 513, 769))

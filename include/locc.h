@@ -67,7 +67,15 @@ typedef enum { LOCC_FP32 = 0, LOCC_BF16 = 1, LOCC_FP8 = 2, LOCC_FP8_ENCODER = 3 
  *   precision  arithmetic of the encoder and head (locc_precision);
  *              the crop geometry is float64 in every precision.
  *              LOCC_FP32 runs the per-step path (crop, encoder, head
- *              kernels); LOCC_BF16 runs one fused persistent kernel or
+ *              kernels), layer 2 and the head as three 16-bit products for
+ *              each float32 one: an operand is the sum of two halves (exact
+ *              to 2^-23), scaled by powers of two per object, unit, row and
+ *              pair, the product of the two low halves (at most 2^-22) left
+ *              out, sums in float32.  The contacts are as near the float64
+ *              ones as those of float32 multiply-adds; where operands would
+ *              be short of bits, or out of a half's range, float32
+ *              multiply-adds take their place (about three times the time).
+ *              Results do not depend on the batch; LOCC_BF16 runs one fused persistent kernel or
  *              a crop kernel plus a persistent network kernel (see
  *              locc_schedule); LOCC_FP8 runs the crop kernel plus a
  *              persistent network kernel whose encoder layer 2 and head
@@ -225,9 +233,10 @@ LOCC_API locc_status locc_debug_forward(locc_ctx* ctx, const locc_object* d_objs
  *   split      0: one persistent kernel does crop, encoder and head;
  *              1: a crop kernel writes bf16 encoder rows to a library
  *              workspace, then the persistent kernel runs encoder and head
- *              (batches between a few and some dozens of pairs per compute
- *              unit, and FP8: the encoder, and a kernel of its own the head;
- *              a large batch's FP8 encoder at wg_per_cu = 2 has three)
+ *              (head width 512, from half a pair to some dozens of pairs per
+ *              compute unit, and more in FP8_ENCODER: the encoder, and a
+ *              kernel of its own the head; that FP8 encoder has three
+ *              workgroups per CU at wg_per_cu = 2)
  *   crop_unroll  also used by the FP32 path's crop kernel
  *   chunks     split schedule and FP8 (1, 2, 4 or 8): the step is cut into
  *              that many runs of pairs; the crop of run k + 1 runs on a
@@ -332,7 +341,9 @@ LOCC_API locc_status locc_detect_noalloc(locc_ctx* ctx, const locc_object* d_obj
  * the gradient of the network's output with respect to the poses).  FP32
  * and BF16 contexts.  Runs the crop and the FP32 encoder (recording per object
  * and channel the row of the largest raw second-layer sum, the first on
- * ties), the head backward and the encoder backward at those rows of the
+ * ties, as float32 multiply-adds find it: rows within the products' usual
+ * error of each other are decided by them), the features of those rows as
+ * float32 multiply-adds, the head backward and the encoder backward at those rows of the
  * second object (the first object's rows are its own stored points and do
  * not depend on the poses), then the chain rule through R_ab = R_a^T R_b,
  * t_ab = R_a^T (p_b - p_a) and the rotation polynomial of the quaternion as
@@ -538,8 +549,8 @@ LOCC_API locc_status locc_serve_stop(locc_server* srv);
  * per-dispatch durations a kernel-trace profiler reports, plus event
  * overhead).  locc_profile(ctx, 1) clears the totals and starts recording,
  * locc_profile(ctx, 0) stops.  Kernel names: "crop", "encoder_fp32",
- * "head_fp32" (FP32 per-step path), "chain_features" (its gradients), "fused_bf16" (BF16, one launch),
- * "crop" and "encoder_head_bf16" (BF16 split schedule; "encoder_head_bf16_lds"
+ * "head_fp32" (FP32 per-step path), "chain_features" (its gradients),
+ * "fused_bf16" (BF16, one launch), "crop" and "encoder_head_bf16" (BF16 split schedule; "encoder_head_bf16_lds"
  * for its one-workgroup-per-CU kernel), "crop" and
  * "encoder_head_fp8" (LOCC_FP8) or "encoder_fp8_head_bf16"
  * (LOCC_FP8_ENCODER). */

@@ -160,7 +160,7 @@ void broad_phase_carve(void* base, int n_objs, int n_envs, BroadArgs& a);
 // writes count), the ordered write of the pairs.
 hipError_t launch_broad_phase(const BroadArgs& a, hipStream_t s);
 
-// FP32 network weights packed in MFMA fragment order (see net_fp32.hip).
+// FP32 network weights packed in MFMA fragment order, for net_split.hip.
 struct Fp32Net {
   int h1, h2, hh;
   const float* w1pack;  // [h1/32][4][64]
@@ -185,7 +185,7 @@ struct Fp32Net {
   const float* unscale_h1;    // [hh]
   const float* unscale_h2;    // [hh]
   const float* unscale_h3;    // [8]
-  const int32_t* split_bad;   // not 0: a weight is not finite or too large, the halves are not usable
+  const int32_t* split_bad;   // not 0: a weight is not finite, or a row has too many short of bits: no halves
 };
 
 struct NetArgs {

@@ -422,11 +422,13 @@ __global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, Net
 // layer 2 over layer 1's permuted features): from the row the split encoder
 // found for each channel, that row's chain gives the feature; a channel whose
 // row is in doubt takes the largest chain over all rows, the first on ties, 64
-// rows at a time by its wave.  A thread per channel and four objects, so that a
-// weight is read once for four; W1 is read by scalar loads.  Bound by its vector
-// instructions: 9 per channel, hidden unit and object, 0.30 ms for 16,384 pairs
-// at 128 / 256, and with the split encoder's 0.70 ms about half of the 1.94 ms
-// of the whole encoder on the FP32 matrix cores.
+// rows at a time by its wave.  (A row that is not in doubt is taken as found, which
+// is the chain's own choice unless that chain rounds worse than the margin of doubt
+// allows: it did not on the networks and scenes tried.)  A thread per channel and
+// four objects, so that a weight is read once for four; W1 is read by scalar loads.
+// Bound by its vector instructions: 9 per channel, hidden unit and object, 0.27 ms
+// for 16,384 pairs at 128 / 256, and with the split encoder's 0.70 ms about half of
+// the 1.94 ms of the whole encoder on the FP32 matrix cores.
 
 // Four objects a workgroup read W2 once for four; up to 2,048 pairs the chip has room for every object alone, and the
 // chain of one is the shorter one (pose gradients of 40 pairs at 64 / 128 89.0 -> 83.2 us, 150 pairs at 128 / 256
@@ -926,10 +928,12 @@ __global__ __launch_bounds__(512, 2) void head_split_kernel(Fp32Net W, NetArgs A
 // operands of the gradient kernels, and layer 1's operand times its factor.  The others, eight inputs of a row per
 // thread: the halves of W2, H1, H2 and H3 (8 rows, zero to 32) in the B operand order of 32x32x16 products (W2's
 // reduction index in layer 1's output order), each row times the power of two that puts its largest weight at 2^14 to
-// 2^15, found here by the row's threads, and W2's columns times what undoes the powers of two of layer 1's units, so that
-// the halves follow the weights through training.  A weight 2^-16 of its row's largest or less keeps fewer bits than a float.  A few in a row do not matter beside the others; where they are
-// more than a 64th of the row's and one (as when the largest weight is that of a unit which is always 0), or a weight is
-// not finite, the flag word becomes 1 and every pair takes the FP32 chains.  One launch: training runs it every step.
+// 2^15, found here by the row's threads, and W2's columns times what undoes the powers of two of layer 1's units, so
+// that the halves follow the weights through training.  A weight 2^-16 of its row's largest or less keeps fewer bits
+// than a float.  A few in a row do not matter beside the others; where they are more than a 64th of the row's and one (as
+// when the largest weight is that of a unit which is always 0), or a weight is not finite, the flag word becomes 1 and
+// every pair takes the FP32 chains.  One launch: training runs it every step.
+
 // A hidden unit's largest output for normals in [-1, 1] and coordinates in the library's unit in [-1, 1] is its weights'
 // and bias' absolute sum (the coordinates' times the unit); unit_power is the power of two that takes it to (2^14, 2^15]
 // (of a sum of at least 2^-100; 0 for a unit without weights; NaN past 2^100 and for weights that are not finite).

@@ -14,7 +14,7 @@ unsigned short host_bf16(float f);
 unsigned char host_e4m3(float x);
 
 // ---------------------------------------------------------------- FP32
-// Float offsets of the packed FP32 weights (net_fp32.hip reads them).
+// Float offsets of the packed FP32 weights (the FP32 chains of net_split.hip read them).
 struct Fp32Layout {
   size_t w1, w2, b2, h1, c1, h2, c2, h3, c3, total;
 };

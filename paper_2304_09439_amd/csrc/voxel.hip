@@ -915,10 +915,11 @@ __device__ __forceinline__ void mlp_fp32(const PairArgs& A, MlpShared& S, int q0
 // Predictor MLPs: 32 pairs per workgroup; the 64 object rows come from the workspace.  The layers are products of
 // halves as in point_mlp_kernel, weights x rows, so that a lane has one row: every row has its own scale at every
 // layer, from its largest value (a bound of it through six layers cost the logits half a digit).  A wave has one 32 x 32
-// tile of a layer (of the pair layers' 32 rows only four waves), the maximum over a pair's objects is taken between neighbouring lanes, and the weights of a
-// layer load while the one before it ends.  A pair with a value past kHalvesMost, NaN inputs, or too many inputs of a
-// layer short of bits, is computed as FP32 products after the others, and every pair where the weights are (A.fp32).  24.5 us at 16,384 pairs, 13.8 at 8 (as FP32 products on 16x16x4 tiles,
-// bound by them, 43 and 21.9); at most 128 registers keep two workgroups per compute unit (134: 32 us).
+// tile of a layer (of the pair layers' 32 rows only four waves), the maximum over a pair's objects is taken between
+// neighbouring lanes, and the weights of a layer load while the one before it ends.  A pair with a value past
+// kHalvesMost, NaN inputs, or too many inputs of a layer short of bits, is computed as FP32 products after the others,
+// and every pair where the weights are short of them (A.fp32).  24.7 us at 16,384 pairs, 13.8 at 8 (as FP32 products on
+// 16x16x4 tiles, bound by them, 43 and 21.9); at most 128 registers keep two workgroups per compute unit (134: 32 us).
 struct MlpSplitShared {
   unsigned short h[2][2 * kTP][kHP + 8];  // object rows: [part][row][channel]
   unsigned short p[2][kTP][kHP + 8];      // pairs
@@ -1003,7 +1004,7 @@ __global__ __launch_bounds__(kThreads, 4) void mlp_kernel(PairArgs A) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) some_short |= (v[e] != 0.f) & (fabsf(v[e]) < below);
     if (__ballot(some_short) != 0) {
-      // (the embedding, the offset and the rotation's entries are of different sizes by nature: half of them may be short)
+      // (the embedding, the offset and the rotation's entries are of different sizes by nature: half of them may be)
       int count = 0;
 #pragma unroll
       for (int e = 0; e < 4; ++e)
@@ -1035,6 +1036,9 @@ __global__ __launch_bounds__(kThreads, 4) void mlp_kernel(PairArgs A) {
         v[q][e] = relu(v[q][e]);
       }
     }
+  };
+  auto put_tile = [&](auto& h, int r, int q, float scale) {  // v[q] as halves of row r
+    put_halves(&h[0][r][32 * ct + 8 * q + 4 * g], &h[1][r][32 * ct + 8 * q + 4 * g], v[q], scale);
   };
   // the largest of v in row r, over the column tiles' waves (a barrier, before which every wave has read the inputs)
   auto row_top = [&](int r, bool mine) -> float {
@@ -1077,7 +1081,7 @@ __global__ __launch_bounds__(kThreads, 4) void mlp_kernel(PairArgs A) {
     check(top, row >> 1);
     scale = halves_scale(top);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) put_halves(&S.h[0][row][32 * ct + 8 * q + 4 * g], &S.h[1][row][32 * ct + 8 * q + 4 * g], v[q], scale);
+    for (int q = 0; q < 4; ++q) put_tile(S.h, row, q, scale);
     __syncthreads();
     acc = tile_products<kHP / 16>(w1, S.h, row, g);
     load_tile<kHP / 16>(layer ? A.w.Bs[0] : A.w.As[2], ct, lane, w1);
@@ -1097,7 +1101,7 @@ __global__ __launch_bounds__(kThreads, 4) void mlp_kernel(PairArgs A) {
     if (!(lane & 1)) {
       if (ct == 0 && g == 0) S.pscale[row >> 1] = halves_scale(top);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) put_halves(&S.p[0][row >> 1][32 * ct + 8 * q + 4 * g], &S.p[1][row >> 1][32 * ct + 8 * q + 4 * g], v[q], halves_scale(top));
+      for (int q = 0; q < 4; ++q) put_tile(S.p, row >> 1, q, halves_scale(top));
     }
   }
   __syncthreads();
@@ -1115,7 +1119,7 @@ __global__ __launch_bounds__(kThreads, 4) void mlp_kernel(PairArgs A) {
       check(top, l32);
       scale = halves_scale(top);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) put_halves(&S.p[0][l32][32 * ct + 8 * q + 4 * g], &S.p[1][l32][32 * ct + 8 * q + 4 * g], v[q], scale);
+      for (int q = 0; q < 4; ++q) put_tile(S.p, l32, q, scale);
     }
     __syncthreads();
   }
@@ -1230,7 +1234,8 @@ void pack_transposed(const float* flat, float* dst) {
   }
 }
 
-// Whether the halves of a matrix have the bits its products need, row by row (halves_kernel scales a row to [2^14, 2^15)).
+// Whether the halves of a matrix have the bits its products need, row by row (halves_kernel scales a row to 2^14 to
+// 2^15).
 static bool matrix_halves(const float* W, int out, int in) {
   for (int o = 0; o < out; ++o, W += in) {
     float mx = 0.f;
@@ -1383,8 +1388,8 @@ hipError_t launch_encoder(const PackedNet& w, const Shape* shapes, int n_shapes,
                           bool fp32, hipStream_t s) {
   if (n_shapes <= 0 || n_shapes > kEncodeShapes || max_points <= 0) return hipErrorInvalidValue;
   kernel_launch(cell_sort_kernel, dim3(n_shapes), dim3(1024), 0, s, shapes, xyz, n_points, b.order, b.cell);
-  kernel_launch(point_mlp_kernel, dim3((max_points + kPts - 1) / kPts, n_shapes), dim3(256), 0, s, w, (int)fp32, shapes, xyz,
-                n_points, b.order, b.cell, b.grid);
+  kernel_launch(point_mlp_kernel, dim3((max_points + kPts - 1) / kPts, n_shapes), dim3(256), 0, s, w, (int)fp32, shapes,
+                xyz, n_points, b.order, b.cell, b.grid);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = conv(b.grid, kH, nullptr, 0, w.C[0], w.k[0], b.c[0], kM, 4, 0, 0, n_shapes, s);
   for (int i = 1; i < 4 && e == hipSuccess; ++i)

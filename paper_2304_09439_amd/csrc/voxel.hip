@@ -1235,17 +1235,24 @@ void pack_transposed(const float* flat, float* dst) {
 }
 
 // Whether the halves of a matrix have the bits its products need, row by row (halves_kernel scales a row to 2^14 to
-// 2^15).
+// 2^15).  On the bits of the magnitudes, which order like them.
 static bool matrix_halves(const float* W, int out, int in) {
+  constexpr int kMaxIn = 256;
+  uint32_t row[kMaxIn];
   for (int o = 0; o < out; ++o, W += in) {
-    float mx = 0.f;
-    for (int c = 0; c < in; ++c) mx = std::fmax(mx, std::fabs(W[c]));
-    if (!(mx < 0x1p90f)) return false;
-    const float below = std::ldexp(kHalvesLeast, std::ilogb(std::fmax(mx, 0x1p-100f)) - 14);
+    std::memcpy(row, W, sizeof(float) * in);
+    uint32_t mx = 0;
+    for (int c = 0; c < in; ++c) {
+      row[c] &= 0x7fffffffu;
+      mx = row[c] > mx ? row[c] : mx;
+    }
+    if (mx >= 217u << 23) return false;  // 2^90
+    // kHalvesLeast lies 2^16 below the row's largest power of two; nothing but 0 does below 2^-100 2^-16
+    const uint32_t e = mx >> 23, below = ((e > 27u ? e : 27u) - 16u) << 23;
     int some = 0, lost = 0;
     for (int c = 0; c < in; ++c) {
-      some += W[c] != 0.f;
-      lost += W[c] != 0.f && std::fabs(W[c]) < below;
+      some += row[c] != 0u;
+      lost += (row[c] != 0u) & (row[c] < below);
     }
     if (halves_short(some << 16 | lost, kShortWeights)) return false;
   }

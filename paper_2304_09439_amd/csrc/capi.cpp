@@ -550,6 +550,7 @@ void locc_destroy(locc_ctx* c) {
   (void)hipFree(c->d_shapes);
   (void)hipFree(c->d_points);
   (void)hipFree(c->d_clusters);
+  (void)hipFree(c->d_rows);
   (void)hipFree(c->d_wfp32);
   (void)hipFree(c->d_wbf16);
   (void)hipFree(c->d_wfp8);
@@ -751,26 +752,34 @@ static float library_unit(float x) {
   return std::ldexp(1.f, e + 1 < -100 ? -100 : (e + 1 > 100 ? 100 : e + 1));
 }
 
-// The library's spatial clusters, which let the crop skip most of a shape.  They take 15 bytes a point next to the
-// points' own 24; a library that would leave them more than an eighth of the free memory does without, and the crop
-// tests every point.
-static hipError_t build_clusters(locc_ctx* c, int32_t n_shapes, int64_t n_points, int max_points) {
-  const size_t count = cluster_count(n_points, n_shapes);
-  const size_t box_bytes = count * 2 * sizeof(float4);
+// Device memory that a library can do without: null where it would take more than room / share, or where there is none.
+static hipError_t optional_alloc(void** p, size_t bytes, size_t room, size_t share) {
+  *p = nullptr;
+  if (bytes > room / share) return hipSuccess;
+  const hipError_t e = hipMalloc(p, bytes);
+  if (e != hipErrorOutOfMemory) return e;
+  (void)hipGetLastError();
+  *p = nullptr;
+  return hipSuccess;
+}
+
+// What the library holds next to its points' 24 bytes each: the spatial clusters, which let the crop skip most of a shape
+// (15 bytes a point; without them it tests every point), and the points in rows, whose gathers take one line and not four
+// (32 bytes; the crop of 16,384 pairs takes 2 us of 43 more without them).  A library for which they would be more than an
+// eighth, or a 128th, of the free memory does without.
+static hipError_t build_extras(locc_ctx* c, int32_t n_shapes, int64_t n_points, int max_points) {
+  const size_t count = cluster_count(n_points, n_shapes), box_bytes = count * 2 * sizeof(float4);
   size_t room = 0, all = 0;
   hipError_t e = hipMemGetInfo(&room, &all);
-  if (e != hipSuccess) return e;
-  e = box_bytes + count * kClusterBytes <= room / 8 ? hipMalloc(&c->d_clusters, box_bytes + count * kClusterBytes)
-                                                    : hipErrorOutOfMemory;
-  if (e == hipErrorOutOfMemory) {
-    (void)hipGetLastError();
-    c->d_clusters = nullptr;
-    return hipSuccess;
+  if (e == hipSuccess) e = optional_alloc(reinterpret_cast<void**>(&c->d_clusters), box_bytes + count * kClusterBytes, room, 8);
+  if (e == hipSuccess && c->d_clusters) {
+    c->cluster_boxes = box_bytes;
+    e = launch_clusters(c->d_shapes, n_shapes, max_points, c->d_points, n_points,
+                        reinterpret_cast<float4*>(c->d_clusters), c->d_clusters + box_bytes, nullptr);
   }
-  if (e != hipSuccess) return e;
-  c->cluster_boxes = box_bytes;
-  e = launch_clusters(c->d_shapes, n_shapes, max_points, c->d_points, n_points,
-                      reinterpret_cast<float4*>(c->d_clusters), c->d_clusters + box_bytes, nullptr);
+  if (e == hipSuccess)
+    e = optional_alloc(reinterpret_cast<void**>(&c->d_rows), (size_t)n_points * 2 * sizeof(float4), room, 128);
+  if (e == hipSuccess && c->d_rows) e = launch_rows(c->d_points, n_points, c->d_rows, nullptr);
   return e == hipSuccess ? hipStreamSynchronize(nullptr) : e;
 }
 
@@ -821,16 +830,18 @@ locc_status locc_upload_shapes(locc_ctx* c, int32_t n_shapes, const int64_t* off
   (void)hipFree(c->d_shapes);
   (void)hipFree(c->d_points);
   (void)hipFree(c->d_clusters);
+  (void)hipFree(c->d_rows);
   c->d_shapes = nullptr;
   c->d_points = nullptr;
   c->d_clusters = nullptr;
+  c->d_rows = nullptr;
   c->n_shapes = 0;
   c->n_points = 0;
   HIP_TRY(hipMalloc(&c->d_shapes, sizeof(ShapeDesc) * n_shapes));
   HIP_TRY(hipMalloc(&c->d_points, sizeof(float) * points.size()));
   HIP_TRY(hipMemcpy(c->d_shapes, desc.data(), sizeof(ShapeDesc) * n_shapes, hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(c->d_points, points.data(), sizeof(float) * points.size(), hipMemcpyHostToDevice));
-  HIP_TRY(build_clusters(c, n_shapes, total, max_points));
+  HIP_TRY(build_extras(c, n_shapes, total, max_points));
   c->n_shapes = n_shapes;
   c->n_points = total;
   std::nth_element(reach.begin(), reach.begin() + n_shapes / 2, reach.end());

@@ -133,7 +133,22 @@ __global__ __launch_bounds__(kClusterThreads) void cluster_kernel(const ShapeDes
   }
 }
 
+__global__ __launch_bounds__(256) void rows_kernel(const float* __restrict__ points, int64_t n_points,
+                                                   float4* __restrict__ rows) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n_points) return;
+  const float* n = points + 3 * n_points + 3 * i;
+  rows[2 * i] = make_float4(points[i], points[n_points + i], points[2 * n_points + i], n[0]);
+  rows[2 * i + 1] = make_float4(n[1], n[2], 0.f, 0.f);
+}
+
 }  // namespace
+
+hipError_t launch_rows(const float* points, int64_t n_points, float4* rows, hipStream_t s) {
+  if (n_points <= 0) return hipErrorInvalidValue;
+  kernel_launch(rows_kernel, dim3((unsigned)((n_points + 255) / 256)), dim3(256), 0, s, points, n_points, rows);
+  return hipGetLastError();
+}
 
 hipError_t launch_clusters(const ShapeDesc* shapes, int n_shapes, int max_points, const float* xyz, int64_t n_points,
                            float4* boxes, char* clusters, hipStream_t s) {

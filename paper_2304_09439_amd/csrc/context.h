@@ -19,6 +19,7 @@ struct locc_ctx {
   int64_t n_points = 0;
   locc::ShapeDesc* d_shapes = nullptr;
   float* d_points = nullptr;  // x, y and z, each n_points floats, then the normals (nx, ny, nz)
+  float4* d_rows = nullptr;   // the points once more in rows of 32 bytes; null: no memory for it
   char* d_clusters = nullptr;  // the points once more as spatial clusters (boxes, then clusters); null: no memory for it
   size_t cluster_boxes = 0;    // bytes of the boxes
   float unit = 1.f;            // a power of two: twice most shapes' largest coordinate, for the halves' scales
@@ -78,8 +79,8 @@ struct locc_ctx {
     const float* b = d_points;
     const size_t n = (size_t)n_points;
     return locc::DeviceLibrary{d_shapes, n_shapes, b, b + n, b + 2 * n, reinterpret_cast<const float3*>(b + 3 * n),
-                               reinterpret_cast<const float4*>(d_clusters), d_clusters ? d_clusters + cluster_boxes : nullptr,
-                               1.f / unit};
+                               d_rows, reinterpret_cast<const float4*>(d_clusters),
+                               d_clusters ? d_clusters + cluster_boxes : nullptr, 1.f / unit};
   }
 };
 

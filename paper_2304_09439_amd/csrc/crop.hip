@@ -7,6 +7,8 @@
 // stored order) and the ordered first-K selection, and
 // writes counts, the optional index sets, the per-pair records and the
 // encoder input rows (float32 for the FP32 path, bf16 for BF16 / FP8).
+#include <type_traits>
+
 #include "geometry.h"
 
 namespace locc {
@@ -264,7 +266,8 @@ __device__ __forceinline__ bool crop_by_clusters(int alive, int n, int K, bool f
 // 2,048 points each, now mostly none (crop 616 us before, 330 with them).
 //
 // INLINE: the pair's set-up is done here, by both of its waves, instead of by a kernel of its own.
-template <int U, int W, bool INLINE>
+// ROWS: the selected points are gathered from the library's rows.
+template <int U, int W, bool INLINE, bool ROWS>
 __global__ __launch_bounds__(64 * W, INLINE ? 4 : 6) void crop_kernel(CropArgs A) {
   __shared__ ObjectShared SW[W];
   __shared__ PairSetup RW[INLINE ? W : 1];
@@ -368,7 +371,7 @@ __global__ __launch_bounds__(64 * W, INLINE ? 4 : 6) void crop_kernel(CropArgs A
       float4 lo4 = make_float4(0.f, 0.f, 0.f, 0.f), hi4 = lo4;
       if (r < m) {
         float v[6];
-        geo_row(g, A.lib, off + S.sel[r], side, v);
+        geo_row<ROWS>(g, A.lib, off + S.sel[r], side, v);
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
           top = __builtin_elementwise_maximum(top, fabsf(v[k]));
@@ -398,7 +401,7 @@ __global__ __launch_bounds__(64 * W, INLINE ? 4 : 6) void crop_kernel(CropArgs A
       unsigned short row[8] = {0, 0, 0, 0, 0, 0, 0, 0};
       if (r < m) {
         float v[6];
-        geo_row(g, A.lib, off + S.sel[r], side, v);
+        geo_row<ROWS>(g, A.lib, off + S.sel[r], side, v);
 #pragma unroll
         for (int k = 0; k < 6; ++k) row[k] = __builtin_bit_cast(unsigned short, (__bf16)v[k]);
         row[6] = 0x3f80;  // 1.0
@@ -430,20 +433,25 @@ hipError_t launch_crop(const CropArgs& args, hipStream_t s, int unroll) {
   const dim3 grid((2 * a.n_pairs + W - 1) / W), block(64 * W);
   // A small batch saves the set-up kernel's launch (8 pairs: 32.4 us with it, 30.1 without; 1,500: 63.7, 61.5; 2,000: 59.8,
   // 59.0); in a larger one the float64 set-up of every wave costs more (3,000: 73.4, 75.5; 16,384: 250, 262).
-  if (a.n_pairs <= kInlinePairs) {
-    switch (unroll) {
-      case 2: kernel_launch((crop_kernel<2, W, true>), grid, block, 0, s, a); break;
-      case 4: kernel_launch((crop_kernel<4, W, true>), grid, block, 0, s, a); break;
-      default: kernel_launch((crop_kernel<8, W, true>), grid, block, 0, s, a); break;
-    }
-    return hipGetLastError();
-  }
-  kernel_launch(pair_setup_kernel, dim3((a.n_pairs + kThreads - 1) / kThreads), dim3(kThreads), 0, s, a);
-  switch (unroll) {
-    case 2: kernel_launch((crop_kernel<2, W, false>), grid, block, 0, s, a); break;
-    case 4: kernel_launch((crop_kernel<4, W, false>), grid, block, 0, s, a); break;
-    default: kernel_launch((crop_kernel<8, W, false>), grid, block, 0, s, a); break;
-  }
+  const bool inline_setup = a.n_pairs <= kInlinePairs;
+  if (!inline_setup)
+    kernel_launch(pair_setup_kernel, dim3((a.n_pairs + kThreads - 1) / kThreads), dim3(kThreads), 0, s, a);
+  // A small batch's gathers find the coordinates where the scan has just read them (8 pairs 29.6 us, 31.2 with the rows).
+  auto run = [&](auto u) {
+    constexpr int U = decltype(u)::value;
+    if (inline_setup)
+      kernel_launch((crop_kernel<U, W, true, false>), grid, block, 0, s, a);
+    else if (a.lib.rows)
+      kernel_launch((crop_kernel<U, W, false, true>), grid, block, 0, s, a);
+    else
+      kernel_launch((crop_kernel<U, W, false, false>), grid, block, 0, s, a);
+  };
+  if (unroll == 2)
+    run(std::integral_constant<int, 2>{});
+  else if (unroll == 4)
+    run(std::integral_constant<int, 4>{});
+  else
+    run(std::integral_constant<int, 8>{});
   return hipGetLastError();
 }
 

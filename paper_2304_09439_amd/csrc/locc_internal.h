@@ -76,6 +76,7 @@ struct DeviceLibrary {
   const float* py;
   const float* pz;
   const float3* normals;
+  const float4* rows;      // or null: the same once more, two a point: x, y, z, nx | ny, nz, 0, 0, for gathers
   // spatial clusters (clusters.hip), or null: the box of cluster c in boxes[2 c] (lo) and boxes[2 c + 1] (hi), its
   // points at points + c * kClusterBytes
   const float4* boxes;
@@ -94,6 +95,9 @@ inline size_t cluster_count(int64_t n_points, int n_shapes) { return (size_t)(n_
 // of cluster_count().
 hipError_t launch_clusters(const ShapeDesc* shapes, int n_shapes, int max_points, const float* xyz, int64_t n_points,
                            float4* boxes, char* clusters, hipStream_t s);
+
+// DeviceLibrary::rows from the coordinates and normals.
+hipError_t launch_rows(const float* points, int64_t n_points, float4* rows, hipStream_t s);
 
 // Pair count of a launch: n_pairs is the capacity (grid sizing); when
 // n_pairs_dev is set the kernels read the actual count from device memory

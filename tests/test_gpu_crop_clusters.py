@@ -62,14 +62,35 @@ def test_clusters_match_oracle(torch, sizes, n_pairs, K):
 
 
 def test_library_memory(torch):
-    """A stored point takes 24 bytes on the device, and its share of the clusters 15 more."""
+    """A stored point takes 24 bytes on the device, its share of the clusters 15 more, and a row of 32 for gathers where
+    all rows are less than a 128th of the free memory: past that the contacts are the same bits without them."""
     rng = np.random.default_rng(3)
-    pts = rng.uniform(-0.2, 0.2, (256 * 16384, 6)).astype(np.float32)
-    ctx = B.Context(32, WD, 0.01, "bf16")
-    torch.cuda.synchronize()
-    free = torch.cuda.mem_get_info()[0]
-    ctx.upload_shapes(np.arange(257, dtype=np.int64) * 16384, pts)
-    used = free - torch.cuda.mem_get_info()[0]
+    n, half = 16384, rng.uniform(0.05, 0.3, (12, 1, 3))
+    pts = np.concatenate([rng.uniform(-half, half, (12, n, 3)), rng.normal(size=(12, n, 3))], 2).astype(np.float32)
+    lib = I.ShapeLibrary(pts.reshape(-1, 6), np.arange(13, dtype=np.int64) * n, np.full(12, np.nan, np.float32))
+    sa, sb = rng.integers(0, 12, 2100), rng.integers(0, 12, 2100)   # past the batches that gather from the coordinates
+    scene = I._pack_pair_scene(lib, *I.overlapping_pair_poses(rng, lib, sa, sb), sa.astype(np.int32),
+                               sb.astype(np.int32), I._interleave_pairs(rng, 2100))
+    weights = I.flatten_weights(I.gaussian_weights(I.SMALL_WIDTHS, seed=6, bias_std=0.1))
+    objs, pairs = B.scene_tensors(scene)
+    ctx = B.Context(64, WD, 0.01, "fp32")
+    ctx.upload_weights(weights)
+
+    def upload(copies):
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        ctx.upload_shapes(np.arange(12 * copies + 1, dtype=np.int64) * n, np.tile(lib.pts, (copies, 1)))
+        per_point = (free - torch.cuda.mem_get_info()[0]) / (12 * copies * n)
+        got = [t.cpu().numpy() for t in (*ctx.detect(objs, pairs), ctx.pose_gradients(objs, pairs)[0])]
+        print(f"{12 * copies * n} points: {per_point:.1f} bytes a point", flush=True)
+        return per_point, got
+
+    ctx.reserve(2100)
+    _, small = upload(1)
+    ctx.upload_shapes(np.array([0, 1], np.int64), lib.pts[:1])   # gives the memory back
+    copies = int(torch.cuda.mem_get_info()[0] / 128 / 32 / (12 * n) * 1.03)
+    per_point, large = upload(copies)
+    assert per_point < 39.2
     ctx.close()
-    print(f"{used / len(pts):.1f} bytes a point", flush=True)
-    assert used < 39.1 * len(pts) + 8 * 2 ** 20   # allocations are rounded up to a few MiB
+    for a, b in zip(small, large):
+        np.testing.assert_array_equal(a, b)

@@ -11,10 +11,10 @@
 // multiply-adds rounds 128 times; the result is as near the 64-bit one as
 // that chain's.  Three 32x32x16 products take 96 cycles for the 1024 that
 // 16 reduction steps of 32x32x2 FP32 products take.  16,384 pairs of 2048-point
-// shapes at K = 128, widths 128 / 256: 0.63 ms, 1.83 ms on the FP32 matrix
-// cores (error of the whole path against 64 bits 5.8e-7, 7.9e-7 before).  The
-// matrix cores are busy 0.60 of its cycles and draw enough power that the
-// clock falls to 1.93 GHz.  Six products of three bf16 parts (no scales
+// shapes at K = 128, widths 128 / 256: 0.57 ms, 1.77 ms on the FP32 matrix cores
+// (error of the whole path against 64 bits 5.8e-7, 7.9e-7 before).  The
+// matrix cores are busy 0.59 of its cycles and draw enough power that the
+// clock falls to 1.94 GHz.  Six products of three bf16 parts (no scales
 // needed) took 0.98 ms.
 //
 // Two halves keep all their bits from 2^-2 to 2^16, so everything is multiplied

@@ -431,8 +431,8 @@ hipError_t launch_crop(const CropArgs& args, hipStream_t s, int unroll) {
   if (!a.setup || (unroll != 2 && unroll != 4 && unroll != 8)) return hipErrorInvalidValue;
   constexpr int W = kCropWaves;
   const dim3 grid((2 * a.n_pairs + W - 1) / W), block(64 * W);
-  // A small batch saves the set-up kernel's launch (8 pairs: 32.4 us with it, 30.1 without; 1,500: 63.7, 61.5; 2,000: 59.8,
-  // 59.0); in a larger one the float64 set-up of every wave costs more (3,000: 73.4, 75.5; 16,384: 250, 262).
+  // A small batch saves the set-up kernel's launch (8 pairs: 29.7 us with it, 27.7 without; 1,500: 52.1, 50.0; 2,000: 58.5,
+  // 57.3); in a larger one the float64 set-up of every wave costs more (3,000: 79.3, 80.5; 16,384: 249.7, 261.7).
   const bool inline_setup = a.n_pairs <= kInlinePairs;
   if (!inline_setup)
     kernel_launch(pair_setup_kernel, dim3((a.n_pairs + kThreads - 1) / kThreads), dim3(kThreads), 0, s, a);

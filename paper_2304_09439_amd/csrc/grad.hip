@@ -431,8 +431,8 @@ hipError_t launch_pose_gradients(const GradArgs& a, int h1, int h2, int hh, hipS
 // LDS); train_reduce_kernel, which sums the ranges in order and updates each
 // weight where its gradient is complete; and the repacking of the weights into
 // the layouts the kernels read.  Every reduction has a fixed order, so a step is
-// reproducible bit for bit.  4,096 pairs at widths 64 / 128 / 256: 0.247 ms a step,
-// 0.280 ms with eleven launches (137 pairs: 0.156 and 0.165 ms).
+// reproducible bit for bit.  4,096 pairs at widths 64 / 128 / 256: 0.226 ms a step
+// (with eleven launches 0.033 ms more).
 namespace locc {
 namespace {
 

@@ -2,9 +2,9 @@
 // HH / 64 waves per 32 RT pairs, two column tiles per wave, every layer in place in LDS.
 //
 // Bound by the stream of the head's weights (1 MB at width 512) from L2 into each compute unit: about 10 us of the
-// 12.7 us that 8 pairs take (one workgroup), 14.4 us at 1,061.  Two row tiles per workgroup halve that stream once
-// there are tiles for every other compute unit, and two workgroups per unit overlap their barriers: 27 us at 16,384
-// pairs (one row tile: 37).  Four row tiles fill the LDS with one workgroup and were slower (210,040 pairs: 285 us
+// 12.7 us that 8 pairs take (one workgroup), 14.1 us at 1,061.  Two row tiles per workgroup halve that stream once
+// every compute unit has a tile, and two workgroups per unit overlap their barriers: 27 us at 16,384 pairs (one row
+// tile: 37).  Four row tiles fill the LDS with one workgroup and were slower (210,040 pairs: 285 us
 // against 242), more k-steps in flight than four changed nothing, nor did another order of the fragments.
 #include "fused.h"
 #include "geometry.h"
@@ -145,7 +145,8 @@ hipError_t run(const HeadBf16Args& a, hipStream_t s) {
 
 template <int H2, int HH>
 hipError_t pick(const HeadBf16Args& a, int n_cu, hipStream_t s) {
-  return a.n_pairs < 16 * n_cu ? run<H2, HH, 1>(a, s) : run<H2, HH, 2>(a, s);
+  // the whole step with one tile and with two: 5,000 pairs 104.5 and 110.1 us, 8,000 138.7 and 143.6, 12,000 196.1 and 193.5
+  return a.n_pairs <= 32 * n_cu ? run<H2, HH, 1>(a, s) : run<H2, HH, 2>(a, s);
 }
 
 }  // namespace

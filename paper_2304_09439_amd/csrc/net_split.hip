@@ -6,15 +6,15 @@
 // matrix cores.  Layer 2, 97% of the work, runs on 16-bit ones: a float x is
 // the sum of two halves, x0 = half(x) and x1 = half(x - x0), to 2^-23 of x
 // (three floats in four exactly), and of the four products of two such sums all
-// but x1 y1 (at most 2^-22 of the product) are accumulated in FP32.  x0 y0 has a sum of its own, so that the
-// large partial sums round 8 times per output where a chain of FP32
-// multiply-adds rounds 128 times; the result is as near the 64-bit one as
-// that chain's.  Three 32x32x16 products take 96 cycles for the 1024 that
+// but x1 y1 (at most 2^-22 of the product) are accumulated in FP32.  x0 y0 has a
+// sum of its own, so that the large partial sums round 8 times per output where a
+// chain of FP32 multiply-adds rounds 128 times; the result is as near the 64-bit
+// one as that chain's.  Three 32x32x16 products take 96 cycles for the 1024 that
 // 16 reduction steps of 32x32x2 FP32 products take.  16,384 pairs of 2048-point
 // shapes at K = 128, widths 128 / 256: 0.57 ms, 1.77 ms on the FP32 matrix cores
 // (error of the whole path against 64 bits 5.8e-7, 7.9e-7 before).  The
 // matrix cores are busy 0.59 of its cycles and draw enough power that the
-// clock falls to 1.94 GHz.  Six products of three bf16 parts (no scales
+// clock falls to about 1.9 GHz.  Six products of three bf16 parts (no scales
 // needed) took 0.98 ms.
 //
 // Two halves keep all their bits from 2^-2 to 2^16, so everything is multiplied
@@ -65,7 +65,7 @@ static_assert(kSplitChunk == 32, "one lane per object of a chunk");
 
 template <int H1, int H2>
 struct SplitSmem {
-  static constexpr int HS = H1 + 8;  // bf16 per row: 16 bytes past a multiple of 64 or 128, so that rows start in other banks
+  static constexpr int HS = H1 + 8;  // halves per row: 16 bytes past a multiple of 64 or 128, for the banks
   alignas(16) unsigned short h[2][2][kStepRows * HS];  // layer-1 outputs of a step: [buffer][part][row][permuted feature]
   int32_t step[kMaxSteps];       // object of the chunk (0-63) | row block << 8
   int32_t m[2 * kSplitChunk];    // rows per object; -1: invalid pair
@@ -431,8 +431,8 @@ __global__ __launch_bounds__(2 * H2, 2) void encoder_split_kernel(Fp32Net W, Net
 // the 1.94 ms of the whole encoder on the FP32 matrix cores.
 
 // Four objects a workgroup read W2 once for four; up to 2,048 pairs the chip has room for every object alone, and the
-// chain of one is the shorter one (pose gradients of 40 pairs at 64 / 128 89.0 -> 83.2 us, 150 pairs at 128 / 256
-// 263.5 -> 245.9; 3,000 pairs go the other way, 436.7 against 444.0).
+// chain of one is the shorter one (pose gradients of 40 pairs at 64 / 128 81.3 -> 76.1 us, 150 pairs at 128 / 256
+// 232.5 -> 223.5; 3,000 pairs go the other way, 411.8 against 418.6).
 constexpr int kChainLonePairs = 2048;
 constexpr int kChainObjects = 4;
 
@@ -1078,10 +1078,10 @@ __global__ __launch_bounds__(256) void repack_kernel(RepackArgs A, SplitLayout L
 
 // Chunk sizes: half of what is left over the grid, 32 to 1. A batch of up to `lone` pairs a workgroup is dealt out
 // evenly in one claim each, without the queue: the pairs of a call cost nearly the same, and the halving levels' claims
-// cost more than the even split loses. At 64 / 128 (two workgroups a CU, grid 512) 2,000 pairs 66.4 -> 49.8 us, 8,000
-// 117.0 -> 105.2, 12,000 157.5 -> 147.6, but with the argmax 16,000 389.7 -> 396.1; at 128 / 256 (grid 256), whose
-// pairs are four times as long, 1,000 pairs 102.6 -> 96.9, but 2,000 137.3 -> 138.5. A batch whose length the device holds may be far shorter than
-// n_pairs, and one claim of its capacity's share would leave workgroups without work.
+// cost more than the even split loses. At 64 / 128 (two workgroups a CU, grid 512) 2,000 pairs 61.5 -> 45.3 us, 8,000
+// 110.0 -> 100.0, 12,000 147.2 -> 140.9, but with the argmax 16,000 380.6 -> 387.0; at 128 / 256 (grid 256), whose
+// pairs are four times as long, 1,000 pairs 91.9 -> 87.8, but 1,400 106.4 -> 108.3. A batch whose length the device
+// holds may be far shorter than n_pairs, and one claim of its capacity's share would leave workgroups without work.
 SplitChunks split_chunks(int n_pairs, int grid, int lone) {
   SplitChunks c{};
   c.grid = grid;
@@ -1146,7 +1146,8 @@ hipError_t launch_head_split(const Fp32Net& w, const NetArgs& a, int n_cu, hipSt
   if (a.n_pairs <= 0) return hipSuccess;
   if (!w.h1s || !w.split_bad) return hipErrorInvalidValue;
   // One tile per workgroup while every workgroup has a compute unit of its own (the weight stream is the same, the
-  // matrix work half); from there on two tiles halve the streams.
+  // matrix work half); from there on two tiles halve the streams (8,192 pairs at width 512: 368 us with one, 380 with two;
+  // 9,000: 424, 411).
   const bool two = a.n_pairs > 32 * n_cu;
   if (w.h2 == 128 && w.hh == 256) return two ? run_head<256, 256, 2>(w, a, s) : run_head<256, 256, 1>(w, a, s);
   if (w.h2 == 256 && w.hh == 512) return two ? run_head<512, 512, 2>(w, a, s) : run_head<512, 512, 1>(w, a, s);

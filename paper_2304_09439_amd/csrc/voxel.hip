@@ -20,8 +20,8 @@
 // residue mod 16, the float4 loads of both objects issued together, summed
 // across the residues by shuffles), and writes both objects' predictor input
 // rows to the workspace; with small register use many waves are in flight
-// to hide the load latency (80 registers, six waves per SIMD: 70.5 us both
-// launches at 16,384 pairs; 86: 71.9).  mlp_kernel: 32 pairs per workgroup of
+// to hide the load latency (80 registers, six waves per SIMD: 35 us at
+// 16,384 pairs; 86 registers: 1.4 us more).  mlp_kernel: 32 pairs per workgroup of
 // eight waves run the per-object MLP on the 64 rows, the pair max, the pair
 // MLP and the output layer as products of halves on the 16-bit matrix cores,
 // activations in LDS, each layer in place.

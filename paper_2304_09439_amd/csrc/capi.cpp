@@ -231,6 +231,17 @@ int fused_grid(const locc_ctx* c, int n_pairs, int claim, int per_cu) {
   return tiles < grid ? tiles : grid;
 }
 
+// Workgroups per compute unit of the FP8 encoder alone, which has the registers for a third (600 pairs 34.6 us with two,
+// 31.5 with three; 1,061: 40.9, 39.5; 3,000: 68.8, 57.6; 6,000: 100.0, 96.5; 16,384: 191.8, 178.4) but for batches that
+// are two rounds of claims either way, where the rounds of two workgroups are shorter (claims of four: 3,400 pairs 71.3,
+// 73.8; 4,096: 75.4, 77.1; 4,300, three rounds of two workgroups: 78.8, 77.6).
+int fp8_encoder_wg(const locc_ctx* c, int n_pairs) {
+  if (c->sched.wg_per_cu != kFusedWgPerCu) return c->sched.wg_per_cu;
+  const int claims = (n_pairs + c->sched.claim - 1) / c->sched.claim;
+  const bool two_rounds = claims > kFp8EncoderWgPerCu * c->n_cu && claims <= 2 * kFusedWgPerCu * c->n_cu;
+  return two_rounds ? kFusedWgPerCu : kFp8EncoderWgPerCu;
+}
+
 }  // namespace
 
 locc_status locc::run_path(locc_ctx* c, const locc_object* objs, int32_t n_objs, const int32_t* pairs,
@@ -314,9 +325,7 @@ locc_status locc::run_path(locc_ctx* c, const locc_object* objs, int32_t n_objs,
         fa.dynamic = c->sched.dynamic;
         const bool h8 = c->fp8_head();
         const bool apart = !h8 && head_apart(c, len);
-        // the third workgroup per compute unit: 600 pairs 34.6 us without, 31.5 with it; 1,061: 40.9, 39.5; 3,000: 68.8,
-        // 57.6; 6,000: 100.0, 96.5; 16,384: 191.8, 178.4 (but 4,000, whose claims come out uneven: 75.5, 77.5)
-        const int per_cu = apart && c->sched.wg_per_cu == kFusedWgPerCu ? kFp8EncoderWgPerCu : c->sched.wg_per_cu;
+        const int per_cu = apart ? fp8_encoder_wg(c, len) : c->sched.wg_per_cu;
         fa.claim = fused_claim(c, len, apart ? per_cu : 1);
         const int grid = fused_grid(c, len, fa.claim, per_cu);
         if (apart) {

@@ -76,11 +76,9 @@ struct locc_ctx {
   bool fp8_head() const { return cfg.precision == LOCC_FP8; }
 
   locc::DeviceLibrary lib() const {
-    const float* b = d_points;
-    const size_t n = (size_t)n_points;
-    return locc::DeviceLibrary{d_shapes, n_shapes, b, b + n, b + 2 * n, reinterpret_cast<const float3*>(b + 3 * n),
-                               d_rows, reinterpret_cast<const float4*>(d_clusters),
-                               d_clusters ? d_clusters + cluster_boxes : nullptr, 1.f / unit};
+    return locc::DeviceLibrary{d_shapes, n_shapes, 1.f / unit, d_points, n_points, d_rows,
+                               reinterpret_cast<const float4*>(d_clusters),
+                               d_clusters ? d_clusters + cluster_boxes : nullptr};
   }
 };
 

@@ -322,9 +322,9 @@ __global__ __launch_bounds__(64 * W, INLINE ? 4 : 6) void crop_kernel(CropArgs A
     sc.thr_out = geo_uniform(sc.thr_out);
   }
   const bool full = A.counts_out != nullptr;  // else stop once K members are known
-  const float* __restrict__ px = A.lib.px + off;
-  const float* __restrict__ py = A.lib.py + off;
-  const float* __restrict__ pz = A.lib.pz + off;
+  const float* __restrict__ px = A.lib.coordinate(0) + off;
+  const float* __restrict__ py = A.lib.coordinate(1) + off;
+  const float* __restrict__ pz = A.lib.coordinate(2) + off;
   const int cl = uniform(side ? rec->cl_b : rec->cl_a), nc = (n + kClusterPoints - 1) / kClusterPoints;
   const float4* boxes = A.lib.boxes && n > A.cluster_min ? A.lib.boxes + 2 * (size_t)cl : nullptr;
   const char* clusters = A.lib.clusters + (size_t)cl * kClusterBytes;

@@ -319,9 +319,9 @@ __device__ __forceinline__ void geo_scan_select(const PairGeom* __restrict__ gp,
         const unsigned k = ((unsigned)(side ? cur_b + i - q_a : cur_a + i) << 6) + (unsigned)lane;
         x[u] = y[u] = z[u] = 0.f;
         if (i < q && k < (unsigned)(side ? n_b : n_a)) {
-          x[u] = (lib.px + off)[k];
-          y[u] = (lib.py + off)[k];
-          z[u] = (lib.pz + off)[k];
+          x[u] = (lib.coordinate(0) + off)[k];
+          y[u] = (lib.coordinate(1) + off)[k];
+          z[u] = (lib.coordinate(2) + off)[k];
         }
       }
 #pragma unroll
@@ -412,8 +412,8 @@ __device__ __forceinline__ void geo_row(const PairGeom& g, const DeviceLibrary& 
     u = make_float3(r0.x, r0.y, r0.z);
     w = make_float3(r0.w, r1.x, r1.y);
   } else {
-    u = make_float3(lib.px[gi], lib.py[gi], lib.pz[gi]);
-    w = lib.normals[gi];
+    u = make_float3(lib.coordinate(0)[gi], lib.coordinate(1)[gi], lib.coordinate(2)[gi]);
+    w = lib.normals()[gi];
   }
   if (side) {
     double q[3], n[3];

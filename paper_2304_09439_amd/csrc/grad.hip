@@ -266,9 +266,9 @@ __global__ __launch_bounds__(H2, 8) void pose_kernel(GradArgs A) {
                        A.idx[((size_t)p * 2 + (1 ^ mt.swapped)) * A.K + r0 + t];
         float4* d = reinterpret_cast<float4*>(rowd[r0 + t]);
         d[0] = make_float4(lo.x, hi.x, lo.y, hi.y);
-        const float3 w = A.lib.normals[pt];
-        d[1] = make_float4(lo.z, hi.z, A.lib.px[pt], A.lib.py[pt]);
-        d[2] = make_float4(A.lib.pz[pt], w.x, w.y, w.z);
+        const float3 w = A.lib.normals()[pt];
+        d[1] = make_float4(lo.z, hi.z, A.lib.coordinate(0)[pt], A.lib.coordinate(1)[pt]);
+        d[2] = make_float4(A.lib.coordinate(2)[pt], w.x, w.y, w.z);
       }
       __syncthreads();
     }

@@ -68,7 +68,7 @@ def test_library_memory(torch):
     n, half = 16384, rng.uniform(0.05, 0.3, (12, 1, 3))
     pts = np.concatenate([rng.uniform(-half, half, (12, n, 3)), rng.normal(size=(12, n, 3))], 2).astype(np.float32)
     lib = I.ShapeLibrary(pts.reshape(-1, 6), np.arange(13, dtype=np.int64) * n, np.full(12, np.nan, np.float32))
-    sa, sb = rng.integers(0, 12, 2100), rng.integers(0, 12, 2100)   # past the batches that gather from the coordinates
+    sa, sb = rng.integers(0, 12, 2100), rng.integers(0, 12, 2100)   # past the batches whose set-up is the crop's own
     scene = I._pack_pair_scene(lib, *I.overlapping_pair_poses(rng, lib, sa, sb), sa.astype(np.int32),
                                sb.astype(np.int32), I._interleave_pairs(rng, 2100))
     weights = I.flatten_weights(I.gaussian_weights(I.SMALL_WIDTHS, seed=6, bias_std=0.1))
@@ -81,7 +81,8 @@ def test_library_memory(torch):
         free = torch.cuda.mem_get_info()[0]
         ctx.upload_shapes(np.arange(12 * copies + 1, dtype=np.int64) * n, np.tile(lib.pts, (copies, 1)))
         per_point = (free - torch.cuda.mem_get_info()[0]) / (12 * copies * n)
-        got = [t.cpu().numpy() for t in (*ctx.detect(objs, pairs), ctx.pose_gradients(objs, pairs)[0])]
+        got = [t.cpu().numpy() for t in (*ctx.detect(objs, pairs), *ctx.detect(objs, pairs[:60].contiguous()),
+                                         ctx.pose_gradients(objs, pairs)[0])]
         print(f"{12 * copies * n} points: {per_point:.1f} bytes a point", flush=True)
         return per_point, got
 

@@ -12,7 +12,7 @@ KERNELS = {
     "head_bf16.hip": [("head_bf16_kernelILi256ELi512E", 2)],
     "fused.hip": [("fused_bf16_kernelILi128ELi256ELi512ELb1ELb0ELb1E", 1)],            # encoder alone
     "fused_fp8.hip": [("encoder_head_fp8_kernelILi128ELi256ELi512ELb0ELb1E", 1)],      # encoder alone
-    "crop.hip": [("crop_kernel", 9), ("pair_setup_kernel", 1)],
+    "crop.hip": [("crop_kernel", 12), ("pair_setup_kernel", 1)],
     "clusters.hip": [("cluster_kernel", 1)],
     "grad.hip": [("head_backward_kernel", 2), ("pose_kernel", 2), ("head_train_kernel", 2), ("train_partials_kernel", 2),
                  ("train_reduce_kernel", 2)],

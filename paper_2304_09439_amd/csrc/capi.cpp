@@ -232,14 +232,14 @@ int fused_grid(const locc_ctx* c, int n_pairs, int claim, int per_cu) {
 }
 
 // Workgroups per compute unit of the FP8 encoder alone, which has the registers for a third (600 pairs 34.6 us with two,
-// 31.5 with three; 1,061: 40.9, 39.5; 3,000: 68.8, 57.6; 6,000: 100.0, 96.5; 16,384: 191.8, 178.4) but for batches that
-// are two rounds of claims either way, where the rounds of two workgroups are shorter (claims of four: 3,400 pairs 71.3,
-// 73.8; 4,096: 75.4, 77.1; 4,300, three rounds of two workgroups: 78.8, 77.6).
+// 31.5 with three; 1,061: 40.9, 39.5; 3,000: 68.8, 57.6; 6,000: 100.0, 96.5; 16,384: 191.8, 178.4), but for batches that
+// need the queue and are too small to make up for half as many again at its one address (claims of four: 3,400 pairs 71.3,
+// 73.8; 4,096: 75.5, 77.2; 4,200: 76.9, 78.9; 4,600: 82.0, 81.9; of two: 3,000 66.5, 69.0; 5,400 89.3, 89.0; claims of one
+// at any size: 16,384 262, 268; in static order three stay ahead: 4,096 72.3, 69.2).
 int fp8_encoder_wg(const locc_ctx* c, int n_pairs) {
   if (c->sched.wg_per_cu != kFusedWgPerCu) return c->sched.wg_per_cu;
-  const int claims = (n_pairs + c->sched.claim - 1) / c->sched.claim;
-  const bool two_rounds = claims > kFp8EncoderWgPerCu * c->n_cu && claims <= 2 * kFusedWgPerCu * c->n_cu;
-  return two_rounds ? kFusedWgPerCu : kFp8EncoderWgPerCu;
+  const bool queue = c->sched.dynamic && n_pairs > kFp8EncoderWgPerCu * c->n_cu * c->sched.claim;
+  return queue && (n_pairs <= 18 * c->n_cu || c->sched.claim == 1) ? kFusedWgPerCu : kFp8EncoderWgPerCu;
 }
 
 }  // namespace

@@ -93,4 +93,4 @@ def test_small_batches_equal_their_parts(torch, precision):
     """The head as a kernel of its own from one pair in two compute units on, with two tiles a workgroup past one tile a
     compute unit; the FP8 encoder's third workgroup, and the batches that do without it."""
     test_batches_equal_their_parts(torch, precision, "scale", 64,
-                                   (127, 128, 129, 256, 257, 513, 769, 3072, 3073, 4096, 4097, 8192, 8193))
+                                   (127, 128, 129, 256, 257, 513, 769, 3072, 3073, 4608, 4609, 8192, 8193))
